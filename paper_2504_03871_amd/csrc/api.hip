@@ -223,9 +223,9 @@ int moe_gemm_block_tile(int32_t kind, int64_t block, int32_t n_rt, int32_t n_ful
       n_split > n_rt - n_full_rt)
     return MOE_ERR_BAD_SHAPE;
   for (int i = 0; i < 6; ++i) out[i] = -1;
-  if (kind == 0) {
+  if (kind == 0 || kind == 3) {
     RowBlock r;
-    out[0] = row_tile_block((int)block, n_rt, n_full_rt, n_split, ntn, r) ? 1 : 0;
+    out[0] = row_tile_block((int)block, n_rt, n_full_rt, n_split, ntn, kind == 3, r) ? 1 : 0;
     if (out[0]) { out[1] = r.rt; out[3] = r.nt; out[4] = r.split_tile; out[5] = r.ksplit; }
     return MOE_OK;
   }
@@ -325,6 +325,7 @@ int ffn_fwd_impl(const moe_cfg* cfg, const void* x_perm, const void* W1, const v
   g.offsets = offsets; g.kept = kept; g.lo = slice_lo; g.hi = slice_hi; g.E = cfg->E;
   // hidden = act(x_perm W1)
   g.A = x_perm; g.B = W1; g.B2 = W1b; g.N = f; g.K = d;
+  g.chunked = row_tiles_chunked(A, d, f, cfg->E, swiglu ? 2 : 1, (int)elt_size(cfg));
   g.C = sv; g.C2 = sv + plane; g.C3 = sv + 2 * plane;
   char* hid = swiglu ? sv + 2 * plane : sv + plane;
   if (saved == nullptr) {   // keep nothing but the hidden activation
@@ -338,6 +339,7 @@ int ffn_fwd_impl(const moe_cfg* cfg, const void* x_perm, const void* W1, const v
   if (y_perm == nullptr) return MOE_OK;
   // y = hidden W2
   g.A = hid; g.B = W2; g.B2 = nullptr; g.N = d; g.K = f;
+  g.chunked = row_tiles_chunked(A, f, d, cfg->E, 1, (int)elt_size(cfg));
   g.C = y_perm; g.C2 = g.C3 = nullptr;
   if (is_half(cfg) && split_k_applies(cfg->E, f))   // smallest row tiles: split-K (gemm.h)
     g.split_ws = reinterpret_cast<float*>(static_cast<char*>(ws) + w.ffn_split);
@@ -466,6 +468,8 @@ int moe_expert_ffn_bwd(const moe_cfg* cfg, const void* dy_perm, const void* x_pe
   gw2.A = hidden; gw2.B = dy_perm; gw2.M = f; gw2.N = d;  gw2.C = dW2;
   gw1.A = x_perm; gw1.B = dact; gw1.M = d; gw1.N = f; gw1.C = dW1;
   gx.A = dact; gx.A2 = dact + plane; gx.B = W1; gx.B2 = W1b; gx.N = d; gx.K = f; gx.C = dx_perm;
+  gh.chunked = row_tiles_chunked(A, d, f, cfg->E, 1, (int)elt_size(cfg));
+  gx.chunked = row_tiles_chunked((swiglu ? 2ll : 1ll) * A, f, d, cfg->E, swiglu ? 2 : 1, (int)elt_size(cfg));
   const int epi_h = swiglu ? EPI_SWIGLU_BWD : EPI_GELU_BWD;
   // bf16: a row-tile GEMM with few rounds of tiles shares its launch with the weight-gradient GEMM that
   // follows it (dH with dW2, dx with dW1), whose tiles then start on the compute units that its last,

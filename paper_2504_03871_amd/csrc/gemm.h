@@ -76,13 +76,49 @@ inline int max_row_tiles(int A, int E, int tile_rows) { return (A + tile_rows - 
 #endif
 constexpr int NUM_XCD = 8;
 
-// Row-tile GEMMs.  Tiles are numbered (row tile, column tile) with the full row tiles first.  The full region
-// is walked in groups of GROUP row tiles, column by column, and cut into one contiguous range per XCD
-// (workgroups go to the eight XCDs round-robin), so tiles that run together on an XCD share operand panels in
-// its L2.  The partly filled row tiles follow in dispatch order: they are the last blocks to start and fill
-// the chip's final round.
-MOE_HD inline bool block_to_tile(int b, int n_rt, int n_full_rt, int ntn, int& rt, int& nt) {
-  constexpr int GROUP = 4;
+// Workgroups go to the eight XCDs round-robin (block b runs on XCD b % 8), each XCD has an L2 of its own, and all of
+// them share the memory-side cache.  The order of the tiles serves both levels.  A compute unit holds one block, so
+// an XCD runs 32 tiles at a time and the chip 256: the tile list is cut into chunks of 256, and XCD x takes the x-th
+// run of 32 tiles of every chunk.  The list itself (patch_tile) goes through the tile matrix so that 32 consecutive
+// tiles are a patch of 4 x 8 (twelve operand panels in the XCD's L2) and 256 consecutive ones a compact block (8 x 32
+// or 16 x 16), whose panels the XCDs read at about the same time and therefore mostly from the memory-side cache.
+// Before, every XCD walked a contiguous eighth of the whole list: the same L2 patches, but eight XCDs in eight
+// different places (different experts, on the Mixtral-like shape) shared nothing beyond their L2.  Eight experts of
+// 8192 rows, d 4096, f 14336, plain store, 256 x 256 tiles: x W 5.89 -> 5.36 ms (1307 -> 1437 TFLOP/s), dy W^T 5.95 ->
+// 5.41 ms; 16 experts of 2048 rows, d 2048, f 8192: 0.92 -> 0.89 and 0.88 -> 0.85 ms.
+constexpr int PATCH_R = 4, PATCH_C = 8, CHUNK_TILES = PATCH_R * PATCH_C * NUM_XCD;
+
+// Position in the tile list of block b of n, `run` tiles per XCD and chunk; the last chunk is shared out evenly as
+// well, its m % 8 last blocks by index.
+MOE_HD inline int chunk_position(int b, int n, int run) {
+  const int chunk = run * NUM_XCD, c0 = b / chunk * chunk, q = b - c0;
+  const int m = (chunk < n - c0) ? chunk : n - c0, per = m / NUM_XCD;
+  return (q < per * NUM_XCD) ? c0 + (q % NUM_XCD) * per + q / NUM_XCD : b;
+}
+
+// Tile p of an nr x nc tile matrix: bands of `band` rows; in a band, column strips PATCH_C wide; in a strip, patches
+// of PATCH_R rows; in a patch, column by column.  Ragged ends shrink the patch, the numbering stays gapless.
+MOE_HD inline void patch_tile(int p, int nr, int nc, int band, int& r, int& c) {
+  const int b = p / (band * nc), in = p - b * (band * nc), first = b * band;
+  const int rows = (band < nr - first) ? band : nr - first;
+  const int strip = in / (rows * PATCH_C), in2 = in - strip * (rows * PATCH_C);
+  const int cols = (PATCH_C < nc - strip * PATCH_C) ? PATCH_C : nc - strip * PATCH_C;
+  const int sub = in2 / (PATCH_R * cols), in3 = in2 - sub * (PATCH_R * cols);
+  const int pr = (PATCH_R < rows - sub * PATCH_R) ? PATCH_R : rows - sub * PATCH_R;
+  r = first + sub * PATCH_R + in3 % pr;
+  c = strip * PATCH_C + in3 / pr;
+}
+
+// Row-tile GEMMs.  Tiles are numbered (row tile, column tile) with the full row tiles first, in patch order.  The
+// partly filled row tiles follow in dispatch order: they are the last blocks to start and fill the chip's final round.
+// Chunked order for operands that do not fit the memory-side cache, in bands of eight row tiles: with 16 the large
+// shapes lose 1-4 %, with 32 4-6 % (a weight panel that all eight XCDs want at the same moment costs more than an
+// activation panel that four of them want).  Operands that do fit are served from that cache in any order; for them
+// one run per XCD in bands of four stays (the tiles an XCD takes one after the other then share their four activation
+// panels, which its L2 keeps from one patch to the next: 61 full row tiles, d 1024, f 4096, dH + dW2 292 against 300
+// us in chunks, GELU forward 176 against 179; SwiGLU forward of d 1088, f 2880: 100 against 104).
+constexpr int ROW_BAND = 8;
+MOE_HD inline bool block_to_tile(int b, int n_rt, int n_full_rt, int ntn, bool chunked, int& rt, int& nt) {
   const int n_full = n_full_rt * ntn, n_all = n_rt * ntn;
   if (b >= n_all) return false;
   if (b >= n_full) {                          // partial row tiles, largest first, in dispatch order
@@ -90,25 +126,25 @@ MOE_HD inline bool block_to_tile(int b, int n_rt, int n_full_rt, int ntn, int& r
     nt = (b - n_full) % ntn;
     return true;
   }
-  const int per = n_full / NUM_XCD;           // full tiles per XCD; the few left over keep their own index
-  const int logical = (b < per * NUM_XCD) ? (b % NUM_XCD) * per + b / NUM_XCD : b;
-  const int per_group = GROUP * ntn;
-  const int grp = logical / per_group, in = logical % per_group;
-  const int first = grp * GROUP, gsz = (GROUP < n_full_rt - first) ? GROUP : n_full_rt - first;
-  rt = first + in % gsz;
-  nt = in / gsz;
+  const int run = chunked ? PATCH_R * PATCH_C : n_full / NUM_XCD + 1;   // + 1: the whole list is one chunk
+  patch_tile(chunk_position(b, n_full, run), n_full_rt, ntn, chunked ? ROW_BAND : PATCH_R, rt, nt);
   return true;
+}
+// (host) whether the operands of a row-tile GEMM exceed the 256 MB memory-side cache; rows = the most it can have
+constexpr long long MEMORY_SIDE_CACHE = 256ll << 20;
+inline bool row_tiles_chunked(long long rows, long long K, long long N, int E, int matrices, int elt) {
+  return (rows * K + (long long)E * K * N * matrices) * elt > MEMORY_SIDE_CACHE;
 }
 
 // Block vb of a row-tile GEMM launch over n_rt row tiles (the first n_full_rt of them walked XCD by XCD), of
 // which the last n_sp are split along K: those are not part of the regular numbering; their blocks follow it,
 // SPLIT_K per (row tile, column tile), each with a K part of its own.  False: no tile (surplus block).
 struct RowBlock { int rt, nt, split_tile, ksplit; };
-MOE_HD inline bool row_tile_block(int vb, int n_rt, int n_full_rt, int n_sp, int ntn, RowBlock& r) {
+MOE_HD inline bool row_tile_block(int vb, int n_rt, int n_full_rt, int n_sp, int ntn, bool chunked, RowBlock& r) {
   const int n_reg = n_rt - n_sp;
   r.split_tile = -1;
   r.ksplit = 0;
-  if (vb < n_reg * ntn) return block_to_tile(vb, n_reg, n_full_rt, ntn, r.rt, r.nt);
+  if (vb < n_reg * ntn) return block_to_tile(vb, n_reg, n_full_rt, ntn, chunked, r.rt, r.nt);
   const int q = vb - n_reg * ntn;
   if (q >= n_sp * ntn * SPLIT_K) return false;
   r.ksplit = q % SPLIT_K;
@@ -118,23 +154,21 @@ MOE_HD inline bool row_tile_block(int vb, int n_rt, int n_full_rt, int n_sp, int
   return true;
 }
 
-// Block vb of a weight-gradient launch: tile (expert slot in descending-size order, m tile, n tile).  Every
-// expert's ntm x ntn tiles are split evenly over the XCDs (block b runs on XCD b % 8), so a skewed load is
-// even across XCDs.  An XCD's share of an expert is a contiguous range of the expert's tiles in patch order
-// (four m tiles at a time, column by column), so the 32 tiles it runs together form a 4 x 8 patch that needs
-// 12 operand panels per K stage from its L2 instead of up to 18 with the tiles dealt one by one.
+// Block vb of a weight-gradient launch: tile (expert slot in descending-size order, m tile, n tile).  A tile costs its
+// expert's row count, so every expert's ntm x ntn tiles are split evenly over the XCDs and a skewed load is even
+// across them; within the expert the order is the chunked patch order above, in bands of 16 (256 tiles at a time are
+// 16 x 16).  With more than one chunk the bands run along the shorter side: dW2 of eight experts of 8192 rows (14336 x
+// 4096) 5.89 -> 5.79 ms, 16 of 2048 rows (8192 x 2048) 1.007 -> 0.985 ms, against one contiguous run of the expert's
+// tiles per XCD; with one chunk that turn costs 3 % instead (4096 x 1024, 2048 rows: 127 -> 131 us).  Wide matrices
+// (4096 x 14336) take the same time in either order.
+constexpr int DW_BAND = 16;
 MOE_HD inline bool dw_block(int vb, int ntm, int ntn, int& slot, int& mt, int& nt) {
-  constexpr int GROUP = 4;
   const int P = ntm * ntn, P8 = (P + NUM_XCD - 1) / NUM_XCD * NUM_XCD;
-  const int q = vb % P8, x = q % NUM_XCD, i = q / NUM_XCD;      // XCD, and the block's turn on it for this expert
-  const int base = P / NUM_XCD, extra = P % NUM_XCD;            // XCD x takes base (+1 for the first `extra`) tiles
-  if (i >= base + (x < extra ? 1 : 0)) return false;
-  const int p = x * base + (x < extra ? x : extra) + i;         // position in patch order
   slot = vb / P8;
-  const int per_group = GROUP * ntn, grp = p / per_group, in = p % per_group;
-  const int first = grp * GROUP, gsz = (GROUP < ntm - first) ? GROUP : ntm - first;
-  mt = first + in % gsz;
-  nt = in / gsz;
+  const int q = vb - slot * P8;
+  if (q >= P) return false;
+  const int p = chunk_position(q, P, PATCH_R * PATCH_C);
+  if (ntm > ntn && P > CHUNK_TILES) patch_tile(p, ntn, ntm, DW_BAND, nt, mt); else patch_tile(p, ntm, ntn, DW_BAND, mt, nt);
   return true;
 }
 
@@ -175,6 +209,7 @@ struct GemmArgs {
   int M, N, K;   // NN/NT: N and K fixed (M unused); TN: M and N fixed (K is the expert's row count)
   int E;
   int accumulate;
+  int chunked;   // row-tile GEMMs: order of the full tiles (block_to_tile)
 };
 
 // table: which GELU table to fill as well (bf16 GELU layers: GELU_TAB_PHI before the forward GEMMs,

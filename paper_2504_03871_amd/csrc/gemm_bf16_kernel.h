@@ -264,13 +264,7 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs& g, const int vb, 
     const int ntn = (g.N + BN - 1) / BN;
     int rt, nt;
     if constexpr (MODE == MODE_TN) {
-      // Weight gradients: tile (expert, m tile, n tile) costs its expert's row count.  Every expert's
-      // tiles are split evenly over the XCDs (block b runs on XCD b % 8), so a skewed load is even across
-      // XCDs; experts start in order of descending row count.  An XCD's share of an expert is a contiguous
-      // range of the expert's tiles in patch order (four m tiles at a time, column by column), so the 32
-      // tiles it runs together form a 4 x 8 patch that needs 12 operand panels per K stage from its L2
-      // instead of up to 18 with the tiles dealt one by one (that order made dW2 of the Mixtral-like shape
-      // read 6.9 times its operands through the fabric).
+      // weight gradients: tile (expert, m tile, n tile), order in gemm.h (dw_block)
       const int ntm = (g.M + BM - 1) / BM;
       int slot, mt;
       if (!dw_block(vb, ntm, ntn, slot, mt, nt)) return;
@@ -290,7 +284,7 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs& g, const int vb, 
       // follow it, SPLIT_K per (row tile, column tile), each with a K range of its own
       const int n_sp = (CAN_SPLIT && g.split_ws != nullptr) ? g.ntiles[2] : 0;
       RowBlock rb;
-      if (!row_tile_block(vb, n_rt, g.ntiles[1], n_sp, ntn, rb)) return;
+      if (!row_tile_block(vb, n_rt, g.ntiles[1], n_sp, ntn, g.chunked != 0, rb)) return;
       rt = rb.rt;
       nt = rb.nt;
       klen = g.K;

@@ -4,6 +4,8 @@ once, nothing is out of range, surplus blocks exit, and the fp32 partial sums of
 their workspace region.  Also the byte-offset bound of the weight-gradient GEMM's operand walk."""
 import itertools
 
+import pytest
+
 from paper_2504_03871_amd import binding as B
 
 SPLIT_K, SPLIT_ROWS, NUM_XCD = 8, 64, 8
@@ -71,3 +73,13 @@ def test_rejects_bad_arguments():
     assert lib.moe_gemm_block_tile(0, 0, 4, 2, 3, 1, 1, out) == -2        # more split tiles than partial ones
     assert lib.moe_gemm_block_tile(2, 0, 4, 2, 0, 1, 1, out) == -3
     assert lib.moe_gemm_block_tile(0, 0, 4, 2, 0, 1, 1, None) == -1
+
+
+@pytest.mark.parametrize("n_full, n_part, ntn", [(0, 3, 5), (1, 0, 1), (7, 2, 9), (8, 0, 32), (13, 1, 23), (67, 8, 16), (40, 3, 56)])
+def test_chunked_row_tile_numbering_covers_every_tile_once(n_full, n_part, ntn):
+    """Full and ragged bands of eight row tiles, strips of eight columns, several chunks of 256 and a ragged last one."""
+    n_rt = n_full + n_part
+    t = [B.moe_gemm_block_tile(3, vb, n_rt, n_full, 0, 1, ntn) for vb in range(n_rt * ntn + 8)]
+    assert sorted((x[1], x[3]) for x in t if x[0]) == list(itertools.product(range(n_rt), range(ntn)))
+    assert not any(x[0] for x in t[n_rt * ntn:])
+    assert all(x[1] >= n_full for x in t[n_full * ntn:n_rt * ntn])      # partly filled row tiles last
