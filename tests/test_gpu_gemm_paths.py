@@ -1,0 +1,43 @@
+"""GPU tests of single paths of the grouped GEMMs at the sizes where they can go wrong: edges of tiles, remainders,
+empty experts."""
+import pytest
+
+from paper_2504_03871_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+
+DT = {"f32": B.DTYPE_F32, "bf16": B.DTYPE_BF16, "f16": B.DTYPE_F16}
+
+
+def filled_layer(T, d, f, E, k, dtype, act=B.ACT_GELU, seed=0):
+    import torch
+    from paper_2504_03871_amd.layer import MoELayer
+    L = MoELayer(T, d, f, E, k, dtype=DT[dtype], act=act)
+    gen = torch.Generator(device="cuda:0").manual_seed(seed)
+    for t, std in ((L.x, 1.0), (L.d_out, 1.0), (L.Wr, d ** -0.5), (L.W1, d ** -0.5), (L.W2, f ** -0.5), (L.W1b, d ** -0.5)):
+        if t is not None:
+            t.copy_(torch.randn(t.shape, generator=gen, device=t.device) * std)
+    return L
+
+
+@pytest.mark.parametrize("T, d, f, E, k, dtype, act", [
+    (700, 192, 320, 4, 2, "bf16", B.ACT_GELU),        # neither width a multiple of the tile, several K stages
+    (300, 64, 576, 3, 1, "f16", B.ACT_SWIGLU),
+    (3, 320, 256, 8, 1, "bf16", B.ACT_SWIGLU),        # experts without rows keep what they had
+])
+def test_accumulated_weight_gradients_are_old_plus_new(T, d, f, E, k, dtype, act):
+    """accumulate = 1 adds, in fp32 and with one rounding, the very sums that accumulate = 0 stores."""
+    import torch
+    L = filled_layer(T, d, f, E, k, dtype, act)
+    L.forward()
+    L.combine_bwd()
+    L.ffn_bwd(0)
+    grads = [g for g in (L.dW1, L.dW1b, L.dW2) if g is not None]
+    new = [g.clone() for g in grads]
+    old = [torch.randn_like(g) for g in grads]
+    for g, o in zip(grads, old):
+        g.copy_(o)
+    L.ffn_bwd(1)
+    torch.cuda.synchronize()
+    for g, o, n in zip(grads, old, new):
+        assert torch.equal(g, o + n)
