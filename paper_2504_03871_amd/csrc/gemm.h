@@ -217,7 +217,7 @@ struct GemmArgs {
 int launch_tile_map(const int32_t* offsets, const int32_t* kept, const int32_t* lo, const int32_t* hi, int E,
                     int tile_rows, TileMap map, int table, hipStream_t s);
 
-// fp32 storage, fp32 FMA (any shape that passes check_cfg)
+// fp32 storage, fp32 MFMA (any shape that passes check_cfg)
 int launch_gemm_f32(int mode, int epi, bool dual, bool chain, const GemmArgs& g, int max_tiles, hipStream_t s);
 // 16-bit storage (dtype = MOE_DTYPE_BF16 or MOE_DTYPE_F16), MFMA with fp32 accumulation
 int launch_gemm_half(int dtype, int mode, int epi, bool dual, bool chain, const GemmArgs& g, int max_tiles, hipStream_t s);
@@ -226,35 +226,33 @@ int launch_gemm_half_pair(int dtype, int epi1, bool chain1, const GemmArgs& g1, 
 int gemm_bf16_tile_rows();
 
 #ifdef __HIPCC__
-// Element-wise epilogues, shared by both kernels.  `row` is the absolute permuted row, `col` the
-// output column, `ldc` the row pitch of the output(s).
-template <typename T, int EPI>
-__device__ __forceinline__ void epilogue(const GemmArgs& g, size_t idx, float acc, float acc2) {
-  if constexpr (EPI == EPI_STORE) {
-    reinterpret_cast<T*>(g.C)[idx] = from_f32<T>(acc);
-  } else if constexpr (EPI == EPI_GELU_FWD) {   // C == NULL: the caller keeps only the hidden activation
-    if (g.C != nullptr) reinterpret_cast<T*>(g.C)[idx] = from_f32<T>(acc);
-    reinterpret_cast<T*>(g.C2)[idx] = from_f32<T>(gelu_f(acc));
-  } else if constexpr (EPI == EPI_SWIGLU_FWD) {
-    if (g.C != nullptr) {
-      reinterpret_cast<T*>(g.C)[idx] = from_f32<T>(acc);
-      reinterpret_cast<T*>(g.C2)[idx] = from_f32<T>(acc2);
-    }
-    reinterpret_cast<T*>(g.C3)[idx] = from_f32<T>(acc * sigmoid_f(acc) * acc2);
-  } else if constexpr (EPI == EPI_GELU_BWD) {
-    const float a = to_f32(reinterpret_cast<const T*>(g.S1)[idx]);
-    reinterpret_cast<T*>(g.C)[idx] = from_f32<T>(acc * gelu_grad_f(a));
-  } else if constexpr (EPI == EPI_SWIGLU_BWD) {
-    const float gg = to_f32(reinterpret_cast<const T*>(g.S1)[idx]);
-    const float uu = to_f32(reinterpret_cast<const T*>(g.S2)[idx]);
-    const float sg = sigmoid_f(gg);
-    reinterpret_cast<T*>(g.C)[idx] = from_f32<T>(acc * uu * sg * (1.f + gg * (1.f - sg)));
-    reinterpret_cast<T*>(g.C2)[idx] = from_f32<T>(acc * gg * sg);
-  } else {
-    float* c = reinterpret_cast<float*>(g.C);
-    c[idx] = g.accumulate ? c[idx] + acc : acc;
-  }
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+
+// ---- global -> LDS loads, shared by both kernels ----
+// Buffer loads: the descriptor's byte count is the part of the operand a tile may read; anything past it reads as zero.
+typedef __attribute__((address_space(3))) char lds_char;
+__device__ __forceinline__ unsigned lds_addr(const char* p) { return (unsigned)(uintptr_t)(const lds_char*)p; }
+typedef u32x4 rsrc_t;
+__device__ __forceinline__ rsrc_t make_rsrc(const void* base, size_t bytes) {
+  const unsigned long long a = (unsigned long long)base;
+  const unsigned n = bytes > 0xffffffffull ? 0xffffffffu : (unsigned)bytes;
+  // raw buffer: base address, stride 0, byte count, 32-bit untyped data format
+  return rsrc_t{(unsigned)a, (unsigned)(a >> 32) & 0xffffu, n, 0x00020000u};
 }
+
+// 16 bytes per lane from a buffer straight into LDS: lane l of the wave lands at LDS byte address
+// lds + 16*l (lds is wave-uniform; the instruction takes it from M0).  Completion is tracked by
+// vmcnt like any other buffer load.  Written as a raw instruction on purpose: the compiler must not
+// know that this load writes LDS, or it waits for every outstanding load before each LDS read it
+// cannot prove disjoint (the transposing reads).  The pipeline orders loads and reads itself with
+// explicit vmcnt waits and block barriers; the memory clobber keeps LDS reads from moving across.
+__device__ __forceinline__ void load_to_lds16(rsrc_t rs, unsigned lds, unsigned voffset) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+               :: "s"(lds), "v"(voffset), "s"(rs) : "memory", "m0");
+}
+// a byte offset past any operand: they are multiples of 16 bytes below 4 GiB (offsets_fit_32_bits)
+constexpr unsigned OUT_OF_RANGE = 0xfffffff0u;
 #endif
 
 }  // namespace moe

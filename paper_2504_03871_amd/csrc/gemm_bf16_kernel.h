@@ -45,8 +45,6 @@ namespace moe {
 
 typedef bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
@@ -112,26 +110,6 @@ __device__ __forceinline__ bf16x8 lds_read_ks2(const char* p) {
 // this tile may read, and the hardware returns zero for anything past it.  That gives the ragged
 // edges (rows past an expert's share, K rows past the share in the weight-gradient GEMM, columns past
 // the matrix) for free, with no predicates, no branches and one 32-bit offset register per load.
-typedef __attribute__((address_space(3))) char lds_char;
-__device__ __forceinline__ unsigned lds_addr(const char* p) { return (unsigned)(uintptr_t)(const lds_char*)p; }
-typedef u32x4 rsrc_t;
-__device__ __forceinline__ rsrc_t make_rsrc(const void* base, size_t bytes) {
-  const unsigned long long a = (unsigned long long)base;
-  const unsigned n = bytes > 0xffffffffull ? 0xffffffffu : (unsigned)bytes;
-  // raw buffer: base address, stride 0, byte count, 32-bit untyped data format
-  return rsrc_t{(unsigned)a, (unsigned)(a >> 32) & 0xffffu, n, 0x00020000u};
-}
-
-// 16 bytes per lane from a buffer straight into LDS: lane l of the wave lands at LDS byte address
-// lds + 16*l (lds is wave-uniform; the instruction takes it from M0).  Completion is tracked by
-// vmcnt like any other buffer load.  Written as a raw instruction on purpose: the compiler must not
-// know that this load writes LDS, or it waits for every outstanding load before each LDS read it
-// cannot prove disjoint (the transposing reads).  The pipeline orders loads and reads itself with
-// explicit vmcnt waits and block barriers; the memory clobber keeps LDS reads from moving across.
-__device__ __forceinline__ void load_to_lds16(rsrc_t rs, unsigned lds, unsigned voffset) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
-               :: "s"(lds), "v"(voffset), "s"(rs) : "memory", "m0");
-}
 
 // One operand tile of one stage, cut into 16-byte chunks; thread tid moves chunks tid + NT*i.
 // KC: [ROWS][BKT], chunk id -> (row id/CPR, chunk id%CPR).

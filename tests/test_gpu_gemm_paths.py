@@ -41,3 +41,29 @@ def test_accumulated_weight_gradients_are_old_plus_new(T, d, f, E, k, dtype, act
     torch.cuda.synchronize()
     for g, o, n in zip(grads, old, new):
         assert torch.equal(g, o + n)
+
+
+@pytest.mark.parametrize("T, d, f, E, k, act", [
+    (5, 4, 4, 2, 1, B.ACT_GELU),            # far below one tile and one K stage in every dimension
+    (65, 36, 64, 1, 1, B.ACT_SWIGLU),       # one row past a row tile, four K values past a stage
+    (200, 132, 260, 3, 2, B.ACT_SWIGLU),    # four columns past a column tile
+    (129, 64, 128, 4, 1, B.ACT_GELU),       # whole tiles and stages
+])
+def test_fp32_gemms_at_tile_and_stage_edges(T, d, f, E, k, act):
+    from paper_2504_03871_amd import synth as S
+    from tests.test_gpu_parity import run_case
+    run_case(S.WORKLOADS["cfg0"].scaled(T=T, d=d, f=f, E=E, k=k, act=act))
+
+
+@pytest.mark.parametrize("dtype, d, f", [("f32", 36, 68), ("bf16", 64, 64)])
+def test_a_row_with_nan_stays_in_its_row(dtype, d, f):
+    """What lies behind the last K value of a row (the next row) takes no part in its sums."""
+    import torch
+    L = filled_layer(90, d, f, 2, 1, dtype)
+    L.route()
+    L.dispatch()
+    L.x_perm[7] = float("nan")
+    L.ffn_fwd()
+    torch.cuda.synchronize()
+    bad = torch.isnan(L.y_perm.float()).any(dim=1).nonzero().flatten().tolist()
+    assert bad == [7]
