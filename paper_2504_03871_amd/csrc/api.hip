@@ -314,7 +314,8 @@ int ffn_fwd_impl(const moe_cfg* cfg, const void* x_perm, const void* W1, const v
   const bool swiglu = cfg->act == MOE_ACT_SWIGLU;
   const WsLayout w = ws_layout(cfg);
   const int A = cfg->T * cfg->k, d = cfg->d_model, f = cfg->d_ff;
-  const int tr = tile_rows_for(cfg), max_tiles = max_row_tiles(A, cfg->E, tr);
+  const bool skinny = is_half(cfg) && skinny_applies(A, cfg->E);   // few rows per expert
+  const int tr = skinny ? SKINNY_ROWS : tile_rows_for(cfg), max_tiles = max_row_tiles(A, cfg->E, tr);
   TileMap map = tile_map_at(static_cast<char*>(ws) + w.tile_map, max_row_tiles(A, cfg->E, TILE_ROWS_MIN), cfg->E);
   CHECK(launch_tile_map(offsets, kept, slice_lo, slice_hi, cfg->E, tr, map,
                         !swiglu && cfg->dtype == MOE_DTYPE_BF16 ? GELU_TAB_PHI : GELU_TAB_NONE, s));
@@ -334,7 +335,9 @@ int ffn_fwd_impl(const moe_cfg* cfg, const void* x_perm, const void* W1, const v
   }
   {
     ProfScope ps(cfg, MOE_PROF_GEMM1_FWD, s);
-    CHECK(launch_gemm(cfg, MODE_NN, swiglu ? EPI_SWIGLU_FWD : EPI_GELU_FWD, swiglu, false, g, max_tiles, s));
+    const int epi = swiglu ? EPI_SWIGLU_FWD : EPI_GELU_FWD;
+    if (skinny) CHECK(launch_gemm_half_skinny(cfg->dtype, epi, swiglu, g, max_tiles, s));
+    else CHECK(launch_gemm(cfg, MODE_NN, epi, swiglu, false, g, max_tiles, s));
   }
   if (y_perm == nullptr) return MOE_OK;
   // y = hidden W2
@@ -344,6 +347,7 @@ int ffn_fwd_impl(const moe_cfg* cfg, const void* x_perm, const void* W1, const v
   if (is_half(cfg) && split_k_applies(cfg->E, f))   // smallest row tiles: split-K (gemm.h)
     g.split_ws = reinterpret_cast<float*>(static_cast<char*>(ws) + w.ffn_split);
   ProfScope ps(cfg, MOE_PROF_GEMM2_FWD, s);
+  if (skinny) return launch_gemm_half_skinny(cfg->dtype, EPI_STORE, false, g, max_tiles, s);
   return launch_gemm(cfg, MODE_NN, EPI_STORE, false, false, g, max_tiles, s);
 }
 }  // namespace

@@ -224,6 +224,15 @@ int launch_gemm_half(int dtype, int mode, int epi, bool dual, bool chain, const 
 // one launch for an NT GEMM (epilogue epi1, chained or not) followed by a TN weight-gradient GEMM
 int launch_gemm_half_pair(int dtype, int epi1, bool chain1, const GemmArgs& g1, int max_tiles, const GemmArgs& g2, hipStream_t s);
 int gemm_bf16_tile_rows();
+// forward GEMMs of experts with few rows (gemm_skinny_kernel.h), on a map of SKINNY_ROWS-row tiles
+constexpr int SKINNY_ROWS = 64;
+int launch_gemm_half_skinny(int dtype, int epi, bool dual, const GemmArgs& g, int max_tiles, hipStream_t s);
+// The line lies where most experts still fit one 64-row tile (each further one reads the weights again).  Forward pass,
+// 256-row kernel -> this one: d 4096, f 14336, eight experts, SwiGLU, 32 rows per expert 694 -> 578 us, 48 rows 709 -> 602,
+// 64 rows 831 -> 796, 96 rows 820 -> 1099; 32 rows under a skewed router 818 -> 655; d 2048, f 1024, 64 rows per expert:
+// 128 experts, SwiGLU, 446 -> 428, 256 experts, GELU, 590 -> 691.
+constexpr int SKINNY_AVERAGE = 48;
+inline bool skinny_applies(long long rows, int E) { return rows <= (long long)SKINNY_AVERAGE * E; }
 
 #ifdef __HIPCC__
 typedef float f32x4 __attribute__((ext_vector_type(4)));

@@ -1,5 +1,6 @@
 // Launchers of the MFMA grouped GEMM for 16-bit storage, bf16 or fp16 (kernel in gemm_bf16_kernel.h).
 #include "gemm_bf16_kernel.h"
+#include "gemm_skinny_kernel.h"
 
 namespace moe {
 
@@ -98,6 +99,35 @@ int launch_gemm_half_pair(int dtype, int epi1, bool chain1, const GemmArgs& g1, 
 
 int launch_gemm_half(int dtype, int mode, int epi, bool dual, bool chain, const GemmArgs& g, int max_tiles, hipStream_t s) {
   return dtype == MOE_DTYPE_F16 ? one_for<f16>(mode, epi, dual, chain, g, max_tiles, s) : one_for<bf16>(mode, epi, dual, chain, g, max_tiles, s);
+}
+
+// Few rows per expert (gemm_skinny_kernel.h); the tile map has SKINNY_ROWS rows per tile.
+template <typename ST, int EPI, bool DUAL>
+static int launch_skinny(const GemmArgs& g, int max_tiles, hipStream_t s) {
+  constexpr int lds = skinny_stages<DUAL>() * skinny_stage_bytes<DUAL>();
+  auto kern = gemm_skinny_kernel<ST, EPI, DUAL>;
+  {
+    hipError_t err = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (err != hipSuccess) return set_hip_error(err);
+  }
+  const int ntn = (g.N + SKINNY_BN - 1) / SKINNY_BN;
+  const bool split = EPI == EPI_STORE && g.split_ws != nullptr;
+  const long long tiles = (long long)ntn * max_tiles + (split ? (long long)g.E * ntn * (SPLIT_K - 1) : 0);
+  if (tiles > 0x7fffffffll) return MOE_ERR_BAD_SHAPE;
+  kern<<<dim3(gemm_bf16_grid(tiles)), 256, lds, s>>>(g);
+  const int rc = launch_status();
+  if (rc != MOE_OK || !split) return rc;
+  return launch_split_reduce<ST>(g, s);
+}
+template <typename ST>
+static int skinny_for(int epi, bool dual, const GemmArgs& g, int max_tiles, hipStream_t s) {
+  if (epi == EPI_GELU_FWD) return launch_skinny<ST, EPI_GELU_FWD, false>(g, max_tiles, s);
+  if (epi == EPI_SWIGLU_FWD && dual) return launch_skinny<ST, EPI_SWIGLU_FWD, true>(g, max_tiles, s);
+  if (epi == EPI_STORE) return launch_skinny<ST, EPI_STORE, false>(g, max_tiles, s);
+  return MOE_ERR_BAD_DTYPE;
+}
+int launch_gemm_half_skinny(int dtype, int epi, bool dual, const GemmArgs& g, int max_tiles, hipStream_t s) {
+  return dtype == MOE_DTYPE_F16 ? skinny_for<f16>(epi, dual, g, max_tiles, s) : skinny_for<bf16>(epi, dual, g, max_tiles, s);
 }
 
 }  // namespace moe

@@ -1,0 +1,159 @@
+// Grouped x W (NN) for 16-bit storage where the experts have few rows each: decode batches and short prompts.
+//
+// Such a GEMM reads every weight once and does next to no arithmetic with it: HBM bounds it, and what counts is how
+// many bytes each compute unit keeps in flight.  The 256-row kernel keeps one block per compute unit with one 32 KB
+// stage of weights in flight and drains it at every stage.  Here a block owns 64 rows x 128 columns, four waves of 32
+// columns each; its K stages of 64 go through a ring of LDS stages that buffer loads fill directly, all but one of
+// them in flight, and two blocks share a compute unit: 64 KB of weights on their way per compute unit at any time.
+// The weights are requested as streaming data.  16 tokens, d 4096, f 14336, eight experts, top-2, SwiGLU: both GEMMs
+// 606 us with the 256-row kernel (4.65 TB/s), 525 with this one at 64 columns and plain loads, 503 at 128 columns, 465
+// at 64 columns with streaming loads, 452 as it is (6.2 TB/s); a third block per compute unit gains nothing.
+#pragma once
+#include "gemm_bf16_kernel.h"
+
+namespace moe {
+
+constexpr int SKINNY_BN = 128;
+template <bool DUAL>
+constexpr int skinny_stage_bytes() { return SKINNY_ROWS * BKT * 2 + SKINNY_BN * BKT * 2 * (DUAL ? 2 : 1); }
+template <bool DUAL>
+constexpr int skinny_stages() { return 80 * 1024 / skinny_stage_bytes<DUAL>(); }   // two blocks per compute unit
+
+// load_to_lds16 for data that one block reads once: the weights do not displace anything in the caches
+__device__ __forceinline__ void load_to_lds16_nt(rsrc_t rs, unsigned lds, unsigned voffset) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen nt lds"
+               :: "s"(lds), "v"(voffset), "s"(rs) : "memory", "m0");
+}
+
+template <typename ST, int EPI, bool DUAL>
+__global__ __launch_bounds__(256, 2) void gemm_skinny_kernel(GemmArgs g) {
+  constexpr int BM = SKINNY_ROWS, BN = SKINNY_BN, A_BYTES = BM * BKT * 2, B_BYTES = BN * BKT * 2;
+  constexpr int STAGE = skinny_stage_bytes<DUAL>(), NB = skinny_stages<DUAL>(), AHEAD = NB - 1;
+  constexpr int TM = BM / 16, TN = BN / 64;                      // 16 x 16 tiles of a wave: all rows, BN / 4 columns
+  constexpr int CHA = BM * BKT / 8 / 256, CHB = BN * BKT / 8 / 256, L = CHA + CHB * (DUAL ? 2 : 1);
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  const int tid = threadIdx.x, lane = tid & 63, c = lane & 15, grp = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+
+  const int ntn = (g.N + BN - 1) / BN, n_rt = g.ntiles[0];
+  constexpr bool CAN_SPLIT = EPI == EPI_STORE;
+  const int n_sp = (CAN_SPLIT && g.split_ws != nullptr) ? g.ntiles[2] : 0;
+  RowBlock rb;
+  if (!row_tile_block(blockIdx.x, n_rt, g.ntiles[1], n_sp, ntn, false, rb)) return;
+  const RowTile t = g.tiles[rb.rt];
+  const int klen = rb.split_tile >= 0 ? g.K / SPLIT_K : g.K, kbase = rb.ksplit * klen;
+  const int n0 = rb.nt * BN, mvalid = t.nrows, ni = (mvalid + 15) / 16;   // ni: row tiles with valid rows
+
+  const rsrc_t ra = make_rsrc(reinterpret_cast<const bf16*>(g.A) + (size_t)t.row0 * g.K + kbase, ((size_t)mvalid * g.K - kbase) * 2);
+  const size_t boff = ((size_t)t.e * g.K + kbase) * g.N + n0, bbytes = ((size_t)(g.K - kbase) * g.N - n0) * 2;
+  const rsrc_t rw = make_rsrc(reinterpret_cast<const bf16*>(g.B) + boff, bbytes);
+  const rsrc_t rw2 = make_rsrc(reinterpret_cast<const bf16*>(DUAL ? g.B2 : g.B) + boff, bbytes);
+  const unsigned pa = g.K * 2, pb = g.N * 2;
+  unsigned a_vo[CHA], b_vo[CHB];
+#pragma unroll
+  for (int i = 0; i < CHA; ++i) {
+    const int id = tid + 256 * i, r = id >> 3;
+    a_vo[i] = (unsigned)r * pa + (unsigned)((id & 7) ^ ((r >> 1) & 7)) * 16u;   // kc_off, inverted
+  }
+#pragma unroll
+  for (int i = 0; i < CHB; ++i) {
+    const int id = tid + 256 * i, r = id / (BN / 8), pc = id % (BN / 8);
+    b_vo[i] = (unsigned)r * pb + (unsigned)(ks_off<BN>(r, pc * 16) - r * BN * 2);   // ks_off, inverted
+  }
+  const unsigned lds0 = lds_addr(smem) + wave * 1024;
+  auto load_stage = [&](int kt, int buf) {
+    const unsigned at = lds0 + buf * STAGE;
+#pragma unroll
+    for (int i = 0; i < CHB; ++i) {
+      load_to_lds16_nt(rw, at + A_BYTES + i * 4096, b_vo[i] + kt * (BKT * pb));
+      if constexpr (DUAL) load_to_lds16_nt(rw2, at + A_BYTES + B_BYTES + i * 4096, b_vo[i] + kt * (BKT * pb));
+    }
+#pragma unroll
+    for (int i = 0; i < CHA; ++i) load_to_lds16(ra, at + i * 4096, a_vo[i] + kt * (BKT * 2));
+  };
+
+  f32x4 acc[TM][TN], acc2[DUAL ? TM : 1][DUAL ? TN : 1];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+      acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+      if constexpr (DUAL) acc2[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+  int b_fr[TN];
+#pragma unroll
+  for (int j = 0; j < TN; ++j)
+    b_fr[j] = A_BYTES + ks_off<BN>(grp * 8 + (c >> 2), (wave * (BN / 4) + j * 16 + (c & 3) * 4) * 2);
+
+  const int KT = klen / BKT;
+#pragma unroll
+  for (int q = 0; q < AHEAD; ++q)
+    if (q < KT) load_stage(q, q);
+  int buf = 0;
+#pragma unroll 1
+  for (int kt = 0; kt < KT; ++kt) {
+    // own loads of this stage have landed (later stages stay in flight) and own reads of the last one are done; behind
+    // the barrier that holds for every wave, and the last stage's buffer is free
+    constexpr int PEND = (AHEAD - 1) * L;
+    static_assert(PEND < 16, "low bits of the wait counter");
+    if (kt + AHEAD <= KT) __builtin_amdgcn_s_waitcnt(PEND | 0x70); else __builtin_amdgcn_s_waitcnt(0x70);
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    if (kt + AHEAD < KT) load_stage(kt + AHEAD, buf + AHEAD >= NB ? buf + AHEAD - NB : buf + AHEAD);
+    const char* st = smem + buf * STAGE;
+#pragma unroll
+    for (int ks = 0; ks < BKT / 32; ++ks) {
+      bf16x8 b[TN], b2[DUAL ? TN : 1];
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        const char* p = st + b_fr[j] + ks * 32 * BN * 2;
+        b[j] = lds_read_ks2<BN>(p);
+        if constexpr (DUAL) b2[j] = lds_read_ks2<BN>(p + B_BYTES);
+      }
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+        if (i < ni) {
+          const bf16x8 a = *reinterpret_cast<const bf16x8*>(st + kc_off(i * 16 + c, ks * 4 + grp));
+#pragma unroll
+          for (int j = 0; j < TN; ++j) {
+            acc[i][j] = Half16<ST>::mfma(a, b[j], acc[i][j]);
+            if constexpr (DUAL) acc2[i][j] = Half16<ST>::mfma(a, b2[j], acc2[i][j]);
+          }
+        }
+    }
+    buf = buf + 1 == NB ? 0 : buf + 1;
+  }
+
+  // accumulators become rows through LDS (the ring is free once every wave has left it)
+  __builtin_amdgcn_s_waitcnt(0x70);
+  __syncthreads();
+  constexpr int P = BN + 4, LPR = BN / 4, RPP = 256 / LPR;
+  float* slab = reinterpret_cast<float*>(smem);
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+    if (i < ni) {
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int at = (i * 16 + grp * 4 + v) * P + wave * (BN / 4) + j * 16 + c;
+          slab[at] = acc[i][j][v];
+          if constexpr (DUAL) slab[BM * P + at] = acc2[i][j][v];
+        }
+    }
+  __syncthreads();
+  const int n = (tid % LPR) * 4;
+  if (n0 + n >= g.N) return;
+  for (int m = tid / LPR; m < mvalid; m += RPP) {
+    const f32x4 va = *reinterpret_cast<const f32x4*>(slab + m * P + n);
+    f32x4 vb = va;
+    if constexpr (DUAL) vb = *reinterpret_cast<const f32x4*>(slab + BM * P + m * P + n);
+    if (CAN_SPLIT && rb.split_tile >= 0)   // fp32 partial sum of this block's K part
+      *reinterpret_cast<f32x4*>(g.split_ws + (((size_t)rb.split_tile * SPLIT_K + rb.ksplit) * SPLIT_ROWS + m) * g.N + n0 + n) = va;
+    else
+      epilogue4<ST, EPI>(g, (size_t)(t.row0 + m) * g.N + n0 + n, va, vb, u32x2{0, 0}, u32x2{0, 0}, g.gelu_tab);
+  }
+}
+
+}  // namespace moe

@@ -67,3 +67,15 @@ def test_a_row_with_nan_stays_in_its_row(dtype, d, f):
     torch.cuda.synchronize()
     bad = torch.isnan(L.y_perm.float()).any(dim=1).nonzero().flatten().tolist()
     assert bad == [7]
+
+
+@pytest.mark.parametrize("T, d, f, E, k, dtype, act, zipf", [
+    (1, 64, 64, 2, 1, "DT_BF16", "ACT_GELU", 0.0),        # one row, one K stage, half a column tile
+    (48, 128, 192, 2, 2, "DT_F16", "ACT_SWIGLU", 0.0),    # 48 rows per expert: the most that still goes this way
+    (96, 192, 320, 4, 2, "DT_BF16", "ACT_SWIGLU", 1.5),   # skewed: an expert with two row tiles, one with next to none
+    (190, 64, 4096, 8, 2, "DT_BF16", "ACT_GELU", 1.5),    # split along K, full 64-row tiles beside the split ones
+])
+def test_few_rows_per_expert(T, d, f, E, k, dtype, act, zipf):
+    from paper_2504_03871_amd import synth as S
+    from tests.test_gpu_parity import run_case
+    run_case(S.WORKLOADS["cfg1"].scaled(T=T, d=d, f=f, E=E, k=k, dtype=getattr(S, dtype), act=getattr(S, act), zipf_s=zipf))
