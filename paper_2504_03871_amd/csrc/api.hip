@@ -42,8 +42,10 @@ WsLayout ws_layout(const moe_cfg* c) {
   w.route_wrt = off;   // shared with the forward's gate weight in MFMA operand layout (never live together)
   off += align_up(std::max((size_t)c->d_model * c->E * 4, route_wfrag_bytes(c->d_model, c->E)), 256);
   w.ffn_split = off;
-  if (is_half(c) && split_k_applies(c->E, c->d_ff))
-    off += align_up(split_ws_bytes(c->E, std::max(c->d_model, 1)), 256);
+  if (is_half(c) && c->d_ff >= SPLIT_MIN_K) {
+    const size_t small = split_k_applies(c->E, c->d_ff) ? split_ws_bytes(c->E, c->d_model) : 0;
+    off += align_up(std::max(small, tail_ws_bytes(max_row_tiles((int)A, c->E, gemm_bf16_tile_rows()), c->d_model)), 256);
+  }
   w.ffn_bwd_dact = off;
   off += align_up((c->act == MOE_ACT_SWIGLU ? 2 : 1) * A * c->d_ff * elt_size(c), 256);
   w.total = off;
@@ -229,6 +231,14 @@ int moe_gemm_block_tile(int32_t kind, int64_t block, int32_t n_rt, int32_t n_ful
     if (out[0]) { out[1] = r.rt; out[3] = r.nt; out[4] = r.split_tile; out[5] = r.ksplit; }
     return MOE_OK;
   }
+  if (kind == 4) {
+    if (ntm < 1) return MOE_ERR_BAD_SHAPE;
+    const TailSplit t = tail_split(n_rt * ntn, ntm * 64);
+    RowBlock r;
+    out[0] = tail_split_block((int)block, n_rt, n_full_rt, ntn, false, t, r) ? 1 : 0;
+    if (out[0]) { out[1] = r.rt; out[2] = t.parts; out[3] = r.nt; out[4] = r.split_tile; out[5] = r.ksplit; }
+    return MOE_OK;
+  }
   if (kind == 1) {
     if (ntm < 1) return MOE_ERR_BAD_SHAPE;
     int slot, mt, nt;
@@ -344,8 +354,9 @@ int ffn_fwd_impl(const moe_cfg* cfg, const void* x_perm, const void* W1, const v
   g.A = hid; g.B = W2; g.B2 = nullptr; g.N = d; g.K = f;
   g.chunked = row_tiles_chunked(A, f, d, cfg->E, 1, (int)elt_size(cfg));
   g.C = y_perm; g.C2 = g.C3 = nullptr;
-  if (is_half(cfg) && split_k_applies(cfg->E, f))   // smallest row tiles: split-K (gemm.h)
-    g.split_ws = reinterpret_cast<float*>(static_cast<char*>(ws) + w.ffn_split);
+  g.split_small = is_half(cfg) && split_k_applies(cfg->E, f);   // split-K: smallest row tiles, last round (gemm.h)
+  g.split_tail = is_half(cfg) && !skinny && f >= SPLIT_MIN_K;
+  if (g.split_small || g.split_tail) g.split_ws = reinterpret_cast<float*>(static_cast<char*>(ws) + w.ffn_split);
   ProfScope ps(cfg, MOE_PROF_GEMM2_FWD, s);
   if (skinny) return launch_gemm_half_skinny(cfg->dtype, EPI_STORE, false, g, max_tiles, s);
   return launch_gemm(cfg, MODE_NN, EPI_STORE, false, false, g, max_tiles, s);
@@ -502,8 +513,11 @@ int moe_expert_ffn_bwd(const moe_cfg* cfg, const void* dy_perm, const void* x_pe
     }
   }
   ProfScope ps(cfg, MOE_PROF_DX_BWD, s);
-  if (bf && !swiglu && split_k_applies(cfg->E, f))   // the smallest row tiles of the GELU dx use split-K (gemm.h)
-    gx.split_ws = reinterpret_cast<float*>(static_cast<char*>(ws) + w.ffn_split);
+  // split-K of the GELU dx: the smallest row tiles; the last round only in a launch of its own (in a shared one the
+  // weight-gradient tiles fill it)
+  gx.split_small = bf && !swiglu && split_k_applies(cfg->E, f);
+  gx.split_tail = bf && !swiglu && !pair_x && f >= SPLIT_MIN_K;
+  if (gx.split_small || gx.split_tail) gx.split_ws = reinterpret_cast<float*>(static_cast<char*>(ws) + w.ffn_split);
   if (pair_x) return launch_gemm_half_pair(cfg->dtype, EPI_STORE, swiglu, gx, max_tiles, gw1, s);
   return launch_gemm(cfg, MODE_NT, EPI_STORE, false, swiglu, gx, max_tiles, s);
 }

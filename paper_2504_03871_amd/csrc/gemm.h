@@ -154,6 +154,43 @@ MOE_HD inline bool row_tile_block(int vb, int n_rt, int n_full_rt, int n_sp, int
   return true;
 }
 
+// Split-K of the last round.  256 blocks run at a time; the tiles behind the last whole round of 256 (all of them, when
+// there are fewer) leave most of the chip idle for the length of one tile.  In the plain-store GEMMs with long K these
+// r tiles are cut along K into `parts` blocks each, at most 256 in all, whose fp32 partial sums [slot][256][256] go to
+// the workspace; split_reduce adds them in part order.  A round costs about 26 us per 1024 K values, a slot about
+// 0.1 us (256 KB written and read again); the parts minimise the sum of the two, and a gain below 8 us, the extra
+// launch, is left.
+// y = hidden W2, with the reduction: 16 experts of 125 rows, d 2048, f 8192 (128 tiles) 198 -> 131 us; eight experts of 512
+// rows, d 1024, f 4096 (about 80 tiles) 101 -> 60; d 2048, f 8192, 16384 rows in 16 skewed experts, per step 4.56 -> 4.38 ms.
+constexpr int TAIL_SLOTS = 256, TAIL_MAX_PARTS = 8;
+struct TailSplit { int first, parts; };   // tiles from `first` on are split; parts == 1: none
+MOE_HD inline TailSplit tail_split(int n_tiles, int K) {
+  TailSplit t = {n_tiles, 1};
+  const int r = n_tiles % TAIL_SLOTS, round = K / 4;   // tenths of a microsecond
+  if (K < SPLIT_MIN_K || r == 0) return t;
+  int best = round - 80;
+  for (int p = 2; p <= TAIL_MAX_PARTS && p * r <= TAIL_SLOTS; ++p)
+    if (round / p + p * r < best) { best = round / p + p * r; t.parts = p; }
+  if (t.parts > 1) t.first = n_tiles - r;
+  return t;
+}
+inline size_t tail_ws_bytes(int max_tiles, int N) {   // 256 x 256 tiles
+  const long long slots = (long long)max_tiles * ((N + 255) / 256) * TAIL_MAX_PARTS;
+  return (size_t)(slots < TAIL_SLOTS ? slots : TAIL_SLOTS) * 256 * 256 * 4;
+}
+// Block vb of a row-tile GEMM launch whose last round is split: r.split_tile = the tile's index among the split ones.
+// Part p of a tile takes the K stages of 64 from p * stages / parts on.
+MOE_HD inline bool tail_split_block(int vb, int n_rt, int n_full_rt, int ntn, bool chunked, const TailSplit& t, RowBlock& r) {
+  r.split_tile = -1;
+  r.ksplit = 0;
+  if (vb >= t.first) {
+    r.split_tile = (vb - t.first) / t.parts;
+    r.ksplit = (vb - t.first) % t.parts;
+    vb = t.first + r.split_tile;
+  }
+  return block_to_tile(vb, n_rt, n_full_rt, ntn, chunked, r.rt, r.nt);
+}
+
 // Block vb of a weight-gradient launch: tile (expert slot in descending-size order, m tile, n tile).  A tile costs its
 // expert's row count, so every expert's ntm x ntn tiles are split evenly over the XCDs and a skewed load is even
 // across them; within the expert the order is the chunked patch order above, in bands of 16 (256 tiles at a time are
@@ -201,7 +238,8 @@ struct GemmArgs {
   const int32_t* ntiles;
   const int32_t* order;     // experts by descending share length (weight-gradient GEMMs start the heaviest first)
   const float* gelu_tab;    // bf16 GELU epilogues: Phi (forward) or gelu' (backward) over the bf16 numbers
-  float* split_ws;          // fp32 partial sums of the split row tiles, or NULL: no split-K (see SPLIT_K)
+  float* split_ws;          // fp32 partial sums of split tiles, or NULL: no split-K
+  int split_small, split_tail;   // which tiles may be split: the smallest row tiles (SPLIT_K), those of the last round (tail_split)
   const int32_t* offsets;
   const int32_t* kept;
   const int32_t* lo;
@@ -244,10 +282,12 @@ typedef __attribute__((address_space(3))) char lds_char;
 __device__ __forceinline__ unsigned lds_addr(const char* p) { return (unsigned)(uintptr_t)(const lds_char*)p; }
 typedef u32x4 rsrc_t;
 __device__ __forceinline__ rsrc_t make_rsrc(const void* base, size_t bytes) {
-  const unsigned long long a = (unsigned long long)base;
-  const unsigned n = bytes > 0xffffffffull ? 0xffffffffu : (unsigned)bytes;
+  // block-uniform; values that went through a vector division come back to scalar registers here
+  const unsigned long long p = (unsigned long long)base;
+  const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)p), hi = __builtin_amdgcn_readfirstlane((unsigned)(p >> 32));
+  const unsigned n = __builtin_amdgcn_readfirstlane(bytes > 0xffffffffull ? 0xffffffffu : (unsigned)bytes);
   // raw buffer: base address, stride 0, byte count, 32-bit untyped data format
-  return rsrc_t{(unsigned)a, (unsigned)(a >> 32) & 0xffffu, n, 0x00020000u};
+  return rsrc_t{lo, hi & 0xffffu, n, 0x00020000u};
 }
 
 // 16 bytes per lane from a buffer straight into LDS: lane l of the wave lands at LDS byte address

@@ -10,11 +10,17 @@ namespace moe {
 constexpr int T_BM = 256, T_BN = 256, T_BN_DUAL = 128, T_WGM = 2, T_WGN = 4;
 int gemm_bf16_tile_rows() { return T_BM; }
 
-// adds the SPLIT_K partial sums of every split row tile and writes the 16-bit rows of C [rows][N]
+// blocks of a split launch beyond one per tile
+static long long split_blocks(const GemmArgs& g, long long ntn) {
+  const long long small = g.split_small ? (long long)g.E * ntn * (SPLIT_K - 1) : 0;
+  return g.split_tail && small < TAIL_SLOTS ? TAIL_SLOTS : small;
+}
+// adds the partial sums of every split tile and writes the 16-bit rows of C [rows][N]
 template <typename ST>
-static int launch_split_reduce(const GemmArgs& g, hipStream_t s) {
-  const dim3 grid((SPLIT_ROWS * (g.N / 4) + 255) / 256, g.E);
-  split_reduce_kernel<ST><<<grid, 256, 0, s>>>(g);
+static int launch_split_reduce(const GemmArgs& g, long long tiles, hipStream_t s) {
+  const long long small = g.split_small ? (long long)g.E * ((SPLIT_ROWS * (g.N / 4) + 255) / 256) : 0;
+  const long long tail = g.split_tail ? (tiles < TAIL_SLOTS / 2 ? tiles : TAIL_SLOTS / 2) * (256 / TAIL_REDUCE_ROWS) : 0;
+  split_reduce_kernel<ST><<<dim3((unsigned)(small > tail ? small : tail)), 256, 0, s>>>(g);
   return launch_status();
 }
 
@@ -35,11 +41,10 @@ static int launch_one(const GemmArgs& g, int max_tiles, hipStream_t s) {
   if (MODE == MODE_TN) tiles = (long long)((ntn * ((g.M + T_BM - 1) / T_BM) + NUM_XCD - 1) / NUM_XCD * NUM_XCD) * g.E;
   else tiles = (long long)ntn * max_tiles;
   const bool split = MODE != MODE_TN && EPI == EPI_STORE && !CHAIN && g.split_ws != nullptr;
-  if (split) tiles += (long long)g.E * ntn * (SPLIT_K - 1);   // every split row tile: SPLIT_K blocks per column tile instead of one
-  kern<<<dim3(gemm_bf16_grid(tiles)), T_WGM * T_WGN * 64, lds, s>>>(g);
+  kern<<<dim3(gemm_bf16_grid(tiles + (split ? split_blocks(g, ntn) : 0))), T_WGM * T_WGN * 64, lds, s>>>(g);
   int rc = launch_status();
   if (rc != MOE_OK || !split) return rc;
-  return launch_split_reduce<ST>(g, s);
+  return launch_split_reduce<ST>(g, tiles, s);
 }
 
 // A row-tile GEMM (NT) and a weight-gradient GEMM (TN) in one launch; the first one's blocks come first.
@@ -60,7 +65,7 @@ static int launch_pair(const GemmArgs& g1, int max_tiles, const GemmArgs& g2, hi
   // (a plain-store first GEMM may split its smallest row tiles along K: SPLIT_K blocks per column tile, see gemm.h)
   const int ntn1 = (g1.N + T_BN - 1) / T_BN;
   const bool split = EPI1 == EPI_STORE && !CHAIN1 && g1.split_ws != nullptr;
-  const long long t1 = (long long)ntn1 * max_tiles + (split ? (long long)g1.E * ntn1 * (SPLIT_K - 1) : 0);
+  const long long tiles1 = (long long)ntn1 * max_tiles, t1 = tiles1 + (split ? split_blocks(g1, ntn1) : 0);
   const long long n1 = (t1 + NUM_XCD - 1) / NUM_XCD * NUM_XCD;
   const long long p2 = (long long)((g2.N + T_BN - 1) / T_BN) * ((g2.M + T_BM - 1) / T_BM);
   const long long n2 = (p2 + NUM_XCD - 1) / NUM_XCD * NUM_XCD * g2.E;
@@ -68,7 +73,7 @@ static int launch_pair(const GemmArgs& g1, int max_tiles, const GemmArgs& g2, hi
   kern<<<dim3(gemm_bf16_grid(n1 + n2)), T_WGM * T_WGN * 64, lds, s>>>(g1, g2, (int)n1);
   const int rc = launch_status();
   if (rc != MOE_OK || !split) return rc;
-  return launch_split_reduce<ST>(g1, s);
+  return launch_split_reduce<ST>(g1, tiles1, s);
 }
 
 template <typename ST>
@@ -112,12 +117,12 @@ static int launch_skinny(const GemmArgs& g, int max_tiles, hipStream_t s) {
   }
   const int ntn = (g.N + SKINNY_BN - 1) / SKINNY_BN;
   const bool split = EPI == EPI_STORE && g.split_ws != nullptr;
-  const long long tiles = (long long)ntn * max_tiles + (split ? (long long)g.E * ntn * (SPLIT_K - 1) : 0);
-  if (tiles > 0x7fffffffll) return MOE_ERR_BAD_SHAPE;
-  kern<<<dim3(gemm_bf16_grid(tiles)), 256, lds, s>>>(g);
+  const long long tiles = (long long)ntn * max_tiles, blocks = tiles + (split ? split_blocks(g, ntn) : 0);
+  if (blocks > 0x7fffffffll) return MOE_ERR_BAD_SHAPE;
+  kern<<<dim3(gemm_bf16_grid(blocks)), 256, lds, s>>>(g);
   const int rc = launch_status();
   if (rc != MOE_OK || !split) return rc;
-  return launch_split_reduce<ST>(g, s);
+  return launch_split_reduce<ST>(g, tiles, s);
 }
 template <typename ST>
 static int skinny_for(int epi, bool dual, const GemmArgs& g, int max_tiles, hipStream_t s) {

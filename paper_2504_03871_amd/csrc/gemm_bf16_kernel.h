@@ -237,7 +237,9 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs& g, const int vb, 
   const int wm = wave / WGN, wn = wave % WGN;
 
   int e, row0, mvalid, klen, m0 = 0, n0;
-  int split_tile = -1, ksplit = 0, kbase = 0;   // >= 0: this block computes one K part of a split row tile
+  int kbase = 0;
+  float* part_sums = nullptr;   // this block computes one K part of a split tile: where its fp32 sums go, and their pitch
+  int part_pitch = 0;
   {
     const int ntn = (g.N + BN - 1) / BN;
     int rt, nt;
@@ -258,20 +260,36 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs& g, const int vb, 
     } else {
       constexpr bool CAN_SPLIT = (EPI == EPI_STORE && !CHAIN);
       const int n_rt = g.ntiles[0];
-      // split-K (gemm.h): the last n_sp row tiles are not part of the regular numbering; their blocks
-      // follow it, SPLIT_K per (row tile, column tile), each with a K range of its own
-      const int n_sp = (CAN_SPLIT && g.split_ws != nullptr) ? g.ntiles[2] : 0;
       RowBlock rb;
-      if (!row_tile_block(vb, n_rt, g.ntiles[1], n_sp, ntn, g.chunked != 0, rb)) return;
-      rt = rb.rt;
-      nt = rb.nt;
       klen = g.K;
-      if (rb.split_tile >= 0) {
-        split_tile = rb.split_tile;
-        ksplit = rb.ksplit;
-        klen = g.K / SPLIT_K;
-        kbase = ksplit * klen;
+      TailSplit ts = {0, 1};
+      if (CAN_SPLIT && g.split_tail) ts = tail_split(n_rt * ntn, g.K);
+      if (CAN_SPLIT && ts.parts > 1) {          // the tiles of the last round are split along K
+        if (!tail_split_block(vb, n_rt, g.ntiles[1], ntn, g.chunked != 0, ts, rb)) return;
+        if (rb.split_tile >= 0) {
+          const int stages = g.K / BKT, k0 = rb.ksplit * stages / ts.parts;
+          kbase = k0 * BKT;
+          klen = ((rb.ksplit + 1) * stages / ts.parts - k0) * BKT;
+          part_sums = g.split_ws + (size_t)(rb.split_tile * ts.parts + rb.ksplit) * (BM * BN);
+          part_pitch = BN;
+        }
+      } else {
+        // or the smallest row tiles: the last n_sp row tiles are not part of the regular numbering; their blocks
+        // follow it, SPLIT_K per (row tile, column tile), each with a K range of its own
+        const int n_sp = (CAN_SPLIT && g.split_small) ? g.ntiles[2] : 0;
+        if (!row_tile_block(vb, n_rt, g.ntiles[1], n_sp, ntn, g.chunked != 0, rb)) return;
+        if (CAN_SPLIT && rb.split_tile >= 0) {
+          klen = g.K / SPLIT_K;
+          kbase = rb.ksplit * klen;
+          part_sums = g.split_ws + (size_t)(rb.split_tile * SPLIT_K + rb.ksplit) * SPLIT_ROWS * g.N + rb.nt * BN;
+          part_pitch = g.N;
+        }
       }
+      // block-uniform, but divided in vector registers: back to scalar ones
+      rt = __builtin_amdgcn_readfirstlane(rb.rt);
+      nt = __builtin_amdgcn_readfirstlane(rb.nt);
+      kbase = __builtin_amdgcn_readfirstlane(kbase);
+      klen = __builtin_amdgcn_readfirstlane(klen);
       const RowTile t = g.tiles[rt];
       e = t.e;
       row0 = t.row0;
@@ -581,8 +599,8 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs& g, const int vb, 
         const int m = (i * WGM + wm) * 32 + p * RPP + rr;
         const int n = wn * C + c4 * 4;
         if (m < mvalid && n < nvalid) {
-          if (MODE != MODE_TN && split_tile >= 0) {   // fp32 partial sum of this block's K part
-            *reinterpret_cast<f32x4*>(g.split_ws + (((size_t)split_tile * SPLIT_K + ksplit) * SPLIT_ROWS + m) * g.N + n0 + n) = va[p];
+          if (MODE != MODE_TN && EPI == EPI_STORE && !CHAIN && part_sums != nullptr) {   // fp32 partial sum of this block's K part
+            *reinterpret_cast<f32x4*>(part_sums + m * part_pitch + n) = va[p];
           } else if constexpr (MODE == MODE_TN) {   // fp32 weight gradient of expert e, 16 bytes per lane
             if (g.accumulate) __builtin_nontemporal_store(old[MODE == MODE_TN ? i & 1 : 0][MODE == MODE_TN ? p : 0] + va[p], grad_at(i, p));
             else __builtin_nontemporal_store(va[p], grad_at(i, p));
@@ -596,22 +614,50 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs& g, const int vb, 
   }
 }
 
-// Second half of split-K: C[row][n..n+3] = sum over the SPLIT_K parts, in part order, of the fp32 partial
-// sums of split row tile blockIdx.y; a thread owns four adjacent columns of one row.
+// Second half of split-K: adds the parts of every split tile in part order and writes the 16-bit rows; a thread owns
+// four adjacent columns of one row.  Whether the tiles of the last round or the smallest row tiles are split follows
+// from the tile counts, as in the GEMM; surplus blocks exit.
+constexpr int TAIL_REDUCE_ROWS = 16;   // rows of a tile a block adds up
 template <typename ST>
 __global__ __launch_bounds__(256) void split_reduce_kernel(GemmArgs g) {
-  const int n_sp = g.ntiles[2], st = blockIdx.y;
+  const int n_rt = g.ntiles[0], ntn = (g.N + 255) / 256;
+  TailSplit ts = {0, 1};
+  if (g.split_tail) ts = tail_split(n_rt * ntn, g.K);
+  auto put = [&](size_t row, int n, const f32x4& v) {
+    *reinterpret_cast<u32x2*>(reinterpret_cast<ST*>(g.C) + row * g.N + n) = u32x2{Half16<ST>::pack2(v[0], v[1]), Half16<ST>::pack2(v[2], v[3])};
+  };
+  if (ts.parts > 1) {
+    constexpr int PER = 256 / TAIL_REDUCE_ROWS;   // blocks per tile
+    const int q = blockIdx.x / PER, n = (threadIdx.x & 63) * 4;
+    if (q >= n_rt * ntn - ts.first) return;
+    int rt, nt;
+    block_to_tile(ts.first + q, n_rt, g.ntiles[1], ntn, g.chunked != 0, rt, nt);
+    const RowTile t = g.tiles[rt];
+    if (nt * 256 + n >= g.N) return;
+#pragma unroll
+    for (int i = 0; i < TAIL_REDUCE_ROWS / 4; ++i) {
+      const int m = (blockIdx.x % PER) * TAIL_REDUCE_ROWS + i * 4 + threadIdx.x / 64;
+      if (m >= t.nrows) return;
+      const float* src = g.split_ws + (size_t)q * ts.parts * 65536 + m * 256 + n;
+      f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int p = 0; p < TAIL_MAX_PARTS; ++p)
+        if (p < ts.parts) sum += *reinterpret_cast<const f32x4*>(src + (size_t)p * 65536);
+      put(t.row0 + m, nt * 256 + n, sum);
+    }
+    return;
+  }
+  if (!g.split_small) return;
+  const int n_sp = g.ntiles[2], per_row = g.N / 4, per_tile = (SPLIT_ROWS * per_row + 255) / 256, st = blockIdx.x / per_tile;
   if (st >= n_sp) return;
-  const RowTile t = g.tiles[g.ntiles[0] - n_sp + st];
-  const int per_row = g.N / 4, i = blockIdx.x * 256 + threadIdx.x;
-  const int m = i / per_row, n = (i % per_row) * 4;
+  const RowTile t = g.tiles[n_rt - n_sp + st];
+  const int i = (blockIdx.x % per_tile) * 256 + threadIdx.x, m = i / per_row, n = (i % per_row) * 4;
   if (m >= t.nrows) return;
   f32x4 sum = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int ks = 0; ks < SPLIT_K; ++ks)
     sum += *reinterpret_cast<const f32x4*>(g.split_ws + (((size_t)st * SPLIT_K + ks) * SPLIT_ROWS + m) * g.N + n);
-  *reinterpret_cast<u32x2*>(reinterpret_cast<ST*>(g.C) + (size_t)(t.row0 + m) * g.N + n) =
-      u32x2{Half16<ST>::pack2(sum[0], sum[1]), Half16<ST>::pack2(sum[2], sum[3])};
+  put(t.row0 + m, n, sum);
 }
 
 template <typename ST, int MODE, int EPI, bool DUAL, bool CHAIN, int BM, int BN, int WGM, int WGN>

@@ -37,7 +37,7 @@ __global__ __launch_bounds__(256, 2) void gemm_skinny_kernel(GemmArgs g) {
 
   const int ntn = (g.N + BN - 1) / BN, n_rt = g.ntiles[0];
   constexpr bool CAN_SPLIT = EPI == EPI_STORE;
-  const int n_sp = (CAN_SPLIT && g.split_ws != nullptr) ? g.ntiles[2] : 0;
+  const int n_sp = (CAN_SPLIT && g.split_small) ? g.ntiles[2] : 0;
   RowBlock rb;
   if (!row_tile_block(blockIdx.x, n_rt, g.ntiles[1], n_sp, ntn, false, rb)) return;
   const RowTile t = g.tiles[rb.rt];

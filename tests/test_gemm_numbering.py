@@ -83,3 +83,23 @@ def test_chunked_row_tile_numbering_covers_every_tile_once(n_full, n_part, ntn):
     assert sorted((x[1], x[3]) for x in t if x[0]) == list(itertools.product(range(n_rt), range(ntn)))
     assert not any(x[0] for x in t[n_rt * ntn:])
     assert all(x[1] >= n_full for x in t[n_full * ntn:n_rt * ntn])      # partly filled row tiles last
+
+
+@pytest.mark.parametrize("n_full, n_part, ntn, stages", [(0, 3, 5, 33), (1, 0, 1, 32), (61, 8, 4, 64), (16, 0, 8, 128), (30, 1, 9, 224), (64, 0, 4, 64), (40, 3, 5, 31)])
+def test_tail_split_numbering_covers_every_tile_and_k_part_once(n_full, n_part, ntn, stages):
+    """Fewer tiles than one round, one round and a few, exactly one round, K too short; stages that parts do not divide."""
+    n_rt = n_full + n_part
+    t = [x for x in (B.moe_gemm_block_tile(4, vb, n_rt, n_full, 0, stages, ntn) for vb in range(n_rt * ntn + 256)) if x[0]]
+    parts, tail = t[0][2], n_rt * ntn % 256
+    whole = [(x[1], x[3]) for x in t if x[4] < 0]
+    split = [(x[1], x[3], x[5]) for x in t if x[4] >= 0]
+    tiles = {(r, c) for r, c, _ in split}
+    assert sorted(whole + list(tiles)) == list(itertools.product(range(n_rt), range(ntn)))
+    assert len(set(split)) == len(split) == len(tiles) * parts
+    assert len(split) <= 256 and len(tiles) in (0, tail)
+    assert (parts > 1) == bool(split)
+    if stages * 64 < 2048 or tail == 0:
+        assert not split
+    # slot (index among the split tiles, part) of every block: 0 .. 255, each once
+    assert sorted(x[4] * parts + x[5] for x in t if x[4] >= 0) == list(range(len(split)))
+    assert parts <= 8 <= stages

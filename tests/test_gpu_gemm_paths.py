@@ -79,3 +79,25 @@ def test_few_rows_per_expert(T, d, f, E, k, dtype, act, zipf):
     from paper_2504_03871_amd import synth as S
     from tests.test_gpu_parity import run_case
     run_case(S.WORKLOADS["cfg1"].scaled(T=T, d=d, f=f, E=E, k=k, dtype=getattr(S, dtype), act=getattr(S, act), zipf_s=zipf))
+
+
+@pytest.mark.parametrize("T, d, f, E, k, dtype, act", [
+    (700, 192, 2112, 4, 2, "DT_BF16", "ACT_GELU"),        # 33 stages of 64 in 8 parts, full and partly filled tiles
+    (450, 320, 2048, 3, 1, "DT_F16", "ACT_SWIGLU"),       # a last column tile of 64
+    (4096, 128, 2048, 40, 2, "DT_BF16", "ACT_SWIGLU"),    # expert-major tile list
+    (9000, 1088, 2048, 4, 2, "DT_F16", "ACT_GELU"),       # a whole round before the split tiles
+])
+def test_last_round_split_along_k(T, d, f, E, k, dtype, act):
+    """y = hidden W2 with the tiles of the last round split along K, against the same rows multiplied in fp64."""
+    import torch
+    from paper_2504_03871_amd import synth as S
+    L = filled_layer(T, d, f, E, k, {"DT_BF16": "bf16", "DT_F16": "f16"}[dtype], getattr(S, act))
+    L.forward()
+    torch.cuda.synchronize()
+    hid = L.saved_plane(2 if act == "ACT_SWIGLU" else 1)
+    tol = {"DT_BF16": 2.0 ** -9, "DT_F16": 2.0 ** -12}[dtype]   # one rounding of the result: 2^-9 (2^-12) relative at most
+    for e in range(E):
+        o, n = int(L.offsets[e]), int(L.kept[e])
+        ref = hid[o:o + n].double() @ L.W2[e].double()
+        err = (L.y_perm[o:o + n].double() - ref).norm() / ref.norm()
+        assert err < tol, (e, float(err))
