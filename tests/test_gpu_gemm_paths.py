@@ -101,3 +101,21 @@ def test_last_round_split_along_k(T, d, f, E, k, dtype, act):
         ref = hid[o:o + n].double() @ L.W2[e].double()
         err = (L.y_perm[o:o + n].double() - ref).norm() / ref.norm()
         assert err < tol, (e, float(err))
+
+
+@pytest.mark.parametrize("A", [1, 1023, 1024, 1025, 4096, 4097])
+@pytest.mark.parametrize("E, cap", [(1, 0), (8, 0), (17, 60), (256, 5)])
+def test_dispatch_of_short_lists(A, E, cap):
+    """One block, whole and ragged blocks, and both sides of the line up to which a block counts the other blocks'
+    ids itself; few and many experts, with and without capacity, ids outside [0, E) among them.  Exact."""
+    import numpy as np
+    import torch
+    from tests import gpu_util as U
+    idx = np.random.default_rng(A * E).integers(-1, E + 1, size=(A, 1)).astype(np.int32)
+    cfg = B.make_cfg(A, 64, 64, E, 1, capacity=cap)
+    out = [torch.full((n,), -7, dtype=torch.int32, device="cuda") for n in (E, E, E + 1, A, A)]
+    ws = torch.empty(B.moe_workspace_bytes(cfg), dtype=torch.uint8, device="cuda")
+    B.moe_dispatch(cfg, None, torch.from_numpy(idx).cuda(), None, None, *out, None, ws)
+    torch.cuda.synchronize()
+    for name, got, want in zip(("counts", "kept", "offsets", "row_of", "src_of"), out, U.O.dispatch_plan(idx, E, cap)):
+        assert (got.cpu().numpy() == want).all(), name
