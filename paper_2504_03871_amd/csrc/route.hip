@@ -404,7 +404,7 @@ __global__ __launch_bounds__(NW * 64) void route_mfma_kernel(
 
 // ---------------------------------------------------------------- backward
 // Four small kernels.
-//  1. WrT[e][i] = Wr[i][e], so that the input-gradient kernel reads contiguous weights.
+//  1. WrT[e][i] = Wr[i][e], so that the input-gradient kernel reads contiguous weights (not for few, short rows).
 //  2. One wave per token: dsel_j = w_j (dw_j - sum_i w_i dw_i); writes the token's d_logits row and
 //     adds sum_j dsel_j WrT[e_j][:] to dx[t][:].
 //  3. dWr = x^T d_logits, dense: token slices accumulate [16 experts] x [columns] blocks in registers, one row
@@ -415,9 +415,10 @@ __global__ void wr_transpose_kernel(const float* __restrict__ Wr, float* __restr
   if (i < d * E) WrT[(size_t)(i % E) * d + i / E] = Wr[i];
 }
 
-template <typename T>
+// TRANSPOSED: the weight comes as WrT [E][d]; else it is Wr [d][E] itself, read element by element.
+template <typename T, bool TRANSPOSED>
 __global__ __launch_bounds__(256) void route_bwd_dx_kernel(
-    const float* __restrict__ WrT, const int32_t* __restrict__ topk_idx, const float* __restrict__ topk_w,
+    const float* __restrict__ W, const int32_t* __restrict__ topk_idx, const float* __restrict__ topk_w,
     const float* __restrict__ d_topk_w, float* __restrict__ d_logits, T* __restrict__ dx, int Tn, int d, int E, int k) {
   constexpr int VN = Vec16<T>::N;
   const int lane = threadIdx.x & (WAVE - 1);
@@ -461,10 +462,15 @@ __global__ __launch_bounds__(256) void route_bwd_dx_kernel(
 #pragma unroll
       for (int j = 0; j < MOE_MAX_K; ++j)
         if (j < k) {
-          const float* wr = WrT + (size_t)max(ej[j], 0) * d + c;
+          const size_t e = max(ej[j], 0);
 #pragma unroll
           for (int i = 0; i < VN; i += 4) {
-            const float4 w4 = *reinterpret_cast<const float4*>(wr + i);
+            float4 w4;
+            if constexpr (TRANSPOSED) w4 = *reinterpret_cast<const float4*>(W + e * d + c + i);
+            else {
+              const float* wr = W + (size_t)(c + i) * E + e;
+              w4 = make_float4(wr[0], wr[E], wr[2 * E], wr[3 * E]);
+            }
             acc[i] = fmaf(ds[j], w4.x, acc[i]);
             acc[i + 1] = fmaf(ds[j], w4.y, acc[i + 1]);
             acc[i + 2] = fmaf(ds[j], w4.z, acc[i + 2]);
@@ -756,18 +762,28 @@ int launch_route(const moe_cfg* c, const void* x, const float* Wr, const float* 
   return launch_status();
 }
 
+// Few tokens of short rows: the input-gradient kernel reads the weight where it lies, because the transpose's launch
+// costs more than scattered reads of a weight that the L2 holds.  Gate backward, transposed -> direct, us: T 512, d 128
+// 17.9 -> 15.5 and d 512 18.4 -> 15.7 (E 8, k 2), T 256, d 1024, E 32 17.4 -> 15.5; beyond the line T 256, d 2048 16.9 ->
+// 19.6, T 1000, d 516 19.2 -> 19.4, T 3000, d 516 23.1 -> 30.8, T 512, d 2048, E 128, k 8 30.0 -> 60.2.
+static bool route_bwd_direct(const moe_cfg* c) {
+  const long long per_token = (long long)c->d_model * c->k;
+  return c->E <= 32 && per_token <= 2048 && c->T * per_token <= 1 << 19;
+}
+
 template <typename T>
 static int route_bwd_typed(const moe_cfg* c, const void* x, const float* Wr, const int32_t* idx, const float* w,
                            const float* dw, float* d_logits, float* dWr, void* dx, int accumulate, float* partials,
                            float* WrT, hipStream_t s) {
-  const int n = c->d_model * c->E;
+  const int n = c->d_model * c->E, grid = (c->T + 3) / 4;
   int rc;
-  if (dx != nullptr) {
+  if (dx != nullptr && !route_bwd_direct(c)) {
     wr_transpose_kernel<<<(n + 255) / 256, 256, 0, s>>>(Wr, WrT, c->d_model, c->E);
     if ((rc = launch_status()) != MOE_OK) return rc;
+    route_bwd_dx_kernel<T, true><<<grid, 256, 0, s>>>(WrT, idx, w, dw, d_logits, (T*)dx, c->T, c->d_model, c->E, c->k);
+  } else {
+    route_bwd_dx_kernel<T, false><<<grid, 256, 0, s>>>(Wr, idx, w, dw, d_logits, (T*)dx, c->T, c->d_model, c->E, c->k);
   }
-  const int grid = (c->T + 3) / 4;
-  route_bwd_dx_kernel<T><<<grid, 256, 0, s>>>(WrT, idx, w, dw, d_logits, (T*)dx, c->T, c->d_model, c->E, c->k);
   if ((rc = launch_status()) != MOE_OK) return rc;
   if (dWr == nullptr) return MOE_OK;
   if constexpr (!std::is_same<T, float>::value) {

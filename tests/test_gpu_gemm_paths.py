@@ -119,3 +119,14 @@ def test_dispatch_of_short_lists(A, E, cap):
     torch.cuda.synchronize()
     for name, got, want in zip(("counts", "kept", "offsets", "row_of", "src_of"), out, U.O.dispatch_plan(idx, E, cap)):
         assert (got.cpu().numpy() == want).all(), name
+
+
+@pytest.mark.parametrize("T, d, E, k, dtype", [
+    (2049, 128, 3, 2, "DT_BF16"), (2048, 128, 3, 2, "DT_BF16"),     # both sides of the line for few, short rows
+    (37, 36, 5, 3, "DT_F32"), (100, 1024, 32, 2, "DT_F16"), (100, 512, 33, 4, "DT_F16"),
+])
+def test_gate_backward_of_short_inputs(T, d, E, k, dtype):
+    from paper_2504_03871_amd import synth as S
+    from tests.test_gpu_parity import run_case
+    base = S.WORKLOADS["cfg0" if dtype == "DT_F32" else "cfg1"]
+    run_case(base.scaled(T=T, d=d, f=128, E=E, k=k, dtype=getattr(S, dtype)))
