@@ -149,12 +149,14 @@ static int check_slices(const int32_t* lo, const int32_t* hi) {
   return ((lo == nullptr) != (hi == nullptr)) ? MOE_ERR_BAD_SLICE : MOE_OK;
 }
 
+static int tile_rows_for(const moe_cfg* c) {   // both row-tile GEMMs of a pass share one map: the wider decides
+  return is_half(c) ? gemm_bf16_tile_rows() : f32_tile_rows((long long)c->T * c->k, c->E / 2, std::max(c->d_model, c->d_ff));
+}
 static int launch_gemm(const moe_cfg* c, int mode, int epi, bool dual, bool chain, const GemmArgs& g, int max_tiles,
                        hipStream_t s) {
   return is_half(c) ? launch_gemm_half(c->dtype, mode, epi, dual, chain, g, max_tiles, s)
-                    : launch_gemm_f32(mode, epi, dual, chain, g, max_tiles, s);
+                    : launch_gemm_f32(mode, epi, dual, chain, g, tile_rows_for(c), max_tiles, s);
 }
-static int tile_rows_for(const moe_cfg* c) { return is_half(c) ? gemm_bf16_tile_rows() : 64; }
 
 }  // namespace moe
 

@@ -86,7 +86,7 @@ inline RouteBwdMfmaGeom route_bwd_mfma_geom(int T, int d, int E) {
   if (gm.rows < 1) gm.rows = 1;
   return gm;
 }
-constexpr int TILE_ROWS_MIN = 64;      // smallest row-tile height any grouped GEMM uses (sizes the tile map)
+constexpr int TILE_ROWS_MIN = 32;      // smallest row-tile height any grouped GEMM uses (sizes the tile map)
 
 // ---------------------------------------------------------------- device side
 #ifdef __HIPCC__

@@ -164,30 +164,37 @@ int launch_tile_map(const int32_t* offsets, const int32_t* kept, const int32_t* 
 // T 2000, d 516, f 1540, eight experts, against the LDS-tiled FMA kernel it replaces: SwiGLU
 // forward 264 -> 144 us, y 177 -> 90, a weight gradient 139 -> 80, dx 343 -> 175 (42 -> 78 TFLOP/s over the step's GEMMs).
 //
+// Problems with few tiles take 32 x 64 ones (BM = 32, line in gemm.h): two waves share 16 rows, each with every other run
+// of 16 K values, and add their sums through LDS at the end, so twice the blocks walk K at twice the speed.
+//
 // K order: lane group g = lane / 16 supplies K value 4 g + s of every run of 16 in step s, for both operands, so a
 // 16-byte read along K serves four steps.  Columns: lane c = lane % 16 holds columns 4 c .. 4 c + 3 of the wave's 64
 // as column tiles j = 0 .. 3, so a 16-byte read across columns serves four tiles and the results leave as 16-byte rows.
 constexpr int SB = 64;   // tile edge
 constexpr int SK = 32;   // K values per stage
-constexpr int F_TILE = SB * SK * 4, F_CH = F_TILE / (256 * 16);   // bytes of an operand tile; 16-byte chunks per thread
+
+// bytes of an operand tile of R rows (or columns); 16-byte chunks of it per thread
+constexpr int f32_tile_bytes(int r) { return r * SK * 4; }
+constexpr int f32_chunks(int r) { return f32_tile_bytes(r) / (256 * 16); }
 
 // Operand tiles in LDS.  K contiguous in memory: [64][32], 128-byte rows whose eight chunks are XOR-swizzled by the
 // row pair (16 lanes reading one chunk of 16 consecutive rows hit 16 different 16-byte bank groups).  K strided:
 // [32][64], 256-byte rows whose 64-byte granules are XOR-swizzled by (K row / 4), so the four lane groups, which read
 // K rows four apart, use different banks.
 __device__ __forceinline__ int f32_kc_off(int row, int chunk) { return row * 128 + ((chunk ^ ((row >> 1) & 7)) << 4); }
-__device__ __forceinline__ int f32_ks_off(int krow, int col_byte) { return krow * 256 + (col_byte ^ (((krow >> 2) & 3) << 6)); }
+template <int R>
+__device__ __forceinline__ int f32_ks_off(int krow, int col_byte) { return krow * (R * 4) + (col_byte ^ (((krow >> 2) & (R / 16 - 1)) << 6)); }
 
 // Chunk id of a tile (its 16 bytes lie at LDS byte 16 id): the operand's byte offset and its first K index.  PERM: LDS
 // row r holds operand row 4 (r % 16) + r / 16, the column order above.
-template <bool KC, bool PERM>
+template <bool KC, bool PERM, int R>
 __device__ __forceinline__ void f32_chunk(int id, unsigned pitch, unsigned& off, int& k) {
   if constexpr (KC) {
     const int r = id >> 3, c = (id & 7) ^ ((r >> 1) & 7), row = PERM ? 4 * (r & 15) + (r >> 4) : r;
     off = (unsigned)row * pitch + c * 16u;
     k = c * 4;
   } else {
-    const int r = id >> 4, c = (id & 15) ^ (((r >> 2) & 3) << 2);
+    const int r = id / (R / 4), c = (id % (R / 4)) ^ (((r >> 2) & (R / 16 - 1)) << 2);
     off = (unsigned)r * pitch + c * 16u;
     k = r;
   }
@@ -228,27 +235,29 @@ __device__ __forceinline__ void epilogue_f32x4(const GemmArgs& g, size_t idx, co
   }
 }
 
-template <int MODE, int EPI, bool DUAL, bool CHAIN>
-__global__ __launch_bounds__(256, 3) void gemm_f32_kernel(GemmArgs g) {
+template <int MODE, int EPI, bool DUAL, bool CHAIN, int BM>
+__global__ __launch_bounds__(256, BM == SB ? 3 : 4) void gemm_f32_kernel(GemmArgs g) {
   constexpr bool A_KC = MODE != MODE_TN, B_KC = MODE == MODE_NT;
-  constexpr int STAGE = F_TILE * (DUAL ? 3 : 2), NBUF = DUAL ? 2 : 3;   // 48 KB either way
+  constexpr int BANDS = BM / 16, KH = 4 / BANDS;                        // KH waves share a band, each with every KH-th run of 16 K values
+  constexpr int A_TILE = f32_tile_bytes(BM), B_TILE = f32_tile_bytes(SB), CHA = f32_chunks(BM), CHB = f32_chunks(SB);
+  constexpr int STAGE = A_TILE + B_TILE * (DUAL ? 2 : 1), NBUF = DUAL ? 2 : 3;   // 48 KB either way (BM 32: 36 and 40 KB)
   constexpr int AHEAD = NBUF - 1;                                       // stages requested ahead of the one in use
-  constexpr int L = F_CH * (DUAL ? 3 : 2);                              // loads per thread and stage
+  constexpr int L = CHA + CHB * (DUAL ? 2 : 1);                         // loads per thread and stage
   __shared__ __attribute__((aligned(1024))) char smem[NBUF * STAGE];
   const int tid = threadIdx.x, lane = tid & 63, c = lane & 15, grp = lane >> 4;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), band = wave % BANDS, kh = wave / BANDS;
   const int ntn = (g.N + SB - 1) / SB;
   int e, row0, mvalid, klen, m0 = 0, nt;
   if constexpr (MODE == MODE_TN) {
     int slot, mt;
-    if (!dw_block(blockIdx.x, (g.M + SB - 1) / SB, ntn, slot, mt, nt)) return;
+    if (!dw_block(blockIdx.x, (g.M + BM - 1) / BM, ntn, slot, mt, nt)) return;
     e = g.order[slot];
-    m0 = mt * SB;
+    m0 = mt * BM;
     int l, h;
     share_of(g.lo, g.hi, g.kept[e], e, l, h);
     row0 = g.offsets[e] + l;
     klen = h - l;
-    mvalid = min(SB, g.M - m0);
+    mvalid = min(BM, g.M - m0);
     if (klen == 0 && g.accumulate) return;
   } else {
     RowBlock rb;
@@ -285,26 +294,25 @@ __global__ __launch_bounds__(256, 3) void gemm_f32_kernel(GemmArgs g) {
   const rsrc_t ra2 = make_rsrc(reinterpret_cast<const float*>(CHAIN ? g.A2 : g.A) + aoff, abytes);
   const rsrc_t rb2 = make_rsrc(reinterpret_cast<const float*>(CHAIN || DUAL ? g.B2 : g.B) + boff, bbytes);
   const int KT1 = (klen + SK - 1) / SK, KT = CHAIN ? 2 * KT1 : KT1;   // a chained GEMM runs its two operand pairs back to back
-  unsigned a_vo[F_CH], b_vo[F_CH];
-  int a_k[F_CH], b_k[F_CH];
+  unsigned a_vo[CHA], b_vo[CHB];
+  int a_k[CHA], b_k[CHB];
 #pragma unroll
-  for (int i = 0; i < F_CH; ++i) {
-    f32_chunk<A_KC, false>(tid + 256 * i, pa, a_vo[i], a_k[i]);
-    f32_chunk<B_KC, true>(tid + 256 * i, pb, b_vo[i], b_k[i]);
-  }
+  for (int i = 0; i < CHA; ++i) f32_chunk<A_KC, false, BM>(tid + 256 * i, pa, a_vo[i], a_k[i]);
+#pragma unroll
+  for (int i = 0; i < CHB; ++i) f32_chunk<B_KC, true, SB>(tid + 256 * i, pb, b_vo[i], b_k[i]);
   const unsigned lds0 = lds_addr(smem) + wave * 1024;   // a wave's load fills 1 KB of the tile
   auto load_stage = [&](int kt, int buf) {
     const bool second = CHAIN && kt >= KT1;
     const unsigned kl = second ? kt - KT1 : kt;
     const int left = klen - (int)kl * SK;   // K values from this stage on; chunks past them must read as zero in both operands
 #pragma unroll
-    for (int i = 0; i < F_CH; ++i)
+    for (int i = 0; i < CHA; ++i)
       load_to_lds16(second ? ra2 : ra, lds0 + buf * STAGE + i * 4096, a_k[i] < left ? a_vo[i] + kl * astep : OUT_OF_RANGE);
 #pragma unroll
-    for (int i = 0; i < F_CH; ++i) {
+    for (int i = 0; i < CHB; ++i) {
       const unsigned o = b_k[i] < left ? b_vo[i] + kl * bstep : OUT_OF_RANGE;
-      load_to_lds16(second ? rb2 : rb, lds0 + buf * STAGE + F_TILE + i * 4096, o);
-      if constexpr (DUAL) load_to_lds16(rb2, lds0 + buf * STAGE + 2 * F_TILE + i * 4096, o);
+      load_to_lds16(second ? rb2 : rb, lds0 + buf * STAGE + A_TILE + i * 4096, o);
+      if constexpr (DUAL) load_to_lds16(rb2, lds0 + buf * STAGE + A_TILE + B_TILE + i * 4096, o);
     }
   };
 
@@ -314,7 +322,7 @@ __global__ __launch_bounds__(256, 3) void gemm_f32_kernel(GemmArgs g) {
     acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
     if constexpr (DUAL) acc2[j] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
-  const bool active = wave * 16 < mvalid;
+  const bool active = band * 16 < mvalid;
 #pragma unroll
   for (int q = 0; q < AHEAD; ++q)
     if (q < KT) load_stage(q, q);
@@ -332,20 +340,21 @@ __global__ __launch_bounds__(256, 3) void gemm_f32_kernel(GemmArgs g) {
     if (kt + AHEAD < KT) load_stage(kt + AHEAD, buf + AHEAD >= NBUF ? buf + AHEAD - NBUF : buf + AHEAD);
     if (active) {
       const char* sa = smem + buf * STAGE;
-      const char* sb = sa + F_TILE;
+      const char* sb = sa + A_TILE;
 #pragma unroll
-      for (int kc = 0; kc < SK / 16; ++kc) {
+      for (int q = 0; q < SK / 16 / KH; ++q) {
+        const int kc = q * KH + kh;
         f32x4 av, bv[4], bv2[DUAL ? 4 : 1];   // bv: K contiguous [tile j][step s], K strided [step s][tile j]
-        if constexpr (A_KC) av = *reinterpret_cast<const f32x4*>(sa + f32_kc_off(wave * 16 + c, kc * 4 + grp));
+        if constexpr (A_KC) av = *reinterpret_cast<const f32x4*>(sa + f32_kc_off(band * 16 + c, kc * 4 + grp));
         else {
 #pragma unroll
-          for (int s = 0; s < 4; ++s) av[s] = *reinterpret_cast<const float*>(sa + f32_ks_off(kc * 16 + grp * 4 + s, (wave * 16 + c) * 4));
+          for (int s = 0; s < 4; ++s) av[s] = *reinterpret_cast<const float*>(sa + f32_ks_off<BM>(kc * 16 + grp * 4 + s, (band * 16 + c) * 4));
         }
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int o = B_KC ? f32_kc_off(q * 16 + c, kc * 4 + grp) : f32_ks_off(kc * 16 + grp * 4 + q, c * 16);
-          bv[q] = *reinterpret_cast<const f32x4*>(sb + o);
-          if constexpr (DUAL) bv2[q] = *reinterpret_cast<const f32x4*>(sb + F_TILE + o);
+        for (int i = 0; i < 4; ++i) {
+          const int o = B_KC ? f32_kc_off(i * 16 + c, kc * 4 + grp) : f32_ks_off<SB>(kc * 16 + grp * 4 + i, c * 16);
+          bv[i] = *reinterpret_cast<const f32x4*>(sb + o);
+          if constexpr (DUAL) bv2[i] = *reinterpret_cast<const f32x4*>(sb + B_TILE + o);
         }
 #pragma unroll
         for (int s = 0; s < 4; ++s)
@@ -358,13 +367,31 @@ __global__ __launch_bounds__(256, 3) void gemm_f32_kernel(GemmArgs g) {
     }
     buf = buf + 1 == NBUF ? 0 : buf + 1;
   }
+  if constexpr (KH == 2) {   // the second half's sums join the first's through LDS, once every wave has left the ring
+    __syncthreads();
+    f32x4* sums = reinterpret_cast<f32x4*>(smem) + band * (DUAL ? 8 : 4) * 64 + lane;
+    if (kh == 1) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        sums[j * 64] = acc[j];
+        if constexpr (DUAL) sums[(4 + j) * 64] = acc2[j];
+      }
+    }
+    __syncthreads();
+    if (kh == 1) return;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      acc[j] += sums[j * 64];
+      if constexpr (DUAL) acc2[j] += sums[(4 + j) * 64];
+    }
+  }
   if (!active || n0 + c * 4 >= g.N) return;
   // accumulator register v of a lane: row 4 grp + v of the wave's 16, one column of each of the four column tiles
   size_t idx[4];
   f32x4 s1[4], s2[4];
 #pragma unroll
   for (int v = 0; v < 4; ++v) {
-    const int m = wave * 16 + grp * 4 + v, mc = min(m, mvalid - 1);
+    const int m = band * 16 + grp * 4 + v, mc = min(m, mvalid - 1);
     if constexpr (MODE == MODE_TN) idx[v] = ((size_t)e * g.M + m0 + mc) * g.N + n0 + c * 4;
     else idx[v] = (size_t)(row0 + mc) * g.N + n0 + c * 4;
     if constexpr (EPI == EPI_GELU_BWD || EPI == EPI_SWIGLU_BWD) s1[v] = *reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(g.S1) + idx[v]);
@@ -374,31 +401,38 @@ __global__ __launch_bounds__(256, 3) void gemm_f32_kernel(GemmArgs g) {
   }
 #pragma unroll
   for (int v = 0; v < 4; ++v)
-    if (wave * 16 + grp * 4 + v < mvalid)
+    if (band * 16 + grp * 4 + v < mvalid)
       epilogue_f32x4<EPI>(g, idx[v], f32x4{acc[0][v], acc[1][v], acc[2][v], acc[3][v]},
                           DUAL ? f32x4{acc2[0][v], acc2[DUAL ? 1 : 0][v], acc2[DUAL ? 2 : 0][v], acc2[DUAL ? 3 : 0][v]} : f32x4{}, s1[v], s2[v]);
 }
 
-template <int MODE, int EPI, bool DUAL, bool CHAIN>
-static int launch_one(const GemmArgs& g, int max_tiles, hipStream_t s) {
+template <int MODE, int EPI, bool DUAL, bool CHAIN, int BM>
+static int launch_bm(const GemmArgs& g, int max_tiles, hipStream_t s) {
   const long long ntn = (g.N + SB - 1) / SB;
   long long blocks;
-  if (MODE == MODE_TN) blocks = (ntn * ((g.M + SB - 1) / SB) + NUM_XCD - 1) / NUM_XCD * NUM_XCD * g.E;
+  if (MODE == MODE_TN) blocks = (ntn * ((g.M + BM - 1) / BM) + NUM_XCD - 1) / NUM_XCD * NUM_XCD * g.E;
   else blocks = ntn * max_tiles;
   if (blocks > 0x7fffffffll) return MOE_ERR_BAD_SHAPE;
-  gemm_f32_kernel<MODE, EPI, DUAL, CHAIN><<<dim3((unsigned)blocks), 256, 0, s>>>(g);
+  gemm_f32_kernel<MODE, EPI, DUAL, CHAIN, BM><<<dim3((unsigned)blocks), 256, 0, s>>>(g);
   return launch_status();
 }
+// tile_rows: rows per entry of the tile map (row-tile GEMMs)
+template <int MODE, int EPI, bool DUAL, bool CHAIN>
+static int launch_one(const GemmArgs& g, int tile_rows, int max_tiles, hipStream_t s) {
+  if (MODE == MODE_TN) tile_rows = f32_tile_rows((long long)g.M * g.E, 0, g.N);
+  return tile_rows == SB ? launch_bm<MODE, EPI, DUAL, CHAIN, SB>(g, max_tiles, s)
+                         : launch_bm<MODE, EPI, DUAL, CHAIN, SB / 2>(g, max_tiles, s);
+}
 
-int launch_gemm_f32(int mode, int epi, bool dual, bool chain, const GemmArgs& g, int max_tiles, hipStream_t s) {
-  if (mode == MODE_NN && epi == EPI_GELU_FWD) return launch_one<MODE_NN, EPI_GELU_FWD, false, false>(g, max_tiles, s);
-  if (mode == MODE_NN && epi == EPI_SWIGLU_FWD && dual) return launch_one<MODE_NN, EPI_SWIGLU_FWD, true, false>(g, max_tiles, s);
-  if (mode == MODE_NN && epi == EPI_STORE) return launch_one<MODE_NN, EPI_STORE, false, false>(g, max_tiles, s);
-  if (mode == MODE_NT && epi == EPI_GELU_BWD) return launch_one<MODE_NT, EPI_GELU_BWD, false, false>(g, max_tiles, s);
-  if (mode == MODE_NT && epi == EPI_SWIGLU_BWD) return launch_one<MODE_NT, EPI_SWIGLU_BWD, false, false>(g, max_tiles, s);
-  if (mode == MODE_NT && epi == EPI_STORE && !chain) return launch_one<MODE_NT, EPI_STORE, false, false>(g, max_tiles, s);
-  if (mode == MODE_NT && epi == EPI_STORE && chain) return launch_one<MODE_NT, EPI_STORE, false, true>(g, max_tiles, s);
-  if (mode == MODE_TN && epi == EPI_DW) return launch_one<MODE_TN, EPI_DW, false, false>(g, max_tiles, s);
+int launch_gemm_f32(int mode, int epi, bool dual, bool chain, const GemmArgs& g, int tile_rows, int max_tiles, hipStream_t s) {
+  if (mode == MODE_NN && epi == EPI_GELU_FWD) return launch_one<MODE_NN, EPI_GELU_FWD, false, false>(g, tile_rows, max_tiles, s);
+  if (mode == MODE_NN && epi == EPI_SWIGLU_FWD && dual) return launch_one<MODE_NN, EPI_SWIGLU_FWD, true, false>(g, tile_rows, max_tiles, s);
+  if (mode == MODE_NN && epi == EPI_STORE) return launch_one<MODE_NN, EPI_STORE, false, false>(g, tile_rows, max_tiles, s);
+  if (mode == MODE_NT && epi == EPI_GELU_BWD) return launch_one<MODE_NT, EPI_GELU_BWD, false, false>(g, tile_rows, max_tiles, s);
+  if (mode == MODE_NT && epi == EPI_SWIGLU_BWD) return launch_one<MODE_NT, EPI_SWIGLU_BWD, false, false>(g, tile_rows, max_tiles, s);
+  if (mode == MODE_NT && epi == EPI_STORE && !chain) return launch_one<MODE_NT, EPI_STORE, false, false>(g, tile_rows, max_tiles, s);
+  if (mode == MODE_NT && epi == EPI_STORE && chain) return launch_one<MODE_NT, EPI_STORE, false, true>(g, tile_rows, max_tiles, s);
+  if (mode == MODE_TN && epi == EPI_DW) return launch_one<MODE_TN, EPI_DW, false, false>(g, tile_rows, max_tiles, s);
   return MOE_ERR_BAD_DTYPE;
 }
 
