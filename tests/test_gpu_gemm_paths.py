@@ -50,6 +50,7 @@ def test_accumulated_weight_gradients_are_old_plus_new(T, d, f, E, k, dtype, act
     (129, 64, 128, 4, 1, B.ACT_GELU),       # whole tiles and stages
     (33, 36, 68, 1, 1, B.ACT_SWIGLU),       # one row past a tile of 32
     (1100, 36, 3076, 2, 1, B.ACT_GELU),     # tiles of 64 rows in the row-tile GEMMs, of 32 in the weight gradients
+    (1100, 36, 3076, 2, 1, B.ACT_SWIGLU),
     (65, 388, 4100, 2, 1, B.ACT_SWIGLU),    # and the other way round
 ])
 def test_fp32_gemms_at_tile_and_stage_edges(T, d, f, E, k, act):
