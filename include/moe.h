@@ -321,10 +321,12 @@ MOE_API int moe_bench_mfma_loop(int32_t kind, int32_t iters, const void* operand
  * `block` of a grouped-GEMM launch of the 16-bit path computes, by the same code the kernels run.
  * kind 0, row-tile GEMMs (x W, dy W^T) over n_rt row tiles of which the first n_full_rt are full and the last
  * n_split are split along K into 8 parts, ntn column tiles: out = {1, row tile, -1, column tile, index among the
- * split tiles or -1, K part}.  kind 3: the same in the chunked order that operands beyond the memory-side cache use.  kind 1, weight-gradient GEMM with ntm x ntn tiles per expert: out = {1, expert slot
- * (position in descending-size order), m tile, n tile, -1, -1}.  kind 4, row-tile GEMMs whose last round of tiles is
- * split along K, ntm = K / 64: out = {1, row tile, parts per split tile (1: none split), column tile, index among the
- * split tiles or -1, K part}.  out[0] = 0: a surplus block that exits at once.
+ * split tiles or -1, K part}.  kind 3: the same in the chunked order that operands beyond the memory-side cache use.
+ * kind 1, weight-gradient GEMM with ntm x ntn tiles per expert: out = {1, expert slot (position in descending-size
+ * order), m tile, n tile, -1, -1}.  kind 4, row-tile GEMMs whose last round of tiles is split along K, ntm = K / 64:
+ * out = {1, row tile, parts per split tile (1: none split), column tile, index among the split tiles or -1, K part}.
+ * kind 5, few-row forward GEMMs of ntm experts on n_rt row tiles, expert by expert: n_full_rt = 1 if an expert has
+ * several, n_split = 1 if the tiles are split along K; out as kind 4.  out[0] = 0: a surplus block that exits at once.
  */
 MOE_API int moe_gemm_block_tile(int32_t kind, int64_t block, int32_t n_rt, int32_t n_full_rt, int32_t n_split,
                         int32_t ntm, int32_t ntn, int32_t* out);

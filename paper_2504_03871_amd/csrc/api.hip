@@ -43,7 +43,8 @@ WsLayout ws_layout(const moe_cfg* c) {
   off += align_up(std::max((size_t)c->d_model * c->E * 4, route_wfrag_bytes(c->d_model, c->E)), 256);
   w.ffn_split = off;
   if (is_half(c) && c->d_ff >= SPLIT_MIN_K) {
-    const size_t small = split_k_applies(c->E, c->d_ff) ? split_ws_bytes(c->E, c->d_model) : 0;
+    const bool sp = split_k_applies(c->E, c->d_ff) || (skinny_applies(A, c->E) && skinny_split(c->E, c->d_ff));
+    const size_t small = sp ? split_ws_bytes(c->E, c->d_model) : 0;
     off += align_up(std::max(small, tail_ws_bytes(max_row_tiles((int)A, c->E, gemm_bf16_tile_rows()), c->d_model)), 256);
   }
   w.ffn_bwd_dact = off;
@@ -241,6 +242,14 @@ int moe_gemm_block_tile(int32_t kind, int64_t block, int32_t n_rt, int32_t n_ful
     if (out[0]) { out[1] = r.rt; out[2] = t.parts; out[3] = r.nt; out[4] = r.split_tile; out[5] = r.ksplit; }
     return MOE_OK;
   }
+  if (kind == 5) {
+    if (ntm < 1 || n_full_rt > 1 || n_split > 1) return MOE_ERR_BAD_SHAPE;
+    const SkinnyOrder o = skinny_order(n_rt, n_full_rt == 1, ntm, n_split == 1);
+    RowBlock r;
+    out[0] = skinny_block((int)block, o, ntn, r) ? 1 : 0;
+    if (out[0]) { out[1] = r.rt; out[2] = 1 << o.shift; out[3] = r.nt; out[4] = r.split_tile; out[5] = r.ksplit; }
+    return MOE_OK;
+  }
   if (kind == 1) {
     if (ntm < 1) return MOE_ERR_BAD_SHAPE;
     int slot, mt, nt;
@@ -329,7 +338,7 @@ int ffn_fwd_impl(const moe_cfg* cfg, const void* x_perm, const void* W1, const v
   const bool skinny = is_half(cfg) && skinny_applies(A, cfg->E);   // few rows per expert
   const int tr = skinny ? SKINNY_ROWS : tile_rows_for(cfg), max_tiles = max_row_tiles(A, cfg->E, tr);
   TileMap map = tile_map_at(static_cast<char*>(ws) + w.tile_map, max_row_tiles(A, cfg->E, TILE_ROWS_MIN), cfg->E);
-  CHECK(launch_tile_map(offsets, kept, slice_lo, slice_hi, cfg->E, tr, map,
+  CHECK(launch_tile_map(offsets, kept, slice_lo, slice_hi, cfg->E, tr, skinny, map,
                         !swiglu && cfg->dtype == MOE_DTYPE_BF16 ? GELU_TAB_PHI : GELU_TAB_NONE, s));
   const size_t plane = (size_t)A * f * elt_size(cfg);
   char* sv = static_cast<char*>(saved);
@@ -356,9 +365,10 @@ int ffn_fwd_impl(const moe_cfg* cfg, const void* x_perm, const void* W1, const v
   g.A = hid; g.B = W2; g.B2 = nullptr; g.N = d; g.K = f;
   g.chunked = row_tiles_chunked(A, f, d, cfg->E, 1, (int)elt_size(cfg));
   g.C = y_perm; g.C2 = g.C3 = nullptr;
-  g.split_small = is_half(cfg) && split_k_applies(cfg->E, f);   // split-K: smallest row tiles, last round (gemm.h)
+  g.split_all = skinny && skinny_split(cfg->E, f);
+  g.split_small = is_half(cfg) && !skinny && split_k_applies(cfg->E, f);   // split-K: smallest row tiles, last round (gemm.h)
   g.split_tail = is_half(cfg) && !skinny && f >= SPLIT_MIN_K;
-  if (g.split_small || g.split_tail) g.split_ws = reinterpret_cast<float*>(static_cast<char*>(ws) + w.ffn_split);
+  if (g.split_all || g.split_small || g.split_tail) g.split_ws = reinterpret_cast<float*>(static_cast<char*>(ws) + w.ffn_split);
   ProfScope ps(cfg, MOE_PROF_GEMM2_FWD, s);
   if (skinny) return launch_gemm_half_skinny(cfg->dtype, EPI_STORE, false, g, max_tiles, s);
   return launch_gemm(cfg, MODE_NN, EPI_STORE, false, false, g, max_tiles, s);
@@ -467,7 +477,7 @@ int moe_expert_ffn_bwd(const moe_cfg* cfg, const void* dy_perm, const void* x_pe
   const int A = cfg->T * cfg->k, d = cfg->d_model, f = cfg->d_ff;
   const int tr = tile_rows_for(cfg), max_tiles = max_row_tiles(A, cfg->E, tr);
   TileMap map = tile_map_at(static_cast<char*>(ws) + w.tile_map, max_row_tiles(A, cfg->E, TILE_ROWS_MIN), cfg->E);
-  CHECK(launch_tile_map(offsets, kept, slice_lo, slice_hi, cfg->E, tr, map,
+  CHECK(launch_tile_map(offsets, kept, slice_lo, slice_hi, cfg->E, tr, false, map,
                         !swiglu && cfg->dtype == MOE_DTYPE_BF16 ? GELU_TAB_GRAD : GELU_TAB_NONE, s));
   const size_t plane = (size_t)A * f * elt_size(cfg);
   const char* sv = static_cast<const char*>(saved);

@@ -14,7 +14,7 @@ struct RowTile {
   int32_t e;      // expert
   int32_t row0;   // first row (absolute index into the permuted buffers)
   int32_t nrows;  // valid rows in this tile (1..tile height)
-  int32_t pad;
+  int32_t mates;  // expert-major lists: whether the expert has other tiles too (0 in the other lists)
 };
 
 // Tables over the bf16 numbers for the bf16 GELU epilogues.  The pre-activation is stored as a bf16
@@ -46,8 +46,8 @@ constexpr int GELU_TAB_FLOATS = 6144;              // 2 * 2432 entries, padded t
 // Tile map in the workspace: header[0] = number of tiles, header[1] = number of tiles at the head of the
 // list that are walked XCD by XCD (the full tiles; with many experts of few tiles each the list is
 // expert-major and this is all of it), header[2] = number of tiles of at most SPLIT_ROWS rows at the
-// end of the list that may be split along K (0 for an expert-major list); then the
-// tiles; then order[E] = the experts by descending share length (heaviest first); then one table as above.
+// end of the list that may be split along K (0 for an expert-major list; in the few-row kernel's list, which is always
+// expert-major, the number of experts with more than one tile); then the tiles; then order[E] = the experts by descending share length (heaviest first); then one table as above.
 struct TileMap {
   int32_t* header;
   RowTile* tiles;
@@ -154,6 +154,38 @@ MOE_HD inline bool row_tile_block(int vb, int n_rt, int n_full_rt, int n_sp, int
   return true;
 }
 
+// Few-row GEMMs (gemm_skinny_kernel.h) on an expert-major list.  Lists without an expert of several row tiles (`mates`)
+// read every weight once: up to 32 experts a block's neighbours are the next columns and K parts of its tile, so that the
+// chip streams whole weight rows; more experts go in patches, one contiguous run per XCD.  With such an expert the XCDs
+// take runs of 64 tiles, 8 rows x 8 columns, in turn: the row tiles that share weights run together on an XCD and find
+// them in its L2, while the chip as a whole reads whole weight rows (runs that walk down a strip of eight columns leave
+// the other half of 4 KB rows, and half of the memory channels, untouched: 256 experts of 48 rows, d 2048, f 1024, second
+// GEMM 244 us against 199; runs of 32 tiles are within 5 % either way, bands of 16 row tiles up to 10 % slower).
+// Split along K (up to 32 experts): eight parts, four where an expert has several tiles, which are at most 1.75 E then.
+constexpr int SKINNY_RUN = 64, SKINNY_BAND = 8;
+struct SkinnyOrder { int n_rt, E, shift; bool mates; };   // 1 << shift K parts per tile
+MOE_HD inline SkinnyOrder skinny_order(int n_rt, bool mates, int E, bool split) {
+  return SkinnyOrder{n_rt, E, !split ? 0 : mates ? 2 : 3, mates};
+}
+MOE_HD inline bool skinny_block(int vb, const SkinnyOrder& o, int ntn, RowBlock& r) {
+  const int nc = ntn << o.shift, n = o.n_rt * nc;
+  if (vb >= n) return false;
+  int c;
+  if (!o.mates && o.E <= SPLIT_MAX_E) {
+    r.ksplit = vb & ((1 << o.shift) - 1);
+    c = vb >> o.shift;
+    r.rt = c / ntn;
+    r.nt = c - r.rt * ntn;
+  } else {
+    if (o.mates) patch_tile(chunk_position(vb, n, SKINNY_RUN), o.n_rt, nc, SKINNY_BAND, r.rt, c);
+    else patch_tile(chunk_position(vb, n, n / NUM_XCD + 1), o.n_rt, nc, PATCH_R, r.rt, c);
+    r.ksplit = c / ntn;
+    r.nt = c - r.ksplit * ntn;
+  }
+  r.split_tile = o.shift > 0 ? r.rt : -1;
+  return true;
+}
+
 // Split-K of the last round.  256 blocks run at a time; the tiles behind the last whole round of 256 (all of them, when
 // there are fewer) leave most of the chip idle for the length of one tile.  In the plain-store GEMMs with long K these
 // r tiles are cut along K into `parts` blocks each, at most 256 in all, whose fp32 partial sums [slot][256][256] go to
@@ -240,6 +272,7 @@ struct GemmArgs {
   const float* gelu_tab;    // bf16 GELU epilogues: Phi (forward) or gelu' (backward) over the bf16 numbers
   float* split_ws;          // fp32 partial sums of split tiles, or NULL: no split-K
   int split_small, split_tail;   // which tiles may be split: the smallest row tiles (SPLIT_K), those of the last round (tail_split)
+  int split_all;                 // few-row GEMMs: every tile is split (skinny_order)
   const int32_t* offsets;
   const int32_t* kept;
   const int32_t* lo;
@@ -252,8 +285,9 @@ struct GemmArgs {
 
 // table: which GELU table to fill as well (bf16 GELU layers: GELU_TAB_PHI before the forward GEMMs,
 // GELU_TAB_GRAD before the backward ones)
+// by_expert: an expert-major list in any case.
 int launch_tile_map(const int32_t* offsets, const int32_t* kept, const int32_t* lo, const int32_t* hi, int E,
-                    int tile_rows, TileMap map, int table, hipStream_t s);
+                    int tile_rows, bool by_expert, TileMap map, int table, hipStream_t s);
 
 // fp32 storage, fp32 MFMA (any shape that passes check_cfg)
 int launch_gemm_f32(int mode, int epi, bool dual, bool chain, const GemmArgs& g, int tile_rows, int max_tiles, hipStream_t s);
@@ -271,11 +305,15 @@ int launch_gemm_half_pair(int dtype, int epi1, bool chain1, const GemmArgs& g1, 
 int gemm_bf16_tile_rows();
 // forward GEMMs of experts with few rows (gemm_skinny_kernel.h), on a map of SKINNY_ROWS-row tiles
 constexpr int SKINNY_ROWS = 64;
+// GEMM2, long K and few experts: the column tiles alone do not fill the chip
+inline bool skinny_split(int E, int K) { return E <= SPLIT_MAX_E && K >= SPLIT_MIN_K; }
 int launch_gemm_half_skinny(int dtype, int epi, bool dual, const GemmArgs& g, int max_tiles, hipStream_t s);
-// The line lies where most experts still fit one 64-row tile (each further one reads the weights again).  Forward pass,
-// 256-row kernel -> this one: d 4096, f 14336, eight experts, SwiGLU, 32 rows per expert 694 -> 578 us, 48 rows 709 -> 602,
-// 64 rows 831 -> 796, 96 rows 820 -> 1099; 32 rows under a skewed router 818 -> 655; d 2048, f 1024, 64 rows per expert:
-// 128 experts, SwiGLU, 446 -> 428, 256 experts, GELU, 590 -> 691.
+// The line lies where most experts still fit one 64-row tile.  Both GEMMs, 256-row kernel -> this one, us, even load | router
+// bias -1.2 log(e + 1): d 4096, f 14336, eight experts, SwiGLU, 24 rows per expert 604 -> 500 | 605 -> 495, 48 rows 616 ->
+// 535 | 616 -> 573, GELU, 48 rows 389 -> 376 | 392 -> 389; d 2048, f 8192, 16 experts, GELU, 8 rows 216 -> 188 | 207 -> 161, 48
+// rows 229 -> 224 | 359 -> 232; d 2048, f 1024, 48 rows: 128 experts, SwiGLU, 374 -> 309 | 255 -> 237, 256 experts, GELU, 476 ->
+// 412 | 241 -> 265 (one expert of 2829 rows).  Hundreds of rows on one of many small experts are what still loses: d 1024, f
+// 512, 128 experts, SwiGLU, same bias, 24 rows 54 -> 57, 40 rows 57 -> 69.
 constexpr int SKINNY_AVERAGE = 48;
 inline bool skinny_applies(long long rows, int E) { return rows <= (long long)SKINNY_AVERAGE * E; }
 

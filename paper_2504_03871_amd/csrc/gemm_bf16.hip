@@ -1,6 +1,7 @@
 // Launchers of the MFMA grouped GEMM for 16-bit storage, bf16 or fp16 (kernel in gemm_bf16_kernel.h).
 #include "gemm_bf16_kernel.h"
 #include "gemm_skinny_kernel.h"
+#include <algorithm>
 
 namespace moe {
 
@@ -116,13 +117,14 @@ static int launch_skinny(const GemmArgs& g, int max_tiles, hipStream_t s) {
     if (err != hipSuccess) return set_hip_error(err);
   }
   const int ntn = (g.N + SKINNY_BN - 1) / SKINNY_BN;
-  const bool split = EPI == EPI_STORE && g.split_ws != nullptr;
-  const long long tiles = (long long)ntn * max_tiles, blocks = tiles + (split ? split_blocks(g, ntn) : 0);
+  const bool split = EPI == EPI_STORE && g.split_all;
+  const long long blocks = (long long)ntn * (split ? std::max(max_tiles * (SPLIT_K / 2), g.E * SPLIT_K) : max_tiles);
   if (blocks > 0x7fffffffll) return MOE_ERR_BAD_SHAPE;
   kern<<<dim3(gemm_bf16_grid(blocks)), 256, lds, s>>>(g);
   const int rc = launch_status();
   if (rc != MOE_OK || !split) return rc;
-  return launch_split_reduce<ST>(g, tiles, s);
+  split_reduce_kernel<ST><<<dim3((unsigned)(max_tiles * ((SKINNY_ROWS * (g.N / 4) + 255) / 256))), 256, 0, s>>>(g);
+  return launch_status();
 }
 template <typename ST>
 static int skinny_for(int epi, bool dual, const GemmArgs& g, int max_tiles, hipStream_t s) {

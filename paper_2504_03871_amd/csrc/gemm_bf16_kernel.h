@@ -647,16 +647,22 @@ __global__ __launch_bounds__(256) void split_reduce_kernel(GemmArgs g) {
     }
     return;
   }
-  if (!g.split_small) return;
-  const int n_sp = g.ntiles[2], per_row = g.N / 4, per_tile = (SPLIT_ROWS * per_row + 255) / 256, st = blockIdx.x / per_tile;
+  const bool all = g.split_all;
+  if (!g.split_small && !all) return;
+  const int n_sp = all ? n_rt : g.ntiles[2], parts = all ? 1 << skinny_order(n_rt, g.ntiles[2] != 0, g.E, true).shift : SPLIT_K, per_row = g.N / 4, per_tile = (SPLIT_ROWS * per_row + 255) / 256, st = blockIdx.x / per_tile;
   if (st >= n_sp) return;
   const RowTile t = g.tiles[n_rt - n_sp + st];
   const int i = (blockIdx.x % per_tile) * 256 + threadIdx.x, m = i / per_row, n = (i % per_row) * 4;
   if (m >= t.nrows) return;
+  const float* src = g.split_ws + ((size_t)st * parts * SPLIT_ROWS + m) * g.N + n;
+  const size_t pitch = (size_t)SPLIT_ROWS * g.N;
   f32x4 sum = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int ks = 0; ks < SPLIT_K; ++ks)
-    sum += *reinterpret_cast<const f32x4*>(g.split_ws + (((size_t)st * SPLIT_K + ks) * SPLIT_ROWS + m) * g.N + n);
+  for (int ks = 0; ks < SPLIT_K / 2; ++ks) sum += *reinterpret_cast<const f32x4*>(src + ks * pitch);
+  if (parts == SPLIT_K) {
+#pragma unroll
+    for (int ks = SPLIT_K / 2; ks < SPLIT_K; ++ks) sum += *reinterpret_cast<const f32x4*>(src + ks * pitch);
+  }
   put(t.row0 + m, n, sum);
 }
 

@@ -9,11 +9,12 @@ namespace moe {
 // Tile order: every full tile (tile_rows valid rows) first, in expert order, then the experts' last,
 // partly filled tiles by descending row count.  Blocks are dispatched in tile order, so the short
 // tiles fill the chip's last round instead of each costing a full round.
-// header[0] = number of tiles, header[1] = tiles walked XCD by XCD, header[2] = trailing tiles that may be split along K (gemm.h).
+// header[0] = number of tiles, header[1] = tiles walked XCD by XCD, header[2] = trailing tiles that may be split along K, or,
+// by_expert, the number of experts with several tiles (gemm.h).
 constexpr int TM_THREADS = 4 * MOE_MAX_E;   // four threads per expert
 __global__ __launch_bounds__(TM_THREADS) void tile_map_kernel(const int32_t* __restrict__ offsets, const int32_t* __restrict__ kept,
                                                               const int32_t* __restrict__ lo, const int32_t* __restrict__ hi,
-                                                              int E, int tile_rows, int32_t* __restrict__ header,
+                                                              int E, int tile_rows, bool by_expert, int32_t* __restrict__ header,
                                                               RowTile* __restrict__ tiles, int32_t* __restrict__ order,
                                                               float* __restrict__ gelu_tab, int table) {
   // sort keys: (value << 32) | (MOE_MAX_E - 1 - id), so that "ahead of me" (larger value, ties by lower id) is
@@ -69,7 +70,7 @@ __global__ __launch_bounds__(TM_THREADS) void tile_map_kernel(const int32_t* __r
   const int rank_len = rank_desc(s_klen), rank_rem = rank_desc(s_krem);
   if (part == 0 && e < E) order[rank_len] = e;   // experts by descending share length, ties by id
   if (tid < WAVE) {   // the first wave scans the experts, four per lane (MOE_MAX_E = 4 x 64)
-    int full[4], some[4], sum_full = 0, sum_part = 0, sum_small = 0;
+    int full[4], some[4], sum_full = 0, sum_part = 0, sum_small = 0, sum_more = 0;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       full[i] = s_full[tid * 4 + i];
@@ -78,13 +79,15 @@ __global__ __launch_bounds__(TM_THREADS) void tile_map_kernel(const int32_t* __r
       sum_full += full[i];
       sum_part += some[i];
       sum_small += (rem > 0 && rem <= SPLIT_ROWS);
+      sum_more += full[i] + some[i] > 1;
     }
     const int run = wave_sum_i(sum_full), parts = wave_sum_i(sum_part), small = wave_sum_i(sum_small);
+    sum_more = wave_sum_i(sum_more);
     // Many experts of few row tiles each: an expert's weight panels are used by two or three tiles only,
     // so these must run together (same XCD, same time) or the panels are fetched once per tile.  The
     // list is then expert-major (each expert's full tiles, then its partly filled one) and the whole of
     // it is walked as the full region is.
-    const bool major = E > SPLIT_MAX_E && run < 3 * E;
+    const bool major = by_expert || (E > SPLIT_MAX_E && run < 3 * E);
     const int mine = major ? sum_full + sum_part : sum_full;
     int pos = wave_scan_i(mine) - mine;
 #pragma unroll
@@ -97,7 +100,7 @@ __global__ __launch_bounds__(TM_THREADS) void tile_map_kernel(const int32_t* __r
       s_major = major;
       header[0] = run + parts;
       header[1] = major ? run + parts : run;
-      header[2] = major ? 0 : small;   // the last entries: the partly filled tiles are sorted by descending size
+      header[2] = by_expert ? sum_more : major ? 0 : small;   // the last entries: the partly filled tiles are sorted by descending size
     }
   }
   __syncthreads();
@@ -119,7 +122,7 @@ __global__ __launch_bounds__(TM_THREADS) void tile_map_kernel(const int32_t* __r
         t.e = e;
         t.row0 = base + i * per;
         t.nrows = min(per, len - i * per);
-        t.pad = 0;
+        t.mates = ntile > 1;
         tiles[s_start[e] + i] = t;
       }
     } else {
@@ -128,7 +131,7 @@ __global__ __launch_bounds__(TM_THREADS) void tile_map_kernel(const int32_t* __r
         t.e = e;
         t.row0 = base + i * tile_rows;
         t.nrows = tile_rows;
-        t.pad = 0;
+        t.mates = 0;
         tiles[s_start[e] + i] = t;
       }
       if (part == 0 && rem > 0) {   // position among the partial tiles: more rows first, ties by expert id
@@ -136,7 +139,7 @@ __global__ __launch_bounds__(TM_THREADS) void tile_map_kernel(const int32_t* __r
         t.e = e;
         t.row0 = base + nfull * tile_rows;
         t.nrows = rem;
-        t.pad = 0;
+        t.mates = 0;
         tiles[s_nfull + rank_rem] = t;
       }
     }
@@ -144,9 +147,9 @@ __global__ __launch_bounds__(TM_THREADS) void tile_map_kernel(const int32_t* __r
 }
 
 int launch_tile_map(const int32_t* offsets, const int32_t* kept, const int32_t* lo, const int32_t* hi, int E,
-                    int tile_rows, TileMap map, int table, hipStream_t s) {
+                    int tile_rows, bool by_expert, TileMap map, int table, hipStream_t s) {
   const int grid = table == GELU_TAB_NONE ? 1 : 1 + (GELU_TAB_FLOATS + TM_THREADS - 1) / TM_THREADS;   // one thread per table entry
-  tile_map_kernel<<<grid, TM_THREADS, 0, s>>>(offsets, kept, lo, hi, E, tile_rows, map.header, map.tiles, map.order,
+  tile_map_kernel<<<grid, TM_THREADS, 0, s>>>(offsets, kept, lo, hi, E, tile_rows, by_expert, map.header, map.tiles, map.order,
                                     map.gelu_tab, table);
   return launch_status();
 }

@@ -5,7 +5,8 @@
 // stage of weights in flight and drains it at every stage.  Here a block owns 64 rows x 128 columns, four waves of 32
 // columns each; its K stages of 64 go through a ring of LDS stages that buffer loads fill directly, all but one of
 // them in flight, and two blocks share a compute unit: 64 KB of weights on their way per compute unit at any time.
-// The weights are requested as streaming data.  16 tokens, d 4096, f 14336, eight experts, top-2, SwiGLU: both GEMMs
+// The weights of an expert with a single row tile are requested as streaming data; row tiles that share weights run
+// together (skinny_block) and take them from the L2.  16 tokens, d 4096, f 14336, eight experts, top-2, SwiGLU: both GEMMs
 // 606 us with the 256-row kernel (4.65 TB/s), 525 with this one at 64 columns and plain loads, 503 at 128 columns, 465
 // at 64 columns with streaming loads, 452 as it is (6.2 TB/s); a third block per compute unit gains nothing.
 #pragma once
@@ -37,11 +38,14 @@ __global__ __launch_bounds__(256, 2) void gemm_skinny_kernel(GemmArgs g) {
 
   const int ntn = (g.N + BN - 1) / BN, n_rt = g.ntiles[0];
   constexpr bool CAN_SPLIT = EPI == EPI_STORE;
-  const int n_sp = (CAN_SPLIT && g.split_small) ? g.ntiles[2] : 0;
+  const SkinnyOrder so = skinny_order(n_rt, g.ntiles[2] != 0, g.E, CAN_SPLIT && g.split_all);
+  const int parts = 1 << so.shift;
   RowBlock rb;
-  if (!row_tile_block(blockIdx.x, n_rt, g.ntiles[1], n_sp, ntn, false, rb)) return;
+  if (!skinny_block(blockIdx.x, so, ntn, rb)) return;
   const RowTile t = g.tiles[rb.rt];
-  const int klen = rb.split_tile >= 0 ? g.K / SPLIT_K : g.K, kbase = rb.ksplit * klen;
+  const bool shared = __builtin_amdgcn_readfirstlane(t.mates) != 0;
+  const int stages = g.K / BKT, k0 = __builtin_amdgcn_readfirstlane((rb.ksplit * stages) >> so.shift), kbase = k0 * BKT;
+  const int KT = __builtin_amdgcn_readfirstlane(((rb.ksplit + 1) * stages) >> so.shift) - k0;
   const int n0 = rb.nt * BN, mvalid = t.nrows, ni = (mvalid + 15) / 16;   // ni: row tiles with valid rows
 
   const rsrc_t ra = make_rsrc(reinterpret_cast<const bf16*>(g.A) + (size_t)t.row0 * g.K + kbase, ((size_t)mvalid * g.K - kbase) * 2);
@@ -63,10 +67,18 @@ __global__ __launch_bounds__(256, 2) void gemm_skinny_kernel(GemmArgs g) {
   const unsigned lds0 = lds_addr(smem) + wave * 1024;
   auto load_stage = [&](int kt, int buf) {
     const unsigned at = lds0 + buf * STAGE;
+    if (shared) {
 #pragma unroll
-    for (int i = 0; i < CHB; ++i) {
-      load_to_lds16_nt(rw, at + A_BYTES + i * 4096, b_vo[i] + kt * (BKT * pb));
-      if constexpr (DUAL) load_to_lds16_nt(rw2, at + A_BYTES + B_BYTES + i * 4096, b_vo[i] + kt * (BKT * pb));
+      for (int i = 0; i < CHB; ++i) {
+        load_to_lds16(rw, at + A_BYTES + i * 4096, b_vo[i] + kt * (BKT * pb));
+        if constexpr (DUAL) load_to_lds16(rw2, at + A_BYTES + B_BYTES + i * 4096, b_vo[i] + kt * (BKT * pb));
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < CHB; ++i) {
+        load_to_lds16_nt(rw, at + A_BYTES + i * 4096, b_vo[i] + kt * (BKT * pb));
+        if constexpr (DUAL) load_to_lds16_nt(rw2, at + A_BYTES + B_BYTES + i * 4096, b_vo[i] + kt * (BKT * pb));
+      }
     }
 #pragma unroll
     for (int i = 0; i < CHA; ++i) load_to_lds16(ra, at + i * 4096, a_vo[i] + kt * (BKT * 2));
@@ -85,7 +97,6 @@ __global__ __launch_bounds__(256, 2) void gemm_skinny_kernel(GemmArgs g) {
   for (int j = 0; j < TN; ++j)
     b_fr[j] = A_BYTES + ks_off<BN>(grp * 8 + (c >> 2), (wave * (BN / 4) + j * 16 + (c & 3) * 4) * 2);
 
-  const int KT = klen / BKT;
 #pragma unroll
   for (int q = 0; q < AHEAD; ++q)
     if (q < KT) load_stage(q, q);
@@ -150,7 +161,7 @@ __global__ __launch_bounds__(256, 2) void gemm_skinny_kernel(GemmArgs g) {
     f32x4 vb = va;
     if constexpr (DUAL) vb = *reinterpret_cast<const f32x4*>(slab + BM * P + m * P + n);
     if (CAN_SPLIT && rb.split_tile >= 0)   // fp32 partial sum of this block's K part
-      *reinterpret_cast<f32x4*>(g.split_ws + (((size_t)rb.split_tile * SPLIT_K + rb.ksplit) * SPLIT_ROWS + m) * g.N + n0 + n) = va;
+      *reinterpret_cast<f32x4*>(g.split_ws + (((size_t)rb.split_tile * parts + rb.ksplit) * SKINNY_ROWS + m) * g.N + n0 + n) = va;
     else
       epilogue4<ST, EPI>(g, (size_t)(t.row0 + m) * g.N + n0 + n, va, vb, u32x2{0, 0}, u32x2{0, 0}, g.gelu_tab);
   }

@@ -103,3 +103,23 @@ def test_tail_split_numbering_covers_every_tile_and_k_part_once(n_full, n_part, 
     # slot (index among the split tiles, part) of every block: 0 .. 255, each once
     assert sorted(x[4] * parts + x[5] for x in t if x[4] >= 0) == list(range(len(split)))
     assert parts <= 8 <= stages
+
+
+@pytest.mark.parametrize("n_rt, E, mates, split, ntn", [
+    (1, 1, 0, 1, 1), (8, 8, 0, 1, 32), (16, 16, 0, 0, 64), (200, 256, 0, 0, 16), (3, 5, 0, 1, 9),   # one row tile per expert
+    (2, 1, 1, 1, 1), (11, 8, 1, 1, 32), (14, 8, 1, 0, 112), (9, 6, 1, 1, 9), (225, 128, 1, 0, 16), (70, 40, 1, 0, 5),
+])
+def test_few_row_numbering_covers_every_tile_and_part_once_and_keeps_row_tiles_together(n_rt, E, mates, split, ntn):
+    t = [x for x in (B.moe_gemm_block_tile(5, vb, n_rt, mates, split, E, ntn) for vb in range(n_rt * ntn * 8 + 8)) if x[0]]
+    parts = t[0][2]
+    assert parts == (1 if not split else 4 if mates else 8)
+    assert sorted((x[1], x[3], x[5]) for x in t) == list(itertools.product(range(n_rt), range(ntn), range(parts)))
+    assert all(x[4] == (x[1] if split else -1) for x in t)
+    if split:                                               # fp32 partial sums: tile slots of the workspace region
+        assert max(x[4] * parts + x[5] for x in t) < E * 8
+    if mates and len(t) >= 1024:
+        # row tiles that share weights are neighbours in the list: the 64 blocks an XCD runs at a time are 8 x 8 patches
+        x0 = t[0:64 * NUM_XCD:NUM_XCD]
+        assert len({x[1] for x in x0}) <= 8 and len({(x[3], x[5]) for x in x0}) <= 9
+        # and the chip as a whole reads whole weight rows: XCDs beside each other take neighbouring columns
+        assert len({(x[3], x[5]) for x in t[:64 * NUM_XCD]}) >= min(64, ntn * parts)

@@ -78,6 +78,9 @@ def test_a_row_with_nan_stays_in_its_row(dtype, d, f):
     (48, 128, 192, 2, 2, "DT_F16", "ACT_SWIGLU", 0.0),    # 48 rows per expert: the most that still goes this way
     (96, 192, 320, 4, 2, "DT_BF16", "ACT_SWIGLU", 1.5),   # skewed: an expert with two row tiles, one with next to none
     (190, 64, 4096, 8, 2, "DT_BF16", "ACT_GELU", 1.5),    # split along K, full 64-row tiles beside the split ones
+    (60, 192, 2112, 5, 2, "DT_BF16", "ACT_SWIGLU", 0.0),  # 33 K stages in eight parts, every expert one row tile
+    (100, 192, 2112, 5, 2, "DT_F16", "ACT_GELU", 2.5),    # and in four, an expert with two; one (almost) without rows
+    (450, 128, 192, 40, 4, "DT_BF16", "ACT_SWIGLU", 1.2), # more than 32 experts, some with several row tiles
 ])
 def test_few_rows_per_expert(T, d, f, E, k, dtype, act, zipf):
     from paper_2504_03871_amd import synth as S
