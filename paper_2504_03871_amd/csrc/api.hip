@@ -26,6 +26,11 @@ int check_cfg(const moe_cfg* c) {
   return MOE_OK;
 }
 
+// 16-bit backward: a row-tile GEMM of N columns with at most about eight rounds of tiles shares its launch (moe_expert_ffn_bwd)
+static bool shares_launch(int N, int max_tiles) {
+  return (long long)((N + gemm_bf16_tile_rows() - 1) / gemm_bf16_tile_rows()) * max_tiles <= 8ll * 256;
+}
+
 WsLayout ws_layout(const moe_cfg* c) {
   WsLayout w{};
   const size_t A = (size_t)c->T * c->k;
@@ -43,9 +48,10 @@ WsLayout ws_layout(const moe_cfg* c) {
   off += align_up(std::max((size_t)c->d_model * c->E * 4, route_wfrag_bytes(c->d_model, c->E)), 256);
   w.ffn_split = off;
   if (is_half(c) && c->d_ff >= SPLIT_MIN_K) {
-    const bool sp = split_k_applies(c->E, c->d_ff) || (skinny_applies(A, c->E) && skinny_split(c->E, c->d_ff));
-    const size_t small = sp ? split_ws_bytes(c->E, c->d_model) : 0;
-    off += align_up(std::max(small, tail_ws_bytes(max_row_tiles((int)A, c->E, gemm_bf16_tile_rows()), c->d_model)), 256);
+    const int max_tiles = max_row_tiles((int)A, c->E, gemm_bf16_tile_rows());
+    const bool skinny = skinny_applies(A, c->E), split = split_k_applies(c->E, c->d_ff) || (skinny && skinny_split(c->E, c->d_ff));
+    const bool tail = !skinny || (c->act == MOE_ACT_GELU && !shares_launch(c->d_model, max_tiles));   // y, or the GELU dx
+    off += align_up(std::max(split ? split_ws_bytes(c->E, c->d_model) : 0, tail ? tail_ws_bytes(max_tiles, c->d_model) : 0), 256);
   }
   w.ffn_bwd_dact = off;
   off += align_up((c->act == MOE_ACT_SWIGLU ? 2 : 1) * A * c->d_ff * elt_size(c), 256);
@@ -242,6 +248,11 @@ int moe_gemm_block_tile(int32_t kind, int64_t block, int32_t n_rt, int32_t n_ful
     if (out[0]) { out[1] = r.rt; out[2] = t.parts; out[3] = r.nt; out[4] = r.split_tile; out[5] = r.ksplit; }
     return MOE_OK;
   }
+  if (kind == 6) {
+    if (ntm < 1) return MOE_ERR_BAD_SHAPE;
+    out[0] = tail_may_split((int)block, n_rt, n_split == 0, ntn, ntm * 64) ? 1 : 0;
+    return MOE_OK;
+  }
   if (kind == 5) {
     if (ntm < 1 || n_full_rt > 1 || n_split > 1) return MOE_ERR_BAD_SHAPE;
     const SkinnyOrder o = skinny_order(n_rt, n_full_rt == 1, ntm, n_split == 1);
@@ -367,7 +378,8 @@ int ffn_fwd_impl(const moe_cfg* cfg, const void* x_perm, const void* W1, const v
   g.C = y_perm; g.C2 = g.C3 = nullptr;
   g.split_all = skinny && skinny_split(cfg->E, f);
   g.split_small = is_half(cfg) && !skinny && split_k_applies(cfg->E, f);   // split-K: smallest row tiles, last round (gemm.h)
-  g.split_tail = is_half(cfg) && !skinny && f >= SPLIT_MIN_K;
+  const bool exact = cfg->capacity == 0 && slice_lo == nullptr;
+  g.split_tail = is_half(cfg) && !skinny && tail_may_split(A, cfg->E, exact, (d + tr - 1) / tr, f);
   if (g.split_all || g.split_small || g.split_tail) g.split_ws = reinterpret_cast<float*>(static_cast<char*>(ws) + w.ffn_split);
   ProfScope ps(cfg, MOE_PROF_GEMM2_FWD, s);
   if (skinny) return launch_gemm_half_skinny(cfg->dtype, EPI_STORE, false, g, max_tiles, s);
@@ -503,9 +515,7 @@ int moe_expert_ffn_bwd(const moe_cfg* cfg, const void* dy_perm, const void* x_pe
   // partly filled round leaves idle.  With many rounds that idle share is small and separate launches
   // keep the cache to one GEMM at a time.  (Timing brackets: a shared launch counts under the row-tile GEMM.)
   const bool bf = is_half(cfg);
-  const long long few = 8ll * 256;   // tiles: about eight rounds on this chip
-  const bool pair_h = bf && (long long)((f + tr - 1) / tr) * max_tiles <= few;
-  const bool pair_x = bf && (long long)((d + tr - 1) / tr) * max_tiles <= few;
+  const bool pair_h = bf && shares_launch(f, max_tiles), pair_x = bf && shares_launch(d, max_tiles);
   {
     ProfScope ps(cfg, MOE_PROF_DH_BWD, s);
     if (pair_h) CHECK(launch_gemm_half_pair(cfg->dtype, epi_h, false, gh, max_tiles, gw2, s));
@@ -528,7 +538,7 @@ int moe_expert_ffn_bwd(const moe_cfg* cfg, const void* dy_perm, const void* x_pe
   // split-K of the GELU dx: the smallest row tiles; the last round only in a launch of its own (in a shared one the
   // weight-gradient tiles fill it)
   gx.split_small = bf && !swiglu && split_k_applies(cfg->E, f);
-  gx.split_tail = bf && !swiglu && !pair_x && f >= SPLIT_MIN_K;
+  gx.split_tail = bf && !swiglu && !pair_x && tail_may_split(A, cfg->E, cfg->capacity == 0 && slice_lo == nullptr, (d + tr - 1) / tr, f);
   if (gx.split_small || gx.split_tail) gx.split_ws = reinterpret_cast<float*>(static_cast<char*>(ws) + w.ffn_split);
   if (pair_x) return launch_gemm_half_pair(cfg->dtype, EPI_STORE, swiglu, gx, max_tiles, gw1, s);
   return launch_gemm(cfg, MODE_NT, EPI_STORE, false, swiglu, gx, max_tiles, s);

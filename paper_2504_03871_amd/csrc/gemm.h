@@ -190,8 +190,11 @@ MOE_HD inline bool skinny_block(int vb, const SkinnyOrder& o, int ntn, RowBlock&
 // there are fewer) leave most of the chip idle for the length of one tile.  In the plain-store GEMMs with long K these
 // r tiles are cut along K into `parts` blocks each, at most 256 in all, whose fp32 partial sums [slot][256][256] go to
 // the workspace; split_reduce adds them in part order.  A round costs about 26 us per 1024 K values, a slot about
-// 0.1 us (256 KB written and read again); the parts minimise the sum of the two, and a gain below 8 us, the extra
-// launch, is left.
+// 0.1 us (256 KB written and read again); the parts minimise the sum of the two, and a gain below 2 us, the model's
+// error, is left.  The reduction is a launch of its own, and the GEMM alone knows how many tiles there are: it is paid
+// (2 us) wherever tail_may_split cannot rule a split out, split or not, and takes no part in the comparison.  (8 us asked
+// for instead, forward pass: d 2048, f 2048, 96 tiles 102.6 -> 95.6 us with 2, 112 tiles 103.0 -> 99.2; d 2560, f 2560,
+// 120 tiles 126.7 -> 115.3.)
 // y = hidden W2, with the reduction: 16 experts of 125 rows, d 2048, f 8192 (128 tiles) 198 -> 131 us; eight experts of 512
 // rows, d 1024, f 4096 (about 80 tiles) 101 -> 60; d 2048, f 8192, 16384 rows in 16 skewed experts, per step 4.56 -> 4.38 ms.
 constexpr int TAIL_SLOTS = 256, TAIL_MAX_PARTS = 8;
@@ -200,11 +203,20 @@ MOE_HD inline TailSplit tail_split(int n_tiles, int K) {
   TailSplit t = {n_tiles, 1};
   const int r = n_tiles % TAIL_SLOTS, round = K / 4;   // tenths of a microsecond
   if (K < SPLIT_MIN_K || r == 0) return t;
-  int best = round - 80;
+  int best = round - 20;
   for (int p = 2; p <= TAIL_MAX_PARTS && p * r <= TAIL_SLOTS; ++p)
     if (round / p + p * r < best) { best = round / p + p * r; t.parts = p; }
   if (t.parts > 1) t.first = n_tiles - r;
   return t;
+}
+// (host) whether any number of row tiles that `rows` rows of E experts can have is split; exact: all of them are computed
+// (no capacity, no slices), else there may be any number of tiles.
+inline bool tail_may_split(int rows, int E, bool exact, int ntn, int K) {
+  if (K < SPLIT_MIN_K) return false;
+  if (!exact) return true;
+  for (int n = (rows + 255) / 256; n <= rows / 256 + E && n <= rows; ++n)
+    if (tail_split(n * ntn, K).parts > 1) return true;
+  return false;
 }
 inline size_t tail_ws_bytes(int max_tiles, int N) {   // 256 x 256 tiles
   const long long slots = (long long)max_tiles * ((N + 255) / 256) * TAIL_MAX_PARTS;

@@ -123,3 +123,13 @@ def test_few_row_numbering_covers_every_tile_and_part_once_and_keeps_row_tiles_t
         assert len({x[1] for x in x0}) <= 8 and len({(x[3], x[5]) for x in x0}) <= 9
         # and the chip as a whole reads whole weight rows: XCDs beside each other take neighbouring columns
         assert len({(x[3], x[5]) for x in t[:64 * NUM_XCD]}) >= min(64, ntn * parts)
+
+
+@pytest.mark.parametrize("rows, E, ntn, stages", [
+    (16384, 8, 4, 64), (6000, 2, 5, 45), (2000, 3, 9, 33), (9003, 6, 5, 45), (16384, 8, 16, 224), (1000, 1, 36, 32), (16384, 8, 4, 31), (1, 4, 1, 32)])
+def test_the_reduction_is_launched_where_a_tile_count_can_split_and_only_there(rows, E, ntn, stages):
+    """Every tile count that rows spread over E experts can have, against the split the kernels themselves compute."""
+    counts = range((rows + 255) // 256, min(rows, rows // 256 + E) + 1)
+    splits = [B.moe_gemm_block_tile(4, 0, n, 0, 0, stages, ntn)[2] > 1 for n in counts]
+    assert B.moe_gemm_block_tile(6, rows, E, 0, 0, stages, ntn)[0] == any(splits)
+    assert B.moe_gemm_block_tile(6, rows, E, 0, 1, stages, ntn)[0] == (stages >= 32)     # some rows left out: any count
