@@ -233,6 +233,10 @@ int moe_gemm_block_tile(int32_t kind, int64_t block, int32_t n_rt, int32_t n_ful
   if (block < 0 || block > 0x7fffffffll || ntn < 1 || n_rt < 0 || n_full_rt < 0 || n_full_rt > n_rt || n_split < 0 ||
       n_split > n_rt - n_full_rt)
     return MOE_ERR_BAD_SHAPE;
+  // the kernels count tiles, K parts and K values in 32 bits
+  const long long parts = kind == 5 ? (long long)(n_split ? SPLIT_K : 1) * n_rt : n_rt + (long long)(SPLIT_K - 1) * n_split;
+  const long long tiles = kind == 1 ? (long long)ntm * ntn : kind == 6 ? (block / 256 + n_rt) * ntn : parts * ntn;
+  if (tiles > 0x7fffffffll - NUM_XCD || ((kind == 4 || kind == 6) && ntm > 0x7fffffff / 64)) return MOE_ERR_BAD_SHAPE;
   for (int i = 0; i < 6; ++i) out[i] = -1;
   if (kind == 0 || kind == 3) {
     RowBlock r;

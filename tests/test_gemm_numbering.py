@@ -133,3 +133,15 @@ def test_the_reduction_is_launched_where_a_tile_count_can_split_and_only_there(r
     splits = [B.moe_gemm_block_tile(4, 0, n, 0, 0, stages, ntn)[2] > 1 for n in counts]
     assert B.moe_gemm_block_tile(6, rows, E, 0, 0, stages, ntn)[0] == any(splits)
     assert B.moe_gemm_block_tile(6, rows, E, 0, 1, stages, ntn)[0] == (stages >= 32)     # some rows left out: any count
+
+
+@pytest.mark.parametrize("kind, n_rt, n_split, ntm, ntn", [
+    (4, 4, 0, 1 << 26, 1), (6, 4, 0, 1 << 26, 1), (6, 1 << 16, 0, 32, 1 << 16),                # K = 64 ntm beyond 32 bits
+    (0, 1 << 16, 0, 1, 1 << 16), (3, 1 << 16, 0, 1, 1 << 16), (4, 1 << 16, 0, 32, 1 << 16),  # tiles beyond 32 bits
+    (0, 1 << 12, 1 << 12, 1, 1 << 17), (5, 1 << 16, 1, 8, 1 << 13),                          # with their K parts
+    (1, 0, 0, 1 << 16, 1 << 16),                                                             # tiles of an expert
+])
+def test_sizes_beyond_32_bits_are_refused(kind, n_rt, n_split, ntm, ntn):
+    import ctypes
+    out = (ctypes.c_int32 * 6)()
+    assert B.lib().moe_gemm_block_tile(kind, 0, n_rt, 0, n_split, ntm, ntn, out) == -2
