@@ -24,6 +24,8 @@ def filled_layer(T, d, f, E, k, dtype, act=B.ACT_GELU, seed=0):
     (700, 192, 320, 4, 2, "bf16", B.ACT_GELU),        # neither width a multiple of the tile, several K stages
     (300, 64, 576, 3, 1, "f16", B.ACT_SWIGLU),
     (3, 320, 256, 8, 1, "bf16", B.ACT_SWIGLU),        # experts without rows keep what they had
+    (40, 36, 68, 3, 1, "f32", B.ACT_GELU),            # fp32: tiles of 32 rows
+    (65, 388, 4100, 2, 1, "f32", B.ACT_SWIGLU),       # and of 64
 ])
 def test_accumulated_weight_gradients_are_old_plus_new(T, d, f, E, k, dtype, act):
     """accumulate = 1 adds, in fp32 and with one rounding, the very sums that accumulate = 0 stores."""
@@ -88,25 +90,59 @@ def test_few_rows_per_expert(T, d, f, E, k, dtype, act, zipf):
     run_case(S.WORKLOADS["cfg1"].scaled(T=T, d=d, f=f, E=E, k=k, dtype=getattr(S, dtype), act=getattr(S, act), zipf_s=zipf))
 
 
+def last_round_parts(kept, f, N):
+    """(tiles, K parts) of a row-tile GEMM over these rows, as the kernels compute them."""
+    n_rt, ntn = sum(-(-int(n) // 256) for n in kept), -(-N // 256)
+    return n_rt * ntn, B.moe_gemm_block_tile(4, 0, n_rt, 0, 0, f // 64, ntn)[2]
+
+
 @pytest.mark.parametrize("T, d, f, E, k, dtype, act", [
-    (700, 192, 2112, 4, 2, "DT_BF16", "ACT_GELU"),        # 33 stages of 64 in 8 parts, full and partly filled tiles
-    (450, 320, 2048, 3, 1, "DT_F16", "ACT_SWIGLU"),       # a last column tile of 64
-    (4096, 128, 2048, 40, 2, "DT_BF16", "ACT_SWIGLU"),    # expert-major tile list
-    (9000, 1088, 2048, 4, 2, "DT_F16", "ACT_GELU"),       # a whole round before the split tiles
+    (700, 192, 2112, 4, 2, "bf16", B.ACT_GELU),        # 33 stages of 64 in 8 parts, full and partly filled tiles
+    (450, 320, 2048, 3, 1, "f16", B.ACT_SWIGLU),       # a last column tile of 64
+    (4096, 128, 2048, 40, 2, "bf16", B.ACT_SWIGLU),    # expert-major tile list
+    (8200, 1088, 4096, 4, 2, "f16", B.ACT_GELU),       # a whole round before the split tiles
 ])
 def test_last_round_split_along_k(T, d, f, E, k, dtype, act):
     """y = hidden W2 with the tiles of the last round split along K, against the same rows multiplied in fp64."""
     import torch
-    from paper_2504_03871_amd import synth as S
-    L = filled_layer(T, d, f, E, k, {"DT_BF16": "bf16", "DT_F16": "f16"}[dtype], getattr(S, act))
+    L = filled_layer(T, d, f, E, k, dtype, act)
     L.forward()
     torch.cuda.synchronize()
-    hid = L.saved_plane(2 if act == "ACT_SWIGLU" else 1)
-    tol = {"DT_BF16": 2.0 ** -9, "DT_F16": 2.0 ** -12}[dtype]   # one rounding of the result: 2^-9 (2^-12) relative at most
+    tiles, parts = last_round_parts(L.kept, f, d)
+    assert parts > 1 and (tiles > 256) == (T == 8200)
+    hid = L.saved_plane(2 if act == B.ACT_SWIGLU else 1)
+    tol = {"bf16": 2.0 ** -9, "f16": 2.0 ** -12}[dtype]   # one rounding of the result: 2^-9 (2^-12) relative at most
     for e in range(E):
         o, n = int(L.offsets[e]), int(L.kept[e])
         ref = hid[o:o + n].double() @ L.W2[e].double()
         err = (L.y_perm[o:o + n].double() - ref).norm() / ref.norm()
+        assert err < tol, (e, float(err))
+
+
+@pytest.mark.parametrize("dtype, cap", [("bf16", 2000), ("f16", 1100)])
+def test_last_round_split_along_k_in_the_gelu_input_gradient(dtype, cap):
+    """dx = dA W1^T in a launch of its own (more than 2048 tiles possible, few there because of the capacity) with 34
+    stages of 64 in parts of unequal length, against the stored dA multiplied in fp64."""
+    import torch
+    from paper_2504_03871_amd.layer import MoELayer
+    T, d, f, E = 131072, 1024, 2176, 2
+    L = MoELayer(T, d, f, E, 1, dtype=DT[dtype], act=B.ACT_GELU, capacity=cap)
+    gen = torch.Generator(device="cuda:0").manual_seed(3)
+    for t, std in ((L.x, 1.0), (L.d_out, 1.0), (L.Wr, d ** -0.5), (L.W1, d ** -0.5), (L.W2, f ** -0.5)):
+        t.normal_(0.0, std, generator=gen)
+    L.forward()
+    L.combine_bwd()
+    L.ffn_bwd()
+    torch.cuda.synchronize()
+    tiles, parts = last_round_parts(L.kept, f, d)
+    assert -(-d // 256) * (-(-T // 256) + E) > 2048 and parts > 1 and f // 64 % parts != 0, (tiles, parts)
+    dact = L.ws[L.ws.numel() - T * f * 2:].view(L.tdtype).view(T, f)     # the workspace's last region
+    tol = {"bf16": 2.0 ** -9, "f16": 2.0 ** -12}[dtype]                  # one rounding of the result
+    for e in range(E):
+        o, n = int(L.offsets[e]), int(L.kept[e])
+        assert n == cap
+        ref = dact[o:o + n].double() @ L.W1[e].double().t()
+        err = (L.dx_perm[o:o + n].double() - ref).norm() / ref.norm()
         assert err < tol, (e, float(err))
 
 
