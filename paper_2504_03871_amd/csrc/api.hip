@@ -46,15 +46,21 @@ WsLayout ws_layout(const moe_cfg* c) {
   off += align_up(partial_rows * c->d_model * c->E * 4, 256);
   w.route_wrt = off;   // shared with the forward's gate weight in MFMA operand layout (never live together)
   off += align_up(std::max((size_t)c->d_model * c->E * 4, route_wfrag_bytes(c->d_model, c->E)), 256);
+  // Partial sums of split-K tiles: the forward's (y) may reach into the region of dA, which only a backward call fills and
+  // reads; the GELU dx reads dA while it writes its own, so those lie in front of it.
   w.ffn_split = off;
+  const size_t dact = align_up((c->act == MOE_ACT_SWIGLU ? 2 : 1) * A * c->d_ff * elt_size(c), 256);
+  size_t fwd = 0, bwd = 0;
   if (is_half(c) && c->d_ff >= SPLIT_MIN_K) {
     const int max_tiles = max_row_tiles((int)A, c->E, gemm_bf16_tile_rows());
-    const bool skinny = skinny_applies(A, c->E), split = split_k_applies(c->E, c->d_ff) || (skinny && skinny_split(c->E, c->d_ff));
-    const bool tail = !skinny || (c->act == MOE_ACT_GELU && !shares_launch(c->d_model, max_tiles));   // y, or the GELU dx
-    off += align_up(std::max(split ? split_ws_bytes(c->E, c->d_model) : 0, tail ? tail_ws_bytes(max_tiles, c->d_model) : 0), 256);
+    const bool skinny = skinny_applies(A, c->E), small = split_k_applies(c->E, c->d_ff);
+    const size_t rows = split_ws_bytes(c->E, c->d_model), tail = tail_ws_bytes(max_tiles, c->d_model);
+    fwd = skinny ? (skinny_split(c->E, c->d_ff) ? rows : 0) : std::max(small ? rows : 0, tail);
+    if (c->act == MOE_ACT_GELU) bwd = std::max(small ? rows : 0, shares_launch(c->d_model, max_tiles) ? 0 : tail);
   }
+  off += align_up(std::max(bwd, fwd > dact ? fwd - dact : 0), 256);
   w.ffn_bwd_dact = off;
-  off += align_up((c->act == MOE_ACT_SWIGLU ? 2 : 1) * A * c->d_ff * elt_size(c), 256);
+  off += dact;
   w.total = off;
   return w;
 }

@@ -34,7 +34,7 @@ struct WsLayout {
   size_t tile_map;          // int32 header + int4 entries (grouped GEMM row tiles)
   size_t route_partials;    // fp32 [token slice][E][d]: partial sums of the gate weight gradient
   size_t route_wrt;         // fp32 [E][d]: transposed router weight
-  size_t ffn_split;         // fp32 partial sums of split-K tiles (gemm.h), for long K
+  size_t ffn_split;         // fp32 partial sums of split-K tiles (gemm.h), for long K; the forward's run on into ffn_bwd_dact
   size_t ffn_bwd_dact;      // storage type [planes][T*k][f]: dA (GELU) or dG | dU (SwiGLU)
   size_t total;
 };

@@ -54,6 +54,16 @@ def test_cfg_validation():
     assert B.moe_workspace_bytes(B.make_cfg(**{**ok, "dtype": B.DTYPE_F32, "d_model": 68, "d_ff": 100})) > 0
 
 
+@pytest.mark.parametrize("T", [16384, 1000])
+def test_partial_sums_of_the_forward_share_the_workspace_of_the_backward(T):
+    """The split of GEMM2 along K (16-bit storage, d_ff >= 2048) holds up to 256 fp32 tiles of 256 x 256; only what does not
+    fit the region of dA, which the backward alone uses, adds to the workspace."""
+    need = lambda f: B.moe_workspace_bytes(B.make_cfg(T, 2048, f, 8, 2, B.DTYPE_BF16, B.ACT_SWIGLU))
+    dact = lambda f: 2 * (2 * T) * f * 2                  # dG | dU
+    sums = 256 * 256 * 256 * 4                            # the 1984 columns before have no split, 2112 no tiles of 64 rows
+    assert need(2112) - need(1984) == max(dact(2112), sums) - dact(1984)
+
+
 def test_pointer_validation_happens_before_any_launch():
     """Fake (never dereferenced) device addresses: every call must fail in validation."""
     cfg = B.make_cfg(8, 64, 128, 4, 2)
