@@ -54,8 +54,10 @@ __global__ __launch_bounds__(DP_THREADS) void dispatch_scan_kernel(int32_t* __re
 // Where the rank kernel finds the assignments of the other blocks: counts per block (dispatch_hist_kernel), exclusive
 // prefixes and a row of totals (dispatch_scan_kernel), or, up to DP_SELF blocks, nowhere: it counts their ids itself.
 // A short list is bound by its launches, not by its bytes.  Histogram and ranks in two launches -> ids counted here, us
-// per call: 512 assignments 11.9 -> 9.5, 2000 12.2 -> 10.0, 4000 (E = 16) 14.7 -> 13.8; at 8000 (E = 16) the gain is
-// 0.9, and with all ids on one expert the LDS additions of a block, which then run one after the other, would eat it.
+// per call, even ids | all ids on one expert (whose LDS additions run one after the other): 1024 assignments, E = 8
+// 11.6 -> 8.9 | 11.4 -> 8.8; 4096, E = 8 11.6 -> 9.1 | 11.5 -> 8.6, E = 16 14.9 -> 12.7 | 11.6 -> 8.6, E = 64 12.5 -> 10.7 | 14.4 ->
+// 13.9, E = 256 12.8 -> 10.7 | 14.7 -> 13.7.  A block's additions grow with the list, the launch they save does not: at 8000
+// (E = 16) the gain on even ids is down to 0.9.
 enum RankFrom { FROM_COUNTS, FROM_PREFIXES, FROM_IDS };
 constexpr int DP_SELF = 4;
 
