@@ -10,6 +10,7 @@ DIR is the `-d` directory of a rocprofv3 run made with `--output-format csv -o <
   --write  rocprofv3 --pmc WRITE_SIZE ...       (same bench command)
   --busy   rocprofv3 --pmc SQ_BUSY_CU_CYCLES SQ_VALU_MFMA_BUSY_CYCLES SQ_WAVE_CYCLES SQ_WAIT_ANY
            SQ_INSTS_VALU_MFMA_MOPS_BF16 SQ_VMEM_TA_ADDR_FIFO_FULL SQ_LDS_BANK_CONFLICT SQ_ACTIVE_INST_LDS ... (same)
+  (a --workload that bench.py does not know is a case of perf/cases.py, traced with the program that its summary states)
 Byte counters are calibrated on the library's own streaming copy, which bench.py runs on 512 MiB for its
 `device` entry in every run: the largest per-dispatch value of `bench_stream_kernel<false>` stands for
 524288 KiB read (FETCH_SIZE) and written (WRITE_SIZE).
@@ -25,6 +26,8 @@ import glob
 import json
 import os
 import re
+
+from . import synth
 
 
 def find_csv(d, suffix):
@@ -44,7 +47,10 @@ def gemm_role(name, nth=0):
         if epi in (3, 4):
             return "dh_bwd", "dH = dy W2^T with the activation-derivative epilogue, and dW2 = H^T dy, one launch"
         return "dx_bwd", "dx = dA W1^T" + (" (two chained products)" if chain else "") + ", and dW1 = x_perm^T dA, one launch"
-    m = re.search(r"gemm_bf16_kernelIDF16[b_]Li(\d)ELi(\d)ELb([01])ELb([01])E", name)
+    m = re.search(r"gemm_skinny_kernelIDF16[b_]Li(\d)ELb([01])E", name)
+    if m:
+        return ("gemm2_fwd", "y_perm = H W2, few rows per expert") if m.group(1) == "0" else ("gemm1_fwd", "GEMM1 and its activation, few rows per expert")
+    m = re.search(r"gemm_(?:bf16_kernelIDF16[b_]|f32_kernelI)Li(\d)ELi(\d)ELb([01])ELb([01])E", name)
     if not m:
         return None, ""
     mode, epi, dual, chain = int(m.group(1)), int(m.group(2)), m.group(3) == "1", m.group(4) == "1"
@@ -67,10 +73,10 @@ def short(n):
     """Readable form of a mangled kernel name: the function name and, for the GEMMs, the integer template arguments
     <MODE, EPI, DUAL, CHAIN, BM, BN, BK, waves M, waves N, stages> (pair: <MODE1, EPI1, CHAIN1, BK1, NB1, MODE2, ...>)."""
     m = re.search(r"_ZN3moe\d+([a-z_0-9]+?)I(.*?)EEv", n)
-    if m and m.group(1).startswith("gemm_bf16"):
+    if m and m.group(1).startswith("gemm_"):
         args = re.findall(r"L[ib](\d+)E", m.group(2))
-        st = "bf16" if "DF16b" in m.group(2) else ("f16" if "DF16_" in m.group(2) else "")
-        return f"{m.group(1)}<{st}, {', '.join(args)}>"
+        st = ["bf16"] if "DF16b" in m.group(2) else (["f16"] if "DF16_" in m.group(2) else [])
+        return f"{m.group(1)}<{', '.join(st + args)}>"
     m = re.search(r"_ZN3moe\d+([a-z_0-9]+?)(?:I|E)", n)
     if m:
         return m.group(1)
@@ -111,6 +117,9 @@ def main():
         bench = json.loads(line)
         title = bench["config"]["workload"]
     bench_cmd = f"python3 bench.py --workload {w} --also none --no-cpu-baseline" + (" --f16" if a.f16 else "")
+    case_run = w not in synth.WORKLOADS
+    if case_run:
+        bench_cmd = "python3 case.py"
     tag = w + ("_f16" if a.f16 else "")   # file name stem
     if a.f16:
         title += " (fp16 storage)"
@@ -163,13 +172,19 @@ def main():
     if a.trace:
         rows = list(csv.DictReader(open(find_csv(a.trace, "kernel_stats.csv"))))
         out = [f"# {title}: per-kernel durations", "",
-               "Command (run from /tmp with TMPDIR=/tmp on the MI355X box):", "",
-               f"    rocprofv3 -M --kernel-trace --stats --output-format csv -d <out> -o {w} -- {bench_cmd}", "",
-               "bench.py runs its warm-up steps, a detail pass (every kernel bracketed by events), the timed steps and a",
-               "cold pass of the HBM-bound calls; durations in microseconds over all of them.", "",
-               "| kernel | calls | avg us | min us | max us | % of GPU time | role |", "|---|---|---|---|---|---|---|"]
+               "Command (run from /tmp with TMPDIR=/tmp on an MI355X):", "",
+               f"    rocprofv3 -M --kernel-trace --stats --output-format csv -d <out> -o {w} -- {bench_cmd}", ""]
+        if case_run:
+            out += ["case.py, with the repository on PYTHONPATH, is thirty passes of the case; durations in microseconds over all of them:", "",
+                    "    import torch", "    from perf import cases as P",
+                    f"    s = P.prepare({{c['name']: c for c in P.listed()}}['{w}'], 1)",
+                    "    for _ in range(30): P.run(s)", "    torch.cuda.synchronize()", ""]
+        else:
+            out += ["bench.py runs its warm-up steps, a detail pass (every kernel bracketed by events), the timed steps and a",
+               "cold pass of the HBM-bound calls; durations in microseconds over all of them.", ""]
+        out += ["| kernel | calls | avg us | min us | max us | % of GPU time | role |", "|---|---|---|---|---|---|---|"]
         for r in rows:
-            if "at::native" in r["Name"] or "rocclr" in r["Name"]:
+            if "at::native" in r["Name"] or "2at6native" in r["Name"] or "rocclr" in r["Name"]:
                 continue
             role, desc = gemm_role(r["Name"])
             if role and role.startswith("dw"):
@@ -236,7 +251,7 @@ def main():
     if a.busy:
         pk = per_kernel(find_csv(a.busy, "counter_collection.csv"))
         lines = [f"# {title}: matrix-core occupancy of the grouped-GEMM launches from rocprofv3 counters", "",
-                 "Command (run from /tmp with TMPDIR=/tmp on the MI355X box):", "",
+                 "Command (run from /tmp with TMPDIR=/tmp on an MI355X):", "",
                  "    rocprofv3 -M --pmc SQ_BUSY_CU_CYCLES SQ_VALU_MFMA_BUSY_CYCLES SQ_WAVE_CYCLES SQ_WAIT_ANY SQ_INSTS_VALU_MFMA_MOPS_BF16 "
                  f"SQ_VMEM_TA_ADDR_FIFO_FULL SQ_LDS_BANK_CONFLICT SQ_ACTIVE_INST_LDS --output-format csv -d <out> -o {w} -- {bench_cmd} --steps 3 --warmup 1", "",
                  "Averages per dispatch.  SQ_VALU_MFMA_BUSY_CYCLES counts the four SIMDs of a compute unit separately, so",
