@@ -47,7 +47,8 @@ constexpr int GELU_TAB_FLOATS = 6144;              // 2 * 2432 entries, padded t
 // list that are walked XCD by XCD (the full tiles; with many experts of few tiles each the list is
 // expert-major and this is all of it), header[2] = number of tiles of at most SPLIT_ROWS rows at the
 // end of the list that may be split along K (0 for an expert-major list; in the few-row kernel's list, which is always
-// expert-major, the number of experts with more than one tile); then the tiles; then order[E] = the experts by descending share length (heaviest first); then one table as above.
+// expert-major, the number of experts with more than one tile); then the tiles; then order[E] = the experts by
+// descending share length (heaviest first); then one table as above.
 struct TileMap {
   int32_t* header;
   RowTile* tiles;
@@ -320,12 +321,16 @@ constexpr int SKINNY_ROWS = 64;
 // GEMM2, long K and few experts: the column tiles alone do not fill the chip
 inline bool skinny_split(int E, int K) { return E <= SPLIT_MAX_E && K >= SPLIT_MIN_K; }
 int launch_gemm_half_skinny(int dtype, int epi, bool dual, const GemmArgs& g, int max_tiles, hipStream_t s);
-// The line lies where most experts still fit one 64-row tile.  Both GEMMs, 256-row kernel -> this one, us, even load | router
-// bias -1.2 log(e + 1): d 4096, f 14336, eight experts, SwiGLU, 24 rows per expert 604 -> 500 | 605 -> 495, 48 rows 616 ->
-// 535 | 616 -> 573, GELU, 48 rows 389 -> 376 | 392 -> 389; d 2048, f 8192, 16 experts, GELU, 8 rows 216 -> 188 | 207 -> 161, 48
-// rows 229 -> 224 | 359 -> 232; d 2048, f 1024, 48 rows: 128 experts, SwiGLU, 374 -> 309 | 255 -> 237, 256 experts, GELU, 476 ->
-// 412 | 241 -> 265 (one expert of 2829 rows).  Hundreds of rows on one of many small experts are what still loses: d 1024, f
-// 512, 128 experts, SwiGLU, same bias, 24 rows 54 -> 57, 40 rows 57 -> 69.
+// The line lies where most experts still fit one 64-row tile.  Both GEMMs with their map, 256-row kernel -> this one, us,
+// even load | router bias -0.7 log(e + 1) | -1.2 log(e + 1).  Up to 16 experts (no 0.7): d 4096, f 14336, eight, SwiGLU, 24 rows
+// per expert 604 -> 500 | 605 -> 495, 48 rows 616 -> 535 | 616 -> 573, GELU, 48 rows 389 -> 376 | 392 -> 389; d 2048, f 8192, 16,
+// GELU, 8 rows 216 -> 188 | 207 -> 161, 48 rows 229 -> 224 | 359 -> 232.  Many: d 1024, f 512, 64, SwiGLU, 16 rows 48 -> 45 | 49 ->
+// 47 | 48 -> 42, 48 rows 49 -> 49 | 83 -> 61 | 51 -> 55; 128, SwiGLU, 16 rows 106 -> 79 | 102 -> 73 | 53 -> 54, 32 rows 110 -> 83 |
+// 115 -> 100 | 57 -> 65, 48 rows 114 -> 102 | 152 -> 109 | 88 -> 85, GELU, 48 rows 75 -> 76 | 126 -> 80 | 73 -> 62; d 2048, f 1024,
+// 128, SwiGLU, 16 rows 348 -> 280 | 329 -> 248 | 180 -> 166, 48 rows 373 -> 311 | 411 -> 340 | 257 -> 241, 256, GELU, 16 rows 452 ->
+// 371 | 346 -> 270 | 139 -> 140, 48 rows 476 -> 419 | 462 -> 442 | 241 -> 263; d 4096, f 1024, 40, SwiGLU, 48 rows 294 -> 206 | 293 ->
+// 225 | 294 -> 230.  What loses (1-15 %) is the steepest bias over 64 and more small experts, most of them idle while one has a
+// thousand rows; the host does not see the load, and a lower line for many experts would give up more than it saves.
 constexpr int SKINNY_AVERAGE = 48;
 inline bool skinny_applies(long long rows, int E) { return rows <= (long long)SKINNY_AVERAGE * E; }
 

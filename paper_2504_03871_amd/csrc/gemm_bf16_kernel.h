@@ -649,7 +649,8 @@ __global__ __launch_bounds__(256) void split_reduce_kernel(GemmArgs g) {
   }
   const bool all = g.split_all;
   if (!g.split_small && !all) return;
-  const int n_sp = all ? n_rt : g.ntiles[2], parts = all ? 1 << skinny_order(n_rt, g.ntiles[2] != 0, g.E, true).shift : SPLIT_K, per_row = g.N / 4, per_tile = (SPLIT_ROWS * per_row + 255) / 256, st = blockIdx.x / per_tile;
+  const int n_sp = all ? n_rt : g.ntiles[2], parts = all ? 1 << skinny_order(n_rt, g.ntiles[2] != 0, g.E, true).shift : SPLIT_K;
+  const int per_row = g.N / 4, per_tile = (SPLIT_ROWS * per_row + 255) / 256, st = blockIdx.x / per_tile;
   if (st >= n_sp) return;
   const RowTile t = g.tiles[n_rt - n_sp + st];
   const int i = (blockIdx.x % per_tile) * 256 + threadIdx.x, m = i / per_row, n = (i % per_row) * 4;
