@@ -321,16 +321,33 @@ constexpr int SKINNY_ROWS = 64;
 // GEMM2, long K and few experts: the column tiles alone do not fill the chip
 inline bool skinny_split(int E, int K) { return E <= SPLIT_MAX_E && K >= SPLIT_MIN_K; }
 int launch_gemm_half_skinny(int dtype, int epi, bool dual, const GemmArgs& g, int max_tiles, hipStream_t s);
-// The line lies where most experts still fit one 64-row tile.  Both GEMMs with their map, 256-row kernel -> this one, us,
-// even load | router bias -0.7 log(e + 1) | -1.2 log(e + 1).  Up to 16 experts (no 0.7): d 4096, f 14336, eight, SwiGLU, 24 rows
-// per expert 604 -> 500 | 605 -> 495, 48 rows 616 -> 535 | 616 -> 573, GELU, 48 rows 389 -> 376 | 392 -> 389; d 2048, f 8192, 16,
-// GELU, 8 rows 216 -> 188 | 207 -> 161, 48 rows 229 -> 224 | 359 -> 232.  Many: d 1024, f 512, 64, SwiGLU, 16 rows 48 -> 45 | 49 ->
-// 47 | 48 -> 42, 48 rows 49 -> 49 | 83 -> 61 | 51 -> 55; 128, SwiGLU, 16 rows 106 -> 79 | 102 -> 73 | 53 -> 54, 32 rows 110 -> 83 |
-// 115 -> 100 | 57 -> 65, 48 rows 114 -> 102 | 152 -> 109 | 88 -> 85, GELU, 48 rows 75 -> 76 | 126 -> 80 | 73 -> 62; d 2048, f 1024,
-// 128, SwiGLU, 16 rows 348 -> 280 | 329 -> 248 | 180 -> 166, 48 rows 373 -> 311 | 411 -> 340 | 257 -> 241, 256, GELU, 16 rows 452 ->
-// 371 | 346 -> 270 | 139 -> 140, 48 rows 476 -> 419 | 462 -> 442 | 241 -> 263; d 4096, f 1024, 40, SwiGLU, 48 rows 294 -> 206 | 293 ->
-// 225 | 294 -> 230.  What loses (1-15 %) is the steepest bias over 64 and more small experts, most of them idle while one has a
-// thousand rows; the host does not see the load, and a lower line for many experts would give up more than it saves.
+// The line lies where most experts still fit one 64-row tile.  Both GEMMs with their map, us, 256-row kernel -> this one
+// (above the line: forced), for an even load and router biases of -0.7 and -1.2 log(e + 1):
+//   rows per expert                                 even          -0.7          -1.2
+//   d 4096, f 14336, 8 experts, SwiGLU     24    604 -> 500                  605 -> 495
+//                                          48    616 -> 535                  616 -> 573
+//                                          56    626 -> 556                  627 -> 593
+//                                          64    630 -> 653                  635 -> 612
+//                                          96    643 -> 701                  823 -> 721
+//                                         128    656 -> 854                  824 -> 863
+//   the same, GELU                         48    389 -> 376                  392 -> 389
+//   d 2048, f 8192, 16 experts, GELU        8    216 -> 188                  207 -> 161
+//                                          48    229 -> 224                  359 -> 232
+//                                          64    235 -> 264                  357 -> 276
+//   d 4096, f 1024, 40 experts, SwiGLU     48    294 -> 206    293 -> 225    294 -> 230
+//   d 2048, f 1024, 128 experts, SwiGLU    16    348 -> 280    329 -> 248    180 -> 166
+//                                          48    373 -> 311    411 -> 340    257 -> 241
+//                                          56    378 -> 325                  197 -> 223
+//                                          80    389 -> 401                  270 -> 273
+//   d 2048, f 1024, 256 experts, GELU      16    452 -> 371    346 -> 270    139 -> 140
+//                                          48    476 -> 419    462 -> 442    241 -> 263
+//   d 1024, f 512, 64 experts, SwiGLU      16     48 -> 45      49 -> 47      48 -> 42
+//                                          48     49 -> 49      83 -> 61      51 -> 55
+//   d 1024, f 512, 128 experts, SwiGLU     16    106 -> 79     102 -> 73      53 -> 54
+//                                          32    110 -> 83     115 -> 100     57 -> 65
+//                                          48    114 -> 102    152 -> 109     88 -> 85
+// What loses below the line (1-15 %) is the steepest bias over 64 and more small experts, most of them idle while one has
+// a thousand rows; the host does not see the load, and a lower line for many experts would give up more than it saves.
 constexpr int SKINNY_AVERAGE = 48;
 inline bool skinny_applies(long long rows, int E) { return rows <= (long long)SKINNY_AVERAGE * E; }
 
