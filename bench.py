@@ -119,15 +119,12 @@ def gemm_flops(w, S_rows, S, present):
     unit = 2 * S_rows * w.d * w.f
     flops = {"gemm1_fwd": unit * (2 if swi else 1), "gemm2_fwd": unit, "dh_bwd": unit, "dw2_bwd": unit,
              "dw1_bwd": unit * (2 if swi else 1), "dx_bwd": unit * (2 if swi else 1)}
-    if w.dtype != S.DT_F32:
-        # moe_expert_ffn_bwd: a row-tile GEMM of at most 2048 tiles shares its launch with the weight-gradient
-        # GEMM after it, and the shared launch is bracketed under the row-tile GEMM
-        max_tiles = (w.T * w.k + 255) // 256 + w.E
-        if ((w.f + 255) // 256) * max_tiles <= 2048:
-            flops["dh_bwd"] += flops.pop("dw2_bwd")
-        if ((w.d + 255) // 256) * max_tiles <= 2048:
-            flops["dx_bwd"] += unit
-            flops["dw1_bwd"] -= unit
+    # moe_expert_ffn_bwd: a row-tile GEMM of at most about eight rounds of tiles shares its launch with the weight
+    # gradients after it, and the shared launch is bracketed under the row-tile GEMM
+    if "dw2_bwd" not in present:
+        flops["dh_bwd"] += flops.pop("dw2_bwd")
+    if "dw1_bwd" not in present:
+        flops["dx_bwd"] += flops.pop("dw1_bwd")
     return {n: v for n, v in flops.items() if n in present and v > 0}
 
 
@@ -316,8 +313,8 @@ def run_workload(name, steps, warmup, args, full):
     tpath = os.path.join(ROOT, "profiles", "hbm_traffic.json")
     if os.path.exists(tpath):
         traffic = json.load(open(tpath)).get(w.name, {}).get(dom)
-    paired = bf and ((dom == "dh_bwd" and "dw2_bwd" not in kern_ms) or (dom == "dx_bwd" and flops[dom] > 2 * S_rows * w.d * w.f * (2 if swi else 1)))
-    kname = ("gemm_bf16_pair_kernel" if paired else "gemm_bf16_kernel") if bf else "gemm_f32_kernel"
+    paired = (dom == "dh_bwd" and "dw2_bwd" not in kern_ms) or (dom == "dx_bwd" and "dw1_bwd" not in kern_ms)
+    kname = f"gemm_{'bf16' if bf else 'f32'}_{'pair_' if paired else ''}kernel"
     res["roofline"] = {"bound": "mfma", "kernel": f"{kname} ({dom})", "achieved": round(dom_tf, 1), "peak": peak,
                        "unit": "TFLOP/s", "frac": round(dom_tf / peak, 4), "traffic": traffic,
                        "flops_per_launch": flops[dom], "us_per_launch": round(dom_st["mean"] * 1e3, 2),

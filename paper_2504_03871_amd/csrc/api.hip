@@ -26,9 +26,10 @@ int check_cfg(const moe_cfg* c) {
   return MOE_OK;
 }
 
-// 16-bit backward: a row-tile GEMM of N columns with at most about eight rounds of tiles shares its launch (moe_expert_ffn_bwd)
-static bool shares_launch(int N, int max_tiles) {
-  return (long long)((N + gemm_bf16_tile_rows() - 1) / gemm_bf16_tile_rows()) * max_tiles <= 8ll * 256;
+// backward: a row-tile GEMM of N columns with at most about eight rounds of tiles shares its launch (moe_expert_ffn_bwd)
+static bool shares_launch(const moe_cfg* c, int N, int max_tiles) {
+  const int cols = is_half(c) ? gemm_bf16_tile_rows() : F32_TILE_COLS;
+  return (long long)((N + cols - 1) / cols) * max_tiles <= 8 * (is_half(c) ? 256 : F32_LOW_TILES);
 }
 
 WsLayout ws_layout(const moe_cfg* c) {
@@ -56,7 +57,7 @@ WsLayout ws_layout(const moe_cfg* c) {
     const bool skinny = skinny_applies(A, c->E), small = split_k_applies(c->E, c->d_ff);
     const size_t rows = split_ws_bytes(c->E, c->d_model), tail = tail_ws_bytes(max_tiles, c->d_model);
     fwd = skinny ? (skinny_split(c->E, c->d_ff) ? rows : 0) : std::max(small ? rows : 0, tail);
-    if (c->act == MOE_ACT_GELU) bwd = std::max(small ? rows : 0, shares_launch(c->d_model, max_tiles) ? 0 : tail);
+    if (c->act == MOE_ACT_GELU) bwd = std::max(small ? rows : 0, shares_launch(c, c->d_model, max_tiles) ? 0 : tail);
   }
   off += align_up(std::max(bwd, fwd > dact ? fwd - dact : 0), 256);
   w.ffn_bwd_dact = off;
@@ -169,6 +170,10 @@ static int launch_gemm(const moe_cfg* c, int mode, int epi, bool dual, bool chai
                        hipStream_t s) {
   return is_half(c) ? launch_gemm_half(c->dtype, mode, epi, dual, chain, g, max_tiles, s)
                     : launch_gemm_f32(mode, epi, dual, chain, g, tile_rows_for(c), max_tiles, s);
+}
+static int launch_pair(const moe_cfg* c, int epi1, bool chain1, const GemmArgs& g1, int max_tiles, const GemmArgs& g2, hipStream_t s) {
+  return is_half(c) ? launch_gemm_half_pair(c->dtype, epi1, chain1, g1, max_tiles, g2, s)
+                    : launch_gemm_f32_pair(epi1, chain1, g1, tile_rows_for(c), max_tiles, g2, s);
 }
 
 }  // namespace moe
@@ -520,29 +525,28 @@ int moe_expert_ffn_bwd(const moe_cfg* cfg, const void* dy_perm, const void* x_pe
   gh.chunked = row_tiles_chunked(A, d, f, cfg->E, 1, (int)elt_size(cfg));
   gx.chunked = row_tiles_chunked((swiglu ? 2ll : 1ll) * A, f, d, cfg->E, swiglu ? 2 : 1, (int)elt_size(cfg));
   const int epi_h = swiglu ? EPI_SWIGLU_BWD : EPI_GELU_BWD;
-  // bf16: a row-tile GEMM with few rounds of tiles shares its launch with the weight-gradient GEMM that
-  // follows it (dH with dW2, dx with dW1), whose tiles then start on the compute units that its last,
-  // partly filled round leaves idle.  With many rounds that idle share is small and separate launches
-  // keep the cache to one GEMM at a time.  (Timing brackets: a shared launch counts under the row-tile GEMM.)
+  // A row-tile GEMM with few rounds of tiles shares its launch with the weight-gradient GEMM that follows it (dH with
+  // dW2, dx with dW1, and dW1b where there is one), whose tiles then start on the compute units that its last, partly
+  // filled round leaves idle.  With many rounds that idle share is small and separate launches keep the cache to one
+  // GEMM at a time.  dW1 and dW1b are one launch in any case.  (Timing brackets: a shared launch counts under the
+  // row-tile GEMM.)  Three to five launches before: fp32, T 2000, d 516, f 1540, SwiGLU step 743 -> 681 us, T 512, d 128,
+  // f 256, GELU 101 -> 92; bf16 SwiGLU (dW1b had its own), 3001 rows, d 1088, f 2880 624 -> 609, 128 experts of 512 rows
+  // 3735 -> 3695.
   const bool bf = is_half(cfg);
-  const bool pair_h = bf && shares_launch(f, max_tiles), pair_x = bf && shares_launch(d, max_tiles);
+  const bool pair_h = shares_launch(cfg, f, max_tiles), pair_x = shares_launch(cfg, d, max_tiles);
+  if (swiglu) { gw1.B2 = dact + plane; gw1.C2 = dW1b; }
   {
     ProfScope ps(cfg, MOE_PROF_DH_BWD, s);
-    if (pair_h) CHECK(launch_gemm_half_pair(cfg->dtype, epi_h, false, gh, max_tiles, gw2, s));
+    if (pair_h) CHECK(launch_pair(cfg, epi_h, false, gh, max_tiles, gw2, s));
     else CHECK(launch_gemm(cfg, MODE_NT, epi_h, false, false, gh, max_tiles, s));
   }
   if (!pair_h) {
     ProfScope ps(cfg, MOE_PROF_DW2_BWD, s);
     CHECK(launch_gemm(cfg, MODE_TN, EPI_DW, false, false, gw2, 0, s));
   }
-  if (!pair_x || swiglu) {
+  if (!pair_x) {
     ProfScope ps(cfg, MOE_PROF_DW1_BWD, s);
-    if (!pair_x) CHECK(launch_gemm(cfg, MODE_TN, EPI_DW, false, false, gw1, 0, s));
-    if (swiglu) {
-      GemmArgs gw1b = gw1;
-      gw1b.B = dact + plane; gw1b.C = dW1b;
-      CHECK(launch_gemm(cfg, MODE_TN, EPI_DW, false, false, gw1b, 0, s));
-    }
+    CHECK(launch_gemm(cfg, MODE_TN, EPI_DW, false, false, gw1, 0, s));
   }
   ProfScope ps(cfg, MOE_PROF_DX_BWD, s);
   // split-K of the GELU dx: the smallest row tiles; the last round only in a launch of its own (in a shared one the
@@ -550,7 +554,7 @@ int moe_expert_ffn_bwd(const moe_cfg* cfg, const void* dy_perm, const void* x_pe
   gx.split_small = bf && !swiglu && split_k_applies(cfg->E, f);
   gx.split_tail = bf && !swiglu && !pair_x && tail_may_split(A, cfg->E, cfg->capacity == 0 && slice_lo == nullptr, (d + tr - 1) / tr, f);
   if (gx.split_small || gx.split_tail) gx.split_ws = reinterpret_cast<float*>(static_cast<char*>(ws) + w.ffn_split);
-  if (pair_x) return launch_gemm_half_pair(cfg->dtype, EPI_STORE, swiglu, gx, max_tiles, gw1, s);
+  if (pair_x) return launch_pair(cfg, EPI_STORE, swiglu, gx, max_tiles, gw1, s);
   return launch_gemm(cfg, MODE_NT, EPI_STORE, false, swiglu, gx, max_tiles, s);
 }
 

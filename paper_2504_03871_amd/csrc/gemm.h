@@ -273,9 +273,9 @@ struct GemmArgs {
   const void* A;
   const void* A2;   // second activation operand (SwiGLU dX: dU)
   const void* B;
-  const void* B2;   // second weight operand (SwiGLU: W1b)
+  const void* B2;   // second weight operand (SwiGLU: W1b); weight gradients: dU, where C2 is given
   void* C;
-  void* C2;
+  void* C2;         // weight gradients: a second one of the same A (SwiGLU: dW1b), in the same launch
   void* C3;
   const void* S1;
   const void* S2;
@@ -304,13 +304,15 @@ int launch_tile_map(const int32_t* offsets, const int32_t* kept, const int32_t* 
 
 // fp32 storage, fp32 MFMA (any shape that passes check_cfg)
 int launch_gemm_f32(int mode, int epi, bool dual, bool chain, const GemmArgs& g, int tile_rows, int max_tiles, hipStream_t s);
+int launch_gemm_f32_pair(int epi1, bool chain1, const GemmArgs& g1, int tile_rows, int max_tiles, const GemmArgs& g2, hipStream_t s);
 // Height of its tiles (64 columns wide): 32 rows where 64 would leave the chip short of its three blocks per compute
 // unit; `parts`: partly filled tiles to expect.  64 -> 32 rows, us: SwiGLU forward T 100, d 1024, f 4096 (8 experts, 512
 // tiles of 64) 203 -> 149, GELU step T 1000, d 512, f 1024 (576 tiles) 261 -> 248,
 // SwiGLU step T 300, d 1024, f 1024 285 -> 276; above the line, forced: T 1000, d 700,
 // f 2048, E 32 forward 218 -> 225, step T 2000, d 1024, f 1024, E 16 639 -> 653, T 4096, d 1024, f 4096 3592 -> 3787.
 constexpr long long F32_LOW_TILES = 768;
-inline int f32_tile_rows(long long rows, int parts, int N) { return ((rows + 63) / 64 + parts) * ((N + 63) / 64) < F32_LOW_TILES ? 32 : 64; }
+constexpr int F32_TILE_COLS = 64;
+inline int f32_tile_rows(long long rows, int parts, int N) { return ((rows + 63) / 64 + parts) * ((N + F32_TILE_COLS - 1) / F32_TILE_COLS) < F32_LOW_TILES ? 32 : 64; }
 // 16-bit storage (dtype = MOE_DTYPE_BF16 or MOE_DTYPE_F16), MFMA with fp32 accumulation
 int launch_gemm_half(int dtype, int mode, int epi, bool dual, bool chain, const GemmArgs& g, int max_tiles, hipStream_t s);
 // one launch for an NT GEMM (epilogue epi1, chained or not) followed by a TN weight-gradient GEMM

@@ -11,6 +11,11 @@ namespace moe {
 constexpr int T_BM = 256, T_BN = 256, T_BN_DUAL = 128, T_WGM = 2, T_WGN = 4;
 int gemm_bf16_tile_rows() { return T_BM; }
 
+// blocks of a weight-gradient launch (dw_block), of two gradients where the second is asked for
+static long long dw_blocks(const GemmArgs& g) {
+  const long long p = (long long)((g.N + T_BN - 1) / T_BN) * ((g.M + T_BM - 1) / T_BM);
+  return (p + NUM_XCD - 1) / NUM_XCD * NUM_XCD * g.E * (g.C2 != nullptr ? 2 : 1);
+}
 // blocks of a split launch beyond one per tile
 static long long split_blocks(const GemmArgs& g, long long ntn) {
   const long long small = g.split_small ? (long long)g.E * ntn * (SPLIT_K - 1) : 0;
@@ -39,7 +44,7 @@ static int launch_one(const GemmArgs& g, int max_tiles, hipStream_t s) {
   }
   const int ntn = (g.N + BN - 1) / BN;
   long long tiles;
-  if (MODE == MODE_TN) tiles = (long long)((ntn * ((g.M + T_BM - 1) / T_BM) + NUM_XCD - 1) / NUM_XCD * NUM_XCD) * g.E;
+  if (MODE == MODE_TN) tiles = dw_blocks(g);
   else tiles = (long long)ntn * max_tiles;
   const bool split = MODE != MODE_TN && EPI == EPI_STORE && !CHAIN && g.split_ws != nullptr;
   kern<<<dim3(gemm_bf16_grid(tiles + (split ? split_blocks(g, ntn) : 0))), T_WGM * T_WGN * 64, lds, s>>>(g);
@@ -48,7 +53,8 @@ static int launch_one(const GemmArgs& g, int max_tiles, hipStream_t s) {
   return launch_split_reduce<ST>(g, tiles, s);
 }
 
-// A row-tile GEMM (NT) and a weight-gradient GEMM (TN) in one launch; the first one's blocks come first.
+// A row-tile GEMM (NT) and a weight-gradient GEMM (TN, one gradient or two of the same A) in one launch; the first one's
+// blocks come first.
 template <typename ST, int EPI1, bool CHAIN1>
 static int launch_pair(const GemmArgs& g1, int max_tiles, const GemmArgs& g2, hipStream_t s) {
   constexpr int lds1 = gemm_bf16_lds_bytes<T_BM, T_BN, false, T_WGM, T_WGN, EPI1 == EPI_GELU_BWD && Half16<ST>::GELU_TABLE>();
@@ -68,8 +74,7 @@ static int launch_pair(const GemmArgs& g1, int max_tiles, const GemmArgs& g2, hi
   const bool split = EPI1 == EPI_STORE && !CHAIN1 && g1.split_ws != nullptr;
   const long long tiles1 = (long long)ntn1 * max_tiles, t1 = tiles1 + (split ? split_blocks(g1, ntn1) : 0);
   const long long n1 = (t1 + NUM_XCD - 1) / NUM_XCD * NUM_XCD;
-  const long long p2 = (long long)((g2.N + T_BN - 1) / T_BN) * ((g2.M + T_BM - 1) / T_BM);
-  const long long n2 = (p2 + NUM_XCD - 1) / NUM_XCD * NUM_XCD * g2.E;
+  const long long n2 = dw_blocks(g2);
   if (n1 + n2 > 0x7fffffffll) return MOE_ERR_BAD_SHAPE;
   kern<<<dim3(gemm_bf16_grid(n1 + n2)), T_WGM * T_WGN * 64, lds, s>>>(g1, g2, (int)n1);
   const int rc = launch_status();

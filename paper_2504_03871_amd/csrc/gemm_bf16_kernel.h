@@ -238,6 +238,7 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs& g, const int vb, 
 
   int e, row0, mvalid, klen, m0 = 0, n0;
   int kbase = 0;
+  bool second = false;          // TN with two gradients: this block's tile is one of the second's (B2, C2)
   float* part_sums = nullptr;   // this block computes one K part of a split tile: where its fp32 sums go, and their pitch
   int part_pitch = 0;
   {
@@ -248,6 +249,7 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs& g, const int vb, 
       const int ntm = (g.M + BM - 1) / BM;
       int slot, mt;
       if (!dw_block(vb, ntm, ntn, slot, mt, nt)) return;
+      if (g.C2 != nullptr) { slot = __builtin_amdgcn_readfirstlane(slot); second = slot & 1; slot >>= 1; }   // the two gradients of an expert follow each other
       e = g.order[slot];
       m0 = mt * BM;
       rt = 0;
@@ -345,7 +347,7 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs& g, const int vb, 
     // back through one pipeline), byte counts the tile may read, pitches and the advance per K stage
     const bf16* A0 = reinterpret_cast<const bf16*>(g.A);
     const bf16* A1 = reinterpret_cast<const bf16*>(CHAIN ? g.A2 : g.A);
-    const bf16* B0 = reinterpret_cast<const bf16*>(g.B);
+    const bf16* B0 = reinterpret_cast<const bf16*>(MODE == MODE_TN && second ? g.B2 : g.B);
     const bf16* B1 = reinterpret_cast<const bf16*>(g.B2);   // SwiGLU: second weight matrix
     size_t aoff, boff, abytes, bbytes;
     unsigned pa, pb, astep, bstep;
@@ -555,7 +557,7 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs& g, const int vb, 
     // plain stores); what is left of it is the 512 KB a tile moves, which 256 tiles at once do at HBM speed.
     f32x4 old[MODE == MODE_TN ? 2 : 1][MODE == MODE_TN ? PASSES : 1];
     auto grad_at = [&](int band, int p) {
-      return reinterpret_cast<f32x4*>(reinterpret_cast<float*>(g.C) + ((size_t)e * g.M + m0 + (band * WGM + wm) * 32 + p * RPP + rr) * g.N + n0 + wn * C + c4 * 4);
+      return reinterpret_cast<f32x4*>(reinterpret_cast<float*>(second ? g.C2 : g.C) + ((size_t)e * g.M + m0 + (band * WGM + wm) * 32 + p * RPP + rr) * g.N + n0 + wn * C + c4 * 4);
     };
     auto load_old = [&](int band, f32x4* d) {
       if (g.accumulate) {

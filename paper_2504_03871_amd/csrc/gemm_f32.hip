@@ -173,7 +173,7 @@ int launch_tile_map(const int32_t* offsets, const int32_t* kept, const int32_t* 
 // K order: lane group g = lane / 16 supplies K value 4 g + s of every run of 16 in step s, for both operands, so a
 // 16-byte read along K serves four steps.  Columns: lane c = lane % 16 holds columns 4 c .. 4 c + 3 of the wave's 64
 // as column tiles j = 0 .. 3, so a 16-byte read across columns serves four tiles and the results leave as 16-byte rows.
-constexpr int SB = 64;   // tile edge
+constexpr int SB = F32_TILE_COLS;   // tile edge
 constexpr int SK = 32;   // K values per stage
 
 // bytes of an operand tile of R rows (or columns); 16-byte chunks of it per thread
@@ -205,7 +205,7 @@ __device__ __forceinline__ void f32_chunk(int id, unsigned pitch, unsigned& off,
 
 template <int EPI>
 __device__ __forceinline__ void epilogue_f32x4(const GemmArgs& g, size_t idx, const f32x4& a, const f32x4& a2, const f32x4& s1,
-                                               const f32x4& s2) {
+                                               const f32x4& s2, bool second_grad) {
   auto at = [&](void* base) { return reinterpret_cast<f32x4*>(reinterpret_cast<float*>(base) + idx); };
   f32x4 r, q;
   if constexpr (EPI == EPI_STORE) {
@@ -234,26 +234,32 @@ __device__ __forceinline__ void epilogue_f32x4(const GemmArgs& g, size_t idx, co
     *at(g.C) = r;
     *at(g.C2) = q;
   } else {
-    *at(g.C) = g.accumulate ? s1 + a : a;
+    *at(second_grad ? g.C2 : g.C) = g.accumulate ? s1 + a : a;
   }
 }
 
+template <bool DUAL, int BM>
+constexpr int f32_lds_bytes() { return (f32_tile_bytes(BM) + f32_tile_bytes(SB) * (DUAL ? 2 : 1)) * (DUAL ? 2 : 3); }
+
+// One output tile; vb = its number in dispatch order.
 template <int MODE, int EPI, bool DUAL, bool CHAIN, int BM>
-__global__ __launch_bounds__(256, BM == SB ? 3 : 4) void gemm_f32_kernel(GemmArgs g) {
+__device__ __forceinline__ void gemm_f32_tile(const GemmArgs& g, const int vb, char* smem) {
   constexpr bool A_KC = MODE != MODE_TN, B_KC = MODE == MODE_NT;
   constexpr int BANDS = BM / 16, KH = 4 / BANDS;                        // KH waves share a band, each with every KH-th run of 16 K values
   constexpr int A_TILE = f32_tile_bytes(BM), B_TILE = f32_tile_bytes(SB), CHA = f32_chunks(BM), CHB = f32_chunks(SB);
   constexpr int STAGE = A_TILE + B_TILE * (DUAL ? 2 : 1), NBUF = DUAL ? 2 : 3;   // 48 KB either way (BM 32: 36 and 40 KB)
   constexpr int AHEAD = NBUF - 1;                                       // stages requested ahead of the one in use
   constexpr int L = CHA + CHB * (DUAL ? 2 : 1);                         // loads per thread and stage
-  __shared__ __attribute__((aligned(1024))) char smem[NBUF * STAGE];
+  static_assert(NBUF * STAGE == f32_lds_bytes<DUAL, BM>(), "the caller's LDS");
   const int tid = threadIdx.x, lane = tid & 63, c = lane & 15, grp = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), band = wave % BANDS, kh = wave / BANDS;
   const int ntn = (g.N + SB - 1) / SB;
   int e, row0, mvalid, klen, m0 = 0, nt;
+  bool second_grad = false;
   if constexpr (MODE == MODE_TN) {
     int slot, mt;
-    if (!dw_block(blockIdx.x, (g.M + BM - 1) / BM, ntn, slot, mt, nt)) return;
+    if (!dw_block(vb, (g.M + BM - 1) / BM, ntn, slot, mt, nt)) return;
+    if (g.C2 != nullptr) { second_grad = slot & 1; slot >>= 1; }   // the two gradients of an expert follow each other
     e = g.order[slot];
     m0 = mt * BM;
     int l, h;
@@ -264,7 +270,7 @@ __global__ __launch_bounds__(256, BM == SB ? 3 : 4) void gemm_f32_kernel(GemmArg
     if (klen == 0 && g.accumulate) return;
   } else {
     RowBlock rb;
-    if (!row_tile_block(blockIdx.x, g.ntiles[0], g.ntiles[1], 0, ntn, false, rb)) return;
+    if (!row_tile_block(vb, g.ntiles[0], g.ntiles[1], 0, ntn, false, rb)) return;
     const RowTile t = g.tiles[rb.rt];
     e = t.e;
     row0 = t.row0;
@@ -293,7 +299,7 @@ __global__ __launch_bounds__(256, BM == SB ? 3 : 4) void gemm_f32_kernel(GemmArg
     }
   }
   const rsrc_t ra = make_rsrc(reinterpret_cast<const float*>(g.A) + aoff, abytes);
-  const rsrc_t rb = make_rsrc(reinterpret_cast<const float*>(g.B) + boff, bbytes);
+  const rsrc_t rb = make_rsrc(reinterpret_cast<const float*>(second_grad ? g.B2 : g.B) + boff, bbytes);
   const rsrc_t ra2 = make_rsrc(reinterpret_cast<const float*>(CHAIN ? g.A2 : g.A) + aoff, abytes);
   const rsrc_t rb2 = make_rsrc(reinterpret_cast<const float*>(CHAIN || DUAL ? g.B2 : g.B) + boff, bbytes);
   const int KT1 = (klen + SK - 1) / SK, KT = CHAIN ? 2 * KT1 : KT1;   // a chained GEMM runs its two operand pairs back to back
@@ -400,29 +406,48 @@ __global__ __launch_bounds__(256, BM == SB ? 3 : 4) void gemm_f32_kernel(GemmArg
     if constexpr (EPI == EPI_GELU_BWD || EPI == EPI_SWIGLU_BWD) s1[v] = *reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(g.S1) + idx[v]);
     if constexpr (EPI == EPI_SWIGLU_BWD) s2[v] = *reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(g.S2) + idx[v]);
     if constexpr (EPI == EPI_DW)
-      if (g.accumulate) s1[v] = *reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(g.C) + idx[v]);
+      if (g.accumulate) s1[v] = *reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(second_grad ? g.C2 : g.C) + idx[v]);
   }
 #pragma unroll
   for (int v = 0; v < 4; ++v)
     if (band * 16 + grp * 4 + v < mvalid)
       epilogue_f32x4<EPI>(g, idx[v], f32x4{acc[0][v], acc[1][v], acc[2][v], acc[3][v]},
-                          DUAL ? f32x4{acc2[0][v], acc2[DUAL ? 1 : 0][v], acc2[DUAL ? 2 : 0][v], acc2[DUAL ? 3 : 0][v]} : f32x4{}, s1[v], s2[v]);
+                          DUAL ? f32x4{acc2[0][v], acc2[DUAL ? 1 : 0][v], acc2[DUAL ? 2 : 0][v], acc2[DUAL ? 3 : 0][v]} : f32x4{}, s1[v], s2[v], second_grad);
 }
 
 template <int MODE, int EPI, bool DUAL, bool CHAIN, int BM>
+__global__ __launch_bounds__(256, BM == SB ? 3 : 4) void gemm_f32_kernel(GemmArgs g) {
+  __shared__ __attribute__((aligned(1024))) char smem[f32_lds_bytes<DUAL, BM>()];
+  gemm_f32_tile<MODE, EPI, DUAL, CHAIN, BM>(g, blockIdx.x, smem);
+}
+
+// A row-tile GEMM (NT) and the weight-gradient GEMM(s) that need no result of it in one launch, the row-tile GEMM's
+// blocks first: the weight-gradient tiles start where its last round leaves the chip idle.
+template <int EPI1, bool CHAIN1, int BM1, int BM2>
+__global__ __launch_bounds__(256, BM1 == SB || BM2 == SB ? 3 : 4) void gemm_f32_pair_kernel(GemmArgs g1, GemmArgs g2, int first_blocks) {
+  constexpr int lds1 = f32_lds_bytes<false, BM1>(), lds2 = f32_lds_bytes<false, BM2>();
+  __shared__ __attribute__((aligned(1024))) char smem[lds1 > lds2 ? lds1 : lds2];
+  if ((int)blockIdx.x < first_blocks) gemm_f32_tile<MODE_NT, EPI1, false, CHAIN1, BM1>(g1, blockIdx.x, smem);
+  else gemm_f32_tile<MODE_TN, EPI_DW, false, false, BM2>(g2, blockIdx.x - first_blocks, smem);
+}
+
+// blocks of a weight-gradient launch (dw_block), of two gradients where the second is asked for
+static long long dw_blocks(const GemmArgs& g, int bm) {
+  const long long p = (long long)((g.N + SB - 1) / SB) * ((g.M + bm - 1) / bm);
+  return (p + NUM_XCD - 1) / NUM_XCD * NUM_XCD * g.E * (g.C2 != nullptr ? 2 : 1);
+}
+template <int MODE, int EPI, bool DUAL, bool CHAIN, int BM>
 static int launch_bm(const GemmArgs& g, int max_tiles, hipStream_t s) {
-  const long long ntn = (g.N + SB - 1) / SB;
-  long long blocks;
-  if (MODE == MODE_TN) blocks = (ntn * ((g.M + BM - 1) / BM) + NUM_XCD - 1) / NUM_XCD * NUM_XCD * g.E;
-  else blocks = ntn * max_tiles;
+  const long long ntn = (g.N + SB - 1) / SB, blocks = MODE == MODE_TN ? dw_blocks(g, BM) : ntn * max_tiles;
   if (blocks > 0x7fffffffll) return MOE_ERR_BAD_SHAPE;
   gemm_f32_kernel<MODE, EPI, DUAL, CHAIN, BM><<<dim3((unsigned)blocks), 256, 0, s>>>(g);
   return launch_status();
 }
+static int dw_tile_rows(const GemmArgs& g) { return f32_tile_rows((long long)g.M * g.E * (g.C2 != nullptr ? 2 : 1), 0, g.N); }
 // tile_rows: rows per entry of the tile map (row-tile GEMMs)
 template <int MODE, int EPI, bool DUAL, bool CHAIN>
 static int launch_one(const GemmArgs& g, int tile_rows, int max_tiles, hipStream_t s) {
-  if (MODE == MODE_TN) tile_rows = f32_tile_rows((long long)g.M * g.E, 0, g.N);
+  if (MODE == MODE_TN) tile_rows = dw_tile_rows(g);
   return tile_rows == SB ? launch_bm<MODE, EPI, DUAL, CHAIN, SB>(g, max_tiles, s)
                          : launch_bm<MODE, EPI, DUAL, CHAIN, SB / 2>(g, max_tiles, s);
 }
@@ -436,6 +461,28 @@ int launch_gemm_f32(int mode, int epi, bool dual, bool chain, const GemmArgs& g,
   if (mode == MODE_NT && epi == EPI_STORE && !chain) return launch_one<MODE_NT, EPI_STORE, false, false>(g, tile_rows, max_tiles, s);
   if (mode == MODE_NT && epi == EPI_STORE && chain) return launch_one<MODE_NT, EPI_STORE, false, true>(g, tile_rows, max_tiles, s);
   if (mode == MODE_TN && epi == EPI_DW) return launch_one<MODE_TN, EPI_DW, false, false>(g, tile_rows, max_tiles, s);
+  return MOE_ERR_BAD_DTYPE;
+}
+
+template <int EPI1, bool CHAIN1, int BM1, int BM2>
+static int launch_pair_bm(const GemmArgs& g1, int max_tiles, const GemmArgs& g2, hipStream_t s) {
+  // a multiple of the XCD count: a tile number still tells the XCD for the second GEMM
+  const long long n1 = ((g1.N + SB - 1) / SB * (long long)max_tiles + NUM_XCD - 1) / NUM_XCD * NUM_XCD, n2 = dw_blocks(g2, BM2);
+  if (n1 + n2 > 0x7fffffffll) return MOE_ERR_BAD_SHAPE;
+  gemm_f32_pair_kernel<EPI1, CHAIN1, BM1, BM2><<<dim3((unsigned)(n1 + n2)), 256, 0, s>>>(g1, g2, (int)n1);
+  return launch_status();
+}
+template <int EPI1, bool CHAIN1>
+static int launch_pair(const GemmArgs& g1, int tile_rows, int max_tiles, const GemmArgs& g2, hipStream_t s) {
+  const bool low1 = tile_rows != SB, low2 = dw_tile_rows(g2) != SB;
+  if (low1) return low2 ? launch_pair_bm<EPI1, CHAIN1, SB / 2, SB / 2>(g1, max_tiles, g2, s) : launch_pair_bm<EPI1, CHAIN1, SB / 2, SB>(g1, max_tiles, g2, s);
+  return low2 ? launch_pair_bm<EPI1, CHAIN1, SB, SB / 2>(g1, max_tiles, g2, s) : launch_pair_bm<EPI1, CHAIN1, SB, SB>(g1, max_tiles, g2, s);
+}
+int launch_gemm_f32_pair(int epi1, bool chain1, const GemmArgs& g1, int tile_rows, int max_tiles, const GemmArgs& g2, hipStream_t s) {
+  if (epi1 == EPI_GELU_BWD) return launch_pair<EPI_GELU_BWD, false>(g1, tile_rows, max_tiles, g2, s);
+  if (epi1 == EPI_SWIGLU_BWD) return launch_pair<EPI_SWIGLU_BWD, false>(g1, tile_rows, max_tiles, g2, s);
+  if (epi1 == EPI_STORE && !chain1) return launch_pair<EPI_STORE, false>(g1, tile_rows, max_tiles, g2, s);
+  if (epi1 == EPI_STORE && chain1) return launch_pair<EPI_STORE, true>(g1, tile_rows, max_tiles, g2, s);
   return MOE_ERR_BAD_DTYPE;
 }
 

@@ -40,13 +40,13 @@ def find_csv(d, suffix):
 def gemm_role(name, nth=0):
     """(bench bracket, description) of a grouped-GEMM kernel from its MANGLED name (rocprofv3 -M: its demangler
     does not know the bf16 type); nth = index of the launch within a step for the weight-gradient kernel, which
-    serves dW2, dW1 (and dW1b) in that order."""
-    m = re.search(r"gemm_bf16_pair_kernelIDF16[b_]Li(\d)ELi(\d)ELb([01])E", name)
+    serves dW2 and dW1 (SwiGLU: with dW1b) in that order."""
+    m = re.search(r"gemm_(?:bf16_pair_kernelIDF16[b_]Li\d|f32_pair_kernelI)E?Li(\d)ELb([01])E", name)
     if m:
-        epi, chain = int(m.group(2)), m.group(3) == "1"
+        epi, chain = int(m.group(1)), m.group(2) == "1"
         if epi in (3, 4):
             return "dh_bwd", "dH = dy W2^T with the activation-derivative epilogue, and dW2 = H^T dy, one launch"
-        return "dx_bwd", "dx = dA W1^T" + (" (two chained products)" if chain else "") + ", and dW1 = x_perm^T dA, one launch"
+        return "dx_bwd", "dx = dA W1^T" + (" (two chained products)" if chain else "") + ", and dW1 = x_perm^T dA (SwiGLU: both), one launch"
     m = re.search(r"gemm_skinny_kernelIDF16[b_]Li(\d)ELb([01])E", name)
     if m:
         return ("gemm2_fwd", "y_perm = H W2, few rows per expert") if m.group(1) == "0" else ("gemm1_fwd", "GEMM1 and its activation, few rows per expert")
@@ -65,7 +65,7 @@ def gemm_role(name, nth=0):
     if mode == 1 and epi == 0:
         return "dx_bwd", "dx_perm = dA W1^T" + (" (dG W1^T + dU W1b^T chained)" if chain else "")
     if mode == 2:
-        return ("dw2_bwd", "dw1_bwd", "dw1_bwd")[min(nth, 2)], "weight gradient x^T dy (dW2, then dW1, then dW1b for SwiGLU)"
+        return ("dw2_bwd", "dw1_bwd")[min(nth, 1)], "weight gradient x^T dy (dW2, then dW1, with dW1b for SwiGLU)"
     return None, ""
 
 
@@ -226,7 +226,7 @@ def main():
             tn = role0.startswith("dw")
             n_per = 1
             if tn and bench:     # launches per step of the weight-gradient kernel
-                n_per = 3 if "SwiGLU" in bench["config"]["workload"] else 2
+                n_per = 2
             for i, ((_, vf), (_, vw)) in enumerate(zip(pf[k], pw[k])):
                 role, desc = gemm_role(k, i % n_per if tn else 0)
                 groups.setdefault((role, desc), []).append((vf["FETCH_SIZE"] * sf, vw["WRITE_SIZE"] * sw))
@@ -234,8 +234,6 @@ def main():
                 rd = sum(x for x, _ in vals) / len(vals)
                 wr = sum(y for _, y in vals) / len(vals)
                 tot = int((rd + wr) * 1024)
-                if tn and n_per == 3 and role == "dw1_bwd":
-                    tot *= 2     # the bracket holds both launches (dW1 and dW1b)
                 tj[role] = tot
                 lines.append(f"| {role} | {rd/1024:.1f} | {wr/1024:.1f} | {tot} | {desc} |")
         lines += ["", "Reads above the algorithmic figure are operand panels fetched again by tiles whose L2 (4 MB per XCD) no longer",

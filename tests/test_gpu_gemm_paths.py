@@ -54,6 +54,8 @@ def test_accumulated_weight_gradients_are_old_plus_new(T, d, f, E, k, dtype, act
     (1100, 36, 3076, 2, 1, B.ACT_GELU),     # tiles of 64 rows in the row-tile GEMMs, of 32 in the weight gradients
     (1100, 36, 3076, 2, 1, B.ACT_SWIGLU),
     (65, 388, 4100, 2, 1, B.ACT_SWIGLU),    # and the other way round
+    (7000, 36, 4100, 2, 1, B.ACT_GELU),     # too many tiles to share a launch: dH and dW2 in their own
+    (7000, 3588, 36, 2, 1, B.ACT_SWIGLU),   # dx in its own, dW1 and dW1b in one
 ])
 def test_fp32_gemms_at_tile_and_stage_edges(T, d, f, E, k, act):
     from paper_2504_03871_amd import synth as S
