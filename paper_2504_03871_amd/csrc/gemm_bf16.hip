@@ -34,7 +34,7 @@ template <typename ST, int MODE, int EPI, bool DUAL, bool CHAIN>
 static int launch_one(const GemmArgs& g, int max_tiles, hipStream_t s) {
   constexpr int BN = DUAL ? T_BN_DUAL : T_BN;
   constexpr bool TAB = (EPI == EPI_GELU_BWD || EPI == EPI_GELU_FWD) && Half16<ST>::GELU_TABLE;
-  constexpr int lds = gemm_bf16_lds_bytes<T_BM, BN, DUAL, T_WGM, T_WGN, TAB>();
+  constexpr int lds = gemm_bf16_lds_bytes<T_BM, BN, DUAL, TAB>();
   auto kern = gemm_bf16_kernel<ST, MODE, EPI, DUAL, CHAIN, T_BM, BN, T_WGM, T_WGN>;
   // more than 64 KB of dynamic LDS needs the attribute on the current device; set on every launch (a cheap
   // host-side call) rather than remembered, so the library keeps no per-process or per-device state
@@ -53,12 +53,11 @@ static int launch_one(const GemmArgs& g, int max_tiles, hipStream_t s) {
   return launch_split_reduce<ST>(g, tiles, s);
 }
 
-// A row-tile GEMM (NT) and a weight-gradient GEMM (TN, one gradient or two of the same A) in one launch; the first one's
-// blocks come first.
+// A row-tile GEMM (NT) and a weight-gradient GEMM (TN) in one launch; the first one's blocks come first.
 template <typename ST, int EPI1, bool CHAIN1>
 static int launch_pair(const GemmArgs& g1, int max_tiles, const GemmArgs& g2, hipStream_t s) {
-  constexpr int lds1 = gemm_bf16_lds_bytes<T_BM, T_BN, false, T_WGM, T_WGN, EPI1 == EPI_GELU_BWD && Half16<ST>::GELU_TABLE>();
-  constexpr int lds2 = gemm_bf16_lds_bytes<T_BM, T_BN, false, T_WGM, T_WGN>();
+  constexpr int lds1 = gemm_bf16_lds_bytes<T_BM, T_BN, false, EPI1 == EPI_GELU_BWD && Half16<ST>::GELU_TABLE>();
+  constexpr int lds2 = gemm_bf16_lds_bytes<T_BM, T_BN, false>();
   constexpr int lds = lds1 > lds2 ? lds1 : lds2;
   auto kern = gemm_bf16_pair_kernel<ST, MODE_NT, EPI1, CHAIN1, MODE_TN, EPI_DW, T_BM, T_BN, T_WGM, T_WGN>;
   // more than 64 KB of dynamic LDS needs the attribute on the current device; set on every launch (a cheap

@@ -32,12 +32,12 @@
 // and read with the transposing 8-byte LDS read of gfx950, so nothing is ever transposed in global
 // memory and the same kernel serves x W (NN), dy W^T (NT) and x^T dy (TN).
 //
-// Epilogue: accumulators go through a per-wave LDS slab to turn the MFMA register layout into rows,
-// so that every output (and every saved tensor the backward epilogues read) moves as 8-byte (bf16) or
-// 16-byte (fp32 weight gradients) pieces per lane that fill whole 128-byte lines.
+// Epilogue: straight from the accumulators.  The weights are the MFMA's first operand, so that a lane ends up with four
+// adjacent columns of one row; exchanges between lanes turn that into 16 bytes per lane and whole 128-byte lines, for
+// the outputs and for the saved tensors that the backward epilogues read ("accumulator layout -> memory layout" below).
 //
 // MFMA 16x16x32 register layout: lane l supplies row/column l%16 and the eight K values (l/16)*8..+7 of
-// the step; accumulator register v of lane l is row (l/16)*4 + v, column l%16 of the 16x16 tile.
+// the step; accumulator register v of lane l is row (l/16)*4 + v of the first operand, row l%16 of the second.
 #pragma once
 #include "gemm.h"
 
@@ -138,85 +138,154 @@ __device__ __forceinline__ float sigmoid_fast(float g) {
   return __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(g * -1.44269504088896340736f));
 }
 
-// Row-layout epilogue on four consecutive columns starting at flat index idx (bf16 tensors).
 // Entry of the LDS copy of a GELU table (layout: gemm.h) for the bf16 number with bit pattern `bits`.
 __device__ __forceinline__ float gelu_tab_lookup(const float* tab, uint32_t bits) {
   const int m = min(max((int)(bits & 0x7fffu) - (GELU_TAB_EXP0 << 7), 0), GELU_TAB_NMAG - 1);
   return tab[m + (int)(bits >> 15) * GELU_TAB_NMAG];
 }
 
+// Four adjacent columns of one row: the accumulator(s) and the saved values (packed) -> the packed 16-bit outputs.
 template <typename ST, int EPI>
-__device__ __forceinline__ void epilogue4(const GemmArgs& g, size_t idx, const f32x4& a, const f32x4& a2,
-                                          const u32x2& sv1, const u32x2& sv2, const float* tab) {
+__device__ __forceinline__ void activate4(const f32x4& a, const f32x4& a2, const u32x2& sv1, const u32x2& sv2, const float* tab,
+                                          u32x2& c, u32x2& c2, u32x2& c3) {
   typedef Half16<ST> H;
-  auto st = [](void* base, size_t i, float v0, float v1, float v2, float v3) {
-    // outputs are written once and read by a later launch: streaming stores keep them from displacing operand
-    // panels in the L2 (measured: dH -1.3 %, the GELU workloads -0.4 to -1.5 % per step; the SwiGLU forward with
-    // its three stores per element is 1 % faster with plain ones)
-    const u32x2 v = u32x2{H::pack2(v0, v1), H::pack2(v2, v3)};
-    u32x2* p = reinterpret_cast<u32x2*>(reinterpret_cast<ST*>(base) + i);
-    if constexpr (EPI == EPI_SWIGLU_FWD) *p = v; else __builtin_nontemporal_store(v, p);
-  };
-  auto ld = [](const u32x2& r, float* f) {   // four saved 16-bit values, loaded by the caller ahead of time
-    f[0] = H::lo(r.x); f[1] = H::hi(r.x);
-    f[2] = H::lo(r.y); f[3] = H::hi(r.y);
-  };
+  auto pk = [](float v0, float v1, float v2, float v3) { return u32x2{H::pack2(v0, v1), H::pack2(v2, v3)}; };
+  auto up = [](const u32x2& r, float* f) { f[0] = H::lo(r.x); f[1] = H::hi(r.x); f[2] = H::lo(r.y); f[3] = H::hi(r.y); };
   if constexpr (EPI == EPI_STORE) {
-    st(g.C, idx, a[0], a[1], a[2], a[3]);
+    c = pk(a[0], a[1], a[2], a[3]);
   } else if constexpr (EPI == EPI_GELU_FWD) {
     // h = a Phi(v), v = the pre-activation as stored: GELU of the saved tensor; Phi looked up (bf16) or evaluated (fp16)
-    const uint32_t p0 = H::pack2(a[0], a[1]), p1 = H::pack2(a[2], a[3]);
-    if (g.C != nullptr) __builtin_nontemporal_store(u32x2{p0, p1}, reinterpret_cast<u32x2*>(reinterpret_cast<ST*>(g.C) + idx));   // NULL: only H is kept
+    c = pk(a[0], a[1], a[2], a[3]);
     if constexpr (H::GELU_TABLE) {
-      st(g.C2, idx, a[0] * gelu_tab_lookup(tab, p0 & 0xffffu), a[1] * gelu_tab_lookup(tab, p0 >> 16),
-         a[2] * gelu_tab_lookup(tab, p1 & 0xffffu), a[3] * gelu_tab_lookup(tab, p1 >> 16));
+      c2 = pk(a[0] * gelu_tab_lookup(tab, c.x & 0xffffu), a[1] * gelu_tab_lookup(tab, c.x >> 16),
+              a[2] * gelu_tab_lookup(tab, c.y & 0xffffu), a[3] * gelu_tab_lookup(tab, c.y >> 16));
     } else {
-      st(g.C2, idx, a[0] * phi_fast(H::lo(p0)), a[1] * phi_fast(H::hi(p0)), a[2] * phi_fast(H::lo(p1)), a[3] * phi_fast(H::hi(p1)));
+      c2 = pk(a[0] * phi_fast(H::lo(c.x)), a[1] * phi_fast(H::hi(c.x)), a[2] * phi_fast(H::lo(c.y)), a[3] * phi_fast(H::hi(c.y)));
     }
   } else if constexpr (EPI == EPI_SWIGLU_FWD) {
-    if (g.C != nullptr) {   // NULL: only H is kept
-      st(g.C, idx, a[0], a[1], a[2], a[3]);
-      st(g.C2, idx, a2[0], a2[1], a2[2], a2[3]);
-    }
+    c = pk(a[0], a[1], a[2], a[3]);
+    c2 = pk(a2[0], a2[1], a2[2], a2[3]);
     float h[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) h[i] = a[i] * sigmoid_fast(a[i]) * a2[i];
-    st(g.C3, idx, h[0], h[1], h[2], h[3]);
+    c3 = pk(h[0], h[1], h[2], h[3]);
   } else if constexpr (EPI == EPI_GELU_BWD) {
     // the derivative at the saved pre-activation: looked up (bf16) or evaluated (fp16)
-    float o0, o1, o2, o3;
     if constexpr (H::GELU_TABLE) {
-      o0 = a[0] * gelu_tab_lookup(tab, sv1.x & 0xffffu); o1 = a[1] * gelu_tab_lookup(tab, sv1.x >> 16);
-      o2 = a[2] * gelu_tab_lookup(tab, sv1.y & 0xffffu); o3 = a[3] * gelu_tab_lookup(tab, sv1.y >> 16);
+      c = pk(a[0] * gelu_tab_lookup(tab, sv1.x & 0xffffu), a[1] * gelu_tab_lookup(tab, sv1.x >> 16),
+             a[2] * gelu_tab_lookup(tab, sv1.y & 0xffffu), a[3] * gelu_tab_lookup(tab, sv1.y >> 16));
     } else {
-      o0 = a[0] * gelu_grad_fast(H::lo(sv1.x)); o1 = a[1] * gelu_grad_fast(H::hi(sv1.x));
-      o2 = a[2] * gelu_grad_fast(H::lo(sv1.y)); o3 = a[3] * gelu_grad_fast(H::hi(sv1.y));
+      c = pk(a[0] * gelu_grad_fast(H::lo(sv1.x)), a[1] * gelu_grad_fast(H::hi(sv1.x)),
+             a[2] * gelu_grad_fast(H::lo(sv1.y)), a[3] * gelu_grad_fast(H::hi(sv1.y)));
     }
-    st(g.C, idx, o0, o1, o2, o3);
   } else if constexpr (EPI == EPI_SWIGLU_BWD) {
     float gg[4], uu[4], dg[4], du[4];
-    ld(sv1, gg);
-    ld(sv2, uu);
+    up(sv1, gg);
+    up(sv2, uu);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const float sg = sigmoid_fast(gg[i]);
       dg[i] = a[i] * uu[i] * sg * fmaf(gg[i], 1.f - sg, 1.f);
       du[i] = a[i] * gg[i] * sg;
     }
-    st(g.C, idx, dg[0], dg[1], dg[2], dg[3]);
-    st(g.C2, idx, du[0], du[1], du[2], du[3]);
+    c = pk(dg[0], dg[1], dg[2], dg[3]);
+    c2 = pk(du[0], du[1], du[2], du[3]);
+  }
+}
+
+// ---- accumulator layout -> memory layout ----
+// The weights are the MFMA's first operand, so a lane holds four adjacent columns (of group g = lane / 16) of one row
+// (lane % 16) per 16 x 16 tile.  Memory wants 16 bytes per lane and whole 128-byte lines per instruction: with half lines
+// (the four lanes of a row, 64 bytes) the stores of an fp32 tile take 20 us instead of 13 as streaming stores, and saved
+// tensors read by halves cost 10 us more per tile.  Two exchanges between registers and lanes do it, both their own inverse:
+//  * join: the odd 16-lane groups of one tile against the even ones of its neighbour (one instruction per register pair):
+//    a lane then has eight adjacent columns of the two tiles' 32, from lane_col8(g) on;
+//  * swap8: lanes 8-15 of every 16 of one register against lanes 0-7 of another: two registers of 16 rows x 64 bytes
+//    become two of 8 rows x 128 bytes.
+__device__ __forceinline__ int lane_col8(int g) { return (g & 1) * 16 + (g >> 1) * 8; }
+__device__ __forceinline__ u32x2 join16(unsigned a, unsigned b) { return __builtin_amdgcn_permlane16_swap(a, b, false, false); }
+__device__ __forceinline__ u32x4 join_tiles(const u32x2& p0, const u32x2& p1) {   // 16-bit: four columns of each -> eight
+  const u32x2 x = join16(p0.x, p1.x), y = join16(p0.y, p1.y);
+  return u32x4{x.x, y.x, x.y, y.y};
+}
+__device__ __forceinline__ void join_tiles(f32x4& a, f32x4& b) {    // fp32: a = the first four of the eight columns, b = the rest
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    const u32x2 x = join16(__float_as_uint(a[v]), __float_as_uint(b[v]));
+    a[v] = __uint_as_float(x.x);
+    b[v] = __uint_as_float(x.y);
+  }
+}
+template <typename V>   // u32x4 or f32x4
+__device__ __forceinline__ void swap8(V& a, V& b) {
+  constexpr int ROR8 = 0x128;
+  const u32x4 x = __builtin_bit_cast(u32x4, a), y = __builtin_bit_cast(u32x4, b);
+  u32x4 p, q;
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    p[v] = (unsigned)__builtin_amdgcn_update_dpp((int)x[v], (int)y[v], ROR8, 0xf, 0xc, false);
+    q[v] = (unsigned)__builtin_amdgcn_update_dpp((int)y[v], (int)x[v], ROR8, 0xf, 0x3, false);
+  }
+  a = __builtin_bit_cast(V, p);
+  b = __builtin_bit_cast(V, q);
+}
+
+// ---- epilogue accesses through buffer descriptors: 32-bit offsets; what lies past the byte count is not touched ----
+constexpr int AUX_NT = 2;   // streaming access
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t out_rsrc(const void* base, size_t bytes) {
+  const unsigned long long p = (unsigned long long)base;
+  const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)p), hi = __builtin_amdgcn_readfirstlane((unsigned)(p >> 32));
+  const unsigned n = __builtin_amdgcn_readfirstlane(bytes > 0xffffffffull ? 0xffffffffu : (unsigned)bytes);
+  return __builtin_amdgcn_make_buffer_rsrc((void*)(lo | (unsigned long long)hi << 32), 0, (int)n, 0x00020000);
+}
+template <int AUX>
+__device__ __forceinline__ void buf_store16(__amdgpu_buffer_rsrc_t r, unsigned off, const u32x4& v) { __builtin_amdgcn_raw_buffer_store_b128(v, r, off, 0, AUX); }
+__device__ __forceinline__ u32x4 buf_load16_nt(__amdgpu_buffer_rsrc_t r, unsigned off) { return __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, AUX_NT); }
+
+// The 16-bit output planes of an epilogue from element `first` on.
+struct OutPlanes { __amdgpu_buffer_rsrc_t c, c2, c3; bool pre; };   // pre: the forward keeps its pre-activation plane(s)
+template <typename ST, int EPI>
+__device__ __forceinline__ OutPlanes out_planes(const GemmArgs& g, size_t first, size_t bytes) {
+  auto at = [&](void* base) { return out_rsrc(reinterpret_cast<ST*>(base) + first, bytes); };
+  OutPlanes o;
+  o.pre = g.C != nullptr;
+  o.c = at(g.C);
+  o.c2 = (EPI == EPI_GELU_FWD || EPI == EPI_SWIGLU_FWD || EPI == EPI_SWIGLU_BWD) ? at(g.C2) : o.c;
+  o.c3 = EPI == EPI_SWIGLU_FWD ? at(g.C3) : o.c;
+  return o;
+}
+// Forward epilogues of 16 rows x 32 NP columns (NP pairs of tiles), eight columns per lane: NP == 2 leaves as two stores
+// of 8 rows x 128 bytes at off[0], off[1], NP == 1 as one of 16 rows x 64 bytes.
+template <typename ST, int EPI, int NP, int AUX>
+__device__ __forceinline__ void epilogue_fwd(const OutPlanes& o, const unsigned (&off)[NP], const f32x4* a, const f32x4* b, const float* tab) {
+  u32x4 v[3][NP];
+#pragma unroll
+  for (int q = 0; q < NP; ++q) {
+    u32x2 c[2] = {}, c2[2] = {}, c3[2] = {};
+#pragma unroll
+    for (int h = 0; h < 2; ++h) activate4<ST, EPI>(a[2 * q + h], b[EPI == EPI_SWIGLU_FWD ? 2 * q + h : 0], u32x2{}, u32x2{}, tab, c[h], c2[h], c3[h]);
+    v[0][q] = join_tiles(c[0], c[1]);
+    v[1][q] = join_tiles(c2[0], c2[1]);
+    v[2][q] = join_tiles(c3[0], c3[1]);
+  }
+  auto put = [&](__amdgpu_buffer_rsrc_t r, u32x4* w) {
+    if constexpr (NP == 2) swap8(w[0], w[1]);
+#pragma unroll
+    for (int q = 0; q < NP; ++q) buf_store16<AUX>(r, off[q], w[q]);
+  };
+  if (EPI == EPI_STORE || o.pre) put(o.c, v[0]);
+  if constexpr (EPI == EPI_GELU_FWD) put(o.c2, v[1]);
+  if constexpr (EPI == EPI_SWIGLU_FWD) {
+    if (o.pre) put(o.c2, v[1]);
+    put(o.c3, v[2]);
   }
 }
 
 template <int BM, int BN, bool DUAL>
 constexpr int gemm_bf16_stage_bytes() { return BM * BKT * 2 + BN * BKT * 2 * (DUAL ? 2 : 1); }
 // TAB: a GELU table sits behind the ring (the GELU epilogues)
-template <int BM, int BN, bool DUAL, int WGM, int WGN, bool TAB = false>
-constexpr int gemm_bf16_lds_bytes() {
-  constexpr int ring = NBUF * gemm_bf16_stage_bytes<BM, BN, DUAL>();
-  constexpr int slab = WGM * WGN * 32 * (BN / WGN + 8) * 4;   // epilogue: one 32-row fp32 slab per wave
-  return (ring > slab ? ring : slab) + (TAB ? GELU_TAB_FLOATS * 4 : 0);
-}
+template <int BM, int BN, bool DUAL, bool TAB = false>
+constexpr int gemm_bf16_lds_bytes() { return NBUF * gemm_bf16_stage_bytes<BM, BN, DUAL>() + (TAB ? GELU_TAB_FLOATS * 4 : 0); }
 
 // One output tile; vb = the tile's number in dispatch order.  Block-uniform control flow; returns at
 // once for numbers past the last tile (the grid is sized for the worst case).
@@ -446,8 +515,8 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs& g, const int vb, 
     _Pragma("unroll") for (int r__ = 0; r__ < NR; ++r__) {                                                  \
       if ((r__ >> 1) < (NI_)) {                                                                             \
         _Pragma("unroll") for (int j__ = 0; j__ < TNN; ++j__) {                                             \
-          acc[r__][j__] = Half16<ST>::mfma(af[r__], bfr[set_][j__], acc[r__][j__]);                         \
-          if constexpr (DUAL) acc2[r__][j__] = Half16<ST>::mfma(af[r__], bfr2[set_][j__], acc2[r__][j__]);  \
+          acc[r__][j__] = Half16<ST>::mfma(bfr[set_][j__], af[r__], acc[r__][j__]);                         \
+          if constexpr (DUAL) acc2[r__][j__] = Half16<ST>::mfma(bfr2[set_][j__], af[r__], acc2[r__][j__]);  \
         }                                                                                                   \
       }                                                                                                     \
       if (DO_NEXT_) {                                                                                       \
@@ -513,9 +582,6 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs& g, const int vb, 
         if (ni == WTM) MOE_MAINLOOP(WTM);
         else MOE_MAINLOOP(ni);
 #undef MOE_MAINLOOP
-        // the epilogue's slabs reuse the ring: every wave must be done reading fragments first
-        __builtin_amdgcn_s_waitcnt(0);
-        MOE_BLOCK_BARRIER();
       }
 #undef MOE_ITER
     }
@@ -528,87 +594,135 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs& g, const int vb, 
 #undef MOE_BLOCK_BARRIER
   }
 
-  {
-    // per-wave slab [32][WTN*32 + 4] fp32 (the stages are free: the loop ended with a block barrier)
-    constexpr int C = WTN * 32, P = C + 4, LPR = C / 4, RPP = 64 / LPR, PASSES = 32 / RPP;
-    float* slab = reinterpret_cast<float*>(smem) + wave * (32 * P);
-    const int rr = lane / LPR, c4 = lane % LPR;
-    constexpr bool NEED_S1 = (EPI == EPI_GELU_BWD || EPI == EPI_SWIGLU_BWD), NEED_S2 = (EPI == EPI_SWIGLU_BWD);
-    const float* tab_lds = reinterpret_cast<const float*>(smem + NBUF * STAGE);
-    // Saved tensors the backward epilogues read: the loads of a band are issued one band ahead (those of
-    // the first band before anything else), so their latency hides behind the previous band's LDS round
-    // trip and arithmetic (rows past the tile read the tile's first row and are dropped).
-    u32x2 s1[NEED_S1 ? 2 : 1][NEED_S1 ? PASSES : 1], s2[NEED_S2 ? 2 : 1][NEED_S2 ? PASSES : 1];
-    auto load_saved = [&](int band, u32x2* d1, u32x2* d2) {
+  // Epilogue, straight from the accumulators (layouts above).  A wave's columns are all valid or all past the matrix
+  // (widths are multiples of 64).  A round trip through LDS took 2.4-2.7 us per tile instead.  Launches of four rounds,
+  // with it -> without, us: plain store x W K 1024 132 -> 123, GELU forward 157 -> 150, GELU backward 163 -> 155, weight
+  // gradient of 1024 rows 153 -> 143; at K 4096 1-2 %; the SwiGLU epilogues (two planes in, two out) stay within 1 %.
+  // What is left is the memory's time: 128 KB per plane and tile, 4 us, and a streaming writer on other compute units
+  // slows a main loop by as much as the writing takes, so that staggered blocks gain nothing.
+  constexpr int C = WTN * 32;
+  if (wn * C >= nvalid) return;
+  const int grp = lane >> 4, r8 = lane & 7, right = (lane >> 3) & 1;   // after swap8: row of eight, left or right half of a line
+  auto band_row = [&](int i) { return ((i >> 1) * WGM + wm) * 32 + (i & 1) * 16; };   // first row of row tile i
+  auto empty = [&](int i) { return band_row(i) >= mvalid; };
+  if (MODE != MODE_TN && EPI == EPI_STORE && !CHAIN && part_sums != nullptr) {   // fp32 partial sums of this block's K part
 #pragma unroll
-      for (int p = 0; p < PASSES; ++p) {
-        const int m = (band * WGM + wm) * 32 + p * RPP + rr, n = wn * C + c4 * 4;
-        const bool ok = m < mvalid && n < nvalid;
-        const size_t idx = (size_t)(row0 + (ok ? m : 0)) * g.N + n0 + (ok ? n : 0);
-        d1[p] = __builtin_nontemporal_load(reinterpret_cast<const u32x2*>(reinterpret_cast<const bf16*>(g.S1) + idx));
-        if constexpr (NEED_S2) d2[p] = __builtin_nontemporal_load(reinterpret_cast<const u32x2*>(reinterpret_cast<const bf16*>(g.S2) + idx));
-      }
-    };
-    if constexpr (NEED_S1) load_saved(0, s1[0], s2[0]);
-    // Accumulating weight gradients: the old values of a band are requested together, a band ahead, and the sums
-    // leave with streaming stores.  Loaded piece by piece between the stores (which the compiler must not move a load
-    // across) the epilogue was a chain of 32 memory round trips, 21-25 us per tile against 4 without accumulation.
-    // Four micro-batches of 2048 tokens, d 1024, f 4096, eight experts: 2294 -> 2199 us per iteration (2273 with
-    // plain stores); what is left of it is the 512 KB a tile moves, which 256 tiles at once do at HBM speed.
-    f32x4 old[MODE == MODE_TN ? 2 : 1][MODE == MODE_TN ? PASSES : 1];
-    auto grad_at = [&](int band, int p) {
-      return reinterpret_cast<f32x4*>(reinterpret_cast<float*>(second ? g.C2 : g.C) + ((size_t)e * g.M + m0 + (band * WGM + wm) * 32 + p * RPP + rr) * g.N + n0 + wn * C + c4 * 4);
-    };
-    auto load_old = [&](int band, f32x4* d) {
-      if (g.accumulate) {
+    for (int i = 0; i < TM; ++i)
+      if (!empty(i)) {
 #pragma unroll
-        for (int p = 0; p < PASSES; ++p)
-          if ((band * WGM + wm) * 32 + p * RPP + rr < mvalid && wn * C + c4 * 4 < nvalid) d[p] = __builtin_nontemporal_load(grad_at(band, p));
-      }
-    };
-    if constexpr (MODE == MODE_TN) load_old(0, old[0]);
+        for (int j = 0; j < TNN; j += 2) {
+          swap8(acc[i][j], acc[i][j + 1]);
 #pragma unroll
-    for (int i = 0; i < WTM; ++i) {
-      f32x4 va[PASSES], vb[DUAL ? PASSES : 1];
-      if constexpr (NEED_S1) {
-        if (i + 1 < WTM) load_saved(i + 1, s1[(i + 1) & 1], s2[NEED_S2 ? (i + 1) & 1 : 0]);
-      }
-      if constexpr (MODE == MODE_TN) {
-        if (i + 1 < WTM) load_old(i + 1, old[(i + 1) & 1]);
-      }
-#pragma unroll
-      for (int half = 0; half < (DUAL ? 2 : 1); ++half) {
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-#pragma unroll
-        for (int j = 0; j < TNN; ++j)
-#pragma unroll
-          for (int v = 0; v < 8; ++v) {   // lane l of a 16 x 16 tile: column l % 16, rows 4 (l / 16) .. + 3
-            const int i2 = v >> 2, r = i2 * 16 + (lane >> 4) * 4 + (v & 3);
-            slab[r * P + j * 16 + (lane & 15)] =
-                (half == 0) ? acc[2 * i + i2][j][v & 3] : acc2[DUAL ? 2 * i + i2 : 0][DUAL ? j : 0][v & 3];
+          for (int h = 0; h < 2; ++h) {
+            const int m = band_row(i) + h * 8 + r8;
+            if (m < mvalid) *reinterpret_cast<f32x4*>(part_sums + (size_t)m * part_pitch + wn * C + j * 16 + right * 16 + grp * 4) = acc[i][j + h];
           }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-#pragma unroll
-        for (int p = 0; p < PASSES; ++p) {
-          const f32x4 t = *reinterpret_cast<const f32x4*>(slab + (p * RPP + rr) * P + c4 * 4);
-          if (half == 0) va[p] = t; else vb[DUAL ? p : 0] = t;
         }
       }
+    return;
+  }
+  if constexpr (MODE == MODE_TN) {   // fp32 weight gradient of expert e; M is a multiple of 64: whole bands
+    static_assert(TNN % 2 == 0, "pairs of column tiles");
+    const size_t first = ((size_t)e * g.M + m0) * g.N + n0;
+    const __amdgpu_buffer_rsrc_t rc = out_rsrc(reinterpret_cast<float*>(second ? g.C2 : g.C) + first, ((size_t)mvalid * g.N - n0) * 4);
+    const unsigned col = (unsigned)(wn * C + right * 16 + grp * 4) * 4u, pitch = (unsigned)g.N * 4u;
+    auto at = [&](int i, int j) { return (unsigned)(band_row(i) + (j & 1) * 8 + r8) * pitch + col + (unsigned)(j >> 1) * 128u; };
+    auto rows_of_8 = [&](int i) {
 #pragma unroll
-      for (int p = 0; p < PASSES; ++p) {
-        const int m = (i * WGM + wm) * 32 + p * RPP + rr;
-        const int n = wn * C + c4 * 4;
-        if (m < mvalid && n < nvalid) {
-          if (MODE != MODE_TN && EPI == EPI_STORE && !CHAIN && part_sums != nullptr) {   // fp32 partial sum of this block's K part
-            *reinterpret_cast<f32x4*>(part_sums + m * part_pitch + n) = va[p];
-          } else if constexpr (MODE == MODE_TN) {   // fp32 weight gradient of expert e, 16 bytes per lane
-            if (g.accumulate) __builtin_nontemporal_store(old[MODE == MODE_TN ? i & 1 : 0][MODE == MODE_TN ? p : 0] + va[p], grad_at(i, p));
-            else __builtin_nontemporal_store(va[p], grad_at(i, p));
-          } else {
-            epilogue4<ST, EPI>(g, (size_t)(row0 + m) * g.N + n0 + n, va[p], vb[DUAL ? p : 0],
-                           s1[NEED_S1 ? i & 1 : 0][NEED_S1 ? p : 0], s2[NEED_S2 ? i & 1 : 0][NEED_S2 ? p : 0], tab_lds);
+      for (int j = 0; j < TNN; j += 2) swap8(acc[i][j], acc[i][j + 1]);
+    };
+    if (g.accumulate) {
+      // The old values are requested AHEAD row tiles ahead, so that a row tile's latency runs beside the others' sums.
+      // (Loaded piece by piece between the stores, which the compiler must not move a load across, this is a chain of
+      // memory round trips: 21-25 us per tile against 4 without accumulation.)
+      constexpr int AHEAD = 4;
+      u32x4 old[AHEAD][TNN];
+      auto load_old = [&](int i) {
+#pragma unroll
+        for (int j = 0; j < TNN; ++j) old[i % AHEAD][j] = buf_load16_nt(rc, empty(i) ? OUT_OF_RANGE : at(i, j));
+      };
+#pragma unroll
+      for (int i = 0; i < AHEAD - 1; ++i) load_old(i);
+#pragma unroll
+      for (int i = 0; i < TM; ++i) {
+        if (i + AHEAD - 1 < TM) load_old(i + AHEAD - 1);
+        if (!empty(i)) {
+          rows_of_8(i);
+#pragma unroll
+          for (int j = 0; j < TNN; ++j)
+            buf_store16<AUX_NT>(rc, at(i, j), __builtin_bit_cast(u32x4, __builtin_bit_cast(f32x4, old[i % AHEAD][j]) + acc[i][j]));
+        }
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+        if (!empty(i)) {
+          rows_of_8(i);
+#pragma unroll
+          for (int j = 0; j < TNN; ++j) buf_store16<AUX_NT>(rc, at(i, j), __builtin_bit_cast(u32x4, acc[i][j]));
+        }
+    }
+  } else {
+    const size_t first = (size_t)row0 * g.N + n0, bytes = ((size_t)mvalid * g.N - n0) * 2;
+    const OutPlanes o = out_planes<ST, EPI>(g, first, bytes);
+    const unsigned pitch = (unsigned)g.N * 2u;
+    const float* tab_lds = reinterpret_cast<const float*>(smem + NBUF * STAGE);
+    if constexpr (DUAL) {   // 32 columns per wave and matrix; plain stores (the neighbouring wave has the other half of each line)
+      static_assert(TNN == 2, "one pair of column tiles");
+      const unsigned col = (unsigned)(wn * C + lane_col8(grp)) * 2u;
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+        if (!empty(i)) {
+          const int m = band_row(i) + (lane & 15);
+          const unsigned off[1] = {m < mvalid ? (unsigned)m * pitch + col : OUT_OF_RANGE};
+          epilogue_fwd<ST, EPI, 1, 0>(o, off, acc[i], acc2[DUAL ? i : 0], tab_lds);
+        }
+    } else {
+      static_assert(TNN == 4, "two pairs of column tiles");
+      const unsigned col = (unsigned)(wn * C + right * 32 + lane_col8(grp)) * 2u;
+      auto at = [&](int i, int h) { const int m = band_row(i) + h * 8 + r8; return m < mvalid ? (unsigned)m * pitch + col : OUT_OF_RANGE; };
+      // outputs are written once and read by a later launch: streaming stores keep them from displacing operand panels
+      // in the L2 (measured: dH -1.3 %, the GELU workloads -0.4 to -1.5 % per step)
+      if constexpr (EPI == EPI_STORE || EPI == EPI_GELU_FWD) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+          if (!empty(i)) {
+            const unsigned off[2] = {at(i, 0), at(i, 1)};
+            epilogue_fwd<ST, EPI, 2, AUX_NT>(o, off, acc[i], acc[i], tab_lds);
+          }
+      } else {
+        // The saved tensors are requested AHEAD row tiles ahead, the first ones before anything else.
+        constexpr bool TWO = EPI == EPI_SWIGLU_BWD;
+        constexpr int AHEAD = 4;
+        u32x4 s1[AHEAD][2], s2[TWO ? AHEAD : 1][2] = {};
+        const __amdgpu_buffer_rsrc_t r1 = out_rsrc(reinterpret_cast<const ST*>(g.S1) + first, bytes);
+        const __amdgpu_buffer_rsrc_t r2 = TWO ? out_rsrc(reinterpret_cast<const ST*>(g.S2) + first, bytes) : r1;
+        auto load_saved = [&](int i) {
+#pragma unroll
+          for (int h = 0; h < 2; ++h) {
+            s1[i % AHEAD][h] = buf_load16_nt(r1, at(i, h));
+            if constexpr (TWO) s2[TWO ? i % AHEAD : 0][h] = buf_load16_nt(r2, at(i, h));
+          }
+        };
+#pragma unroll
+        for (int i = 0; i < AHEAD - 1; ++i) load_saved(i);
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+          if (i + AHEAD - 1 < TM) load_saved(i + AHEAD - 1);
+          if (!empty(i)) {
+            join_tiles(acc[i][0], acc[i][1]);
+            join_tiles(acc[i][2], acc[i][3]);
+            swap8(acc[i][0], acc[i][2]);
+            swap8(acc[i][1], acc[i][3]);   // rows 0-7: columns 0-3 in [0], 4-7 in [1]; rows 8-15: [2], [3]
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+              u32x2 c[2] = {}, c2[2] = {}, unused;
+              const u32x4 p = s1[i % AHEAD][h], q = s2[TWO ? i % AHEAD : 0][h];
+              activate4<ST, EPI>(acc[i][2 * h], f32x4{}, u32x2{p.x, p.y}, u32x2{q.x, q.y}, tab_lds, c[0], c2[0], unused);
+              activate4<ST, EPI>(acc[i][2 * h + 1], f32x4{}, u32x2{p.z, p.w}, u32x2{q.z, q.w}, tab_lds, c[1], c2[1], unused);
+              buf_store16<AUX_NT>(o.c, at(i, h), u32x4{c[0].x, c[0].y, c[1].x, c[1].y});
+              if constexpr (TWO) buf_store16<AUX_NT>(o.c2, at(i, h), u32x4{c2[0].x, c2[0].y, c2[1].x, c2[1].y});
+            }
           }
         }
       }

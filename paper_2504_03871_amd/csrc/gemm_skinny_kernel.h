@@ -128,43 +128,41 @@ __global__ __launch_bounds__(256, 2) void gemm_skinny_kernel(GemmArgs g) {
           const bf16x8 a = *reinterpret_cast<const bf16x8*>(st + kc_off(i * 16 + c, ks * 4 + grp));
 #pragma unroll
           for (int j = 0; j < TN; ++j) {
-            acc[i][j] = Half16<ST>::mfma(a, b[j], acc[i][j]);
-            if constexpr (DUAL) acc2[i][j] = Half16<ST>::mfma(a, b2[j], acc2[i][j]);
+            acc[i][j] = Half16<ST>::mfma(b[j], a, acc[i][j]);
+            if constexpr (DUAL) acc2[i][j] = Half16<ST>::mfma(b2[j], a, acc2[i][j]);
           }
         }
     }
     buf = buf + 1 == NB ? 0 : buf + 1;
   }
 
-  // accumulators become rows through LDS (the ring is free once every wave has left it)
-  __builtin_amdgcn_s_waitcnt(0x70);
-  __syncthreads();
-  constexpr int P = BN + 4, LPR = BN / 4, RPP = 256 / LPR;
-  float* slab = reinterpret_cast<float*>(smem);
+  // Epilogue straight from the accumulators (layout: gemm_bf16_kernel.h); a wave's 32 columns are all valid or none is
+  static_assert(TN == 2, "one pair of column tiles per wave");
+  const int c0 = wave * (BN / 4);
+  if (n0 + c0 >= g.N) return;
+  if (CAN_SPLIT && rb.split_tile >= 0) {   // fp32 partial sums of this block's K part
+    const int r8 = lane & 7, right = (lane >> 3) & 1;
+    float* sums = g.split_ws + ((size_t)rb.split_tile * parts + rb.ksplit) * SKINNY_ROWS * g.N + n0 + c0 + right * 16 + grp * 4;
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+      if (i < ni) {
+        swap8(acc[i][0], acc[i][1]);
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const int m = i * 16 + h * 8 + r8;
+          if (m < mvalid) *reinterpret_cast<f32x4*>(sums + (size_t)m * g.N) = acc[i][h];
+        }
+      }
+    return;
+  }
+  const OutPlanes o = out_planes<ST, EPI>(g, (size_t)t.row0 * g.N + n0, ((size_t)mvalid * g.N - n0) * 2);
 #pragma unroll
   for (int i = 0; i < TM; ++i)
     if (i < ni) {
-#pragma unroll
-      for (int j = 0; j < TN; ++j)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const int at = (i * 16 + grp * 4 + v) * P + wave * (BN / 4) + j * 16 + c;
-          slab[at] = acc[i][j][v];
-          if constexpr (DUAL) slab[BM * P + at] = acc2[i][j][v];
-        }
+      const int m = i * 16 + c;
+      const unsigned off[1] = {m < mvalid ? ((unsigned)m * g.N + c0 + lane_col8(grp)) * 2u : OUT_OF_RANGE};
+      epilogue_fwd<ST, EPI, 1, 0>(o, off, acc[i], acc2[DUAL ? i : 0], g.gelu_tab);
     }
-  __syncthreads();
-  const int n = (tid % LPR) * 4;
-  if (n0 + n >= g.N) return;
-  for (int m = tid / LPR; m < mvalid; m += RPP) {
-    const f32x4 va = *reinterpret_cast<const f32x4*>(slab + m * P + n);
-    f32x4 vb = va;
-    if constexpr (DUAL) vb = *reinterpret_cast<const f32x4*>(slab + BM * P + m * P + n);
-    if (CAN_SPLIT && rb.split_tile >= 0)   // fp32 partial sum of this block's K part
-      *reinterpret_cast<f32x4*>(g.split_ws + (((size_t)rb.split_tile * parts + rb.ksplit) * SKINNY_ROWS + m) * g.N + n0 + n) = va;
-    else
-      epilogue4<ST, EPI>(g, (size_t)(t.row0 + m) * g.N + n0 + n, va, vb, u32x2{0, 0}, u32x2{0, 0}, g.gelu_tab);
-  }
 }
 
 }  // namespace moe

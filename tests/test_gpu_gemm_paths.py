@@ -92,6 +92,38 @@ def test_few_rows_per_expert(T, d, f, E, k, dtype, act, zipf):
     run_case(S.WORKLOADS["cfg1"].scaled(T=T, d=d, f=f, E=E, k=k, dtype=getattr(S, dtype), act=getattr(S, act), zipf_s=zipf))
 
 
+@pytest.mark.parametrize("act", [B.ACT_GELU, B.ACT_SWIGLU])
+def test_rows_past_a_tile_whose_offsets_wrap_32_bits_are_not_stored(act):
+    """Three rows of 2^22 elements and more: row 255 of a tile lies beyond 4 GiB from the tile's start."""
+    import torch
+    T, d, f = 3, 64, 9 << 20
+    L = filled_layer(T, d, f, 1, 1, "bf16", act)
+    L.forward()
+    L.combine_bwd()
+    L.ffn_bwd()
+    torch.cuda.synchronize()
+    assert 255 * f * 2 > 1 << 32
+    # the last region of the workspace: dA, or dG and dU
+    planes = 2 if act == B.ACT_SWIGLU else 1
+    dact = L.ws[L.ws.numel() - planes * T * f * 2:].view(L.tdtype).view(planes, T, f).float()
+    x, dy, saved = L.x_perm.float(), L.dy_perm.float(), [L.saved_plane(i).float() for i in range(planes + 1)]
+    step = 1 << 20
+    for c in range(0, f, step):
+        s = slice(c, min(c + step, f))
+        dh = dy @ L.W2[0, s].float().t()
+        pre = [x @ w[0, :, s].float() for w in (L.W1, L.W1b) if w is not None]
+        if act == B.ACT_SWIGLU:
+            sg = torch.sigmoid(saved[0][:, s])
+            want = pre + [torch.nn.functional.silu(pre[0]) * pre[1], dh * saved[1][:, s] * sg * (1 + saved[0][:, s] * (1 - sg)), dh * saved[0][:, s] * sg]
+        else:
+            a = saved[0][:, s].double()
+            grad = 0.5 * torch.erfc(-a / 2 ** 0.5) + a * torch.exp(-a * a / 2) / (2 * torch.pi) ** 0.5
+            want = pre + [torch.nn.functional.gelu(pre[0]), dh * grad.float()]
+        for got, ref in zip([t[:, s] for t in saved] + [t[:, s] for t in dact], want):
+            # two roundings to bf16 (2^-9 each) at most, the pre-activation's and the result's
+            assert (got - ref).norm() <= 2.0 ** -7 * ref.norm()
+
+
 def last_round_parts(kept, f, N):
     """(tiles, K parts) of a row-tile GEMM over these rows, as the kernels compute them."""
     n_rt, ntn = sum(-(-int(n) // 256) for n in kept), -(-N // 256)
