@@ -259,6 +259,62 @@ MOE_API int moe_route_bwd(const moe_cfg* cfg, const void* x, const float* Wr, co
                   float* d_logits, float* dWr, void* dx, int32_t accumulate, void* ws, size_t ws_bytes, void* stream);
 
 /*
+ * A whole layer in one call: the calls above in the order of the block, with the same kernels and the same bits, but
+ * with the small jobs (tile maps, tables, the transposed gate weight) riding in other kernels' launches and the two
+ * halves of the input gradient in one pass: a step of 17 to 20 launches and eight calls becomes one of 11 to 15 and two.
+ * The struct is a HOST struct of DEVICE pointers, read during the call only; each field is the argument of that name
+ * above.  `saved` holds every plane in both modes of the forward that use one.
+ */
+typedef struct moe_layer_bufs {
+  const void* x;
+  const float* Wr;
+  const float* bias;            /* may be NULL */
+  const void* W1;
+  const void* W1b;              /* SwiGLU only */
+  const void* W2;
+  const int32_t* slice_lo;      /* both or neither */
+  const int32_t* slice_hi;
+  float* logits;
+  int32_t* topk_idx;
+  float* topk_w;
+  int32_t* counts;
+  int32_t* kept;
+  int32_t* offsets;
+  int32_t* row_of;
+  int32_t* src_of;
+  void* x_perm;
+  void* saved;
+  void* y_perm;
+  void* out;
+  const void* d_out;            /* from here on backward only */
+  void* dy_perm;
+  float* d_topk_w;
+  void* dx_perm;
+  float* dW1;
+  float* dW1b;                  /* SwiGLU only */
+  float* dW2;
+  float* dWr;
+  float* d_logits;
+  void* dx;
+  void* ws;
+  size_t ws_bytes;
+} moe_layer_bufs;
+
+/*
+ * moe_route, moe_dispatch, then by `mode`: MOE_FWD_FULL moe_expert_ffn_fwd and moe_combine; MOE_FWD_LIGHT
+ * moe_expert_ffn_fwd_light (H goes to its plane of `saved`, the last one) and moe_combine; MOE_FWD_RECOMPUTE
+ * moe_expert_ffn_recompute alone (y_perm, out and W2 may be NULL).
+ */
+enum { MOE_FWD_FULL = 0, MOE_FWD_LIGHT = 1, MOE_FWD_RECOMPUTE = 2 };
+MOE_API int moe_layer_fwd(const moe_cfg* cfg, const moe_layer_bufs* b, int32_t mode, void* stream);
+
+/*
+ * moe_combine_bwd, moe_expert_ffn_bwd, moe_combine of dx_perm with unit weights into dx, and moe_route_bwd; `accumulate`
+ * as there, for the expert and the gate weight gradients alike.
+ */
+MOE_API int moe_layer_bwd(const moe_cfg* cfg, const moe_layer_bufs* b, int32_t accumulate, void* stream);
+
+/*
  * Planner of the asymmetric expert assignment (Section 4.2 of the paper, Algorithm 1 and the paragraph
  * on memory limits).  HOST-ONLY: runs on the CPU, enqueues nothing, and `o` is a HOST pointer.
  *

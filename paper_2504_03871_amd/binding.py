@@ -19,13 +19,19 @@ MAX_E, MAX_K = 256, 8
 
 SYMBOLS = ("moe_error_string", "moe_last_hip_error", "moe_workspace_bytes", "moe_saved_bytes", "moe_route",
            "moe_dispatch", "moe_dispatch_static", "moe_expert_ffn_fwd", "moe_expert_ffn_fwd_light", "moe_expert_ffn_recompute", "moe_combine", "moe_combine_bwd", "moe_expert_ffn_bwd",
-           "moe_route_bwd", "moe_asymea_plan", "moe_asymea_shares", "moe_bench_stream", "moe_bench_clock_probe", "moe_bench_mfma_loop", "moe_gemm_block_tile")
+           "moe_route_bwd", "moe_layer_fwd", "moe_layer_bwd", "moe_asymea_plan", "moe_asymea_shares", "moe_bench_stream", "moe_bench_clock_probe", "moe_bench_mfma_loop", "moe_gemm_block_tile")
 
 PROF = {"gemm1_fwd": 0, "gemm2_fwd": 1, "dh_bwd": 2, "dw2_bwd": 3, "dw1_bwd": 4, "dx_bwd": 5, "gather": 6,
         "combine": 7, "combine_bwd": 8, "route": 9}
 
 
 PROF_COUNT = 10
+
+FWD_FULL, FWD_LIGHT, FWD_RECOMPUTE = 0, 1, 2
+# the fields of moe_layer_bufs in front of ws_bytes, in order
+LAYER_BUFS = ("x", "Wr", "bias", "W1", "W1b", "W2", "slice_lo", "slice_hi", "logits", "topk_idx", "topk_w", "counts", "kept",
+              "offsets", "row_of", "src_of", "x_perm", "saved", "y_perm", "out", "d_out", "dy_perm", "d_topk_w", "dx_perm", "dW1",
+              "dW1b", "dW2", "dWr", "d_logits", "dx", "ws")
 
 
 class MoeProf(ctypes.Structure):
@@ -73,6 +79,8 @@ def lib():
             "moe_combine_bwd": [cfgp] + [p] * 12,
             "moe_expert_ffn_bwd": [cfgp] + [p] * 14 + [i32, p, sz, p],
             "moe_route_bwd": [cfgp] + [p] * 8 + [i32, p, sz, p],
+            "moe_layer_fwd": [cfgp, p, i32, p],
+            "moe_layer_bwd": [cfgp, p, i32, p],
             "moe_asymea_plan": [i32] * 4 + [ctypes.c_double] * 3 + [i32, i32, ctypes.POINTER(i32)],
             "moe_asymea_shares": [i32] * 6 + [ctypes.POINTER(i32), ctypes.POINTER(i32)],
             "moe_bench_stream": [p, p, sz, i32, p],
@@ -214,6 +222,33 @@ def moe_route_bwd(cfg, x, Wr, topk_idx, topk_w, d_topk_w, d_logits, dWr, dx, ws,
                                                 _ptr(d_topk_w), _ptr(d_logits), _ptr(dWr), _ptr(dx), int(accumulate), _ptr(ws),
                                                 _nbytes(ws) if ws_bytes is None else ws_bytes,
                                                 _stream() if stream is None else stream))
+
+
+def _layer_bufs(bufs):
+    """moe_layer_bufs from tensors (or raw addresses, or None) in the order of LAYER_BUFS: pointers and one size, all of
+    pointer size."""
+    vals = [0] * (len(LAYER_BUFS) + 1)
+    for i, t in enumerate(bufs):
+        if t is None:
+            continue
+        if isinstance(t, int):
+            vals[i] = t
+        elif t.is_contiguous():
+            vals[i] = t.data_ptr()
+        else:
+            raise ValueError("tensor must be contiguous")
+    vals[-1] = _nbytes(bufs[-1])
+    return (ctypes.c_size_t * len(vals))(*vals)
+
+
+def moe_layer_fwd(cfg, bufs, mode=FWD_FULL, stream=None):
+    """Gate, dispatch, FFN and combine in one call; bufs in the order of LAYER_BUFS."""
+    _check("moe_layer_fwd", lib().moe_layer_fwd(ctypes.byref(cfg), _layer_bufs(bufs), int(mode), _stream() if stream is None else stream))
+
+
+def moe_layer_bwd(cfg, bufs, accumulate=0, stream=None):
+    """The layer's backward in one call; bufs in the order of LAYER_BUFS."""
+    _check("moe_layer_bwd", lib().moe_layer_bwd(ctypes.byref(cfg), _layer_bufs(bufs), int(accumulate), _stream() if stream is None else stream))
 
 
 def moe_asymea_plan(n, L, M, N, T_A_attn, T_E_attn, T_E_exp, n_min=0, n_max=-1):

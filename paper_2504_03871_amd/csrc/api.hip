@@ -2,6 +2,7 @@
 #include "common.h"
 #include "gemm.h"
 #include "prof.h"
+#include "tile_map.h"
 #include <algorithm>
 
 namespace moe {
@@ -72,12 +73,15 @@ int launch_route(const moe_cfg*, const void*, const float*, const float*, const 
 int launch_route_bwd(const moe_cfg*, const void*, const float*, const int32_t*, const float*, const float*, float*,
                      float*, void*, int, float*, float*, hipStream_t);
 int launch_dispatch(const moe_cfg*, const void*, const int32_t*, const int32_t*, const int32_t*, int32_t*, int32_t*,
-                    int32_t*, int32_t*, int32_t*, void*, int32_t*, hipStream_t);
+                    int32_t*, int32_t*, int32_t*, void*, int32_t*, const SideWork*, hipStream_t);
 int dispatch_static_scratch(int32_t** out);
 int launch_combine(const moe_cfg*, const void*, const float*, const int32_t*, const int32_t*, const int32_t*,
                    const int32_t*, const int32_t*, const int32_t*, void*, int, hipStream_t);
 int launch_combine_bwd(const moe_cfg*, const void*, const void*, const float*, const int32_t*, const int32_t*,
-                       const int32_t*, const int32_t*, const int32_t*, const int32_t*, void*, float*, hipStream_t);
+                       const int32_t*, const int32_t*, const int32_t*, const int32_t*, void*, float*, const SideWork*, hipStream_t);
+bool input_grad_has_dwr(const moe_cfg*);
+int launch_input_grad(const moe_cfg*, const moe_layer_bufs*, const float*, float*, bool, hipStream_t);
+int launch_gate_dwr(const moe_cfg*, const void*, const float*, float*, int, float*, bool, hipStream_t);
 
 __global__ void fill_zero_kernel(float* p, int n) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -330,7 +334,7 @@ int moe_dispatch(const moe_cfg* cfg, const void* x, const int32_t* topk_idx, con
   int32_t* blk_cnt = reinterpret_cast<int32_t*>(static_cast<char*>(ws) + w.dispatch_blk_cnt);
   // T == 0 still has to produce zero counts and offsets: the kernels handle an empty assignment list
   return launch_dispatch(cfg, x, topk_idx, slice_lo, slice_hi, counts, kept, offsets, row_of, src_of, x_perm, blk_cnt,
-                         (hipStream_t)stream);
+                         nullptr, (hipStream_t)stream);
 }
 
 int moe_dispatch_static(const moe_cfg* cfg, const void* x, const int32_t* topk_idx, const int32_t* slice_lo,
@@ -349,23 +353,34 @@ int moe_dispatch_static(const moe_cfg* cfg, const void* x, const int32_t* topk_i
   int32_t* blk_cnt = nullptr;
   CHECK(dispatch_static_scratch(&blk_cnt));
   return launch_dispatch(cfg, x, topk_idx, slice_lo, slice_hi, counts, kept, offsets, row_of, src_of, x_perm, blk_cnt,
-                         (hipStream_t)stream);
+                         nullptr, (hipStream_t)stream);
 }
 
 namespace {
+bool fwd_skinny(const moe_cfg* cfg) { return is_half(cfg) && skinny_applies(cfg->T * cfg->k, cfg->E); }   // few rows per expert
+// the row-tile map of a forward or backward FFN call and its table
+TileMapArgs tile_map_args(const moe_cfg* cfg, const int32_t* offsets, const int32_t* kept, const int32_t* lo, const int32_t* hi, bool forward, void* ws) {
+  TileMapArgs t = {offsets, kept, lo, hi, cfg->E};
+  const bool skinny = forward && fwd_skinny(cfg);
+  t.tile_rows = skinny ? SKINNY_ROWS : tile_rows_for(cfg);
+  t.by_expert = skinny;
+  t.table = cfg->act != MOE_ACT_GELU || cfg->dtype != MOE_DTYPE_BF16 ? GELU_TAB_NONE : forward ? GELU_TAB_PHI : GELU_TAB_GRAD;
+  t.map = tile_map_at(static_cast<char*>(ws) + ws_layout(cfg).tile_map, max_row_tiles(cfg->T * cfg->k, cfg->E, TILE_ROWS_MIN), cfg->E);
+  return t;
+}
 // GEMM1 with its activation epilogue into `saved` (or, saved == NULL, its hidden activation alone into
 // `hidden`), then (y_perm != NULL) GEMM2.
 int ffn_fwd_impl(const moe_cfg* cfg, const void* x_perm, const void* W1, const void* W1b, const void* W2,
                  const int32_t* offsets, const int32_t* kept, const int32_t* slice_lo, const int32_t* slice_hi,
-                 void* saved, void* hidden, void* y_perm, void* ws, hipStream_t s) {
+                 void* saved, void* hidden, void* y_perm, void* ws, bool map_built, hipStream_t s) {
   const bool swiglu = cfg->act == MOE_ACT_SWIGLU;
   const WsLayout w = ws_layout(cfg);
   const int A = cfg->T * cfg->k, d = cfg->d_model, f = cfg->d_ff;
-  const bool skinny = is_half(cfg) && skinny_applies(A, cfg->E);   // few rows per expert
-  const int tr = skinny ? SKINNY_ROWS : tile_rows_for(cfg), max_tiles = max_row_tiles(A, cfg->E, tr);
-  TileMap map = tile_map_at(static_cast<char*>(ws) + w.tile_map, max_row_tiles(A, cfg->E, TILE_ROWS_MIN), cfg->E);
-  CHECK(launch_tile_map(offsets, kept, slice_lo, slice_hi, cfg->E, tr, skinny, map,
-                        !swiglu && cfg->dtype == MOE_DTYPE_BF16 ? GELU_TAB_PHI : GELU_TAB_NONE, s));
+  const bool skinny = fwd_skinny(cfg);
+  const TileMapArgs tm = tile_map_args(cfg, offsets, kept, slice_lo, slice_hi, true, ws);
+  const TileMap& map = tm.map;
+  const int tr = tm.tile_rows, max_tiles = max_row_tiles(A, cfg->E, tr);
+  if (!map_built) CHECK(launch_tile_map(tm, s));
   const size_t plane = (size_t)A * f * elt_size(cfg);
   char* sv = static_cast<char*>(saved);
   GemmArgs g = {};
@@ -416,7 +431,7 @@ int moe_expert_ffn_fwd(const moe_cfg* cfg, const void* x_perm, const void* W1, c
   CHECK(check_ws(cfg, ws, ws_bytes));
   if (cfg->T == 0) return MOE_OK;
   return ffn_fwd_impl(cfg, x_perm, W1, W1b, W2, offsets, kept, slice_lo, slice_hi, saved, nullptr, y_perm, ws,
-                      (hipStream_t)stream);
+                      false, (hipStream_t)stream);
 }
 
 int moe_expert_ffn_fwd_light(const moe_cfg* cfg, const void* x_perm, const void* W1, const void* W1b, const void* W2,
@@ -434,7 +449,7 @@ int moe_expert_ffn_fwd_light(const moe_cfg* cfg, const void* x_perm, const void*
   CHECK(check_ws(cfg, ws, ws_bytes));
   if (cfg->T == 0) return MOE_OK;
   return ffn_fwd_impl(cfg, x_perm, W1, W1b, W2, offsets, kept, slice_lo, slice_hi, nullptr, hidden, y_perm, ws,
-                      (hipStream_t)stream);
+                      false, (hipStream_t)stream);
 }
 
 int moe_expert_ffn_recompute(const moe_cfg* cfg, const void* x_perm, const void* W1, const void* W1b,
@@ -451,7 +466,7 @@ int moe_expert_ffn_recompute(const moe_cfg* cfg, const void* x_perm, const void*
   CHECK(check_ws(cfg, ws, ws_bytes));
   if (cfg->T == 0) return MOE_OK;
   return ffn_fwd_impl(cfg, x_perm, W1, W1b, nullptr, offsets, kept, slice_lo, slice_hi, saved, nullptr, nullptr, ws,
-                      (hipStream_t)stream);
+                      false, (hipStream_t)stream);
 }
 
 int moe_combine(const moe_cfg* cfg, const void* y_perm, const float* topk_w, const int32_t* topk_idx,
@@ -480,32 +495,20 @@ int moe_combine_bwd(const moe_cfg* cfg, const void* d_out, const void* y_perm, c
   if (cfg->T == 0) return MOE_OK;
   ProfScope ps(cfg, MOE_PROF_COMBINE_BWD, (hipStream_t)stream);
   return launch_combine_bwd(cfg, d_out, y_perm, topk_w, topk_idx, row_of, offsets, kept, slice_lo, slice_hi, dy_perm,
-                            d_topk_w, (hipStream_t)stream);
+                            d_topk_w, nullptr, (hipStream_t)stream);
 }
 
-int moe_expert_ffn_bwd(const moe_cfg* cfg, const void* dy_perm, const void* x_perm, const void* saved, const void* W1,
-                       const void* W1b, const void* W2, const int32_t* offsets, const int32_t* kept,
-                       const int32_t* slice_lo, const int32_t* slice_hi, void* dx_perm, float* dW1, float* dW1b,
-                       float* dW2, int32_t accumulate, void* ws, size_t ws_bytes, void* stream) {
-  CHECK(check_cfg(cfg));
-  CHECK(check_slices(slice_lo, slice_hi));
-  REQUIRE(dy_perm); REQUIRE(x_perm); REQUIRE(saved); REQUIRE(W1); REQUIRE(W2); REQUIRE(offsets); REQUIRE(kept);
-  REQUIRE(dx_perm); REQUIRE(dW1); REQUIRE(dW2); REQUIRE(ws);
+namespace {
+int ffn_bwd_impl(const moe_cfg* cfg, const void* dy_perm, const void* x_perm, const void* saved, const void* W1, const void* W1b,
+                 const void* W2, const int32_t* offsets, const int32_t* kept, const int32_t* slice_lo, const int32_t* slice_hi,
+                 void* dx_perm, float* dW1, float* dW1b, float* dW2, int32_t accumulate, void* ws, bool map_built, hipStream_t s) {
   const bool swiglu = cfg->act == MOE_ACT_SWIGLU;
-  if (swiglu) { REQUIRE(W1b); REQUIRE(dW1b); }
-  if (!swiglu && (W1b != nullptr || dW1b != nullptr)) return MOE_ERR_BAD_DTYPE;
-  ALIGNED(dy_perm); ALIGNED(x_perm); ALIGNED(saved); ALIGNED(W1); ALIGNED(W1b); ALIGNED(W2); ALIGNED(offsets);
-  ALIGNED(kept); ALIGNED(slice_lo); ALIGNED(slice_hi); ALIGNED(dx_perm); ALIGNED(dW1); ALIGNED(dW1b); ALIGNED(dW2);
-  ALIGNED(ws);
-  CHECK(check_ws(cfg, ws, ws_bytes));
-  if (cfg->T == 0) return MOE_OK;
-  hipStream_t s = (hipStream_t)stream;
   const WsLayout w = ws_layout(cfg);
   const int A = cfg->T * cfg->k, d = cfg->d_model, f = cfg->d_ff;
-  const int tr = tile_rows_for(cfg), max_tiles = max_row_tiles(A, cfg->E, tr);
-  TileMap map = tile_map_at(static_cast<char*>(ws) + w.tile_map, max_row_tiles(A, cfg->E, TILE_ROWS_MIN), cfg->E);
-  CHECK(launch_tile_map(offsets, kept, slice_lo, slice_hi, cfg->E, tr, false, map,
-                        !swiglu && cfg->dtype == MOE_DTYPE_BF16 ? GELU_TAB_GRAD : GELU_TAB_NONE, s));
+  const TileMapArgs tm = tile_map_args(cfg, offsets, kept, slice_lo, slice_hi, false, ws);
+  const TileMap& map = tm.map;
+  const int tr = tm.tile_rows, max_tiles = max_row_tiles(A, cfg->E, tr);
+  if (!map_built) CHECK(launch_tile_map(tm, s));
   const size_t plane = (size_t)A * f * elt_size(cfg);
   const char* sv = static_cast<const char*>(saved);
   char* dact = static_cast<char*>(ws) + w.ffn_bwd_dact;
@@ -557,6 +560,27 @@ int moe_expert_ffn_bwd(const moe_cfg* cfg, const void* dy_perm, const void* x_pe
   if (pair_x) return launch_pair(cfg, EPI_STORE, swiglu, gx, max_tiles, gw1, s);
   return launch_gemm(cfg, MODE_NT, EPI_STORE, false, swiglu, gx, max_tiles, s);
 }
+}  // namespace
+
+int moe_expert_ffn_bwd(const moe_cfg* cfg, const void* dy_perm, const void* x_perm, const void* saved, const void* W1,
+                       const void* W1b, const void* W2, const int32_t* offsets, const int32_t* kept,
+                       const int32_t* slice_lo, const int32_t* slice_hi, void* dx_perm, float* dW1, float* dW1b,
+                       float* dW2, int32_t accumulate, void* ws, size_t ws_bytes, void* stream) {
+  CHECK(check_cfg(cfg));
+  CHECK(check_slices(slice_lo, slice_hi));
+  REQUIRE(dy_perm); REQUIRE(x_perm); REQUIRE(saved); REQUIRE(W1); REQUIRE(W2); REQUIRE(offsets); REQUIRE(kept);
+  REQUIRE(dx_perm); REQUIRE(dW1); REQUIRE(dW2); REQUIRE(ws);
+  const bool swiglu = cfg->act == MOE_ACT_SWIGLU;
+  if (swiglu) { REQUIRE(W1b); REQUIRE(dW1b); }
+  if (!swiglu && (W1b != nullptr || dW1b != nullptr)) return MOE_ERR_BAD_DTYPE;
+  ALIGNED(dy_perm); ALIGNED(x_perm); ALIGNED(saved); ALIGNED(W1); ALIGNED(W1b); ALIGNED(W2); ALIGNED(offsets);
+  ALIGNED(kept); ALIGNED(slice_lo); ALIGNED(slice_hi); ALIGNED(dx_perm); ALIGNED(dW1); ALIGNED(dW1b); ALIGNED(dW2);
+  ALIGNED(ws);
+  CHECK(check_ws(cfg, ws, ws_bytes));
+  if (cfg->T == 0) return MOE_OK;
+  return ffn_bwd_impl(cfg, dy_perm, x_perm, saved, W1, W1b, W2, offsets, kept, slice_lo, slice_hi, dx_perm, dW1, dW1b, dW2, accumulate,
+                      ws, false, (hipStream_t)stream);
+}
 
 int moe_route_bwd(const moe_cfg* cfg, const void* x, const float* Wr, const int32_t* topk_idx, const float* topk_w,
                   const float* d_topk_w, float* d_logits, float* dWr, void* dx, int32_t accumulate, void* ws,
@@ -578,6 +602,79 @@ int moe_route_bwd(const moe_cfg* cfg, const void* x, const float* Wr, const int3
   float* partials = reinterpret_cast<float*>(static_cast<char*>(ws) + w.route_partials);
   float* wrt = reinterpret_cast<float*>(static_cast<char*>(ws) + w.route_wrt);
   return launch_route_bwd(cfg, x, Wr, topk_idx, topk_w, d_topk_w, d_logits, dWr, dx, accumulate != 0, partials, wrt, s);
+}
+
+namespace {
+// Arguments of the calls that a whole-layer call stands for, checked before anything is launched
+int check_layer(const moe_cfg* cfg, const moe_layer_bufs* b, bool combine, bool backward) {
+  CHECK(check_cfg(cfg));
+  REQUIRE(b);
+  CHECK(check_slices(b->slice_lo, b->slice_hi));
+  const bool swiglu = cfg->act == MOE_ACT_SWIGLU;
+  REQUIRE(b->x); REQUIRE(b->Wr); REQUIRE(b->W1); REQUIRE(b->topk_idx); REQUIRE(b->topk_w); REQUIRE(b->kept); REQUIRE(b->offsets);
+  REQUIRE(b->row_of); REQUIRE(b->x_perm); REQUIRE(b->saved); REQUIRE(b->ws);
+  if (!backward) { REQUIRE(b->logits); REQUIRE(b->counts); REQUIRE(b->src_of); }
+  if (combine || backward) { REQUIRE(b->W2); REQUIRE(b->y_perm); }
+  if (combine) REQUIRE(b->out);
+  if (backward) {
+    REQUIRE(b->d_out); REQUIRE(b->dy_perm); REQUIRE(b->d_topk_w); REQUIRE(b->dx_perm); REQUIRE(b->dW1); REQUIRE(b->dW2); REQUIRE(b->dWr);
+    REQUIRE(b->d_logits); REQUIRE(b->dx);
+  }
+  if (swiglu) { REQUIRE(b->W1b); if (backward) REQUIRE(b->dW1b); }
+  if (!swiglu && (b->W1b != nullptr || (backward && b->dW1b != nullptr))) return MOE_ERR_BAD_DTYPE;
+  const void* const fwd[] = {b->x, b->Wr, b->bias, b->W1, b->W1b, b->W2, b->slice_lo, b->slice_hi, b->logits, b->topk_idx, b->topk_w, b->counts, b->kept,
+                             b->offsets, b->row_of, b->src_of, b->x_perm, b->saved, b->y_perm, b->out, b->ws};
+  for (const void* p : fwd) ALIGNED(p);
+  const void* const bwd[] = {b->d_out, b->dy_perm, b->d_topk_w, b->dx_perm, b->dW1, b->dW1b, b->dW2, b->dWr, b->d_logits, b->dx};
+  if (backward)
+    for (const void* p : bwd) ALIGNED(p);
+  return check_ws(cfg, b->ws, b->ws_bytes);
+}
+}  // namespace
+
+int moe_layer_fwd(const moe_cfg* cfg, const moe_layer_bufs* b, int32_t mode, void* stream) {
+  if (mode < MOE_FWD_FULL || mode > MOE_FWD_RECOMPUTE) return MOE_ERR_BAD_DTYPE;
+  CHECK(check_layer(cfg, b, mode != MOE_FWD_RECOMPUTE, false));
+  hipStream_t s = (hipStream_t)stream;
+  char* ws = static_cast<char*>(b->ws);
+  const WsLayout w = ws_layout(cfg);
+  if (cfg->T > 0) {
+    ProfScope ps(cfg, MOE_PROF_ROUTE, s);
+    CHECK(launch_route(cfg, b->x, b->Wr, b->bias, nullptr, b->logits, b->topk_idx, b->topk_w, ws + w.route_wrt, s));
+  }
+  const SideWork side = side_work(tile_map_args(cfg, b->offsets, b->kept, b->slice_lo, b->slice_hi, true, b->ws), nullptr, nullptr, 0);
+  CHECK(launch_dispatch(cfg, b->x, b->topk_idx, b->slice_lo, b->slice_hi, b->counts, b->kept, b->offsets, b->row_of, b->src_of, b->x_perm,
+                        reinterpret_cast<int32_t*>(ws + w.dispatch_blk_cnt), &side, s));
+  if (cfg->T == 0) return MOE_OK;
+  void* hidden = nullptr;
+  if (mode == MOE_FWD_LIGHT)
+    hidden = static_cast<char*>(b->saved) + (size_t)(cfg->act == MOE_ACT_SWIGLU ? 2 : 1) * cfg->T * cfg->k * cfg->d_ff * elt_size(cfg);
+  CHECK(ffn_fwd_impl(cfg, b->x_perm, b->W1, b->W1b, b->W2, b->offsets, b->kept, b->slice_lo, b->slice_hi, mode == MOE_FWD_LIGHT ? nullptr : b->saved,
+                     hidden, mode == MOE_FWD_RECOMPUTE ? nullptr : b->y_perm, b->ws, true, s));
+  if (mode == MOE_FWD_RECOMPUTE) return MOE_OK;
+  ProfScope ps(cfg, MOE_PROF_COMBINE, s);
+  return launch_combine(cfg, b->y_perm, b->topk_w, b->topk_idx, b->row_of, b->offsets, b->kept, b->slice_lo, b->slice_hi, b->out, 0, s);
+}
+
+int moe_layer_bwd(const moe_cfg* cfg, const moe_layer_bufs* b, int32_t accumulate, void* stream) {
+  CHECK(check_layer(cfg, b, false, true));
+  if (cfg->T == 0)
+    return moe_route_bwd(cfg, b->x, b->Wr, b->topk_idx, b->topk_w, b->d_topk_w, b->d_logits, b->dWr, b->dx, accumulate, b->ws, b->ws_bytes, stream);
+  hipStream_t s = (hipStream_t)stream;
+  char* ws = static_cast<char*>(b->ws);
+  const WsLayout w = ws_layout(cfg);
+  float *wrt = reinterpret_cast<float*>(ws + w.route_wrt), *partials = reinterpret_cast<float*>(ws + w.route_partials);
+  const SideWork side = side_work(tile_map_args(cfg, b->offsets, b->kept, b->slice_lo, b->slice_hi, false, b->ws), b->Wr, wrt, cfg->d_model);
+  {
+    ProfScope ps(cfg, MOE_PROF_COMBINE_BWD, s);
+    CHECK(launch_combine_bwd(cfg, b->d_out, b->y_perm, b->topk_w, b->topk_idx, b->row_of, b->offsets, b->kept, b->slice_lo, b->slice_hi, b->dy_perm,
+                             b->d_topk_w, &side, s));
+  }
+  CHECK(ffn_bwd_impl(cfg, b->dy_perm, b->x_perm, b->saved, b->W1, b->W1b, b->W2, b->offsets, b->kept, b->slice_lo, b->slice_hi, b->dx_perm, b->dW1,
+                     b->dW1b, b->dW2, accumulate, b->ws, true, s));
+  const bool dwr = input_grad_has_dwr(cfg);
+  CHECK(launch_input_grad(cfg, b, wrt, partials, dwr, s));
+  return launch_gate_dwr(cfg, b->x, b->d_logits, b->dWr, accumulate != 0, partials, dwr, s);
 }
 
 }  // extern "C"

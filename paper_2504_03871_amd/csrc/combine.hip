@@ -5,24 +5,11 @@
 // fp32 sum has a fixed order and no atomics are needed.  Section 5: the gradient of the block output
 // feeds both the expert outputs (dy = w * dOut) and the scores (dw = <dOut, y>).
 #include "common.h"
+#include "tile_map.h"
 
 namespace moe {
 
-constexpr int CB_THREADS = 256;
-
-// Row of slot a if it is kept and inside this GPU's share, else -1.
-__device__ __forceinline__ int live_row(int a, const int32_t* __restrict__ topk_idx, const int32_t* __restrict__ row_of,
-                                        const int32_t* __restrict__ offsets, const int32_t* __restrict__ kept,
-                                        const int32_t* __restrict__ lo, const int32_t* __restrict__ hi) {
-  const int row = row_of[a];
-  if (row < 0) return -1;
-  if (lo == nullptr) return row;
-  const int e = topk_idx[a];
-  int l, h;
-  share_of(lo, hi, kept[e], e, l, h);
-  const int pos = row - offsets[e];
-  return (pos >= l && pos < h) ? row : -1;
-}
+constexpr int CB_THREADS = SIDE_THREADS;
 
 // KMAX: compile-time bound on k (2, 4 or 8); CU: column chunks of 16 bytes per lane kept in flight
 // (k * CU loads are issued before anything is used).  y_perm is read once: non-temporal loads.
@@ -84,15 +71,17 @@ __global__ __launch_bounds__(CB_THREADS) void combine_kernel(
   }
 }
 
+// The first `side_blocks` blocks build what the backward needs beside dy (tile_map.h).
 template <typename T, int KMAX, int CU>
 __global__ __launch_bounds__(CB_THREADS) void combine_bwd_kernel(
     const T* __restrict__ d_out, const T* __restrict__ y_perm, const float* __restrict__ topk_w,
     const int32_t* __restrict__ topk_idx, const int32_t* __restrict__ row_of, const int32_t* __restrict__ offsets,
     const int32_t* __restrict__ kept, const int32_t* __restrict__ lo, const int32_t* __restrict__ hi,
-    T* __restrict__ dy_perm, float* __restrict__ d_topk_w, int Tn, int d, int k) {
+    T* __restrict__ dy_perm, float* __restrict__ d_topk_w, int Tn, int d, int k, SideWork side, int side_blocks) {
   constexpr int VN = Vec16<T>::N;
+  if ((int)blockIdx.x < side_blocks) return run_side_work(side, blockIdx.x);
   const int lane = threadIdx.x & (WAVE - 1);
-  const int t = (blockIdx.x * CB_THREADS + threadIdx.x) / WAVE;
+  const int t = ((blockIdx.x - side_blocks) * CB_THREADS + threadIdx.x) / WAVE;
   if (t >= Tn) return;
   int rows[KMAX];
   float wj[KMAX], dot[KMAX];
@@ -159,10 +148,11 @@ static void launch_combine_one(const moe_cfg* c, const void* y_perm, const float
 template <typename TY, int KM, int CU>
 static void launch_combine_bwd_one(const moe_cfg* c, const void* d_out, const void* y_perm, const float* w, const int32_t* idx,
                                    const int32_t* row_of, const int32_t* offsets, const int32_t* kept, const int32_t* lo,
-                                   const int32_t* hi, void* dy_perm, float* dw, hipStream_t s) {
-  const int grid = (c->T + CB_THREADS / WAVE - 1) / (CB_THREADS / WAVE);
+                                   const int32_t* hi, void* dy_perm, float* dw, const SideWork* side, hipStream_t s) {
+  const int sb = side != nullptr ? side->blocks() : 0, grid = sb + (c->T + CB_THREADS / WAVE - 1) / (CB_THREADS / WAVE);
   combine_bwd_kernel<TY, KM, CU><<<grid, CB_THREADS, 0, s>>>((const TY*)d_out, (const TY*)y_perm, w, idx, row_of, offsets, kept,
-                                                             lo, hi, (TY*)dy_perm, dw, c->T, c->d_model, c->k);
+                                                             lo, hi, (TY*)dy_perm, dw, c->T, c->d_model, c->k,
+                                                             side != nullptr ? *side : SideWork{}, sb);
 }
 // true when a row spans more than `units` column units of a wave (16 bytes per lane each)
 template <typename TY>
@@ -181,8 +171,8 @@ static void launch_combine_typed(const moe_cfg* c, const void* y_perm, const flo
 template <typename TY>
 static void launch_combine_bwd_typed(const moe_cfg* c, const void* d_out, const void* y_perm, const float* w, const int32_t* idx,
                                      const int32_t* row_of, const int32_t* offsets, const int32_t* kept, const int32_t* lo,
-                                     const int32_t* hi, void* dy_perm, float* dw, hipStream_t s) {
-#define MOE_ARGS c, d_out, y_perm, w, idx, row_of, offsets, kept, lo, hi, dy_perm, dw, s
+                                     const int32_t* hi, void* dy_perm, float* dw, const SideWork* side, hipStream_t s) {
+#define MOE_ARGS c, d_out, y_perm, w, idx, row_of, offsets, kept, lo, hi, dy_perm, dw, side, s
   if (c->k <= 2) { if (long_row<TY>(c, 4)) launch_combine_bwd_one<TY, 2, 8>(MOE_ARGS); else launch_combine_bwd_one<TY, 2, 4>(MOE_ARGS); }
   else if (c->k <= 4) { if (long_row<TY>(c, 2)) launch_combine_bwd_one<TY, 4, 4>(MOE_ARGS); else launch_combine_bwd_one<TY, 4, 2>(MOE_ARGS); }
   else { if (long_row<TY>(c, 2)) launch_combine_bwd_one<TY, 8, 4>(MOE_ARGS); else launch_combine_bwd_one<TY, 8, 2>(MOE_ARGS); }
@@ -200,10 +190,10 @@ int launch_combine(const moe_cfg* c, const void* y_perm, const float* w, const i
 
 int launch_combine_bwd(const moe_cfg* c, const void* d_out, const void* y_perm, const float* w, const int32_t* idx,
                        const int32_t* row_of, const int32_t* offsets, const int32_t* kept, const int32_t* lo,
-                       const int32_t* hi, void* dy_perm, float* dw, hipStream_t s) {
-  if (c->dtype == MOE_DTYPE_BF16) launch_combine_bwd_typed<bf16>(c, d_out, y_perm, w, idx, row_of, offsets, kept, lo, hi, dy_perm, dw, s);
-  else if (c->dtype == MOE_DTYPE_F16) launch_combine_bwd_typed<f16>(c, d_out, y_perm, w, idx, row_of, offsets, kept, lo, hi, dy_perm, dw, s);
-  else launch_combine_bwd_typed<float>(c, d_out, y_perm, w, idx, row_of, offsets, kept, lo, hi, dy_perm, dw, s);
+                       const int32_t* hi, void* dy_perm, float* dw, const SideWork* side, hipStream_t s) {
+  if (c->dtype == MOE_DTYPE_BF16) launch_combine_bwd_typed<bf16>(c, d_out, y_perm, w, idx, row_of, offsets, kept, lo, hi, dy_perm, dw, side, s);
+  else if (c->dtype == MOE_DTYPE_F16) launch_combine_bwd_typed<f16>(c, d_out, y_perm, w, idx, row_of, offsets, kept, lo, hi, dy_perm, dw, side, s);
+  else launch_combine_bwd_typed<float>(c, d_out, y_perm, w, idx, row_of, offsets, kept, lo, hi, dy_perm, dw, side, s);
   return launch_status();
 }
 

@@ -188,6 +188,20 @@ __device__ __forceinline__ void share_of(const int32_t* __restrict__ lo, const i
   }
 }
 
+// Row of slot a if it is kept and inside this GPU's share, else -1.
+__device__ __forceinline__ int live_row(int a, const int32_t* __restrict__ topk_idx, const int32_t* __restrict__ row_of,
+                                        const int32_t* __restrict__ offsets, const int32_t* __restrict__ kept,
+                                        const int32_t* __restrict__ lo, const int32_t* __restrict__ hi) {
+  const int row = row_of[a];
+  if (row < 0) return -1;
+  if (lo == nullptr) return row;
+  const int e = topk_idx[a];
+  int l, h;
+  share_of(lo, hi, kept[e], e, l, h);
+  const int pos = row - offsets[e];
+  return (pos >= l && pos < h) ? row : -1;
+}
+
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll
   for (int s = 32; s > 0; s >>= 1) v += __shfl_xor(v, s, WAVE);

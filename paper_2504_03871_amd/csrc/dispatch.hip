@@ -7,6 +7,7 @@
 // a scan over blocks, and an in-block stable rank built from wave ballots.
 #include "common.h"
 #include "prof.h"
+#include "tile_map.h"
 #include <mutex>
 
 namespace moe {
@@ -226,15 +227,17 @@ __global__ __launch_bounds__(DP_THREADS) void dispatch_rank_kernel(
 // of its live slots, so the read traffic is the T*d elements the algorithm needs however large k is.  Every
 // in-share row belongs to exactly one slot, so all of them are written and no other row is touched.
 // The stores are non-temporal (x_perm is far larger than the caches and is read next by another kernel).
+// The first `side_blocks` blocks build what the FFN needs beside the rows (tile_map.h).
 constexpr int GU = 8;   // 16-byte column pieces per lane in flight: a row of 4096 16-bit elements in one pass
 template <typename T, int KMAX>
-__global__ __launch_bounds__(256) void dispatch_gather_kernel(
+__global__ __launch_bounds__(SIDE_THREADS) void dispatch_gather_kernel(
     const T* __restrict__ x, const int32_t* __restrict__ topk_idx, const int32_t* __restrict__ row_of,
     const int32_t* __restrict__ offsets, const int32_t* __restrict__ kept, const int32_t* __restrict__ lo,
-    const int32_t* __restrict__ hi, T* __restrict__ x_perm, int Tn, int d, int k) {
+    const int32_t* __restrict__ hi, T* __restrict__ x_perm, int Tn, int d, int k, SideWork side, int side_blocks) {
   constexpr int VN = Vec16<T>::N;
+  if ((int)blockIdx.x < side_blocks) return run_side_work(side, blockIdx.x);
   const int lane = threadIdx.x & (WAVE - 1);
-  const int t = (blockIdx.x * blockDim.x + threadIdx.x) / WAVE;
+  const int t = ((blockIdx.x - side_blocks) * SIDE_THREADS + threadIdx.x) / WAVE;
   if (t >= Tn) return;
   int rows[KMAX];
   bool any = false;
@@ -304,7 +307,7 @@ int dispatch_static_scratch(int32_t** out) {
 
 int launch_dispatch(const moe_cfg* c, const void* x, const int32_t* idx, const int32_t* lo, const int32_t* hi,
                     int32_t* counts, int32_t* kept, int32_t* offsets, int32_t* row_of, int32_t* src_of, void* x_perm,
-                    int32_t* blk_cnt, hipStream_t s) {
+                    int32_t* blk_cnt, const SideWork* side, hipStream_t s) {
   const int A = c->T * c->k;
   const int nblk = (A + DISPATCH_CHUNK - 1) / DISPATCH_CHUNK;
   int rc = MOE_OK;
@@ -327,9 +330,10 @@ int launch_dispatch(const moe_cfg* c, const void* x, const int32_t* idx, const i
   rc = launch_status();
   if (rc != MOE_OK || x_perm == nullptr || A == 0) return rc;
   ProfScope ps(c, MOE_PROF_GATHER, s);
-  const int grid = (c->T + 256 / WAVE - 1) / (256 / WAVE);
+  const int sb = side != nullptr ? side->blocks() : 0, grid = sb + (c->T + SIDE_THREADS / WAVE - 1) / (SIDE_THREADS / WAVE);
+  const SideWork sw = side != nullptr ? *side : SideWork{};
 #define MOE_GATHER(TY, KM) \
-  dispatch_gather_kernel<TY, KM><<<grid, 256, 0, s>>>((const TY*)x, idx, row_of, offsets, kept, lo, hi, (TY*)x_perm, c->T, c->d_model, c->k)
+  dispatch_gather_kernel<TY, KM><<<grid, SIDE_THREADS, 0, s>>>((const TY*)x, idx, row_of, offsets, kept, lo, hi, (TY*)x_perm, c->T, c->d_model, c->k, sw, sb)
   if (c->dtype == MOE_DTYPE_BF16) { if (c->k <= 2) MOE_GATHER(bf16, 2); else if (c->k <= 4) MOE_GATHER(bf16, 4); else MOE_GATHER(bf16, 8); }
   else if (c->dtype == MOE_DTYPE_F16) { if (c->k <= 2) MOE_GATHER(f16, 2); else if (c->k <= 4) MOE_GATHER(f16, 4); else MOE_GATHER(f16, 8); }
   else { if (c->k <= 2) MOE_GATHER(float, 2); else if (c->k <= 4) MOE_GATHER(float, 4); else MOE_GATHER(float, 8); }

@@ -296,11 +296,8 @@ struct GemmArgs {
   int chunked;   // row-tile GEMMs: order of the full tiles (block_to_tile)
 };
 
-// table: which GELU table to fill as well (bf16 GELU layers: GELU_TAB_PHI before the forward GEMMs,
-// GELU_TAB_GRAD before the backward ones)
-// by_expert: an expert-major list in any case.
-int launch_tile_map(const int32_t* offsets, const int32_t* kept, const int32_t* lo, const int32_t* hi, int E,
-                    int tile_rows, bool by_expert, TileMap map, int table, hipStream_t s);
+struct TileMapArgs;   // tile_map.h
+int launch_tile_map(const TileMapArgs& tm, hipStream_t s);
 
 // fp32 storage, fp32 MFMA (any shape that passes check_cfg)
 int launch_gemm_f32(int mode, int epi, bool dual, bool chain, const GemmArgs& g, int tile_rows, int max_tiles, hipStream_t s);

@@ -4,6 +4,7 @@
 // stored fp32 logits and the softmax over the selected ones.
 // Backward: softmax-over-selected backward, dWr = x^T dlogits, dx += dlogits Wr^T.
 #include "common.h"
+#include "gate_bwd.h"
 #include <type_traits>
 
 namespace moe {
@@ -426,26 +427,8 @@ __global__ __launch_bounds__(256) void route_bwd_dx_kernel(
   if (t >= Tn) return;
   float ds[MOE_MAX_K];
   int ej[MOE_MAX_K];
-  float gsum = 0.f;
-#pragma unroll
-  for (int j = 0; j < MOE_MAX_K; ++j)
-    if (j < k) gsum = fmaf(topk_w[(size_t)t * k + j], d_topk_w[(size_t)t * k + j], gsum);
-#pragma unroll
-  for (int j = 0; j < MOE_MAX_K; ++j) {
-    ds[j] = 0.f;
-    ej[j] = 0;
-    if (j < k) {
-      ds[j] = topk_w[(size_t)t * k + j] * (d_topk_w[(size_t)t * k + j] - gsum);
-      ej[j] = topk_idx[(size_t)t * k + j];
-      if (ej[j] < 0 || ej[j] >= E) { ej[j] = -1; ds[j] = 0.f; }   // an id outside [0, E) contributes nothing
-    }
-  }
-  for (int e = lane; e < E; e += WAVE) {
-    float v = 0.f;
-#pragma unroll
-    for (int j = 0; j < MOE_MAX_K; ++j) v = (j < k && ej[j] == e) ? ds[j] : v;
-    d_logits[(size_t)t * E + e] = v;
-  }
+  gate_dsel(topk_idx, topk_w, d_topk_w, t, E, k, ds, ej);
+  gate_dlogits_row(d_logits, t, E, k, lane, ds, ej);
   if (dx == nullptr) return;
   constexpr int U = 4;   // 16-byte pieces of the dx row per lane in flight (dx is touched once here: streaming access)
   for (int c0 = lane * VN; c0 < d; c0 += WAVE * VN * U) {
@@ -483,67 +466,13 @@ __global__ __launch_bounds__(256) void route_bwd_dx_kernel(
   }
 }
 
-// Gate weight gradient dWr = x^T d_logits.  Experts in groups of EB <= 16 along gridDim.z: every thread keeps an [EB] x
-// (16-byte column group) block of the weight gradient in registers and adds d_logits[t][:] (x) x[t][cols] token after token,
-// zeros of the unselected experts included; no LDS read-modify-write, no branches, one 16-byte load of
-// x per token.  The slice's d_logits rows are staged in LDS once, padded with zeros to EB per row, and
-// read back as 16-byte broadcasts.  Geometry: RouteBwdGeom.
+// Gate weight gradient, dense form (gate_bwd.h); expert groups along gridDim.z
 template <typename T, int EB>
 __global__ __launch_bounds__(256) void route_bwd_dwr_dense_kernel(
     const T* __restrict__ x, const float* __restrict__ d_logits, float* __restrict__ partials, int Tn, int d, int E,
     RouteBwdGeom gm) {
-  extern __shared__ float4 s_dl4[];   // [slices_per_block][tps][EB] floats
-  float* s_dl = reinterpret_cast<float*>(s_dl4);
-  constexpr int VN = Vec16<T>::N, U = 8;   // tokens whose x pieces a thread keeps in flight
-  const int c = threadIdx.x & (gm.cg_pow2 - 1), slice = threadIdx.x / gm.cg_pow2;
-  const int col = (blockIdx.x * gm.cg_pow2 + c) * VN;
-  const int row = blockIdx.y * gm.slices_per_block + slice;   // row of partial sums = token slice
-  const int e0 = blockIdx.z * EB;                               // this block's group of experts (more than EB experts: x is read once per group)
-  const int t0 = row * gm.tps;
-  const int nt = max(0, min(gm.tps, Tn - t0));
-  {   // the block's slices are adjacent tokens: one pass over them, zero past the last token and past E
-    const int tb = blockIdx.y * gm.slices_per_block * gm.tps, n = gm.slices_per_block * gm.tps * EB;
-    for (int i = threadIdx.x; i < n; i += 256) {
-      const int t = tb + i / EB, e = i % EB;
-      s_dl[i] = (t < Tn && e0 + e < E) ? d_logits[(size_t)t * E + e0 + e] : 0.f;
-    }
-  }
-  __syncthreads();
-  if (col >= d) return;
-  const float4* dl = s_dl4 + (size_t)slice * gm.tps * (EB / 4);
-  float acc[EB][VN];
-#pragma unroll
-  for (int e = 0; e < EB; ++e)
-#pragma unroll
-    for (int v = 0; v < VN; ++v) acc[e][v] = 0.f;
-  for (int tb = 0; tb < nt; tb += U) {
-    Vec16<T> xv[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) xv[u].load_nt(x + (size_t)(t0 + min(tb + u, nt - 1)) * d + col);
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      float xf[VN];
-      xv[u].unpack(xf);
-      const float live = (tb + u < nt) ? 1.f : 0.f;   // the clamped reload of the last token counts once
-#pragma unroll
-      for (int q = 0; q < EB / 4; ++q) {
-        const float4 g4 = dl[min(tb + u, nt - 1) * (EB / 4) + q];
-        const float g[4] = {g4.x * live, g4.y * live, g4.z * live, g4.w * live};
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-          for (int v = 0; v < VN; ++v) acc[q * 4 + j][v] = fmaf(g[j], xf[v], acc[q * 4 + j][v]);
-      }
-    }
-  }
-  float* out = partials + (size_t)row * E * d + col;   // [row][e][col]: 16-byte stores, adjacent lanes adjacent
-#pragma unroll
-  for (int e = 0; e < EB; ++e)
-    if (e0 + e < E) {
-#pragma unroll
-      for (int v = 0; v < VN; v += 4)
-        *reinterpret_cast<float4*>(out + (size_t)(e0 + e) * d + v) = make_float4(acc[e][v], acc[e][v + 1], acc[e][v + 2], acc[e][v + 3]);
-    }
+  extern __shared__ float4 s_dl4[];
+  gate_dwr_dense<T, EB, false>(x, d_logits, nullptr, nullptr, nullptr, partials, Tn, d, E, 0, gm, blockIdx.x, blockIdx.y, blockIdx.z, s_dl4);
 }
 
 // Gate weight gradient on the matrix cores (bf16 x, more than 16 experts, where the kernel above is bound by its
@@ -771,6 +700,37 @@ static bool route_bwd_direct(const moe_cfg* c) {
   return c->E <= 32 && per_token <= 2048 && c->T * per_token <= 1 << 19;
 }
 
+// dWr from its rows of partial sums
+static int launch_dwr_reduce(const moe_cfg* c, const float* partials, float* dWr, int rows, int accumulate, hipStream_t s) {
+  route_bwd_reduce_kernel<<<(c->d_model * c->E + 63) / 64, 256, 0, s>>>(partials, dWr, c->d_model, c->E, rows, accumulate);
+  return launch_status();
+}
+// dWr = x^T d_logits
+template <typename T>
+static int launch_dwr(const moe_cfg* c, const void* x, const float* d_logits, float* dWr, int accumulate, float* partials, hipStream_t s) {
+  int rc;
+  if constexpr (!std::is_same<T, float>::value) {
+    if (route_bwd_uses_mfma(1, c->E)) {
+      switch (route_expert_tiles(c->E)) {
+        case 2: rc = launch_dwr_mfma<T, 2>(c, x, d_logits, partials, s); break;
+        case 4: rc = launch_dwr_mfma<T, 4>(c, x, d_logits, partials, s); break;
+        default: rc = launch_dwr_mfma<T, 8>(c, x, d_logits, partials, s); break;   // 128 experts per block
+      }
+      return rc != MOE_OK ? rc : launch_dwr_reduce(c, partials, dWr, route_bwd_mfma_geom(c->T, c->d_model, c->E).rows, accumulate, s);
+    }
+  }
+  const RouteBwdGeom gm = route_bwd_geom(c->T, c->d_model, (int)sizeof(T), c->E);
+  const int eb = c->E <= 4 ? 4 : (c->E <= 8 ? 8 : 16);
+  const dim3 dgrid(gm.col_blocks, gm.row_blocks, (c->E + eb - 1) / eb);
+  const size_t lds = (size_t)gm.slices_per_block * gm.tps * eb * 4;
+#define MOE_DWR_DENSE(EB) \
+  route_bwd_dwr_dense_kernel<T, EB><<<dgrid, 256, lds, s>>>((const T*)x, d_logits, partials, c->T, c->d_model, c->E, gm)
+  if (eb == 4) MOE_DWR_DENSE(4); else if (eb == 8) MOE_DWR_DENSE(8); else MOE_DWR_DENSE(16);
+#undef MOE_DWR_DENSE
+  if ((rc = launch_status()) != MOE_OK) return rc;
+  return launch_dwr_reduce(c, partials, dWr, gm.partial_rows, accumulate, s);
+}
+
 template <typename T>
 static int route_bwd_typed(const moe_cfg* c, const void* x, const float* Wr, const int32_t* idx, const float* w,
                            const float* dw, float* d_logits, float* dWr, void* dx, int accumulate, float* partials,
@@ -785,31 +745,15 @@ static int route_bwd_typed(const moe_cfg* c, const void* x, const float* Wr, con
     route_bwd_dx_kernel<T, false><<<grid, 256, 0, s>>>(Wr, idx, w, dw, d_logits, (T*)dx, c->T, c->d_model, c->E, c->k);
   }
   if ((rc = launch_status()) != MOE_OK) return rc;
-  if (dWr == nullptr) return MOE_OK;
-  if constexpr (!std::is_same<T, float>::value) {
-    if (route_bwd_uses_mfma(1, c->E)) {
-      switch (route_expert_tiles(c->E)) {
-        case 2: rc = launch_dwr_mfma<T, 2>(c, x, d_logits, partials, s); break;
-        case 4: rc = launch_dwr_mfma<T, 4>(c, x, d_logits, partials, s); break;
-        default: rc = launch_dwr_mfma<T, 8>(c, x, d_logits, partials, s); break;   // 128 experts per block
-      }
-      if (rc != MOE_OK) return rc;
-      route_bwd_reduce_kernel<<<(n + 63) / 64, 256, 0, s>>>(partials, dWr, c->d_model, c->E,
-                                                          route_bwd_mfma_geom(c->T, c->d_model, c->E).rows, accumulate);
-      return launch_status();
-    }
-  }
-  const RouteBwdGeom gm = route_bwd_geom(c->T, c->d_model, (int)sizeof(T), c->E);
-  const int eb = c->E <= 4 ? 4 : (c->E <= 8 ? 8 : 16);
-  const dim3 dgrid(gm.col_blocks, gm.row_blocks, (c->E + eb - 1) / eb);
-  const size_t lds = (size_t)gm.slices_per_block * gm.tps * eb * 4;
-#define MOE_DWR_DENSE(EB) \
-  route_bwd_dwr_dense_kernel<T, EB><<<dgrid, 256, lds, s>>>((const T*)x, d_logits, partials, c->T, c->d_model, c->E, gm)
-  if (eb == 4) MOE_DWR_DENSE(4); else if (eb == 8) MOE_DWR_DENSE(8); else MOE_DWR_DENSE(16);
-#undef MOE_DWR_DENSE
-  if ((rc = launch_status()) != MOE_OK) return rc;
-  route_bwd_reduce_kernel<<<(n + 63) / 64, 256, 0, s>>>(partials, dWr, c->d_model, c->E, gm.partial_rows, accumulate);
-  return launch_status();
+  return dWr == nullptr ? MOE_OK : launch_dwr<T>(c, x, d_logits, dWr, accumulate, partials, s);
+}
+
+// The gate weight gradient alone: from d_logits, or (from_partials) from the partial sums that launch_input_grad left
+int launch_gate_dwr(const moe_cfg* c, const void* x, const float* d_logits, float* dWr, int accumulate, float* partials, bool from_partials, hipStream_t s) {
+  if (from_partials) return launch_dwr_reduce(c, partials, dWr, route_bwd_geom(c->T, c->d_model, (int)elt_size(c), c->E).partial_rows, accumulate, s);
+  if (c->dtype == MOE_DTYPE_BF16) return launch_dwr<bf16>(c, x, d_logits, dWr, accumulate, partials, s);
+  if (c->dtype == MOE_DTYPE_F16) return launch_dwr<f16>(c, x, d_logits, dWr, accumulate, partials, s);
+  return launch_dwr<float>(c, x, d_logits, dWr, accumulate, partials, s);
 }
 
 int launch_route_bwd(const moe_cfg* c, const void* x, const float* Wr, const int32_t* idx, const float* w,

@@ -77,6 +77,13 @@ class MoELayer:
             self.slice_lo = torch.as_tensor(lo, dtype=torch.int32).to(self.device).contiguous()
             self.slice_hi = torch.as_tensor(hi, dtype=torch.int32).to(self.device).contiguous()
 
+    def bufs(self):
+        """Everything the whole-layer calls take, in the order of binding.LAYER_BUFS."""
+        return (self.x, self.Wr, self.bias, self.W1, self.W1b, self.W2, self.slice_lo, self.slice_hi, self.logits, self.topk_idx,
+                self.topk_w, self.counts, self.kept, self.offsets, self.row_of, self.src_of, self.x_perm, self.saved, self.y_perm,
+                self.out, self.d_out, self.dy_perm, self.d_topk_w, self.dx_perm, self.dW1, self.dW1b, self.dW2, self.dWr,
+                self.d_logits, self.dx, self.ws)
+
     # ---- the hot path, one library call per line -------------------------------------------------
     def route(self, logits_in=None):
         B.moe_route(self.cfg, self.x, self.Wr, self.bias, logits_in, self.logits, self.topk_idx, self.topk_w, self.ws)
@@ -122,7 +129,10 @@ class MoELayer:
         B.moe_route_bwd(self.cfg, self.x, self.Wr, self.topk_idx, self.topk_w, self.d_topk_w, self.d_logits,
                         self.dWr, self.dx, self.ws, accumulate)
 
+    # ---- whole passes: the calls above in one, with the same results ------------------------------
     def forward(self, logits_in=None):
+        if logits_in is None:
+            return B.moe_layer_fwd(self.cfg, self.bufs())
         self.route(logits_in)
         self.dispatch()
         self.ffn_fwd()
@@ -132,10 +142,7 @@ class MoELayer:
         """accumulate = 1 adds this batch's weight gradients (experts and gate) to the buffers."""
         if self.side is not None:
             return self.backward_overlapped(accumulate)
-        self.combine_bwd()
-        self.ffn_bwd(accumulate)
-        self.dispatch_bwd()
-        self.route_bwd(accumulate)
+        B.moe_layer_bwd(self.cfg, self.bufs(), accumulate)
 
     def enable_gate_overlap(self):
         """Run the gate's weight gradient on a second stream next to the expert backward (both need only
@@ -169,11 +176,6 @@ class MoELayer:
         """Forward, then the backward of a checkpointed layer: gate, dispatch and the saved activations
         are computed again from the layer input before the gradients (y_perm is kept: the combine
         backward needs the expert outputs).  The forward keeps only the hidden activation."""
-        self.route()
-        self.dispatch()
-        self.ffn_fwd_light()
-        self.combine()
-        self.route()
-        self.dispatch()
-        self.ffn_recompute()
+        B.moe_layer_fwd(self.cfg, self.bufs(), B.FWD_LIGHT)
+        B.moe_layer_fwd(self.cfg, self.bufs(), B.FWD_RECOMPUTE)
         self.backward()

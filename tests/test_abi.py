@@ -198,3 +198,42 @@ def test_static_scratch_limit_is_checked_before_any_launch():
     with pytest.raises(B.MoeError) as ei:
         B.moe_dispatch_static(B.make_cfg(8, 64, 64, 4, 2), P, None, None, None, P, P, P, P, P, P, stream=s)
     assert ei.value.code == -1
+
+
+@pytest.mark.parametrize("act", [B.ACT_GELU, B.ACT_SWIGLU])
+def test_layer_calls_validate_before_any_launch(act):
+    """Fake (never dereferenced) device addresses: every missing or misaligned pointer, a lone slice bound and a small
+    workspace are refused as by the single calls."""
+    cfg = B.make_cfg(8, 64, 128, 4, 2, act=act)
+    P, Q = 0x10000, 0x10008
+    single = ("W1b", "dW1b") if act == B.ACT_GELU else ()
+    base = {n: None if n in single + ("bias", "slice_lo", "slice_hi") else P for n in B.LAYER_BUFS}
+
+    def code(call, ws_bytes=1 << 40, **over):
+        import ctypes
+        b = {**base, **over}
+        vals = [b[n] or 0 for n in B.LAYER_BUFS] + [ws_bytes]
+        return call(ctypes.byref(cfg), (ctypes.c_size_t * len(vals))(*vals), 0, None)
+
+    lib = B.lib()
+    optional = {"bias", "slice_lo", "slice_hi"} | set(single)
+    backward = ("d_out", "dy_perm", "d_topk_w", "dx_perm", "dW1", "dW1b", "dW2", "dWr", "d_logits", "dx")
+    forward_only = ("logits", "counts", "src_of", "out")
+    for n in B.LAYER_BUFS:
+        if n not in optional:
+            if n not in backward:
+                assert code(lib.moe_layer_fwd, **{n: 0}) == -1, n
+            if n not in forward_only:
+                assert code(lib.moe_layer_bwd, **{n: 0}) == -1, n
+        if n not in single and n not in ("slice_lo", "slice_hi"):
+            if n not in backward:
+                assert code(lib.moe_layer_fwd, **{n: Q}) == -5, n
+            assert code(lib.moe_layer_bwd, **{n: Q}) == -5, n
+    for call in (lib.moe_layer_fwd, lib.moe_layer_bwd):
+        assert code(call, slice_lo=P) == -4
+        assert code(call, ws_bytes=256) == -7
+        if act == B.ACT_GELU:
+            assert code(call, W1b=P) == -3
+    import ctypes
+    assert lib.moe_layer_fwd(ctypes.byref(cfg), None, 0, None) == -1
+    assert lib.moe_layer_fwd(ctypes.byref(cfg), None, 3, None) == -3
