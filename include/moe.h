@@ -315,6 +315,19 @@ MOE_API int moe_layer_fwd(const moe_cfg* cfg, const moe_layer_bufs* b, int32_t m
 MOE_API int moe_layer_bwd(const moe_cfg* cfg, const moe_layer_bufs* b, int32_t accumulate, void* stream);
 
 /*
+ * moe_layer_bwd in two parts, for a layer that sees several micro-batches with the same weights.
+ * moe_layer_bwd_inputs does everything but the expert weight gradients (dW1, dW1b, dW2 may be NULL; `accumulate` is dWr's)
+ * and leaves dA in the call's workspace.  moe_layer_expert_dw then sums the expert weight gradients over n such calls
+ * (same cfg, each with buffers and a workspace of its own, untouched since) into the buffers of calls[0], overwriting or,
+ * accumulate != 0, adding to them: 16-bit storage multiplies the rows of up to eight calls through one pass over the
+ * gradients instead of reading and writing them once per call.
+ * A workspace of moe_layer_bwd_inputs_ws_bytes (at least moe_workspace_bytes) lets dx's last round of tiles be split.
+ */
+MOE_API int moe_layer_bwd_inputs_ws_bytes(const moe_cfg* cfg, size_t* bytes);
+MOE_API int moe_layer_bwd_inputs(const moe_cfg* cfg, const moe_layer_bufs* b, int32_t accumulate, void* stream);
+MOE_API int moe_layer_expert_dw(const moe_cfg* cfg, const moe_layer_bufs* const* calls, int32_t n, int32_t accumulate, void* stream);
+
+/*
  * Planner of the asymmetric expert assignment (Section 4.2 of the paper, Algorithm 1 and the paragraph
  * on memory limits).  HOST-ONLY: runs on the CPU, enqueues nothing, and `o` is a HOST pointer.
  *

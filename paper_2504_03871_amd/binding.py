@@ -19,7 +19,8 @@ MAX_E, MAX_K = 256, 8
 
 SYMBOLS = ("moe_error_string", "moe_last_hip_error", "moe_workspace_bytes", "moe_saved_bytes", "moe_route",
            "moe_dispatch", "moe_dispatch_static", "moe_expert_ffn_fwd", "moe_expert_ffn_fwd_light", "moe_expert_ffn_recompute", "moe_combine", "moe_combine_bwd", "moe_expert_ffn_bwd",
-           "moe_route_bwd", "moe_layer_fwd", "moe_layer_bwd", "moe_asymea_plan", "moe_asymea_shares", "moe_bench_stream", "moe_bench_clock_probe", "moe_bench_mfma_loop", "moe_gemm_block_tile")
+           "moe_route_bwd", "moe_layer_fwd", "moe_layer_bwd", "moe_layer_bwd_inputs_ws_bytes", "moe_layer_bwd_inputs",
+           "moe_layer_expert_dw", "moe_asymea_plan", "moe_asymea_shares", "moe_bench_stream", "moe_bench_clock_probe", "moe_bench_mfma_loop", "moe_gemm_block_tile")
 
 PROF = {"gemm1_fwd": 0, "gemm2_fwd": 1, "dh_bwd": 2, "dw2_bwd": 3, "dw1_bwd": 4, "dx_bwd": 5, "gather": 6,
         "combine": 7, "combine_bwd": 8, "route": 9}
@@ -81,6 +82,9 @@ def lib():
             "moe_route_bwd": [cfgp] + [p] * 8 + [i32, p, sz, p],
             "moe_layer_fwd": [cfgp, p, i32, p],
             "moe_layer_bwd": [cfgp, p, i32, p],
+            "moe_layer_bwd_inputs_ws_bytes": [cfgp, ctypes.POINTER(ctypes.c_size_t)],
+            "moe_layer_bwd_inputs": [cfgp, p, i32, p],
+            "moe_layer_expert_dw": [cfgp, p, i32, i32, p],
             "moe_asymea_plan": [i32] * 4 + [ctypes.c_double] * 3 + [i32, i32, ctypes.POINTER(i32)],
             "moe_asymea_shares": [i32] * 6 + [ctypes.POINTER(i32), ctypes.POINTER(i32)],
             "moe_bench_stream": [p, p, sz, i32, p],
@@ -249,6 +253,26 @@ def moe_layer_fwd(cfg, bufs, mode=FWD_FULL, stream=None):
 def moe_layer_bwd(cfg, bufs, accumulate=0, stream=None):
     """The layer's backward in one call; bufs in the order of LAYER_BUFS."""
     _check("moe_layer_bwd", lib().moe_layer_bwd(ctypes.byref(cfg), _layer_bufs(bufs), int(accumulate), _stream() if stream is None else stream))
+
+
+def moe_layer_bwd_inputs_ws_bytes(cfg) -> int:
+    n = ctypes.c_size_t(0)
+    _check("moe_layer_bwd_inputs_ws_bytes", lib().moe_layer_bwd_inputs_ws_bytes(ctypes.byref(cfg), ctypes.byref(n)))
+    return n.value
+
+
+def moe_layer_bwd_inputs(cfg, bufs, accumulate=0, stream=None):
+    """moe_layer_bwd without the expert weight gradients."""
+    _check("moe_layer_bwd_inputs", lib().moe_layer_bwd_inputs(ctypes.byref(cfg), _layer_bufs(bufs), int(accumulate),
+                                                              _stream() if stream is None else stream))
+
+
+def moe_layer_expert_dw(cfg, calls, accumulate=0, stream=None):
+    """Expert weight gradients summed over several moe_layer_bwd_inputs calls (a list of bufs) into the first one's buffers."""
+    bufs = [_layer_bufs(b) for b in calls]
+    ptrs = (ctypes.c_size_t * max(len(bufs), 1))(*[ctypes.addressof(b) for b in bufs])
+    _check("moe_layer_expert_dw", lib().moe_layer_expert_dw(ctypes.byref(cfg), ptrs, len(bufs), int(accumulate),
+                                                            _stream() if stream is None else stream))
 
 
 def moe_asymea_plan(n, L, M, N, T_A_attn, T_E_attn, T_E_exp, n_min=0, n_max=-1):

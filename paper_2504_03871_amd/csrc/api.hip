@@ -499,9 +499,11 @@ int moe_combine_bwd(const moe_cfg* cfg, const void* d_out, const void* y_perm, c
 }
 
 namespace {
+// inputs_only: dA and dx_perm, no weight gradients; dx_sums: room for dx's partial sums (inputs_split_bytes), or NULL
 int ffn_bwd_impl(const moe_cfg* cfg, const void* dy_perm, const void* x_perm, const void* saved, const void* W1, const void* W1b,
                  const void* W2, const int32_t* offsets, const int32_t* kept, const int32_t* slice_lo, const int32_t* slice_hi,
-                 void* dx_perm, float* dW1, float* dW1b, float* dW2, int32_t accumulate, void* ws, bool map_built, hipStream_t s) {
+                 void* dx_perm, float* dW1, float* dW1b, float* dW2, int32_t accumulate, void* ws, bool map_built, hipStream_t s,
+                 bool inputs_only = false, float* dx_sums = nullptr) {
   const bool swiglu = cfg->act == MOE_ACT_SWIGLU;
   const WsLayout w = ws_layout(cfg);
   const int A = cfg->T * cfg->k, d = cfg->d_model, f = cfg->d_ff;
@@ -536,27 +538,28 @@ int ffn_bwd_impl(const moe_cfg* cfg, const void* dy_perm, const void* x_perm, co
   // f 256, GELU 101 -> 92; bf16 SwiGLU (dW1b had its own), 3001 rows, d 1088, f 2880 624 -> 609, 128 experts of 512 rows
   // 3735 -> 3695.
   const bool bf = is_half(cfg);
-  const bool pair_h = shares_launch(cfg, f, max_tiles), pair_x = shares_launch(cfg, d, max_tiles);
+  const bool pair_h = !inputs_only && shares_launch(cfg, f, max_tiles), pair_x = !inputs_only && shares_launch(cfg, d, max_tiles);
   if (swiglu) { gw1.B2 = dact + plane; gw1.C2 = dW1b; }
   {
     ProfScope ps(cfg, MOE_PROF_DH_BWD, s);
     if (pair_h) CHECK(launch_pair(cfg, epi_h, false, gh, max_tiles, gw2, s));
     else CHECK(launch_gemm(cfg, MODE_NT, epi_h, false, false, gh, max_tiles, s));
   }
-  if (!pair_h) {
+  if (!pair_h && !inputs_only) {
     ProfScope ps(cfg, MOE_PROF_DW2_BWD, s);
     CHECK(launch_gemm(cfg, MODE_TN, EPI_DW, false, false, gw2, 0, s));
   }
-  if (!pair_x) {
+  if (!pair_x && !inputs_only) {
     ProfScope ps(cfg, MOE_PROF_DW1_BWD, s);
     CHECK(launch_gemm(cfg, MODE_TN, EPI_DW, false, false, gw1, 0, s));
   }
   ProfScope ps(cfg, MOE_PROF_DX_BWD, s);
   // split-K of the GELU dx: the smallest row tiles; the last round only in a launch of its own (in a shared one the
-  // weight-gradient tiles fill it)
+  // weight-gradient tiles fill it), for SwiGLU where the caller gives room for the partial sums
+  const bool may_split = !pair_x && tail_may_split(A, cfg->E, cfg->capacity == 0 && slice_lo == nullptr, (d + tr - 1) / tr, swiglu ? 2 * f : f);
   gx.split_small = bf && !swiglu && split_k_applies(cfg->E, f);
-  gx.split_tail = bf && !swiglu && !pair_x && tail_may_split(A, cfg->E, cfg->capacity == 0 && slice_lo == nullptr, (d + tr - 1) / tr, f);
-  if (gx.split_small || gx.split_tail) gx.split_ws = reinterpret_cast<float*>(static_cast<char*>(ws) + w.ffn_split);
+  gx.split_tail = bf && may_split && (dx_sums != nullptr || (!swiglu && !shares_launch(cfg, d, max_tiles)));
+  if (gx.split_small || gx.split_tail) gx.split_ws = dx_sums != nullptr ? dx_sums : reinterpret_cast<float*>(static_cast<char*>(ws) + w.ffn_split);
   if (pair_x) return launch_pair(cfg, EPI_STORE, swiglu, gx, max_tiles, gw1, s);
   return launch_gemm(cfg, MODE_NT, EPI_STORE, false, swiglu, gx, max_tiles, s);
 }
@@ -605,8 +608,15 @@ int moe_route_bwd(const moe_cfg* cfg, const void* x, const float* Wr, const int3
 }
 
 namespace {
+// Room for dx's partial sums behind the workspace of a backward that leaves the weight gradients to a later call: the
+// chip has nothing else to do beside dx's last round then
+size_t inputs_split_bytes(const moe_cfg* c) {
+  if (!is_half(c) || (c->act == MOE_ACT_SWIGLU ? 2 : 1) * c->d_ff < SPLIT_MIN_K) return 0;
+  const bool small = c->act == MOE_ACT_GELU && split_k_applies(c->E, c->d_ff);
+  return align_up(std::max(small ? split_ws_bytes(c->E, c->d_model) : 0, tail_ws_bytes(max_row_tiles(c->T * c->k, c->E, gemm_bf16_tile_rows()), c->d_model)), 256);
+}
 // Arguments of the calls that a whole-layer call stands for, checked before anything is launched
-int check_layer(const moe_cfg* cfg, const moe_layer_bufs* b, bool combine, bool backward) {
+int check_layer(const moe_cfg* cfg, const moe_layer_bufs* b, bool combine, bool backward, bool dw = true) {
   CHECK(check_cfg(cfg));
   REQUIRE(b);
   CHECK(check_slices(b->slice_lo, b->slice_hi));
@@ -617,10 +627,10 @@ int check_layer(const moe_cfg* cfg, const moe_layer_bufs* b, bool combine, bool 
   if (combine || backward) { REQUIRE(b->W2); REQUIRE(b->y_perm); }
   if (combine) REQUIRE(b->out);
   if (backward) {
-    REQUIRE(b->d_out); REQUIRE(b->dy_perm); REQUIRE(b->d_topk_w); REQUIRE(b->dx_perm); REQUIRE(b->dW1); REQUIRE(b->dW2); REQUIRE(b->dWr);
-    REQUIRE(b->d_logits); REQUIRE(b->dx);
+    REQUIRE(b->d_out); REQUIRE(b->dy_perm); REQUIRE(b->d_topk_w); REQUIRE(b->dx_perm); REQUIRE(b->dWr); REQUIRE(b->d_logits); REQUIRE(b->dx);
+    if (dw) { REQUIRE(b->dW1); REQUIRE(b->dW2); }
   }
-  if (swiglu) { REQUIRE(b->W1b); if (backward) REQUIRE(b->dW1b); }
+  if (swiglu) { REQUIRE(b->W1b); if (backward && dw) REQUIRE(b->dW1b); }
   if (!swiglu && (b->W1b != nullptr || (backward && b->dW1b != nullptr))) return MOE_ERR_BAD_DTYPE;
   const void* const fwd[] = {b->x, b->Wr, b->bias, b->W1, b->W1b, b->W2, b->slice_lo, b->slice_hi, b->logits, b->topk_idx, b->topk_w, b->counts, b->kept,
                              b->offsets, b->row_of, b->src_of, b->x_perm, b->saved, b->y_perm, b->out, b->ws};
@@ -656,8 +666,9 @@ int moe_layer_fwd(const moe_cfg* cfg, const moe_layer_bufs* b, int32_t mode, voi
   return launch_combine(cfg, b->y_perm, b->topk_w, b->topk_idx, b->row_of, b->offsets, b->kept, b->slice_lo, b->slice_hi, b->out, 0, s);
 }
 
-int moe_layer_bwd(const moe_cfg* cfg, const moe_layer_bufs* b, int32_t accumulate, void* stream) {
-  CHECK(check_layer(cfg, b, false, true));
+namespace {
+int layer_bwd(const moe_cfg* cfg, const moe_layer_bufs* b, int32_t accumulate, bool inputs_only, void* stream) {
+  CHECK(check_layer(cfg, b, false, true, !inputs_only));
   if (cfg->T == 0)
     return moe_route_bwd(cfg, b->x, b->Wr, b->topk_idx, b->topk_w, b->d_topk_w, b->d_logits, b->dWr, b->dx, accumulate, b->ws, b->ws_bytes, stream);
   hipStream_t s = (hipStream_t)stream;
@@ -670,11 +681,81 @@ int moe_layer_bwd(const moe_cfg* cfg, const moe_layer_bufs* b, int32_t accumulat
     CHECK(launch_combine_bwd(cfg, b->d_out, b->y_perm, b->topk_w, b->topk_idx, b->row_of, b->offsets, b->kept, b->slice_lo, b->slice_hi, b->dy_perm,
                              b->d_topk_w, &side, s));
   }
+  const size_t room = inputs_only ? inputs_split_bytes(cfg) : 0, behind = align_up(w.total, 256);
+  float* dx_sums = room > 0 && b->ws_bytes >= behind + room ? reinterpret_cast<float*>(ws + behind) : nullptr;
   CHECK(ffn_bwd_impl(cfg, b->dy_perm, b->x_perm, b->saved, b->W1, b->W1b, b->W2, b->offsets, b->kept, b->slice_lo, b->slice_hi, b->dx_perm, b->dW1,
-                     b->dW1b, b->dW2, accumulate, b->ws, true, s));
+                     b->dW1b, b->dW2, accumulate, b->ws, true, s, inputs_only, dx_sums));
   const bool dwr = input_grad_has_dwr(cfg);
   CHECK(launch_input_grad(cfg, b, wrt, partials, dwr, s));
   return launch_gate_dwr(cfg, b->x, b->d_logits, b->dWr, accumulate != 0, partials, dwr, s);
+}
+}  // namespace
+
+int moe_layer_bwd(const moe_cfg* cfg, const moe_layer_bufs* b, int32_t accumulate, void* stream) { return layer_bwd(cfg, b, accumulate, false, stream); }
+
+int moe_layer_bwd_inputs(const moe_cfg* cfg, const moe_layer_bufs* b, int32_t accumulate, void* stream) { return layer_bwd(cfg, b, accumulate, true, stream); }
+
+int moe_layer_bwd_inputs_ws_bytes(const moe_cfg* cfg, size_t* bytes) {
+  CHECK(check_cfg(cfg));
+  REQUIRE(bytes);
+  *bytes = align_up(ws_layout(cfg).total, 256) + inputs_split_bytes(cfg);
+  return MOE_OK;
+}
+
+int moe_layer_expert_dw(const moe_cfg* cfg, const moe_layer_bufs* const* calls, int32_t n, int32_t accumulate, void* stream) {
+  CHECK(check_cfg(cfg));
+  REQUIRE(calls);
+  if (n < 1) return MOE_ERR_BAD_SHAPE;
+  const bool swiglu = cfg->act == MOE_ACT_SWIGLU;
+  for (int i = 0; i < n; ++i) {
+    const moe_layer_bufs* b = calls[i];
+    REQUIRE(b);
+    CHECK(check_slices(b->slice_lo, b->slice_hi));
+    REQUIRE(b->offsets); REQUIRE(b->kept); REQUIRE(b->x_perm); REQUIRE(b->saved); REQUIRE(b->dy_perm); REQUIRE(b->ws);
+    const void* const in[] = {b->offsets, b->kept, b->slice_lo, b->slice_hi, b->x_perm, b->saved, b->dy_perm, b->ws};
+    for (const void* p : in) ALIGNED(p);
+    CHECK(check_ws(cfg, b->ws, b->ws_bytes));
+  }
+  const moe_layer_bufs* out = calls[0];
+  REQUIRE(out->dW1); REQUIRE(out->dW2);
+  if (swiglu) REQUIRE(out->dW1b);
+  if (!swiglu && out->dW1b != nullptr) return MOE_ERR_BAD_DTYPE;
+  ALIGNED(out->dW1); ALIGNED(out->dW1b); ALIGNED(out->dW2);
+  if (cfg->T == 0) return MOE_OK;
+  hipStream_t s = (hipStream_t)stream;
+  const WsLayout w = ws_layout(cfg);
+  const size_t plane = (size_t)cfg->T * cfg->k * cfg->d_ff * elt_size(cfg);
+  auto hidden = [&](const moe_layer_bufs* b) { return static_cast<const char*>(b->saved) + (swiglu ? 2 : 1) * plane; };
+  auto dact = [&](const moe_layer_bufs* b) { return static_cast<const char*>(b->ws) + w.ffn_bwd_dact; };
+  const int per = is_half(cfg) ? DW_MAX_SEGS : 1;
+  for (int i = 0; i < n; i += per) {
+    const moe_layer_bufs* b = calls[i];
+    GemmArgs g = {};
+    g.order = tile_map_args(cfg, b->offsets, b->kept, b->slice_lo, b->slice_hi, false, b->ws).map.order;
+    g.offsets = b->offsets; g.kept = b->kept; g.lo = b->slice_lo; g.hi = b->slice_hi; g.E = cfg->E;
+    g.accumulate = accumulate || i > 0;
+    GemmArgs gw2 = g, gw1 = g;   // dW2[e] = H^T dy;  dW1[e] = x_perm^T dA (SwiGLU: dW1 from dG, dW1b from dU)
+    gw2.A = hidden(b); gw2.B = b->dy_perm; gw2.M = cfg->d_ff; gw2.N = cfg->d_model; gw2.C = out->dW2;
+    gw1.A = b->x_perm; gw1.B = dact(b); gw1.M = cfg->d_model; gw1.N = cfg->d_ff; gw1.C = out->dW1;
+    if (swiglu) { gw1.B2 = dact(b) + plane; gw1.C2 = out->dW1b; }
+    ProfScope ps(cfg, MOE_PROF_DW2_BWD, s);
+    if (!is_half(cfg)) {
+      CHECK(launch_gemm(cfg, MODE_TN, EPI_DW, false, false, gw2, 0, s));
+      CHECK(launch_gemm(cfg, MODE_TN, EPI_DW, false, false, gw1, 0, s));
+      continue;
+    }
+    DwSegs s2 = {}, s1 = {};
+    s1.n = s2.n = std::min(per, n - i);
+    for (int q = 0; q < s1.n; ++q) {
+      const moe_layer_bufs* c = calls[i + q];
+      s2.A[q] = hidden(c); s2.B[q] = s2.B2[q] = c->dy_perm;
+      s1.A[q] = c->x_perm; s1.B[q] = dact(c); s1.B2[q] = dact(c) + (swiglu ? plane : 0);
+      s1.offsets[q] = s2.offsets[q] = c->offsets; s1.kept[q] = s2.kept[q] = c->kept;
+      s1.lo[q] = s2.lo[q] = c->slice_lo; s1.hi[q] = s2.hi[q] = c->slice_hi;
+    }
+    CHECK(launch_gemm_half_dw_segs(cfg->dtype, gw2, s2, gw1, s1, s));
+  }
+  return MOE_OK;
 }
 
 }  // extern "C"

@@ -350,6 +350,17 @@ int launch_gemm_half_skinny(int dtype, int epi, bool dual, const GemmArgs& g, in
 constexpr int SKINNY_AVERAGE = 48;
 inline bool skinny_applies(long long rows, int E) { return rows <= (long long)SKINNY_AVERAGE * E; }
 
+// A weight gradient over the rows of several calls (micro-batches) at once: operand s of call s, each with its own share
+// bounds.  GemmArgs holds what they have in common.
+constexpr int DW_MAX_SEGS = 8;
+struct DwSegs {
+  const void *A[DW_MAX_SEGS], *B[DW_MAX_SEGS], *B2[DW_MAX_SEGS];
+  const int32_t *offsets[DW_MAX_SEGS], *kept[DW_MAX_SEGS], *lo[DW_MAX_SEGS], *hi[DW_MAX_SEGS];
+  int n;
+};
+// both weight gradients (g1 over s1, then g2 over s2) in one launch
+int launch_gemm_half_dw_segs(int dtype, const GemmArgs& g1, const DwSegs& s1, const GemmArgs& g2, const DwSegs& s2, hipStream_t s);
+
 #ifdef __HIPCC__
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));

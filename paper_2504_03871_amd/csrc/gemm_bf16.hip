@@ -46,7 +46,7 @@ static int launch_one(const GemmArgs& g, int max_tiles, hipStream_t s) {
   long long tiles;
   if (MODE == MODE_TN) tiles = dw_blocks(g);
   else tiles = (long long)ntn * max_tiles;
-  const bool split = MODE != MODE_TN && EPI == EPI_STORE && !CHAIN && g.split_ws != nullptr;
+  const bool split = MODE != MODE_TN && EPI == EPI_STORE && g.split_ws != nullptr;
   kern<<<dim3(gemm_bf16_grid(tiles + (split ? split_blocks(g, ntn) : 0))), T_WGM * T_WGN * 64, lds, s>>>(g);
   int rc = launch_status();
   if (rc != MOE_OK || !split) return rc;
@@ -82,6 +82,18 @@ static int launch_pair(const GemmArgs& g1, int max_tiles, const GemmArgs& g2, hi
 }
 
 template <typename ST>
+static int dw_segs_for(const GemmArgs& g1, const DwSegs& s1, const GemmArgs& g2, const DwSegs& s2, hipStream_t s) {
+  constexpr int lds = gemm_bf16_lds_bytes<T_BM, T_BN, false>();
+  auto kern = gemm_bf16_dw_segs_kernel<ST, T_BM, T_BN, T_WGM, T_WGN>;
+  hipError_t err = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+  if (err != hipSuccess) return set_hip_error(err);
+  const long long n1 = dw_blocks(g1), n2 = dw_blocks(g2);
+  if (n1 + n2 > 0x7fffffffll) return MOE_ERR_BAD_SHAPE;
+  kern<<<dim3(gemm_bf16_grid(n1 + n2)), T_WGM * T_WGN * 64, lds, s>>>(DwSegsPair{{g1, g2}, {s1, s2}, (int)n1});
+  return launch_status();
+}
+
+template <typename ST>
 static int pair_for(int epi1, bool chain1, const GemmArgs& g1, int max_tiles, const GemmArgs& g2, hipStream_t s) {
   if (epi1 == EPI_GELU_BWD) return launch_pair<ST, EPI_GELU_BWD, false>(g1, max_tiles, g2, s);
   if (epi1 == EPI_SWIGLU_BWD) return launch_pair<ST, EPI_SWIGLU_BWD, false>(g1, max_tiles, g2, s);
@@ -101,6 +113,10 @@ static int one_for(int mode, int epi, bool dual, bool chain, const GemmArgs& g, 
   if (mode == MODE_NT && epi == EPI_STORE && chain) return launch_one<ST, MODE_NT, EPI_STORE, false, true>(g, max_tiles, s);
   if (mode == MODE_TN && epi == EPI_DW) return launch_one<ST, MODE_TN, EPI_DW, false, false>(g, max_tiles, s);
   return MOE_ERR_BAD_DTYPE;
+}
+
+int launch_gemm_half_dw_segs(int dtype, const GemmArgs& g1, const DwSegs& s1, const GemmArgs& g2, const DwSegs& s2, hipStream_t s) {
+  return dtype == MOE_DTYPE_F16 ? dw_segs_for<f16>(g1, s1, g2, s2, s) : dw_segs_for<bf16>(g1, s1, g2, s2, s);
 }
 
 int launch_gemm_half_pair(int dtype, int epi1, bool chain1, const GemmArgs& g1, int max_tiles, const GemmArgs& g2, hipStream_t s) {

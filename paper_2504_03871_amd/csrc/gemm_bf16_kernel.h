@@ -289,8 +289,9 @@ constexpr int gemm_bf16_lds_bytes() { return NBUF * gemm_bf16_stage_bytes<BM, BN
 
 // One output tile; vb = the tile's number in dispatch order.  Block-uniform control flow; returns at
 // once for numbers past the last tile (the grid is sized for the worst case).
-template <typename ST, int MODE, int EPI, bool DUAL, bool CHAIN, int BM, int BN, int WGM, int WGN>
-__device__ __forceinline__ void gemm_bf16_tile(const GemmArgs& g, const int vb, char* smem) {
+// SEGS (weight gradients): the K range is that of several calls, one after the other through one pipeline.
+template <typename ST, int MODE, int EPI, bool DUAL, bool CHAIN, int BM, int BN, int WGM, int WGN, bool SEGS = false>
+__device__ __forceinline__ void gemm_bf16_tile(const GemmArgs& g, const int vb, char* smem, const DwSegs* segs = nullptr) {
   constexpr int NT = WGM * WGN * 64;
   constexpr int WTM = BM / WGM / 32, WTN = BN / WGN / 32;
   constexpr int KS = BKT / 32;               // MFMA K steps per stage
@@ -306,7 +307,9 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs& g, const int vb, 
   const int wm = wave / WGN, wn = wave % WGN;
 
   int e, row0, mvalid, klen, m0 = 0, n0;
-  int kbase = 0;
+  int kbase = 0, skip = 0, part_stages = 0;   // CHAIN: first stage and number of stages of this block's K part (0: all)
+  int seg_rows = 0, seg_row0 = 0, seg_stages = 0;          // SEGS: lane s holds segment s's rows and first row; stages in all
+  unsigned seg_a[2] = {}, seg_b[2] = {};                   // and its operands' addresses
   bool second = false;          // TN with two gradients: this block's tile is one of the second's (B2, C2)
   float* part_sums = nullptr;   // this block computes one K part of a split tile: where its fp32 sums go, and their pitch
   int part_pitch = 0;
@@ -323,33 +326,55 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs& g, const int vb, 
       m0 = mt * BM;
       rt = 0;
       int l, h;
-      share_of(g.lo, g.hi, g.kept[e], e, l, h);
-      row0 = g.offsets[e] + l;
-      klen = h - l;
+      if constexpr (SEGS) {
+        static_assert(MODE == MODE_TN, "weight gradients");
+        int all = 0;
+#pragma unroll
+        for (int q = 0; q < DW_MAX_SEGS; ++q)
+          if (q < segs->n) {
+            share_of(segs->lo[q], segs->hi[q], segs->kept[q][e], e, l, h);
+            const unsigned long long pa = (unsigned long long)segs->A[q], pb = (unsigned long long)(second ? segs->B2[q] : segs->B[q]);
+            if (lane == q) {
+              seg_rows = h - l;
+              seg_row0 = segs->offsets[q][e] + l;
+              seg_a[0] = (unsigned)pa; seg_a[1] = (unsigned)(pa >> 32);
+              seg_b[0] = (unsigned)pb; seg_b[1] = (unsigned)(pb >> 32);
+            }
+            all += (h - l + BKT - 1) / BKT;
+          }
+        seg_stages = __builtin_amdgcn_readfirstlane(all);
+        row0 = 0;
+        klen = seg_stages;
+      } else {
+        share_of(g.lo, g.hi, g.kept[e], e, l, h);
+        row0 = g.offsets[e] + l;
+        klen = h - l;
+      }
       mvalid = min(BM, g.M - m0);
       if (klen == 0 && g.accumulate) return;
     } else {
-      constexpr bool CAN_SPLIT = (EPI == EPI_STORE && !CHAIN);
+      constexpr bool CAN_SPLIT = EPI == EPI_STORE;
+      const int kall = CHAIN ? 2 * g.K : g.K;
       const int n_rt = g.ntiles[0];
       RowBlock rb;
       klen = g.K;
       TailSplit ts = {0, 1};
-      if (CAN_SPLIT && g.split_tail) ts = tail_split(n_rt * ntn, g.K);
+      if (CAN_SPLIT && g.split_tail) ts = tail_split(n_rt * ntn, kall);
       if (CAN_SPLIT && ts.parts > 1) {          // the tiles of the last round are split along K
         if (!tail_split_block(vb, n_rt, g.ntiles[1], ntn, g.chunked != 0, ts, rb)) return;
         if (rb.split_tile >= 0) {
-          const int stages = g.K / BKT, k0 = rb.ksplit * stages / ts.parts;
-          kbase = k0 * BKT;
-          klen = ((rb.ksplit + 1) * stages / ts.parts - k0) * BKT;
+          const int stages = kall / BKT, k0 = rb.ksplit * stages / ts.parts, k1 = (rb.ksplit + 1) * stages / ts.parts;
+          if constexpr (CHAIN) { skip = k0; part_stages = k1 - k0; }
+          else { kbase = k0 * BKT; klen = (k1 - k0) * BKT; }
           part_sums = g.split_ws + (size_t)(rb.split_tile * ts.parts + rb.ksplit) * (BM * BN);
           part_pitch = BN;
         }
       } else {
         // or the smallest row tiles: the last n_sp row tiles are not part of the regular numbering; their blocks
         // follow it, SPLIT_K per (row tile, column tile), each with a K range of its own
-        const int n_sp = (CAN_SPLIT && g.split_small) ? g.ntiles[2] : 0;
+        const int n_sp = (CAN_SPLIT && !CHAIN && g.split_small) ? g.ntiles[2] : 0;
         if (!row_tile_block(vb, n_rt, g.ntiles[1], n_sp, ntn, g.chunked != 0, rb)) return;
-        if (CAN_SPLIT && rb.split_tile >= 0) {
+        if (CAN_SPLIT && !CHAIN && rb.split_tile >= 0) {
           klen = g.K / SPLIT_K;
           kbase = rb.ksplit * klen;
           part_sums = g.split_ws + (size_t)(rb.split_tile * SPLIT_K + rb.ksplit) * SPLIT_ROWS * g.N + rb.nt * BN;
@@ -361,6 +386,8 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs& g, const int vb, 
       nt = __builtin_amdgcn_readfirstlane(rb.nt);
       kbase = __builtin_amdgcn_readfirstlane(kbase);
       klen = __builtin_amdgcn_readfirstlane(klen);
+      skip = __builtin_amdgcn_readfirstlane(skip);
+      part_stages = __builtin_amdgcn_readfirstlane(part_stages);
       const RowTile t = g.tiles[rt];
       e = t.e;
       row0 = t.row0;
@@ -436,10 +463,25 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs& g, const int vb, 
       boff = ((size_t)e * g.N + n0) * g.K + kbase;  bbytes = ((size_t)(g.N - n0) * g.K - kbase) * 2;
       pa = g.K * 2; pb = g.K * 2; astep = BKT * 2; bstep = BKT * 2;
     }
-    const rsrc_t ra = make_rsrc(A0 + aoff, abytes), ra1 = make_rsrc(A1 + aoff, abytes);
-    const rsrc_t rb = make_rsrc(B0 + boff, bbytes), rb1 = make_rsrc(B1 + boff, bbytes);
+    rsrc_t ra = make_rsrc(A0 + aoff, abytes), rb = make_rsrc(B0 + boff, bbytes);
+    const rsrc_t ra1 = make_rsrc(A1 + aoff, abytes), rb1 = make_rsrc(B1 + boff, bbytes);
+    // SEGS: the segment whose stages are being requested, the next stage of it and how many it has; stages are requested
+    // strictly in order, and never more than there are, so a segment with rows follows whenever one is asked for
+    int seg = -1, seg_k = 0, seg_n = 0;
+    auto next_stage = [&]() {
+      if (seg_k < seg_n) return;
+      int rows;
+      do rows = __builtin_amdgcn_readlane(seg_rows, ++seg); while (rows == 0 && seg + 1 < DW_MAX_SEGS);
+      const size_t r0 = __builtin_amdgcn_readlane(seg_row0, seg);
+      const unsigned long long a = (unsigned)__builtin_amdgcn_readlane(seg_a[0], seg) | (unsigned long long)(unsigned)__builtin_amdgcn_readlane(seg_a[1], seg) << 32;
+      const unsigned long long b = (unsigned)__builtin_amdgcn_readlane(seg_b[0], seg) | (unsigned long long)(unsigned)__builtin_amdgcn_readlane(seg_b[1], seg) << 32;
+      ra = make_rsrc(reinterpret_cast<const bf16*>(a) + r0 * g.M + m0, ((size_t)rows * g.M - m0) * 2);
+      rb = make_rsrc(reinterpret_cast<const bf16*>(b) + r0 * g.N + n0, ((size_t)rows * g.N - n0) * 2);
+      seg_k = 0;
+      seg_n = (rows + BKT - 1) / BKT;
+    };
     const int KT1 = KT;                      // stages of one operand pair
-    const int KTT = CHAIN ? 2 * KT1 : KT1;   // stages in all
+    const int KTT = SEGS ? seg_stages : !CHAIN ? KT1 : part_stages > 0 ? part_stages : 2 * KT1;   // stages in all
     // Iteration kt issues the loads of stage kt+D, multiplies stage kt (reading the fragments of stage
     // kt+1 meanwhile), then waits until its own loads of stage kt+2 have landed (all but the newest D-2
     // stages) and joins the block barrier, after which stage kt+2 is visible to every wave and stage
@@ -469,12 +511,14 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs& g, const int vb, 
     bf16x8 af[TM], bfr[2][TNN], bfr2[2][DUAL ? TNN : 1];
 #define MOE_LOAD(kt_, buf_)                                                                                 \
   do {                                                                                                      \
+    if constexpr (SEGS) next_stage();                                                                       \
     _Pragma("unroll") for (int q__ = 0; q__ < L; ++q__) MOE_LOAD1(kt_, buf_, q__);                          \
+    if constexpr (SEGS) ++seg_k;                                                                            \
   } while (0)
 // load q_ (0 .. L-1) of a stage: the A chunks, then the B chunks (DUAL: both weight matrices in turn)
 #define MOE_LOAD1(kt_, buf_, q_)                                                                            \
   do {                                                                                                      \
-    const int kq__ = (kt_);                                                                                 \
+    const int kq__ = SEGS ? seg_k : CHAIN ? (kt_) + skip : (kt_);                                           \
     const bool sec__ = CHAIN && kq__ >= KT1;                                                                \
     const unsigned kl__ = (unsigned)(sec__ ? kq__ - KT1 : kq__);                                            \
     const unsigned st__ = smem_base + (buf_) + wbase;                                                       \
@@ -558,7 +602,9 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs& g, const int vb, 
       __builtin_amdgcn_s_waitcnt(0);   /* vmcnt(0) lgkmcnt(0): own loads of stage S+1, own reads of stage S */ \
       MOE_BLOCK_BARRIER();                                                                                  \
     }                                                                                                       \
+    if constexpr (SEGS) { if (DO_LOAD_) next_stage(); }                                                     \
     MOE_STEP(1, DO_NEXT_, b1, 0, DO_LOAD_, (S_) + 2, b0, 0, L, NI_);                                        \
+    if constexpr (SEGS) { if (DO_LOAD_) ++seg_k; }                                                          \
     { const int t__ = b0; b0 = b1; b1 = t__; }                                                              \
   } while (0)
       if (KTT > 0) {
@@ -605,7 +651,7 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs& g, const int vb, 
   const int grp = lane >> 4, r8 = lane & 7, right = (lane >> 3) & 1;   // after swap8: row of eight, left or right half of a line
   auto band_row = [&](int i) { return ((i >> 1) * WGM + wm) * 32 + (i & 1) * 16; };   // first row of row tile i
   auto empty = [&](int i) { return band_row(i) >= mvalid; };
-  if (MODE != MODE_TN && EPI == EPI_STORE && !CHAIN && part_sums != nullptr) {   // fp32 partial sums of this block's K part
+  if (MODE != MODE_TN && EPI == EPI_STORE && part_sums != nullptr) {   // fp32 partial sums of this block's K part
 #pragma unroll
     for (int i = 0; i < TM; ++i)
       if (!empty(i)) {
@@ -738,7 +784,7 @@ template <typename ST>
 __global__ __launch_bounds__(256) void split_reduce_kernel(GemmArgs g) {
   const int n_rt = g.ntiles[0], ntn = (g.N + 255) / 256;
   TailSplit ts = {0, 1};
-  if (g.split_tail) ts = tail_split(n_rt * ntn, g.K);
+  if (g.split_tail) ts = tail_split(n_rt * ntn, g.B2 != nullptr ? 2 * g.K : g.K);   // B2: two products chained
   auto put = [&](size_t row, int n, const f32x4& v) {
     *reinterpret_cast<u32x2*>(reinterpret_cast<ST*>(g.C) + row * g.N + n) = u32x2{Half16<ST>::pack2(v[0], v[1]), Half16<ST>::pack2(v[2], v[3])};
   };
@@ -800,6 +846,19 @@ __global__ __launch_bounds__(WGM* WGN * 64, 1) void gemm_bf16_pair_kernel(GemmAr
     gemm_bf16_tile<ST, MODE1, EPI1, false, CHAIN1, BM, BN, WGM, WGN>(g1, blockIdx.x, smem);
   else
     gemm_bf16_tile<ST, MODE2, EPI2, false, false, BM, BN, WGM, WGN>(g2, blockIdx.x - first_blocks, smem);
+}
+
+// Both weight gradients over the rows of several calls: blocks below `first_blocks` take a tile of the first.
+// Per call, a micro-batch of 512 rows per expert has eight K stages of arithmetic per tile and moves 512 KB of old and new
+// sums for it; over all calls the sums are written once.  Four micro-batches of 2048 tokens, d 1024, f 4096, eight experts:
+// backward GEMMs 1040 us with the gradients accumulated call by call in launches shared with dH and dx, 4 x 122 + 278 now,
+// an iteration 1939 -> 1670.
+struct DwSegsPair { GemmArgs g[2]; DwSegs s[2]; int first_blocks; };
+template <typename ST, int BM, int BN, int WGM, int WGN>
+__global__ __launch_bounds__(WGM* WGN * 64, 1) void gemm_bf16_dw_segs_kernel(DwSegsPair p) {
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  const int w = (int)blockIdx.x >= p.first_blocks;
+  gemm_bf16_tile<ST, MODE_TN, EPI_DW, false, false, BM, BN, WGM, WGN, true>(p.g[w], blockIdx.x - w * p.first_blocks, smem, &p.s[w]);
 }
 
 inline unsigned gemm_bf16_grid(long long tiles) { return (unsigned)(tiles > 0 ? tiles : 1); }

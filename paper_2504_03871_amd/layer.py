@@ -13,9 +13,10 @@ from . import binding as B
 
 class MoELayer:
     def __init__(self, T, d_model, d_ff, E, k, dtype=B.DTYPE_BF16, act=B.ACT_GELU, capacity=0, device="cuda:0",
-                 params=None):
+                 params=None, defer_dw=False):
         """`params`: another MoELayer whose weights and weight-gradient buffers this one aliases (one
-        layer seen by several micro-batches, each with activation buffers of its own)."""
+        layer seen by several micro-batches, each with activation buffers of its own).  `defer_dw`: backward_inputs
+        will be used, with a workspace for it."""
         self.cfg = B.make_cfg(T, d_model, d_ff, E, k, dtype, act, capacity)
         self.T, self.d, self.f, self.E, self.k, self.act = T, d_model, d_ff, E, k, act
         self.tdtype = {B.DTYPE_BF16: torch.bfloat16, B.DTYPE_F16: torch.float16}.get(dtype, torch.float32)
@@ -48,7 +49,8 @@ class MoELayer:
         self.saved = torch.empty(B.moe_saved_bytes(self.cfg), dtype=torch.uint8, device=dev)
         self.y_perm = e(A, d_model, dtype=td, device=dev)
         self.out = e(T, d_model, dtype=td, device=dev)
-        self.ws = torch.empty(max(B.moe_workspace_bytes(self.cfg), 256), dtype=torch.uint8, device=dev)
+        need = B.moe_layer_bwd_inputs_ws_bytes if defer_dw else B.moe_workspace_bytes
+        self.ws = torch.empty(max(need(self.cfg), 256), dtype=torch.uint8, device=dev)
         # backward state
         self.dy_perm = e(A, d_model, dtype=td, device=dev)
         self.d_topk_w = e(T, k, **f32)
@@ -143,6 +145,15 @@ class MoELayer:
         if self.side is not None:
             return self.backward_overlapped(accumulate)
         B.moe_layer_bwd(self.cfg, self.bufs(), accumulate)
+
+    def backward_inputs(self, accumulate=0):
+        """The backward without the expert weight gradients (`accumulate`: the gate's); expert_dw adds them up."""
+        B.moe_layer_bwd_inputs(self.cfg, self.bufs(), accumulate)
+
+    @staticmethod
+    def expert_dw(calls, accumulate=0):
+        """Expert weight gradients of layers that share weights and have run backward_inputs, summed into the first's."""
+        B.moe_layer_expert_dw(calls[0].cfg, [m.bufs() for m in calls], accumulate)
 
     def enable_gate_overlap(self):
         """Run the gate's weight gradient on a second stream next to the expert backward (both need only

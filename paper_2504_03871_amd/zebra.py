@@ -10,7 +10,9 @@ attention computation, a layer's output is the next layer's input), and the expe
 library's MoE layer, one call sequence per (layer, micro-batch) on the compute stream.
 
 Nothing is computed here: the copies are `Tensor.copy_` on a stream, everything else is a library call.
-Weight gradients of a layer are accumulated over its micro-batches by the library (accumulate flag).
+A layer's gate weight gradient is accumulated over its micro-batches (accumulate flag); its expert weight gradients are
+summed over all of them at once, after the last micro-batch's backward (moe_layer_expert_dw), so that the input gradients
+travel back before them and the gradients are written once instead of read and written per micro-batch.
 All streams have the default priority.
 """
 from __future__ import annotations
@@ -48,9 +50,9 @@ class ZebraExpertEngine:
         self.L, self.R, self.T_mb = L, R, T_mb
         self.device = torch.device(device)
         # one parameter set per layer; one set of activation buffers per (layer, micro-batch)
-        self.params = [MoELayer(T_mb, d_model, d_ff, E, k, dtype, act, device=device) for _ in range(L)]
+        self.params = [MoELayer(T_mb, d_model, d_ff, E, k, dtype, act, device=device, defer_dw=True) for _ in range(L)]
         self.mb = [[self.params[i] if j == 0 else
-                    MoELayer(T_mb, d_model, d_ff, E, k, dtype, act, device=device, params=self.params[i])
+                    MoELayer(T_mb, d_model, d_ff, E, k, dtype, act, device=device, params=self.params[i], defer_dw=True)
                     for j in range(R)] for i in range(L)]
         td = self.params[0].tdtype
         buf = lambda: [torch.empty(T_mb, d_model, dtype=td, device=self.device) for _ in range(R)]
@@ -98,8 +100,10 @@ class ZebraExpertEngine:
                     self.recv_b[i][j].record(self.combine)
                 with torch.cuda.stream(self.compute):            # E^B_{i,j}
                     self.compute.wait_event(self.recv_b[i][j])
-                    m.backward(accumulate=1 if j > 0 else 0)
+                    m.backward_inputs(accumulate=1 if j > 0 else 0)
                     self.done_b[i][j].record(self.compute)
+                    if j == R - 1:
+                        MoELayer.expert_dw(self.mb[i])
                 with torch.cuda.stream(self.dispatch):
                     self.dispatch.wait_event(self.done_b[i][j])
                     self.grad[i][j].copy_(m.dx, non_blocking=True)

@@ -237,3 +237,25 @@ def test_layer_calls_validate_before_any_launch(act):
     import ctypes
     assert lib.moe_layer_fwd(ctypes.byref(cfg), None, 0, None) == -1
     assert lib.moe_layer_fwd(ctypes.byref(cfg), None, 3, None) == -3
+
+
+def test_weight_gradients_over_calls_validate_before_any_launch():
+    import ctypes
+    cfg = B.make_cfg(8, 64, 128, 4, 2, act=B.ACT_GELU)
+    lib, P, Q = B.lib(), 0x10000, 0x10008
+
+    def code(n=2, acc=0, **over):
+        ok = {b: P for b in ("offsets", "kept", "x_perm", "saved", "dy_perm", "ws", "dW1", "dW2")}
+        calls = []
+        for i in range(2):
+            v = {**ok, **(over if i == n - 1 else {})}
+            calls.append((ctypes.c_size_t * (len(B.LAYER_BUFS) + 1))(*[v.get(b, 0) for b in B.LAYER_BUFS], v.get("ws_bytes", 1 << 40)))
+        ptrs = (ctypes.c_size_t * 2)(*[ctypes.addressof(c) for c in calls])
+        return lib.moe_layer_expert_dw(ctypes.byref(cfg), ptrs, n, acc, None)
+
+    for b in ("offsets", "kept", "x_perm", "saved", "dy_perm", "ws"):
+        assert code(**{b: 0}) == -1 and code(**{b: Q}) == -5, b
+    assert code(slice_lo=P) == -4 and code(ws_bytes=256) == -7 and code(n=0) == -2
+    assert code(n=1, dW1=0) == -1 and code(n=1, dW2=Q) == -5 and code(n=1, dW1b=P) == -3
+    assert lib.moe_layer_expert_dw(ctypes.byref(cfg), None, 1, 0, None) == -1
+    assert B.moe_layer_bwd_inputs_ws_bytes(cfg) >= B.moe_workspace_bytes(cfg)

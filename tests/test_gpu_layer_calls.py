@@ -81,3 +81,82 @@ def test_layer_calls_of_no_tokens():
     B.moe_layer_bwd(L.cfg, L.bufs(), 1)
     torch.cuda.synchronize()
     assert bool((L.dWr == 3.0).all())
+
+
+@pytest.mark.parametrize("T, d, f, E, k, dtype, act, n", [
+    (40, 64, 192, 6, 1, "bf16", B.ACT_GELU, 9),        # nine calls: eight in one pass and one added; experts without rows in some
+    (300, 320, 576, 3, 2, "f16", B.ACT_SWIGLU, 3),     # whole and ragged stages, tiles past both widths
+    (130, 128, 64, 2, 2, "bf16", B.ACT_SWIGLU, 1),     # every expert has all the rows: two stages and a remainder of two
+    (50, 36, 68, 3, 1, "f32", B.ACT_SWIGLU, 3),
+])
+@pytest.mark.parametrize("acc", [0, 1])
+def test_weight_gradients_over_several_calls(T, d, f, E, k, dtype, act, n, acc):
+    """The sum over the calls of H^T dy and x^T dA, multiplied in fp64 from the stored tensors."""
+    import torch
+    from paper_2504_03871_amd.layer import MoELayer
+    first = filled_layer(T, d, f, E, k, dtype, act, seed=1)
+    calls = [first]
+    for j in range(1, n):
+        m = MoELayer(T, d, f, E, k, dtype=first.cfg.dtype, act=act, params=first, defer_dw=True)
+        gen = torch.Generator(device="cuda:0").manual_seed(j + 5)
+        for t in (m.x, m.d_out):
+            t.copy_(torch.randn(t.shape, generator=gen, device="cuda"))
+        calls.append(m)
+    if n == 9:
+        calls[4].set_slices([0] * E, [0] * E)                                # a call without any rows
+        first.bias = calls[1].bias = torch.arange(E, device="cuda").float() * 3   # most rows on the last experts
+    old = 0.25 if acc else 0.0
+    grads = [g for g in (first.dW1, first.dW1b, first.dW2) if g is not None]
+    for g in grads:
+        g.fill_(0.25 if acc else U.SENTINEL)
+    for j, m in enumerate(calls):
+        m.forward()
+        m.backward_inputs(1 if j > 0 else 0)
+    MoELayer.expert_dw(calls, acc)
+    torch.cuda.synchronize()
+    planes = 2 if act == B.ACT_SWIGLU else 1
+    el = first.x.element_size()
+    want = [torch.full(g.shape, old, dtype=torch.float64, device="cuda") for g in grads]
+    for m in calls:
+        at = B.moe_workspace_bytes(m.cfg) - planes * T * k * f * el          # the standard workspace's last region
+        at = at if planes * T * k * f * el % 256 == 0 else at // 256 * 256
+        da = m.ws[at:at + planes * T * k * f * el].view(m.tdtype).view(planes, T * k, f).double()
+        hid, dy, x = m.saved_plane(planes).double(), m.dy_perm.double(), m.x_perm.double()
+        for e in range(E):
+            o, c = int(m.offsets[e]), int(m.kept[e])
+            lo, hi = (0, c) if m.slice_lo is None else (0, 0)
+            r = slice(o + lo, o + hi)
+            for i in range(planes):
+                want[i][e] += x[r].t() @ da[i][r]
+            want[planes][e] += hid[r].t() @ dy[r]
+    for g, w in zip(grads, want):
+        assert (g.double() - w).norm() <= 1e-5 * w.norm()      # fp32 sums
+
+
+@pytest.mark.parametrize("T, d, f, E, k, dtype, act", [
+    (700, 192, 2112, 4, 2, "bf16", B.ACT_GELU),        # 33 stages in eight parts
+    (700, 192, 1088, 4, 2, "f16", B.ACT_SWIGLU),       # 17 and 17 stages of two products, a part across the seam
+    (450, 320, 2048, 3, 1, "bf16", B.ACT_SWIGLU),
+    (450, 320, 4096, 3, 1, "f16", B.ACT_GELU),         # and 64-row tiles that would be split on their own
+])
+def test_input_gradient_split_along_k(T, d, f, E, k, dtype, act):
+    """dx_perm of the backward that leaves the weight gradients out, its tiles split along K, against the unsplit one."""
+    import torch
+    from paper_2504_03871_amd.layer import MoELayer
+    src = filled_layer(T, d, f, E, k, dtype, act)
+    L = MoELayer(T, d, f, E, k, dtype=src.cfg.dtype, act=act, params=src, defer_dw=True)
+    L.x.copy_(src.x)
+    L.d_out.copy_(src.d_out)
+    L.forward()
+    L.backward()
+    whole = L.dx_perm.double()
+    n_rt, ntn = sum(-(-int(c) // 256) for c in L.kept), -(-d // 256)
+    parts = B.moe_gemm_block_tile(4, 0, n_rt, 0, 0, (2 if act == B.ACT_SWIGLU else 1) * f // 64, ntn)[2]
+    assert parts > 1 and B.moe_layer_bwd_inputs_ws_bytes(L.cfg) > B.moe_workspace_bytes(L.cfg)
+    L.dx_perm.fill_(U.SENTINEL)
+    L.backward_inputs()
+    torch.cuda.synchronize()
+    n = int(L.offsets[E])
+    err = (L.dx_perm.double()[:n] - whole[:n]).norm() / whole[:n].norm()
+    # two results rounded to the storage type once each
+    assert err < {"bf16": 2.0 ** -8, "f16": 2.0 ** -11}[dtype], float(err)
