@@ -12,53 +12,74 @@
 
 namespace moe {
 
-constexpr int DP_THREADS = 256;
+constexpr int DP_THREADS = 1024;
 constexpr int DP_WAVES = DP_THREADS / WAVE;
-constexpr int DP_ROUNDS = DISPATCH_CHUNK / DP_THREADS;   // 4
-constexpr int DP_SUB = DP_ROUNDS * DP_WAVES;             // 16 sub-chunks of 64 assignments, ascending
+constexpr int DP_SUB = DP_WAVES;                         // 16 sub-chunks of 64 assignments, ascending
+static_assert(DP_THREADS == DISPATCH_CHUNK, "one assignment per thread");
 static_assert(MOE_MAX_E == 4 * WAVE, "the rank kernel scans the experts four per lane of one wave");
+
+// The lanes of this wave with the same expert (those with a valid one): one ballot per bit of the id.  `bits`: how many
+// bits the ids below E have.
+__device__ __forceinline__ unsigned long long same_expert(int e, bool valid, int bits) {
+  unsigned long long m = __ballot(valid);
+#pragma unroll
+  for (int b = 0; b < 8; ++b)
+    if (b < bits) {
+      const bool one = (e >> b) & 1;
+      const unsigned long long v = __ballot(one);
+      m &= one ? v : ~v;
+    }
+  return m;
+}
+__device__ __forceinline__ int id_bits(int E) { return 32 - __clz(E - 1); }   // E = 1: 0
+// counts[e] += the number of lanes with expert e: one addition per expert present in the wave
+__device__ __forceinline__ void count_wave(int* counts, int e, bool valid, int bits, int lane) {
+  const unsigned long long m = same_expert(e, valid, bits);
+  if (valid && __popcll(m & ((1ull << lane) - 1ull)) == 0) atomicAdd(&counts[e], __popcll(m));
+}
 
 __global__ __launch_bounds__(DP_THREADS) void dispatch_hist_kernel(const int32_t* __restrict__ topk_idx, int A, int E,
                                                                   int32_t* __restrict__ blk_cnt) {
   __shared__ int s_cnt[MOE_MAX_E];
-  for (int e = threadIdx.x; e < E; e += DP_THREADS) s_cnt[e] = 0;
+  const int a = blockIdx.x * DISPATCH_CHUNK + threadIdx.x, e = a < A ? topk_idx[a] : -1;
+  if (threadIdx.x < MOE_MAX_E) s_cnt[threadIdx.x] = 0;
   __syncthreads();
-  const int base = blockIdx.x * DISPATCH_CHUNK;
-#pragma unroll
-  for (int r = 0; r < DP_ROUNDS; ++r) {
-    const int a = base + r * DP_THREADS + threadIdx.x;
-    if (a < A) {
-      const int e = topk_idx[a];
-      if (e >= 0 && e < E) atomicAdd(&s_cnt[e], 1);   // an id outside [0, E) is a dropped assignment
-    }
-  }
+  count_wave(s_cnt, e, e >= 0 && e < E, id_bits(E), threadIdx.x & (WAVE - 1));   // an id outside [0, E) is a dropped assignment
   __syncthreads();
-  for (int e = threadIdx.x; e < E; e += DP_THREADS) blk_cnt[(size_t)blockIdx.x * E + e] = s_cnt[e];
+  if (threadIdx.x < E) blk_cnt[(size_t)blockIdx.x * E + threadIdx.x] = s_cnt[threadIdx.x];
 }
 
 // Many blocks (more than DP_INLINE_SCAN): the per-block counts are turned into exclusive prefixes over the
 // blocks once, in place, one thread per expert, and row nblk receives the totals; the rank kernel then reads
 // two rows instead of scanning all of them (which would make the work quadratic in the number of blocks).
 constexpr int DP_INLINE_SCAN = 64;
-__global__ __launch_bounds__(DP_THREADS) void dispatch_scan_kernel(int32_t* __restrict__ blk_cnt, int E, int nblk) {
-  const int e = blockIdx.x * DP_THREADS + threadIdx.x;
+constexpr int DP_SCAN_THREADS = 64, DP_SCAN_BATCH = 32;   // counts in flight per thread
+__global__ __launch_bounds__(DP_SCAN_THREADS) void dispatch_scan_kernel(int32_t* __restrict__ blk_cnt, int E, int nblk) {
+  const int e = blockIdx.x * DP_SCAN_THREADS + threadIdx.x;
   if (e >= E) return;
   int run = 0;
-  for (int b = 0; b < nblk; ++b) {
-    const int c = blk_cnt[(size_t)b * E + e];
-    blk_cnt[(size_t)b * E + e] = run;
-    run += c;
+  for (int b0 = 0; b0 < nblk; b0 += DP_SCAN_BATCH) {
+    int c[DP_SCAN_BATCH];
+#pragma unroll
+    for (int u = 0; u < DP_SCAN_BATCH; ++u) c[u] = b0 + u < nblk ? blk_cnt[(size_t)(b0 + u) * E + e] : 0;
+#pragma unroll
+    for (int u = 0; u < DP_SCAN_BATCH; ++u) {
+      if (b0 + u < nblk) blk_cnt[(size_t)(b0 + u) * E + e] = run;
+      run += c[u];
+    }
   }
   blk_cnt[(size_t)nblk * E + e] = run;
 }
 
 // Where the rank kernel finds the assignments of the other blocks: counts per block (dispatch_hist_kernel), exclusive
 // prefixes and a row of totals (dispatch_scan_kernel), or, up to DP_SELF blocks, nowhere: it counts their ids itself.
-// A short list is bound by its launches, not by its bytes.  Histogram and ranks in two launches -> ids counted here, us
-// per call, even ids | all ids on one expert (whose LDS additions run one after the other): 1024 assignments, E = 8
-// 11.6 -> 8.9 | 11.4 -> 8.8; 4096, E = 8 11.6 -> 9.1 | 11.5 -> 8.6, E = 16 14.9 -> 12.7 | 11.6 -> 8.6, E = 64 12.5 -> 10.7 | 14.4 ->
-// 13.9, E = 256 12.8 -> 10.7 | 14.7 -> 13.7.  A block's additions grow with the list, the launch they save does not: at 8000
-// (E = 16) the gain on even ids is down to 0.9.
+// A short list is bound by its launches, not by its bytes: 4096 assignments take 4.3 us with the ids counted here (256 experts
+// 6.0), 4097 with a histogram 5.9 (7.4); a block's counting grows by 0.3 (0.5) us per 1024, the launch it saves does not.
+// One thread per assignment and one ballot per bit of the expert id.  Four assignments per thread and a pass of ballots per
+// distinct expert (16 and fewer) or 64 comparisons before, us per call of index work, even ids | all on one expert:
+// 1024 assignments, 8 experts 8.7 -> 3.3 | 5.4 -> 3.1, 16 experts 12.4 -> 3.3 | 5.4 -> 3.2, 256 experts 10.5 -> 4.1 | 11.6 -> 3.9; 16384,
+// 8 experts 11.1 -> 6.0 | 8.1 -> 5.8; 65536, 256 experts 18.7 -> 9.3; 262144, 16 experts 56.7 -> 18.7 (the scan over blocks had
+// one count in flight per thread).
 enum RankFrom { FROM_COUNTS, FROM_PREFIXES, FROM_IDS };
 constexpr int DP_SELF = 4;
 
@@ -74,38 +95,28 @@ __global__ __launch_bounds__(DP_THREADS) void dispatch_rank_kernel(
   const int tid = threadIdx.x, lane = tid & (WAVE - 1), wave = tid / WAVE;
 
   // this block's assignments: loaded first, so that their latency runs beside the scan over blocks
-  const int base = blockIdx.x * DISPATCH_CHUNK;
-  int my_e[DP_ROUNDS], my_rank[DP_ROUNDS];
+  const int a = blockIdx.x * DISPATCH_CHUNK + tid, bits = id_bits(E);
+  int my_e = a < A ? topk_idx[a] : -1;
+  int id[FROM == FROM_IDS ? DP_SELF : 1];   // the other blocks' ids, all loads in flight together
+  if constexpr (FROM == FROM_IDS) {
 #pragma unroll
-  for (int r = 0; r < DP_ROUNDS; ++r) {
-    const int a = base + r * DP_THREADS + tid;
-    int e = (a < A) ? topk_idx[a] : -1;
-    if (e < 0 || e >= E) e = -1;        // past the end, or an id outside [0, E): dropped, never an index
-    my_e[r] = e;
+    for (int b = 0; b < DP_SELF; ++b) {
+      const int o = b * DISPATCH_CHUNK + tid;
+      id[b] = (b != (int)blockIdx.x && o < A) ? topk_idx[o] : -1;
+    }
   }
+  const bool valid = my_e >= 0 && my_e < E;   // past the end, or an id outside [0, E): dropped, never an index
 
   // the other blocks: s_before = assignments of e in earlier blocks, s_kept = all of them for now
-  for (int e = tid; e < MOE_MAX_E; e += DP_THREADS) { s_before[e] = 0; s_kept[e] = 0; }
-  for (int sc = 0; sc < DP_SUB; ++sc)
-    for (int e = tid; e < E; e += DP_THREADS) s_sub[sc][e] = 0;
+  if (tid < MOE_MAX_E) { s_before[tid] = 0; s_kept[tid] = 0; }
+  for (int i = tid; i < DP_SUB * E; i += DP_THREADS) s_sub[i / E][i % E] = 0;
   __syncthreads();
   if constexpr (FROM == FROM_IDS) {
     // s_before = assignments in earlier blocks, s_kept = those in later ones; the block's own are added below
-    int id[DP_SELF][DP_ROUNDS];   // all loads in flight together
 #pragma unroll
     for (int b = 0; b < DP_SELF; ++b)
-#pragma unroll
-      for (int r = 0; r < DP_ROUNDS; ++r) {
-        const int a = b * DISPATCH_CHUNK + r * DP_THREADS + tid;
-        id[b][r] = (b != (int)blockIdx.x && a < A) ? topk_idx[a] : -1;
-      }
-#pragma unroll
-    for (int b = 0; b < DP_SELF; ++b)
-#pragma unroll
-      for (int r = 0; r < DP_ROUNDS; ++r) {
-        const int e = id[b][r];
-        if (e >= 0 && e < E) atomicAdd(b < (int)blockIdx.x ? &s_before[e] : &s_kept[e], 1);
-      }
+      if (b != (int)blockIdx.x && b * DISPATCH_CHUNK < A)
+        count_wave(b < (int)blockIdx.x ? s_before : s_kept, id[b], id[b] >= 0 && id[b] < E, bits, lane);
   } else if constexpr (FROM == FROM_PREFIXES) {
     for (int e = tid; e < E; e += DP_THREADS)
       if (nblk > 0) { s_before[e] = blk_cnt[(size_t)blockIdx.x * E + e]; s_kept[e] = blk_cnt[(size_t)nblk * E + e]; }
@@ -142,41 +153,18 @@ __global__ __launch_bounds__(DP_THREADS) void dispatch_rank_kernel(
     if (tot != 0) atomicAdd(&s_kept[cur], tot);
     if (bef != 0) atomicAdd(&s_before[cur], bef);
   }
-#pragma unroll
-  for (int r = 0; r < DP_ROUNDS; ++r) {
-    const int e = my_e[r];
-    const bool valid = e >= 0;
-    // rank among the lanes of this wave with the same expert, and the number of such lanes
-    int rank = 0;
-    if (E <= 16) {   // few experts: one pass of ballots per distinct expert present
-      unsigned long long todo = __ballot(valid);
-      while (todo) {
-        const int leader = __ffsll((long long)todo) - 1;
-        const int e0 = __shfl(e, leader, WAVE);
-        const unsigned long long same = __ballot(valid && e == e0);
-        if (valid && e == e0) {
-          rank = __popcll(same & ((1ull << lane) - 1ull));
-          if (rank == 0) s_sub[r * DP_WAVES + wave][e0] = __popcll(same);   // one writer per (sub-chunk, expert)
-        }
-        todo &= ~same;
-      }
-    } else {         // many experts, up to 64 distinct ones in the wave: compare with every lane in turn
-      int cnt = 0;
-#pragma unroll
-      for (int l = 0; l < WAVE; ++l) {
-        const bool same = __builtin_amdgcn_readlane(e, l) == e;
-        cnt += same;
-        rank += same && l < lane;
-      }
-      if (valid && rank == 0) s_sub[r * DP_WAVES + wave][e] = cnt;
-    }
-    my_rank[r] = rank;
-  }
+  // rank among the lanes of this wave with the same expert, and the number of such lanes: one writer per (sub-chunk, expert)
+  const unsigned long long same = same_expert(my_e, valid, bits);
+  const int my_rank = __popcll(same & ((1ull << lane) - 1ull));
+  if (valid && my_rank == 0) s_sub[wave][my_e] = __popcll(same);
   __syncthreads();
-  for (int e = tid; e < E; e += DP_THREADS) {
-    int run = s_before[e];
-    for (int sc = 0; sc < DP_SUB; ++sc) { const int c = s_sub[sc][e]; s_sub[sc][e] = run; run += c; }
-    if constexpr (FROM == FROM_IDS) s_kept[e] += run;   // earlier, own and later blocks
+  if (tid < E) {
+    int c[DP_SUB], run = s_before[tid];
+#pragma unroll
+    for (int sc = 0; sc < DP_SUB; ++sc) c[sc] = s_sub[sc][tid];
+#pragma unroll
+    for (int sc = 0; sc < DP_SUB; ++sc) { s_sub[sc][tid] = run; run += c[sc]; }
+    if constexpr (FROM == FROM_IDS) s_kept[tid] += run;   // earlier, own and later blocks
   }
   __syncthreads();
   // kept counts and their exclusive scan over the experts: the first wave, four experts per lane
@@ -206,20 +194,14 @@ __global__ __launch_bounds__(DP_THREADS) void dispatch_rank_kernel(
   if (blockIdx.x == 0)
     for (int e = tid; e <= E; e += DP_THREADS) offsets[e] = s_off[e];
 
-  const int R = s_off[E];
-#pragma unroll
-  for (int r = 0; r < DP_ROUNDS; ++r) {
-    const int a = base + r * DP_THREADS + tid;
-    if (a >= A) continue;
-    const int e = my_e[r];
-    int row = -1;
-    if (e >= 0) {
-      const int rank = s_sub[r * DP_WAVES + wave][e] + my_rank[r];
-      if (rank < s_kept[e]) { row = s_off[e] + rank; src_of[row] = a; }
-    }
-    row_of[a] = row;
-    if (a >= R) src_of[a] = -1;   // rows past the end of the kept lists
+  if (a >= A) return;
+  int row = -1;
+  if (valid) {
+    const int rank = s_sub[wave][my_e] + my_rank;
+    if (rank < s_kept[my_e]) { row = s_off[my_e] + rank; src_of[row] = a; }
   }
+  row_of[a] = row;
+  if (a >= s_off[E]) src_of[a] = -1;   // rows past the end of the kept lists
 }
 
 // x_perm[row_of[t*k+j]] = x[t] for the slots that are kept and inside this GPU's shares.  Token-major: a wave
@@ -318,7 +300,7 @@ int launch_dispatch(const moe_cfg* c, const void* x, const int32_t* idx, const i
   }
   // with no assignments one block still writes the (all-zero) counts, kept and offsets
   if (nblk > DP_INLINE_SCAN) {
-    dispatch_scan_kernel<<<(c->E + DP_THREADS - 1) / DP_THREADS, DP_THREADS, 0, s>>>(blk_cnt, c->E, nblk);
+    dispatch_scan_kernel<<<(c->E + DP_SCAN_THREADS - 1) / DP_SCAN_THREADS, DP_SCAN_THREADS, 0, s>>>(blk_cnt, c->E, nblk);
     rc = launch_status();
     if (rc != MOE_OK) return rc;
     dispatch_rank_kernel<FROM_PREFIXES><<<nblk, DP_THREADS, 0, s>>>(idx, blk_cnt, A, c->E, c->capacity, nblk, counts, kept, offsets, row_of, src_of);
