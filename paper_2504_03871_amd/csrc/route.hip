@@ -9,7 +9,7 @@
 
 namespace moe {
 
-// Forward kernel for fp32 inputs and for routing from given logits.  A block of 256 threads owns TOK tokens.  Thread (token, k part, expert group) keeps
+// Forward kernel for fp32 inputs with more than 32 experts and for routing from given logits.  A block of 256 threads owns TOK tokens.  Thread (token, k part, expert group) keeps
 // the dot products of its token with four experts over its share of every d chunk, so x Wr needs no
 // cross-lane reduction beyond adding the k parts (adjacent lanes) at the end.  x chunks [TOK][DC] and
 // Wr chunks [DC][E4] are staged through LDS (coalesced global loads, prefetched into registers one
@@ -403,6 +403,103 @@ __global__ __launch_bounds__(NW * 64) void route_mfma_kernel(
   route_select(part, LD, tl, tid & 7, 8, tl < ntok, tok0 + tl, E, k, topk_idx, topk_w);
 }
 
+// ---------------------------------------------------------------- forward of few tokens, on the matrix cores
+// The same product for batches that do not fill the chip with 32 or 64 tokens per block: 16 tokens per block, all of its
+// waves along K (16-bit: blocks of 128 values, fp32: of 64), so that a wave's share of a row is one or two blocks whose loads
+// are in flight together.  The gate weight is read where it lies: its layout pass would be a launch as long as this one.
+// fp32 storage multiplies on v_mfma_f32_16x16x4_f32 (fp32 products and sums).  Bound by one round trip to memory for x and Wr,
+// the reduction over the waves and the selection.
+// Lane (row or expert r = l % 16, quarter c = l / 16) supplies the K values k0 .. k0 + KB / 4 - 1 of its row or expert, k0 = kb KB + c KB / 4,
+// a 16-byte piece of x at a time.
+template <typename T> struct SmallGate { static constexpr int KB = 128, PIECE = 8; };
+template <> struct SmallGate<float> { static constexpr int KB = 64, PIECE = 4; };
+
+template <typename T, int NET, int NW>
+__global__ __launch_bounds__(NW * 64) void route_small_kernel(
+    const T* __restrict__ x, const float* __restrict__ Wr, const float* __restrict__ bias,
+    float* __restrict__ logits_out, int32_t* __restrict__ topk_idx, float* __restrict__ topk_w, int Tn, int d, int E, int k) {
+  extern __shared__ float part[];   // [NW waves][16 tokens][LD]; the sum ends up in part[0]
+  constexpr int TOK = 16, LD = NET * 16, KB = SmallGate<T>::KB, P = SmallGate<T>::PIECE;
+  static_assert(KB == 16 * P, "four pieces per lane");
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), r = lane & 15, c = lane >> 4;
+  const int tok0 = blockIdx.x * TOK, nkb = (d + KB - 1) / KB;
+  const T* xrow = x + (size_t)min(tok0 + r, Tn - 1) * d + c * (KB / 4);   // rows past the batch repeat the last token
+  rt_f32x4 acc[NET];
+#pragma unroll
+  for (int nt = 0; nt < NET; ++nt) acc[nt] = rt_f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int kb = wave; kb < nkb; kb += NW) {
+    const int k0 = kb * KB + c * (KB / 4);
+    const float* wk = Wr + (size_t)kb * KB * E;
+    uint4 raw[4];
+    float w[NET][4][P];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {   // d is a multiple of the piece (fp32) or of two quarters (16-bit): a piece is inside the row or past it
+      raw[s] = uint4{0u, 0u, 0u, 0u};
+#pragma unroll
+      for (int nt = 0; nt < NET; ++nt)
+#pragma unroll
+        for (int i = 0; i < P; ++i) w[nt][s][i] = 0.f;
+      if (k0 + s * P < d) {
+        raw[s] = *reinterpret_cast<const uint4*>(xrow + (size_t)kb * KB + s * P);
+#pragma unroll
+        for (int nt = 0; nt < NET; ++nt) {   // experts from E on: sums that nothing reads
+          const unsigned off = (unsigned)(c * (KB / 4) * E + min(nt * 16 + r, E - 1));
+#pragma unroll
+          for (int i = 0; i < P; ++i) w[nt][s][i] = wk[off + (unsigned)(s * P + i) * (unsigned)E];
+        }
+      }
+    }
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      if constexpr (std::is_same<T, float>::value) {
+        const float xv[4] = {__uint_as_float(raw[s].x), __uint_as_float(raw[s].y), __uint_as_float(raw[s].z), __uint_as_float(raw[s].w)};
+#pragma unroll
+        for (int i = 0; i < P; ++i)
+#pragma unroll
+          for (int nt = 0; nt < NET; ++nt) acc[nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(xv[i], w[nt][s][i], acc[nt], 0, 0, 0);
+      } else {
+        constexpr int XT = XTerms<T>::N;
+        rt_bf16x8 t[XT];
+        XTerms<T>::split(raw[s], t);
+#pragma unroll
+        for (int nt = 0; nt < NET; ++nt) {
+          rt_bf16x8 hi, lo;   // the two bf16 terms of the weight
+#pragma unroll
+          for (int i = 0; i < P; ++i) {
+            hi[i] = (bf16)w[nt][s][i];
+            lo[i] = (bf16)(w[nt][s][i] - (float)hi[i]);
+          }
+#pragma unroll
+          for (int xt = 0; xt < XT; ++xt) {
+            acc[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(t[xt], hi, acc[nt], 0, 0, 0);
+            acc[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(t[xt], lo, acc[nt], 0, 0, 0);
+          }
+        }
+      }
+    }
+  }
+  // accumulator register v of lane l is token (l/16)*4 + v, expert l%16 of its tile
+  float* mine = part + (size_t)wave * TOK * LD;
+#pragma unroll
+  for (int nt = 0; nt < NET; ++nt)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) mine[(c * 4 + v) * LD + nt * 16 + r] = acc[nt][v];
+  __syncthreads();
+  const int ntok = min(TOK, Tn - tok0);
+  for (int i = tid; i < TOK * LD; i += NW * 64) {
+    const int e = i % LD, tl = i / LD;
+    float sum = part[i];
+#pragma unroll
+    for (int q = 1; q < NW; ++q) sum += part[q * TOK * LD + i];   // wave order: deterministic
+    sum += (bias != nullptr && e < E) ? bias[e] : 0.f;
+    part[i] = sum;
+    if (tl < ntok && e < E) logits_out[(size_t)(tok0 + tl) * E + e] = sum;
+  }
+  __syncthreads();
+  if (wave >= TOK * 8 / 64) return;   // eight lanes per token: whole waves
+  route_select(part, LD, tid >> 3, tid & 7, 8, (tid >> 3) < ntok, tok0 + (tid >> 3), E, k, topk_idx, topk_w);
+}
+
 // ---------------------------------------------------------------- backward
 // Four small kernels.
 //  1. WrT[e][i] = Wr[i][e], so that the input-gradient kernel reads contiguous weights (not for few, short rows).
@@ -673,8 +770,34 @@ static int route_mfma_typed(const moe_cfg* c, const void* x, const float* Wr, co
   }
 }
 
+// Where route_small_kernel is used: up to 32 experts; 16-bit storage up to 4096 tokens (one round of blocks; with a second
+// one the weight's conversion in every block costs more than the layout pass), fp32 for any number.  us per call, before ->
+// now, at 1024 | 4096 | 8192 tokens (forced above the line): bf16, 8 experts, d 1024 9.2 -> 5.0 | 9.1 -> 5.2 | 9.5 -> 7.7, d 2048 14.9 -> 7.3 | 14.8 ->
+// 8.9 | 15.6 -> 16.0, d 4096 23.8 -> 10.6 | 24.2 -> 12.9 | 24.5 -> 25.4; fp16, 16 experts, d 2048 19.3 -> 8.3 | 19.5 -> 10.1 |
+// 20.8 -> 18.2; bf16, 32 experts, d 512 10.3 -> 6.6 | 10.4 -> 7.0 | 10.4 -> 12.6; fp32, 8 experts, d 128 6.3 -> 3.8 | 6.4 -> 3.9 | 6.4 -> 4.5,
+// d 1024 18.3 -> 6.0 | 20.0 -> 6.8 | 20.5 -> 10.8, 32 experts, d 1024 35.4 -> 9.5 | 41.5 -> 10.9 | 41.8 -> 19.9.
+static bool route_small_applies(const moe_cfg* c) { return c->E <= 32 && (c->dtype == MOE_DTYPE_F32 || c->T <= 4096); }
+template <typename T, int NET, int NW>
+static void launch_route_small(const moe_cfg* c, const void* x, const float* Wr, const float* bias, float* logits_out, int32_t* idx, float* w, hipStream_t s) {
+  route_small_kernel<T, NET, NW><<<(c->T + 15) / 16, NW * 64, (size_t)NW * 16 * NET * 16 * 4, s>>>((const T*)x, Wr, bias, logits_out, idx, w, c->T,
+                                                                                                   c->d_model, c->E, c->k);
+}
+template <typename T>
+static int route_small_typed(const moe_cfg* c, const void* x, const float* Wr, const float* bias, float* logits_out, int32_t* idx, float* w, hipStream_t s) {
+  const bool wide = c->d_model > 8 * SmallGate<T>::KB;   // sixteen waves find something to do
+  if (c->E <= 16 && wide) launch_route_small<T, 1, 16>(c, x, Wr, bias, logits_out, idx, w, s);
+  else if (c->E <= 16) launch_route_small<T, 1, 8>(c, x, Wr, bias, logits_out, idx, w, s);
+  else if (wide && std::is_same<T, float>::value) launch_route_small<float, 2, 16>(c, x, Wr, bias, logits_out, idx, w, s);
+  else launch_route_small<T, 2, 8>(c, x, Wr, bias, logits_out, idx, w, s);   // 16-bit: two expert tiles' operands take more than 128 registers
+  return launch_status();
+}
+
 int launch_route(const moe_cfg* c, const void* x, const float* Wr, const float* bias, const float* logits_in,
                  float* logits_out, int32_t* idx, float* w, void* wfrag, hipStream_t s) {
+  if (logits_in == nullptr && route_small_applies(c))
+    return c->dtype == MOE_DTYPE_BF16  ? route_small_typed<bf16>(c, x, Wr, bias, logits_out, idx, w, s)
+           : c->dtype == MOE_DTYPE_F16 ? route_small_typed<f16>(c, x, Wr, bias, logits_out, idx, w, s)
+                                       : route_small_typed<float>(c, x, Wr, bias, logits_out, idx, w, s);
   if ((c->dtype == MOE_DTYPE_BF16 || c->dtype == MOE_DTYPE_F16) && logits_in == nullptr)
     return c->dtype == MOE_DTYPE_BF16 ? route_mfma_typed<bf16>(c, x, Wr, bias, logits_out, idx, w, wfrag, s)
                                       : route_mfma_typed<f16>(c, x, Wr, bias, logits_out, idx, w, wfrag, s);

@@ -207,3 +207,35 @@ def test_gate_backward_of_short_inputs(T, d, E, k, dtype):
     from tests.test_gpu_parity import run_case
     base = S.WORKLOADS["cfg0" if dtype == "DT_F32" else "cfg1"]
     run_case(base.scaled(T=T, d=d, f=128, E=E, k=k, dtype=getattr(S, dtype)))
+
+
+@pytest.mark.parametrize("T, d, E, k, dtype", [
+    (1, 64, 1, 1, "DT_BF16"), (17, 192, 16, 3, "DT_F16"),           # one token; one past a block, half a K block at the end
+    (48, 2112, 17, 2, "DT_BF16"), (31, 1088, 32, 4, "DT_F16"),      # two expert tiles; one wave with a second K block
+    (15, 1152, 9, 2, "DT_BF16"),                                    # sixteen waves, nine of them busy
+    (33, 36, 5, 3, "DT_F32"), (16, 516, 32, 2, "DT_F32"),           # fp32: a row that ends inside a quarter
+    (100, 4, 16, 2, "DT_F32"), (40, 1100, 20, 2, "DT_F32"),
+    (4096, 64, 8, 2, "DT_BF16"), (4097, 64, 8, 2, "DT_BF16"),       # both sides of the line
+    (64, 128, 33, 2, "DT_F32"),                                     # more than 32 experts
+])
+def test_gate_of_few_tokens(T, d, E, k, dtype):
+    from paper_2504_03871_amd import synth as S
+    from tests.test_gpu_parity import run_case
+    base = S.WORKLOADS["cfg0" if dtype == "DT_F32" else "cfg1"]
+    run_case(base.scaled(T=T, d=d, f=64, E=E, k=k, dtype=getattr(S, dtype)))
+
+
+@pytest.mark.parametrize("A, E", [(65 * 1024, 5), (97 * 1024 + 3, 256), (200000, 100)])
+def test_dispatch_with_scanned_prefixes(A, E):
+    """More than 64 blocks: whole and ragged batches of the scan, more experts than one of its blocks has threads.  Exact."""
+    import numpy as np
+    import torch
+    from tests import gpu_util as U
+    idx = np.random.default_rng(E).integers(-1, E + 1, size=(A, 1)).astype(np.int32)
+    cfg = B.make_cfg(A, 64, 64, E, 1, capacity=A // E)
+    out = [torch.full((n,), -7, dtype=torch.int32, device="cuda") for n in (E, E, E + 1, A, A)]
+    ws = torch.empty(B.moe_workspace_bytes(cfg), dtype=torch.uint8, device="cuda")
+    B.moe_dispatch(cfg, None, torch.from_numpy(idx).cuda(), None, None, *out, None, ws)
+    torch.cuda.synchronize()
+    for name, got, want in zip(("counts", "kept", "offsets", "row_of", "src_of"), out, U.O.dispatch_plan(idx, E, A // E)):
+        assert (got.cpu().numpy() == want).all(), name
