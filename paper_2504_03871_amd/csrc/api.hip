@@ -27,6 +27,12 @@ int check_cfg(const moe_cfg* c) {
   return MOE_OK;
 }
 
+static int tile_rows_for(const moe_cfg* c) {   // both row-tile GEMMs of a pass share one map: the wider decides
+  if (is_half(c)) return mid_applies((long long)c->T * c->k, c->E) ? MID_ROWS : gemm_bf16_tile_rows();
+  return f32_tile_rows((long long)c->T * c->k, c->E / 2, std::max(c->d_model, c->d_ff));
+}
+// The smallest row tiles of a 16-bit GEMM with K = d_ff are split along K (gemm.h): 256-row tiles only
+static bool splits_small_tiles(const moe_cfg* c) { return is_half(c) && tile_rows_for(c) != MID_ROWS && split_k_applies(c->E, c->d_ff); }
 // backward: a row-tile GEMM of N columns with at most about eight rounds of tiles shares its launch (moe_expert_ffn_bwd)
 static bool shares_launch(const moe_cfg* c, int N, int max_tiles) {
   const int cols = is_half(c) ? gemm_bf16_tile_rows() : F32_TILE_COLS;
@@ -54,8 +60,8 @@ WsLayout ws_layout(const moe_cfg* c) {
   const size_t dact = align_up((c->act == MOE_ACT_SWIGLU ? 2 : 1) * A * c->d_ff * elt_size(c), 256);
   size_t fwd = 0, bwd = 0;
   if (is_half(c) && c->d_ff >= SPLIT_MIN_K) {
-    const int max_tiles = max_row_tiles((int)A, c->E, gemm_bf16_tile_rows());
-    const bool skinny = skinny_applies(A, c->E), small = split_k_applies(c->E, c->d_ff);
+    const int max_tiles = max_row_tiles((int)A, c->E, tile_rows_for(c));
+    const bool skinny = skinny_applies(A, c->E), small = splits_small_tiles(c);
     const size_t rows = split_ws_bytes(c->E, c->d_model), tail = tail_ws_bytes(max_tiles, c->d_model);
     fwd = skinny ? (skinny_split(c->E, c->d_ff) ? rows : 0) : std::max(small ? rows : 0, tail);
     if (c->act == MOE_ACT_GELU) bwd = std::max(small ? rows : 0, shares_launch(c, c->d_model, max_tiles) ? 0 : tail);
@@ -167,9 +173,6 @@ static int check_slices(const int32_t* lo, const int32_t* hi) {
   return ((lo == nullptr) != (hi == nullptr)) ? MOE_ERR_BAD_SLICE : MOE_OK;
 }
 
-static int tile_rows_for(const moe_cfg* c) {   // both row-tile GEMMs of a pass share one map: the wider decides
-  return is_half(c) ? gemm_bf16_tile_rows() : f32_tile_rows((long long)c->T * c->k, c->E / 2, std::max(c->d_model, c->d_ff));
-}
 static int launch_gemm(const moe_cfg* c, int mode, int epi, bool dual, bool chain, const GemmArgs& g, int max_tiles,
                        hipStream_t s) {
   return is_half(c) ? launch_gemm_half(c->dtype, mode, epi, dual, chain, g, max_tiles, s)
@@ -363,7 +366,7 @@ TileMapArgs tile_map_args(const moe_cfg* cfg, const int32_t* offsets, const int3
   TileMapArgs t = {offsets, kept, lo, hi, cfg->E};
   const bool skinny = forward && fwd_skinny(cfg);
   t.tile_rows = skinny ? SKINNY_ROWS : tile_rows_for(cfg);
-  t.by_expert = skinny;
+  t.by_expert = skinny || (is_half(cfg) && t.tile_rows == MID_ROWS);
   t.table = cfg->act != MOE_ACT_GELU || cfg->dtype != MOE_DTYPE_BF16 ? GELU_TAB_NONE : forward ? GELU_TAB_PHI : GELU_TAB_GRAD;
   t.map = tile_map_at(static_cast<char*>(ws) + ws_layout(cfg).tile_map, max_row_tiles(cfg->T * cfg->k, cfg->E, TILE_ROWS_MIN), cfg->E);
   return t;
@@ -384,7 +387,7 @@ int ffn_fwd_impl(const moe_cfg* cfg, const void* x_perm, const void* W1, const v
   const size_t plane = (size_t)A * f * elt_size(cfg);
   char* sv = static_cast<char*>(saved);
   GemmArgs g = {};
-  g.tiles = map.tiles; g.ntiles = map.header; g.order = map.order; g.gelu_tab = map.gelu_tab;
+  g.tiles = map.tiles; g.ntiles = map.header; g.order = map.order; g.gelu_tab = map.gelu_tab; g.tile_rows = tr;
   g.offsets = offsets; g.kept = kept; g.lo = slice_lo; g.hi = slice_hi; g.E = cfg->E;
   // hidden = act(x_perm W1)
   g.A = x_perm; g.B = W1; g.B2 = W1b; g.N = f; g.K = d;
@@ -407,9 +410,9 @@ int ffn_fwd_impl(const moe_cfg* cfg, const void* x_perm, const void* W1, const v
   g.chunked = row_tiles_chunked(A, f, d, cfg->E, 1, (int)elt_size(cfg));
   g.C = y_perm; g.C2 = g.C3 = nullptr;
   g.split_all = skinny && skinny_split(cfg->E, f);
-  g.split_small = is_half(cfg) && !skinny && split_k_applies(cfg->E, f);   // split-K: smallest row tiles, last round (gemm.h)
+  g.split_small = !skinny && splits_small_tiles(cfg);   // split-K: smallest row tiles, last round (gemm.h)
   const bool exact = cfg->capacity == 0 && slice_lo == nullptr;
-  g.split_tail = is_half(cfg) && !skinny && tail_may_split(A, cfg->E, exact, (d + tr - 1) / tr, f);
+  g.split_tail = is_half(cfg) && !skinny && tail_may_split(A, cfg->E, exact, (d + 255) / 256, f, tr);
   if (g.split_all || g.split_small || g.split_tail) g.split_ws = reinterpret_cast<float*>(static_cast<char*>(ws) + w.ffn_split);
   ProfScope ps(cfg, MOE_PROF_GEMM2_FWD, s);
   if (skinny) return launch_gemm_half_skinny(cfg->dtype, EPI_STORE, false, g, max_tiles, s);
@@ -516,7 +519,7 @@ int ffn_bwd_impl(const moe_cfg* cfg, const void* dy_perm, const void* x_perm, co
   char* dact = static_cast<char*>(ws) + w.ffn_bwd_dact;
   const void* hidden = swiglu ? sv + 2 * plane : sv + plane;
   GemmArgs g = {};
-  g.tiles = map.tiles; g.ntiles = map.header; g.order = map.order; g.gelu_tab = map.gelu_tab;
+  g.tiles = map.tiles; g.ntiles = map.header; g.order = map.order; g.gelu_tab = map.gelu_tab; g.tile_rows = tr;
   g.offsets = offsets; g.kept = kept; g.lo = slice_lo; g.hi = slice_hi; g.E = cfg->E;
   g.accumulate = accumulate;
   // Four GEMMs: dH = dy W2^T fused with the activation derivative -> dA (GELU) or dG, dU (SwiGLU);
@@ -556,8 +559,8 @@ int ffn_bwd_impl(const moe_cfg* cfg, const void* dy_perm, const void* x_perm, co
   ProfScope ps(cfg, MOE_PROF_DX_BWD, s);
   // split-K of the GELU dx: the smallest row tiles; the last round only in a launch of its own (in a shared one the
   // weight-gradient tiles fill it), for SwiGLU where the caller gives room for the partial sums
-  const bool may_split = !pair_x && tail_may_split(A, cfg->E, cfg->capacity == 0 && slice_lo == nullptr, (d + tr - 1) / tr, swiglu ? 2 * f : f);
-  gx.split_small = bf && !swiglu && split_k_applies(cfg->E, f);
+  const bool may_split = !pair_x && tail_may_split(A, cfg->E, cfg->capacity == 0 && slice_lo == nullptr, (d + 255) / 256, swiglu ? 2 * f : f, tr);
+  gx.split_small = !swiglu && splits_small_tiles(cfg);
   gx.split_tail = bf && may_split && (dx_sums != nullptr || (!swiglu && !shares_launch(cfg, d, max_tiles)));
   if (gx.split_small || gx.split_tail) gx.split_ws = dx_sums != nullptr ? dx_sums : reinterpret_cast<float*>(static_cast<char*>(ws) + w.ffn_split);
   if (pair_x) return launch_pair(cfg, EPI_STORE, swiglu, gx, max_tiles, gw1, s);
@@ -612,8 +615,8 @@ namespace {
 // chip has nothing else to do beside dx's last round then
 size_t inputs_split_bytes(const moe_cfg* c) {
   if (!is_half(c) || (c->act == MOE_ACT_SWIGLU ? 2 : 1) * c->d_ff < SPLIT_MIN_K) return 0;
-  const bool small = c->act == MOE_ACT_GELU && split_k_applies(c->E, c->d_ff);
-  return align_up(std::max(small ? split_ws_bytes(c->E, c->d_model) : 0, tail_ws_bytes(max_row_tiles(c->T * c->k, c->E, gemm_bf16_tile_rows()), c->d_model)), 256);
+  const bool small = c->act == MOE_ACT_GELU && splits_small_tiles(c);
+  return align_up(std::max(small ? split_ws_bytes(c->E, c->d_model) : 0, tail_ws_bytes(max_row_tiles(c->T * c->k, c->E, tile_rows_for(c)), c->d_model)), 256);
 }
 // Arguments of the calls that a whole-layer call stands for, checked before anything is launched
 int check_layer(const moe_cfg* cfg, const moe_layer_bufs* b, bool combine, bool backward, bool dw = true) {

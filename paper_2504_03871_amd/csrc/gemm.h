@@ -189,7 +189,7 @@ MOE_HD inline bool skinny_block(int vb, const SkinnyOrder& o, int ntn, RowBlock&
 
 // Split-K of the last round.  256 blocks run at a time; the tiles behind the last whole round of 256 (all of them, when
 // there are fewer) leave most of the chip idle for the length of one tile.  In the plain-store GEMMs with long K these
-// r tiles are cut along K into `parts` blocks each, at most 256 in all, whose fp32 partial sums [slot][256][256] go to
+// r tiles are cut along K into `parts` blocks each, at most 256 in all, whose fp32 partial sums [slot][rows of a tile][256] go to
 // the workspace; split_reduce adds them in part order.  A round costs about 26 us per 1024 K values, a slot about
 // 0.1 us (256 KB written and read again); the parts minimise the sum of the two, and a gain below 2 us, the model's
 // error, is left.  The reduction is a launch of its own, and the GEMM alone knows how many tiles there are: it is paid
@@ -212,14 +212,14 @@ MOE_HD inline TailSplit tail_split(int n_tiles, int K) {
 }
 // (host) whether any number of row tiles that `rows` rows of E experts can have is split; exact: all of them are computed
 // (no capacity, no slices), else there may be any number of tiles.
-inline bool tail_may_split(int rows, int E, bool exact, int ntn, int K) {
+inline bool tail_may_split(int rows, int E, bool exact, int ntn, int K, int tile_rows = 256) {
   if (K < SPLIT_MIN_K) return false;
   if (!exact) return true;
-  for (int n = (rows + 255) / 256; n <= rows / 256 + E && n <= rows; ++n)
+  for (int n = (rows + tile_rows - 1) / tile_rows; n <= rows / tile_rows + E && n <= rows; ++n)
     if (tail_split(n * ntn, K).parts > 1) return true;
   return false;
 }
-inline size_t tail_ws_bytes(int max_tiles, int N) {   // 256 x 256 tiles
+inline size_t tail_ws_bytes(int max_tiles, int N) {   // room for slots of 256 x 256; lower tiles pack theirs
   const long long slots = (long long)max_tiles * ((N + 255) / 256) * TAIL_MAX_PARTS;
   return (size_t)(slots < TAIL_SLOTS ? slots : TAIL_SLOTS) * 256 * 256 * 4;
 }
@@ -294,6 +294,7 @@ struct GemmArgs {
   int E;
   int accumulate;
   int chunked;   // row-tile GEMMs: order of the full tiles (block_to_tile)
+  int tile_rows; // row-tile GEMMs: rows per entry of the tile map
 };
 
 struct TileMapArgs;   // tile_map.h
@@ -315,39 +316,53 @@ int launch_gemm_half(int dtype, int mode, int epi, bool dual, bool chain, const 
 // one launch for an NT GEMM (epilogue epi1, chained or not) followed by a TN weight-gradient GEMM
 int launch_gemm_half_pair(int dtype, int epi1, bool chain1, const GemmArgs& g1, int max_tiles, const GemmArgs& g2, hipStream_t s);
 int gemm_bf16_tile_rows();
+// Height of the 16-bit row tiles.  256 rows (two stages of operands in LDS) move the fewest bytes per product; 160 rows
+// leave room for a third stage, so loads may take one iteration longer, and fill the chip more evenly where an expert has
+// few tiles.  The line is on the average rows per expert: skew only favours the low tiles.  256 -> 160 rows:
+//   up to 128 rows, 8 to 128 experts, even and skewed load: forward x0.75 to 0.98, backward x0.92 to 0.99
+//   129 to 512 rows, up to 32 experts: forward x0.76 to 1.06 (worst: 16 experts of 144 to 224 rows each, exactly even;
+//     skewed x0.75 to 0.90), backward x0.88 to 1.00.  eight experts of 512 rows, d 1024, f 4096, us:
+//     GEMM1 57 -> 48, GEMM2 49 -> 41, dH 57 -> 48, dx 50 -> 41
+//   129 to 512 rows, 64 and 128 experts: forward x0.92 to 1.15, backward x0.97 to 1.00; the tiles are many either way
+//   above 512 rows: 2048 rows, d 1024, f 4096, GEMM1 189 -> 196, dH with dW2 324 -> 329; 3001 rows, d 1088, f 2880,
+//     SwiGLU GEMM1 113 -> 135
+constexpr int MID_ROWS = 160;
+constexpr int MID_FEW_EXPERTS = 32, MID_AVERAGE_FEW = 512, MID_AVERAGE_MANY = 128;
+inline bool mid_applies(long long rows, int E) { return rows <= (long long)(E <= MID_FEW_EXPERTS ? MID_AVERAGE_FEW : MID_AVERAGE_MANY) * E; }
 // forward GEMMs of experts with few rows (gemm_skinny_kernel.h), on a map of SKINNY_ROWS-row tiles
 constexpr int SKINNY_ROWS = 64;
 // GEMM2, long K and few experts: the column tiles alone do not fill the chip
 inline bool skinny_split(int E, int K) { return E <= SPLIT_MAX_E && K >= SPLIT_MIN_K; }
 int launch_gemm_half_skinny(int dtype, int epi, bool dual, const GemmArgs& g, int max_tiles, hipStream_t s);
-// The line lies where most experts still fit one 64-row tile.  Both GEMMs with their map, us, 256-row kernel -> this one
-// (above the line: forced), for an even load and router biases of -0.7 and -1.2 log(e + 1):
+// An expert's weights are read again for every 64 rows: the line lies where that evens out over the loads.  Both GEMMs
+// with their map, us, 160-row kernel -> this one (above the line: forced), for an even load and router biases of
+// -0.7 and -1.2 log(e + 1):
 //   rows per expert                                 even          -0.7          -1.2
-//   d 4096, f 14336, 8 experts, SwiGLU     24    604 -> 500                  605 -> 495
-//                                          48    616 -> 535                  616 -> 573
-//                                          56    626 -> 556                  627 -> 593
-//                                          64    630 -> 653                  635 -> 612
-//                                          96    643 -> 701                  823 -> 721
-//                                         128    656 -> 854                  824 -> 863
-//   the same, GELU                         48    389 -> 376                  392 -> 389
-//   d 2048, f 8192, 16 experts, GELU        8    216 -> 188                  207 -> 161
-//                                          48    229 -> 224                  359 -> 232
-//                                          64    235 -> 264                  357 -> 276
-//   d 4096, f 1024, 40 experts, SwiGLU     48    294 -> 206    293 -> 225    294 -> 230
-//   d 2048, f 1024, 128 experts, SwiGLU    16    348 -> 280    329 -> 248    180 -> 166
-//                                          48    373 -> 311    411 -> 340    257 -> 241
-//                                          56    378 -> 325                  197 -> 223
-//                                          80    389 -> 401                  270 -> 273
-//   d 2048, f 1024, 256 experts, GELU      16    452 -> 371    346 -> 270    139 -> 140
-//                                          48    476 -> 419    462 -> 442    241 -> 263
-//   d 1024, f 512, 64 experts, SwiGLU      16     48 -> 45      49 -> 47      48 -> 42
-//                                          48     49 -> 49      83 -> 61      51 -> 55
-//   d 1024, f 512, 128 experts, SwiGLU     16    106 -> 79     102 -> 73      53 -> 54
-//                                          32    110 -> 83     115 -> 100     57 -> 65
-//                                          48    114 -> 102    152 -> 109     88 -> 85
-// What loses below the line (1-15 %) is the steepest bias over 64 and more small experts, most of them idle while one has
-// a thousand rows; the host does not see the load, and a lower line for many experts would give up more than it saves.
-constexpr int SKINNY_AVERAGE = 48;
+//   d 4096, f 14336, 8 experts, SwiGLU     16   502 -> 494   500 -> 493   507 -> 496
+//                                          32   522 -> 527   525 -> 520   540 -> 515
+//                                          48   537 -> 552   549 -> 540   570 -> 582
+//   d 4096, f 14336, 8 experts, GELU       16   325 -> 331   328 -> 332   301 -> 303
+//                                          32   332 -> 364   344 -> 335   356 -> 336
+//                                          48   342 -> 387   360 -> 390   376 -> 392
+//   d 2048, f 8192, 16 experts, GELU       16   206 -> 200   195 -> 189   187 -> 175
+//                                          32   211 -> 220   219 -> 215   244 -> 225
+//                                          48   218 -> 234   252 -> 239   244 -> 234
+//   d 4096, f 1024, 40 experts, SwiGLU     16   214 -> 190   207 -> 183   134 -> 136
+//                                          32   218 -> 201   217 -> 210   142 -> 168
+//                                          48   225 -> 210   219 -> 234   195 -> 197
+//   d 2048, f 1024, 128 experts, SwiGLU    16   304 -> 282   286 -> 284   194 -> 192
+//                                          32   318 -> 298   319 -> 310   250 -> 250
+//                                          48   327 -> 316   336 -> 351   272 -> 285
+//   d 2048, f 1024, 256 experts, GELU      16   380 -> 375   320 -> 322   155 -> 167
+//                                          32   392 -> 408   396 -> 415   221 -> 240
+//                                          48   406 -> 426   432 -> 482   252 -> 312
+//   d 1024, f 512, 64 experts, SwiGLU      16    44 ->  46    44 ->  48    37 ->  41
+//                                          32    46 ->  47    65 ->  52    40 ->  45
+//                                          48    47 ->  55    65 ->  62    43 ->  54
+//   d 1024, f 512, 128 experts, SwiGLU     16    90 ->  74    84 ->  74    44 ->  50
+//                                          32    98 ->  84   116 ->  99    66 ->  67
+//                                          48   103 -> 101   115 -> 108    70 ->  84
+constexpr int SKINNY_AVERAGE = 32;
 inline bool skinny_applies(long long rows, int E) { return rows <= (long long)SKINNY_AVERAGE * E; }
 
 // A weight gradient over the rows of several calls (micro-batches) at once: operand s of call s, each with its own share

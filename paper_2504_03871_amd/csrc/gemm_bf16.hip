@@ -25,17 +25,17 @@ static long long split_blocks(const GemmArgs& g, long long ntn) {
 template <typename ST>
 static int launch_split_reduce(const GemmArgs& g, long long tiles, hipStream_t s) {
   const long long small = g.split_small ? (long long)g.E * ((SPLIT_ROWS * (g.N / 4) + 255) / 256) : 0;
-  const long long tail = g.split_tail ? (tiles < TAIL_SLOTS / 2 ? tiles : TAIL_SLOTS / 2) * (256 / TAIL_REDUCE_ROWS) : 0;
+  const long long tail = g.split_tail ? (tiles < TAIL_SLOTS / 2 ? tiles : TAIL_SLOTS / 2) * (g.tile_rows / TAIL_REDUCE_ROWS) : 0;
   split_reduce_kernel<ST><<<dim3((unsigned)(small > tail ? small : tail)), 256, 0, s>>>(g);
   return launch_status();
 }
 
-template <typename ST, int MODE, int EPI, bool DUAL, bool CHAIN>
-static int launch_one(const GemmArgs& g, int max_tiles, hipStream_t s) {
+template <typename ST, int MODE, int EPI, bool DUAL, bool CHAIN, int BM>
+static int launch_rows(const GemmArgs& g, int max_tiles, hipStream_t s) {
   constexpr int BN = DUAL ? T_BN_DUAL : T_BN;
   constexpr bool TAB = (EPI == EPI_GELU_BWD || EPI == EPI_GELU_FWD) && Half16<ST>::GELU_TABLE;
-  constexpr int lds = gemm_bf16_lds_bytes<T_BM, BN, DUAL, TAB>();
-  auto kern = gemm_bf16_kernel<ST, MODE, EPI, DUAL, CHAIN, T_BM, BN, T_WGM, T_WGN>;
+  constexpr int lds = gemm_bf16_lds_bytes<BM, BN, DUAL, TAB>();
+  auto kern = gemm_bf16_kernel<ST, MODE, EPI, DUAL, CHAIN, BM, BN, T_WGM, T_WGN>;
   // more than 64 KB of dynamic LDS needs the attribute on the current device; set on every launch (a cheap
   // host-side call) rather than remembered, so the library keeps no per-process or per-device state
   {
@@ -53,13 +53,22 @@ static int launch_one(const GemmArgs& g, int max_tiles, hipStream_t s) {
   return launch_split_reduce<ST>(g, tiles, s);
 }
 
-// A row-tile GEMM (NT) and a weight-gradient GEMM (TN) in one launch; the first one's blocks come first.
-template <typename ST, int EPI1, bool CHAIN1>
-static int launch_pair(const GemmArgs& g1, int max_tiles, const GemmArgs& g2, hipStream_t s) {
-  constexpr int lds1 = gemm_bf16_lds_bytes<T_BM, T_BN, false, EPI1 == EPI_GELU_BWD && Half16<ST>::GELU_TABLE>();
+template <typename ST, int MODE, int EPI, bool DUAL, bool CHAIN>
+static int launch_one(const GemmArgs& g, int max_tiles, hipStream_t s) {
+  if constexpr (MODE != MODE_TN) {
+    if (g.tile_rows == MID_ROWS) return launch_rows<ST, MODE, EPI, DUAL, CHAIN, MID_ROWS>(g, max_tiles, s);
+  }
+  return launch_rows<ST, MODE, EPI, DUAL, CHAIN, T_BM>(g, max_tiles, s);
+}
+
+// A row-tile GEMM (NT) and a weight-gradient GEMM (TN, one gradient or two of the same A) in one launch; the first one's
+// blocks come first.
+template <typename ST, int EPI1, bool CHAIN1, int BM1>
+static int launch_pair_rows(const GemmArgs& g1, int max_tiles, const GemmArgs& g2, hipStream_t s) {
+  constexpr int lds1 = gemm_bf16_lds_bytes<BM1, T_BN, false, EPI1 == EPI_GELU_BWD && Half16<ST>::GELU_TABLE>();
   constexpr int lds2 = gemm_bf16_lds_bytes<T_BM, T_BN, false>();
   constexpr int lds = lds1 > lds2 ? lds1 : lds2;
-  auto kern = gemm_bf16_pair_kernel<ST, MODE_NT, EPI1, CHAIN1, MODE_TN, EPI_DW, T_BM, T_BN, T_WGM, T_WGN>;
+  auto kern = gemm_bf16_pair_kernel<ST, MODE_NT, EPI1, CHAIN1, BM1, MODE_TN, EPI_DW, T_BM, T_BN, T_WGM, T_WGN>;
   // more than 64 KB of dynamic LDS needs the attribute on the current device; set on every launch (a cheap
   // host-side call) rather than remembered, so the library keeps no per-process or per-device state
   {
@@ -79,6 +88,11 @@ static int launch_pair(const GemmArgs& g1, int max_tiles, const GemmArgs& g2, hi
   const int rc = launch_status();
   if (rc != MOE_OK || !split) return rc;
   return launch_split_reduce<ST>(g1, tiles1, s);
+}
+
+template <typename ST, int EPI1, bool CHAIN1>
+static int launch_pair(const GemmArgs& g1, int max_tiles, const GemmArgs& g2, hipStream_t s) {
+  return g1.tile_rows == MID_ROWS ? launch_pair_rows<ST, EPI1, CHAIN1, MID_ROWS>(g1, max_tiles, g2, s) : launch_pair_rows<ST, EPI1, CHAIN1, T_BM>(g1, max_tiles, g2, s);
 }
 
 template <typename ST>

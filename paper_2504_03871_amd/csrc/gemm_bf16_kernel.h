@@ -23,6 +23,12 @@
 // an operand with contiguous K as 64-byte pieces of 128-byte lines, which fills the address FIFO of the
 // memory pipe (counters: full thirteen times as often); the operands with strided K gain a little from the
 // halved number of barriers (weight gradients +2 % against a ring of four 32-wide stages).
+// A tile of 160 rows and 256 columns (or twice 128) leaves LDS for a third stage (156 of 160 KB): loads then have two
+// stages' worth of MFMAs to land instead of one, which is what a GEMM of few rows per expert waits for, and the chip is
+// left with smaller remainders (512 micro-batch rows per expert, d 1024, f 4096: GEMM1 57 -> 48 us; 125 rows, d 2048,
+// f 8192, forward pass 282 -> 271).  It moves 13 % more bytes per product from L2, so 256 rows stay ahead where tiles are
+// many and full (the line: mid_applies).  Its five bands of 32 rows go three and two to the two wave rows, one wave of
+// either on each SIMD.
 // The direct loads are raw instructions: if the compiler knew that they write LDS it would wait for
 // every outstanding load before each LDS read it cannot prove disjoint.  The pipeline orders loads and
 // reads itself (explicit vmcnt waits, block barriers); the LDS reads stay compiler-tracked.
@@ -71,7 +77,9 @@ template <> struct Half16<f16> {
 };
 
 constexpr int BKT = 64;   // K values per LDS stage: two MFMA K steps; an operand row with contiguous K is one 128-byte line
-constexpr int NBUF = 2;   // LDS stages
+// LDS stages: two of a 256-row tile (128 KB), three of a 160-row one (156 KB)
+template <int BM>
+constexpr int gemm_bf16_stages() { return BM == 256 ? 2 : 3; }
 
 // ---- LDS layouts -------------------------------------------------------------------------------
 // K-contiguous tile: [rows][BKT] bf16.  The 16-byte chunks of a row are XOR-swizzled with the index
@@ -117,8 +125,9 @@ __device__ __forceinline__ bf16x8 lds_read_ks2(const char* p) {
 template <bool KC, int ROWS, int NT>
 struct Stage {
   static constexpr int CPR = KC ? BKT / 8 : ROWS / 8;
-  static constexpr int CH = ROWS * BKT / 8 / NT;
-  static_assert(CH >= 1, "tile too small for this many threads");
+  static constexpr int CH = (ROWS * BKT / 8 + NT - 1) / NT;
+  static constexpr int LAST = ROWS * BKT / 8 - (CH - 1) * NT;   // threads that move a chunk with the last load: all, or whole waves
+  static_assert(CH >= 1 && LAST % 64 == 0, "a load is made by whole waves");
   // A direct load places lane l of a wave at byte 16*l of the instruction's LDS window, so chunk id
   // lands at byte 16*id of the tile; this is the operand byte offset (pitch in bytes) whose data
   // belongs there: the tile's swizzle, inverted.
@@ -283,9 +292,12 @@ __device__ __forceinline__ void epilogue_fwd(const OutPlanes& o, const unsigned 
 
 template <int BM, int BN, bool DUAL>
 constexpr int gemm_bf16_stage_bytes() { return BM * BKT * 2 + BN * BKT * 2 * (DUAL ? 2 : 1); }
-// TAB: a GELU table sits behind the ring (the GELU epilogues)
+// TAB: a GELU table (the GELU epilogues) sits behind two stages; three leave no room, it then takes the stage that is free
+// before the loop's last two iterations
 template <int BM, int BN, bool DUAL, bool TAB = false>
-constexpr int gemm_bf16_lds_bytes() { return NBUF * gemm_bf16_stage_bytes<BM, BN, DUAL>() + (TAB ? GELU_TAB_FLOATS * 4 : 0); }
+constexpr int gemm_bf16_lds_bytes() {
+  return gemm_bf16_stages<BM>() * gemm_bf16_stage_bytes<BM, BN, DUAL>() + (TAB && gemm_bf16_stages<BM>() == 2 ? GELU_TAB_FLOATS * 4 : 0);
+}
 
 // One output tile; vb = the tile's number in dispatch order.  Block-uniform control flow; returns at
 // once for numbers past the last tile (the grid is sized for the worst case).
@@ -293,14 +305,16 @@ constexpr int gemm_bf16_lds_bytes() { return NBUF * gemm_bf16_stage_bytes<BM, BN
 template <typename ST, int MODE, int EPI, bool DUAL, bool CHAIN, int BM, int BN, int WGM, int WGN, bool SEGS = false>
 __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs& g, const int vb, char* smem, const DwSegs* segs = nullptr) {
   constexpr int NT = WGM * WGN * 64;
-  constexpr int WTM = BM / WGM / 32, WTN = BN / WGN / 32;
+  constexpr int WTM = (BM / 32 + WGM - 1) / WGM, WTN = BN / WGN / 32;   // (an odd number of bands: the last wave row has one less)
   constexpr int KS = BKT / 32;               // MFMA K steps per stage
   constexpr int TM = 2 * WTM, TNN = 2 * WTN; // 16 x 16 MFMA tiles of a wave
   constexpr bool A_KC = (MODE != MODE_TN);   // A stored with K contiguous
   constexpr bool B_KC = (MODE == MODE_NT);
   constexpr int A_BYTES = BM * BKT * 2, B_BYTES = BN * BKT * 2;
   constexpr int STAGE = gemm_bf16_stage_bytes<BM, BN, DUAL>();
-  static_assert(KS == 2 && NBUF == 2, "the pipeline below: two stages of two K steps");
+  constexpr int NBUF = gemm_bf16_stages<BM>();
+  constexpr bool TAB = (EPI == EPI_GELU_BWD || EPI == EPI_GELU_FWD) && Half16<ST>::GELU_TABLE;
+  static_assert(KS == 2 && (NBUF == 2 || NBUF == 3), "the pipeline below: two or three stages of two K steps");
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform: keeps wave-dependent values scalar
@@ -407,6 +421,7 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs& g, const int vb, 
     }
 
   const int KT = (klen + BKT - 1) / BKT;
+  int tab_stage = 0;   // (three stages) the buffer that ends up with the GELU table
   // MFMA row bands of this wave that contain valid rows
   // (row band b of the tile belongs to wave row b % WGM, as its band b / WGM: a partly filled tile then
   // spreads its valid bands over all wave rows instead of loading the first ones only)
@@ -482,15 +497,19 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs& g, const int vb, 
     };
     const int KT1 = KT;                      // stages of one operand pair
     const int KTT = SEGS ? seg_stages : !CHAIN ? KT1 : part_stages > 0 ? part_stages : 2 * KT1;   // stages in all
+    tab_stage = KTT % NBUF;
     // Iteration kt issues the loads of stage kt+D, multiplies stage kt (reading the fragments of stage
     // kt+1 meanwhile), then waits until its own loads of stage kt+2 have landed (all but the newest D-2
     // stages) and joins the block barrier, after which stage kt+2 is visible to every wave and stage
     // kt's buffer may be overwritten.
     constexpr int L = StA::CH + StB::CH * (DUAL ? 2 : 1);   // loads per thread per stage
-    constexpr int PEND = L;                                  // loads that may stay in flight at the prologue's barrier: stage 1
-    static_assert(PEND < 64, "the wait counter has six bits");
-    constexpr int WAIT_L = (PEND & 15) | ((PEND >> 4) << 14) | 0x70 | (15 << 8);   // s_waitcnt vmcnt(PEND) only
+    constexpr int LMIN = L - (StA::LAST < NT ? 1 : 0);       // of the waves that sit out the last load of A
+    static_assert(StB::LAST == NT, "whole loads of B");
+    constexpr int PEND = (NBUF - 1) * LMIN;                  // loads that may stay in flight at the prologue's barrier: all but stage 0's
+    static_assert(PEND < 64 && LMIN < 16, "the wait counter has six bits");
+    constexpr int WAIT_P = (PEND & 15) | ((PEND >> 4) << 14) | 0x70 | (15 << 8);   // s_waitcnt vmcnt(PEND) only
     constexpr int WAIT_0 = 0x70 | (15 << 8);                                       // s_waitcnt vmcnt(0) only
+    constexpr int WAIT_AHEAD = LMIN | 0x70;                                        // s_waitcnt vmcnt(LMIN) lgkmcnt(0)
     constexpr int WAIT_LGKM0 = 0xC07F;                                             // s_waitcnt lgkmcnt(0) only
     unsigned a_vo[StA::CH], b_vo[StB::CH];
 #pragma unroll
@@ -523,6 +542,7 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs& g, const int vb, 
     const unsigned kl__ = (unsigned)(sec__ ? kq__ - KT1 : kq__);                                            \
     const unsigned st__ = smem_base + (buf_) + wbase;                                                       \
     if ((q_) < StA::CH) {                                                                                   \
+      if ((q_) < StA::CH - 1 || StA::LAST == NT || wave < StA::LAST / 64)                                   \
       load_to_lds16(sec__ ? ra1 : ra, st__ + NT * 16 * (q_), a_vo[(q_) < StA::CH ? (q_) : 0] + kl__ * astep); \
     } else {                                                                                                \
       const int c__ = ((q_) - StA::CH) / (DUAL ? 2 : 1) % StB::CH;                                          \
@@ -580,52 +600,63 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs& g, const int vb, 
     __builtin_amdgcn_s_barrier();                                                                           \
     asm volatile("" ::: "memory");                                                                          \
   } while (0)
-    if constexpr ((EPI == EPI_GELU_BWD || EPI == EPI_GELU_FWD) && Half16<ST>::GELU_TABLE) {
-      // the GELU table rides along with the first stage loads (older than they are, so the
-      // first wait of the pipeline covers it): 1 KB per wave and instruction, behind the ring
+    // GELU table into LDS at `at`, 1 KB per wave and instruction
+    auto load_table = [&](unsigned at) {
       static_assert(GELU_TAB_FLOATS * 4 % (NT * 16) == 0, "whole block-wide loads");
       const rsrc_t rt = make_rsrc(g.gelu_tab, (size_t)GELU_TAB_FLOATS * 4);
 #pragma unroll
       for (int i = 0; i < GELU_TAB_FLOATS * 4 / (NT * 16); ++i)
-        load_to_lds16(rt, smem_base + NBUF * STAGE + i * NT * 16 + wbase, (unsigned)(i * NT + tid) * 16u);
-    }
+        load_to_lds16(rt, smem_base + at + i * NT * 16 + wbase, (unsigned)(i * NT + tid) * 16u);
+    };
+    if constexpr (TAB && NBUF == 2) load_table(NBUF * STAGE);   // with the first stage loads, older than they are: the first wait covers it
     {
-      // Iteration S multiplies stage S (two K steps) out of buffer S % 2.  K step 0 reads the fragments of
-      // K step 1; then every wave waits for its own loads of stage S+1 and for its fragment reads and joins
-      // the one block barrier of the iteration, after which stage S+1 is visible to all and nobody reads
-      // buffer S % 2 again; K step 1 reads the fragments of step 0 of stage S+1 and issues the loads of
-      // stage S+2 into buffer S % 2 (they have about a stage's worth of MFMAs to land).
-#define MOE_ITER(S_, DO_NEXT_, DO_LOAD_, NI_)                                                                \
+      // Iteration S multiplies stage S (two K steps) out of buffer S % NBUF.  K step 0 reads the fragments of
+      // K step 1; then every wave waits for its own loads of stage S+1 (three stages: those of S+2 stay in flight) and for
+      // its fragment reads and joins the one block barrier of the iteration, after which stage S+1 is visible to all and
+      // nobody reads buffer S % NBUF again; K step 1 reads the fragments of step 0 of stage S+1 and issues the loads of
+      // stage S+NBUF into buffer S % NBUF (they have NBUF - 1 stages' worth of MFMAs to land).  MORE_: stage S+2 exists.
+#define MOE_ITER(S_, DO_NEXT_, DO_LOAD_, MORE_, NI_)                                                         \
   do {                                                                                                      \
     MOE_STEP(0, true, b0, 1, false, 0, 0, 0, 0, NI_);                                                       \
     if (DO_NEXT_) {                                                                                         \
-      __builtin_amdgcn_s_waitcnt(0);   /* vmcnt(0) lgkmcnt(0): own loads of stage S+1, own reads of stage S */ \
+      if (NBUF == 3 && (MORE_)) __builtin_amdgcn_s_waitcnt(WAIT_AHEAD);                                     \
+      else __builtin_amdgcn_s_waitcnt(0);   /* vmcnt(0) lgkmcnt(0) */                                       \
       MOE_BLOCK_BARRIER();                                                                                  \
     }                                                                                                       \
     if constexpr (SEGS) { if (DO_LOAD_) next_stage(); }                                                     \
-    MOE_STEP(1, DO_NEXT_, b1, 0, DO_LOAD_, (S_) + 2, b0, 0, L, NI_);                                        \
+    MOE_STEP(1, DO_NEXT_, b1, 0, DO_LOAD_, (S_) + NBUF, b0, 0, L, NI_);                                     \
     if constexpr (SEGS) { if (DO_LOAD_) ++seg_k; }                                                          \
-    { const int t__ = b0; b0 = b1; b1 = t__; }                                                              \
+    if constexpr (NBUF == 2) { const int t__ = b0; b0 = b1; b1 = t__; }                                     \
+    else { const int t__ = b0; b0 = b1; b1 = b2; b2 = t__; }                                                \
   } while (0)
       if (KTT > 0) {
-        int b0 = 0, b1 = STAGE;
-        MOE_LOAD(0, 0);
-        if (KTT > 1) {
-          MOE_LOAD(1, STAGE);
-          __builtin_amdgcn_s_waitcnt(WAIT_L);   // stage 0 (and the table) have landed, stage 1 may be in flight
+        int b0 = 0, b1 = STAGE, b2 = 2 * STAGE;
+#pragma unroll
+        for (int q = 0; q < NBUF; ++q)
+          if (q < KTT) MOE_LOAD(q, q * STAGE);
+        if (KTT >= NBUF) {
+          __builtin_amdgcn_s_waitcnt(WAIT_P);   // stage 0 (and a table) have landed, the others may be in flight
         } else {
+          if constexpr (TAB && NBUF == 3) load_table(KTT * STAGE);
           __builtin_amdgcn_s_waitcnt(WAIT_0);
         }
         MOE_BLOCK_BARRIER();
+        // (three stages) the table takes the buffer of stage KTT - 3 once that is free; the wait and the barrier of the
+        // iteration after that make it visible to all
 #define MOE_MAINLOOP(NI_)                                                                        \
   do {                                                                                          \
     MOE_FRAGS(0, b0, 0);                                                                        \
     __builtin_amdgcn_s_waitcnt(WAIT_LGKM0);   /* nothing pending at the loop head: the waits inside the loop then count only its own reads */ \
     int S = 0;                                                                                  \
-    _Pragma("unroll 1") for (; S + 2 < KTT; ++S) MOE_ITER(S, true, true, NI_);                   \
-    _Pragma("unroll 1") for (; S < KTT; ++S) MOE_ITER(S, S + 1 < KTT, S + 2 < KTT, NI_);         \
+    _Pragma("unroll 1") for (; S + NBUF < KTT; ++S) MOE_ITER(S, true, true, true, NI_);          \
+    _Pragma("unroll 1") for (; S < KTT; ++S) {                                                   \
+      const int free__ = b0;                                                                    \
+      MOE_ITER(S, S + 1 < KTT, NBUF == 2 && S + 2 < KTT, S + 2 < KTT, NI_);                      \
+      if constexpr (TAB && NBUF == 3) { if (S + 3 == KTT) load_table(free__); }                  \
+    }                                                                                           \
   } while (0)
         if (ni == WTM) MOE_MAINLOOP(WTM);
+        else if (NBUF == 3 && ni == WTM - 1) MOE_MAINLOOP(WTM - 1);
         else MOE_MAINLOOP(ni);
 #undef MOE_MAINLOOP
       }
@@ -712,7 +743,7 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs& g, const int vb, 
     const size_t first = (size_t)row0 * g.N + n0, bytes = ((size_t)mvalid * g.N - n0) * 2;
     const OutPlanes o = out_planes<ST, EPI>(g, first, bytes);
     const unsigned pitch = (unsigned)g.N * 2u;
-    const float* tab_lds = reinterpret_cast<const float*>(smem + NBUF * STAGE);
+    const float* tab_lds = reinterpret_cast<const float*>(smem + (NBUF == 2 ? NBUF * STAGE : tab_stage * STAGE));
     if constexpr (DUAL) {   // 32 columns per wave and matrix; plain stores (the neighbouring wave has the other half of each line)
       static_assert(TNN == 2, "one pair of column tiles");
       const unsigned col = (unsigned)(wn * C + lane_col8(grp)) * 2u;
@@ -789,7 +820,7 @@ __global__ __launch_bounds__(256) void split_reduce_kernel(GemmArgs g) {
     *reinterpret_cast<u32x2*>(reinterpret_cast<ST*>(g.C) + row * g.N + n) = u32x2{Half16<ST>::pack2(v[0], v[1]), Half16<ST>::pack2(v[2], v[3])};
   };
   if (ts.parts > 1) {
-    constexpr int PER = 256 / TAIL_REDUCE_ROWS;   // blocks per tile
+    const int PER = g.tile_rows / TAIL_REDUCE_ROWS, slot = g.tile_rows * 256;   // blocks per tile, floats per part
     const int q = blockIdx.x / PER, n = (threadIdx.x & 63) * 4;
     if (q >= n_rt * ntn - ts.first) return;
     int rt, nt;
@@ -800,11 +831,11 @@ __global__ __launch_bounds__(256) void split_reduce_kernel(GemmArgs g) {
     for (int i = 0; i < TAIL_REDUCE_ROWS / 4; ++i) {
       const int m = (blockIdx.x % PER) * TAIL_REDUCE_ROWS + i * 4 + threadIdx.x / 64;
       if (m >= t.nrows) return;
-      const float* src = g.split_ws + (size_t)q * ts.parts * 65536 + m * 256 + n;
+      const float* src = g.split_ws + (size_t)q * ts.parts * slot + m * 256 + n;
       f32x4 sum = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int p = 0; p < TAIL_MAX_PARTS; ++p)
-        if (p < ts.parts) sum += *reinterpret_cast<const f32x4*>(src + (size_t)p * 65536);
+        if (p < ts.parts) sum += *reinterpret_cast<const f32x4*>(src + (size_t)p * slot);
       put(t.row0 + m, nt * 256 + n, sum);
     }
     return;
@@ -839,11 +870,11 @@ __global__ __launch_bounds__(WGM* WGN * 64, 1) void gemm_bf16_kernel(GemmArgs g)
 // tile of the second.  Blocks are dispatched in order, so the second GEMM's tiles start on the compute
 // units that the first one's last, partly filled round leaves idle (no stream or event in between,
 // and the two never compete for the cache from the start as two concurrent kernels would).
-template <typename ST, int MODE1, int EPI1, bool CHAIN1, int MODE2, int EPI2, int BM, int BN, int WGM, int WGN>
+template <typename ST, int MODE1, int EPI1, bool CHAIN1, int BM1, int MODE2, int EPI2, int BM, int BN, int WGM, int WGN>
 __global__ __launch_bounds__(WGM* WGN * 64, 1) void gemm_bf16_pair_kernel(GemmArgs g1, GemmArgs g2, int first_blocks) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   if ((int)blockIdx.x < first_blocks)
-    gemm_bf16_tile<ST, MODE1, EPI1, false, CHAIN1, BM, BN, WGM, WGN>(g1, blockIdx.x, smem);
+    gemm_bf16_tile<ST, MODE1, EPI1, false, CHAIN1, BM1, BN, WGM, WGN>(g1, blockIdx.x, smem);
   else
     gemm_bf16_tile<ST, MODE2, EPI2, false, false, BM, BN, WGM, WGN>(g2, blockIdx.x - first_blocks, smem);
 }

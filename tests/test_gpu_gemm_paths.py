@@ -79,7 +79,9 @@ def test_a_row_with_nan_stays_in_its_row(dtype, d, f):
 
 @pytest.mark.parametrize("T, d, f, E, k, dtype, act, zipf", [
     (1, 64, 64, 2, 1, "DT_BF16", "ACT_GELU", 0.0),        # one row, one K stage, half a column tile
-    (48, 128, 192, 2, 2, "DT_F16", "ACT_SWIGLU", 0.0),    # 48 rows per expert: the most that still goes this way
+    (32, 128, 192, 2, 2, "DT_F16", "ACT_SWIGLU", 0.0),    # 32 rows per expert: the most that still goes this way
+    (33, 128, 192, 2, 2, "DT_F16", "ACT_SWIGLU", 0.0),    # 160-row tiles
+    (48, 128, 192, 2, 2, "DT_F16", "ACT_SWIGLU", 0.0),
     (96, 192, 320, 4, 2, "DT_BF16", "ACT_SWIGLU", 1.5),   # skewed: an expert with two row tiles, one with next to none
     (190, 64, 4096, 8, 2, "DT_BF16", "ACT_GELU", 1.5),    # split along K, full 64-row tiles beside the split ones
     (60, 192, 2112, 5, 2, "DT_BF16", "ACT_SWIGLU", 0.0),  # 33 K stages in eight parts, every expert one row tile
@@ -124,9 +126,9 @@ def test_rows_past_a_tile_whose_offsets_wrap_32_bits_are_not_stored(act):
             assert (got - ref).norm() <= 2.0 ** -7 * ref.norm()
 
 
-def last_round_parts(kept, f, N):
+def last_round_parts(kept, f, N, rows=256):
     """(tiles, K parts) of a row-tile GEMM over these rows, as the kernels compute them."""
-    n_rt, ntn = sum(-(-int(n) // 256) for n in kept), -(-N // 256)
+    n_rt, ntn = sum(-(-int(n) // rows) for n in kept), -(-N // 256)
     return n_rt * ntn, B.moe_gemm_block_tile(4, 0, n_rt, 0, 0, f // 64, ntn)[2]
 
 
@@ -178,6 +180,54 @@ def test_last_round_split_along_k_in_the_gelu_input_gradient(dtype, cap):
         ref = dact[o:o + n].double() @ L.W1[e].double().t()
         err = (L.dx_perm[o:o + n].double() - ref).norm() / ref.norm()
         assert err < tol, (e, float(err))
+
+
+@pytest.mark.parametrize("T, d, f, E, k, dtype, act, zipf", [
+    (159, 64, 64, 1, 1, "bf16", "gelu", 0.0),         # one row short of a tile; one K stage of the three
+    (160, 128, 128, 1, 1, "bf16", "swiglu", 0.0),     # two stages
+    (161, 192, 192, 1, 1, "bf16", "gelu", 0.0),       # a tile of one row; three stages
+    (512, 256, 576, 1, 1, "f16", "gelu", 0.0),        # the most rows that go this way; four stages and nine
+    (513, 256, 576, 1, 1, "bf16", "gelu", 0.0),       # 256-row tiles
+    (130, 320, 256, 2, 1, "bf16", "swiglu", 0.0),     # bands of 32 rows at both wave rows' ends
+    (700, 64, 2112, 4, 2, "bf16", "gelu", 1.5),       # GEMM2 split along K; experts with several tiles and with a part of one
+    (512, 128, 192, 33, 8, "f16", "swiglu", 0.0),     # more than 32 experts, below their line
+    (529, 128, 192, 33, 8, "bf16", "gelu", 1.2),      # and above it
+])
+def test_experts_of_few_row_tiles(T, d, f, E, k, dtype, act, zipf):
+    from paper_2504_03871_amd import synth as S
+    from tests.test_gpu_parity import run_case
+    run_case(S.WORKLOADS["cfg1"].scaled(T=T, d=d, f=f, E=E, k=k, dtype=getattr(S, "DT_" + dtype.upper()), act=getattr(S, "ACT_" + act.upper()), zipf_s=zipf))
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+def test_last_round_split_along_k_in_the_input_gradient_of_low_tiles(dtype):
+    """dx = dA W1^T of 160-row tiles, which are too many to share a launch where 256-row ones would not be, with the last
+    round split: partial sums and the rows they come from each in their own part of the workspace."""
+    import torch
+    from paper_2504_03871_amd.layer import MoELayer
+    T, d, f, E, k, cap = 8192, 4160, 2112, 32, 2, 150
+    L = MoELayer(T, d, f, E, k, dtype=DT[dtype], act=B.ACT_GELU, capacity=cap)
+    gen = torch.Generator(device="cuda:0").manual_seed(3)
+    for t, std in ((L.x, 1.0), (L.d_out, 1.0), (L.Wr, d ** -0.5), (L.W1, d ** -0.5), (L.W2, f ** -0.5)):
+        t.normal_(0.0, std, generator=gen)
+    L.forward()
+    L.combine_bwd()
+    L.ffn_bwd()
+    torch.cuda.synchronize()
+    ntn = -(-d // 256)
+    tiles, parts = last_round_parts(L.kept, f, d, 160)
+    assert ntn * (-(-T * k // 160) + E) > 2048 >= ntn * (-(-T * k // 256) + E) and tiles % 256 and parts > 1, (tiles, parts)
+    dact = L.ws[L.ws.numel() - T * k * f * 2:].view(L.tdtype).view(T * k, f)   # the workspace's last region
+    tol = {"bf16": 2.0 ** -9, "f16": 2.0 ** -12}[dtype]                        # one rounding of the result
+    dh = {"bf16": 2.0 ** -8, "f16": 2.0 ** -11}[dtype]                         # two: the pre-activation's and the result's
+    for e in range(E):
+        o, n = int(L.offsets[e]), int(L.kept[e])
+        ref = dact[o:o + n].double() @ L.W1[e].double().t()
+        assert (L.dx_perm[o:o + n].double() - ref).norm() < tol * ref.norm(), e
+        a = L.saved_plane(0)[o:o + n].double()
+        grad = 0.5 * torch.erfc(-a / 2 ** 0.5) + a * torch.exp(-a * a / 2) / (2 * torch.pi) ** 0.5
+        ref = (L.dy_perm[o:o + n].double() @ L.W2[e].double().t()) * grad
+        assert (dact[o:o + n].double() - ref).norm() < dh * ref.norm(), e
 
 
 @pytest.mark.parametrize("A", [1, 1023, 1024, 1025, 4096, 4097])
