@@ -392,6 +392,7 @@ int ffn_fwd_impl(const moe_cfg* cfg, const void* x_perm, const void* W1, const v
   // hidden = act(x_perm W1)
   g.A = x_perm; g.B = W1; g.B2 = W1b; g.N = f; g.K = d;
   g.chunked = row_tiles_chunked(A, d, f, cfg->E, swiglu ? 2 : 1, (int)elt_size(cfg));
+  g.near = hidden_near(A, f);
   g.C = sv; g.C2 = sv + plane; g.C3 = sv + 2 * plane;
   char* hid = swiglu ? sv + 2 * plane : sv + plane;
   if (saved == nullptr) {   // keep nothing but the hidden activation

@@ -284,6 +284,7 @@ struct GemmArgs {
   const int32_t* order;     // experts by descending share length (weight-gradient GEMMs start the heaviest first)
   const float* gelu_tab;    // bf16 GELU epilogues: Phi (forward) or gelu' (backward) over the bf16 numbers
   float* split_ws;          // fp32 partial sums of split tiles, or NULL: no split-K
+  int near;                      // GELU forward: the hidden plane is stored for the caches (hidden_near)
   int split_small, split_tail;   // which tiles may be split: the smallest row tiles (SPLIT_K), those of the last round (tail_split)
   int split_all;                 // few-row GEMMs: every tile is split (skinny_order)
   const int32_t* offsets;
@@ -329,6 +330,12 @@ int gemm_bf16_tile_rows();
 constexpr int MID_ROWS = 160;
 constexpr int MID_FEW_EXPERTS = 32, MID_AVERAGE_FEW = 512, MID_AVERAGE_MANY = 128;
 inline bool mid_applies(long long rows, int E) { return rows <= (long long)(E <= MID_FEW_EXPERTS ? MID_AVERAGE_FEW : MID_AVERAGE_MANY) * E; }
+// Whether GELU's hidden plane, which GEMM2 reads next, is stored plainly instead of streamed.  Up to about twice the L2
+// caches' 32 MB much of it is still near when GEMM2 starts; beyond, it only displaces operands.  Forward pass, us, streamed
+// -> plain: eight experts of 1000 rows, d 832, f 3264 (52 MB) 168 -> 158; six of 1200, d 1088, f 2880 (41 MB) 138 -> 126;
+// 12 of the same (83 MB) 225 -> 230; eight of 2048, d 1024, f 4096 (134 MB) 303 -> 313.  SwiGLU: from -4 to +4 %.
+constexpr long long NEAR_BYTES = 64ll << 20;
+inline bool hidden_near(long long rows, int f) { return rows * f * 2 <= NEAR_BYTES; }
 // forward GEMMs of experts with few rows (gemm_skinny_kernel.h), on a map of SKINNY_ROWS-row tiles
 constexpr int SKINNY_ROWS = 64;
 // GEMM2, long K and few experts: the column tiles alone do not fill the chip

@@ -35,7 +35,13 @@ static int launch_rows(const GemmArgs& g, int max_tiles, hipStream_t s) {
   constexpr int BN = DUAL ? T_BN_DUAL : T_BN;
   constexpr bool TAB = (EPI == EPI_GELU_BWD || EPI == EPI_GELU_FWD) && Half16<ST>::GELU_TABLE;
   constexpr int lds = gemm_bf16_lds_bytes<BM, BN, DUAL, TAB>();
-  auto kern = gemm_bf16_kernel<ST, MODE, EPI, DUAL, CHAIN, BM, BN, T_WGM, T_WGN>;
+  // Two matrices of 128 columns: 4 x 2 waves of 64 rows and 64 columns of either, which write whole lines, streamed
+  // (2 x 4: 32 columns, half lines).  GEMM1 of SwiGLU, 16 rounds of tiles, us per round, 2 x 4 and plain stores -> 4 x 2:
+  // K 512 28.8 -> 25.0, 1024 38.6 -> 35.5, 2048 62.4 -> 60.2, 4096 112 -> 108.5; forward passes: eight experts of 2048 rows,
+  // d 1024, f 4096 510 -> 457, 16 of 600, d 2048, f 8192 1149 -> 1112, six of 1200, d 1088, f 2880 194 -> 195.  160 rows
+  // have five bands, which four wave rows would share unevenly.
+  constexpr int WGM = DUAL && BM == T_BM ? 4 : T_WGM;
+  auto kern = gemm_bf16_kernel<ST, MODE, EPI, DUAL, CHAIN, BM, BN, WGM, 8 / WGM>;
   // more than 64 KB of dynamic LDS needs the attribute on the current device; set on every launch (a cheap
   // host-side call) rather than remembered, so the library keeps no per-process or per-device state
   {

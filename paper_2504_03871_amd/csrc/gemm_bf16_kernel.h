@@ -240,7 +240,11 @@ __device__ __forceinline__ void swap8(V& a, V& b) {
 }
 
 // ---- epilogue accesses through buffer descriptors: 32-bit offsets; what lies past the byte count is not touched ----
-constexpr int AUX_NT = 2;   // streaming access
+// Outputs are streamed, which keeps them from displacing operand panels in the L2 (dH -1.3 %, whole GELU steps -0.4 to
+// -1.5 % against plain stores): a writer of 3.7 TB/s on half of the compute units slows the two-stage main loop on the
+// others from 84 to 187 us with plain stores, to 87 with streaming and to 80 with streaming, written through.
+constexpr int AUX_NT = 2;    // streaming access
+constexpr int AUX_WT = 18;   // streaming and written through: for half lines
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t out_rsrc(const void* base, size_t bytes) {
   const unsigned long long p = (unsigned long long)base;
   const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)p), hi = __builtin_amdgcn_readfirstlane((unsigned)(p >> 32));
@@ -252,12 +256,13 @@ __device__ __forceinline__ void buf_store16(__amdgpu_buffer_rsrc_t r, unsigned o
 __device__ __forceinline__ u32x4 buf_load16_nt(__amdgpu_buffer_rsrc_t r, unsigned off) { return __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, AUX_NT); }
 
 // The 16-bit output planes of an epilogue from element `first` on.
-struct OutPlanes { __amdgpu_buffer_rsrc_t c, c2, c3; bool pre; };   // pre: the forward keeps its pre-activation plane(s)
+struct OutPlanes { __amdgpu_buffer_rsrc_t c, c2, c3; bool pre, near; };   // pre: the forward keeps its pre-activation plane(s); near: GemmArgs.near
 template <typename ST, int EPI>
 __device__ __forceinline__ OutPlanes out_planes(const GemmArgs& g, size_t first, size_t bytes) {
   auto at = [&](void* base) { return out_rsrc(reinterpret_cast<ST*>(base) + first, bytes); };
   OutPlanes o;
   o.pre = g.C != nullptr;
+  o.near = g.near != 0;
   o.c = at(g.C);
   o.c2 = (EPI == EPI_GELU_FWD || EPI == EPI_SWIGLU_FWD || EPI == EPI_SWIGLU_BWD) ? at(g.C2) : o.c;
   o.c3 = EPI == EPI_SWIGLU_FWD ? at(g.C3) : o.c;
@@ -280,7 +285,10 @@ __device__ __forceinline__ void epilogue_fwd(const OutPlanes& o, const unsigned 
   auto put = [&](__amdgpu_buffer_rsrc_t r, u32x4* w) {
     if constexpr (NP == 2) swap8(w[0], w[1]);
 #pragma unroll
-    for (int q = 0; q < NP; ++q) buf_store16<AUX>(r, off[q], w[q]);
+    for (int q = 0; q < NP; ++q) {
+      if (EPI == EPI_GELU_FWD && w == v[1] && o.near) buf_store16<0>(r, off[q], w[q]);
+      else buf_store16<AUX>(r, off[q], w[q]);
+    }
   };
   if (EPI == EPI_STORE || o.pre) put(o.c, v[0]);
   if constexpr (EPI == EPI_GELU_FWD) put(o.c2, v[1]);
@@ -744,28 +752,25 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs& g, const int vb, 
     const OutPlanes o = out_planes<ST, EPI>(g, first, bytes);
     const unsigned pitch = (unsigned)g.N * 2u;
     const float* tab_lds = reinterpret_cast<const float*>(smem + (NBUF == 2 ? NBUF * STAGE : tab_stage * STAGE));
-    if constexpr (DUAL) {   // 32 columns per wave and matrix; plain stores (the neighbouring wave has the other half of each line)
-      static_assert(TNN == 2, "one pair of column tiles");
+    if constexpr (TNN == 2) {   // 32 columns per wave and matrix, half lines (the neighbouring wave has the other half)
       const unsigned col = (unsigned)(wn * C + lane_col8(grp)) * 2u;
 #pragma unroll
       for (int i = 0; i < TM; ++i)
         if (!empty(i)) {
           const int m = band_row(i) + (lane & 15);
           const unsigned off[1] = {m < mvalid ? (unsigned)m * pitch + col : OUT_OF_RANGE};
-          epilogue_fwd<ST, EPI, 1, 0>(o, off, acc[i], acc2[DUAL ? i : 0], tab_lds);
+          epilogue_fwd<ST, EPI, 1, AUX_WT>(o, off, acc[i], acc2[DUAL ? i : 0], tab_lds);
         }
     } else {
       static_assert(TNN == 4, "two pairs of column tiles");
       const unsigned col = (unsigned)(wn * C + right * 32 + lane_col8(grp)) * 2u;
       auto at = [&](int i, int h) { const int m = band_row(i) + h * 8 + r8; return m < mvalid ? (unsigned)m * pitch + col : OUT_OF_RANGE; };
-      // outputs are written once and read by a later launch: streaming stores keep them from displacing operand panels
-      // in the L2 (measured: dH -1.3 %, the GELU workloads -0.4 to -1.5 % per step)
-      if constexpr (EPI == EPI_STORE || EPI == EPI_GELU_FWD) {
+      if constexpr (EPI == EPI_STORE || EPI == EPI_GELU_FWD || EPI == EPI_SWIGLU_FWD) {
 #pragma unroll
         for (int i = 0; i < TM; ++i)
           if (!empty(i)) {
             const unsigned off[2] = {at(i, 0), at(i, 1)};
-            epilogue_fwd<ST, EPI, 2, AUX_NT>(o, off, acc[i], acc[i], tab_lds);
+            epilogue_fwd<ST, EPI, 2, AUX_NT>(o, off, acc[i], DUAL ? acc2[DUAL ? i : 0] : acc[i], tab_lds);
           }
       } else {
         // The saved tensors are requested AHEAD row tiles ahead, the first ones before anything else.

@@ -199,6 +199,19 @@ def test_experts_of_few_row_tiles(T, d, f, E, k, dtype, act, zipf):
     run_case(S.WORKLOADS["cfg1"].scaled(T=T, d=d, f=f, E=E, k=k, dtype=getattr(S, "DT_" + dtype.upper()), act=getattr(S, "ACT_" + act.upper()), zipf_s=zipf))
 
 
+@pytest.mark.parametrize("T, d, f, E, k, dtype, act", [
+    (513, 64, 64, 1, 1, "bf16", "swiglu"),       # SwiGLU in 256-row tiles: a tile of one row, half a column tile
+    (545, 128, 192, 1, 1, "f16", "swiglu"),      # two bands of 32 rows for four wave rows
+    (1400, 192, 320, 2, 1, "bf16", "swiglu"),    # six bands or so, three column tiles
+    (1100, 64, 4096, 2, 1, "bf16", "gelu"),      # GELU, hidden plane stored plainly (9 MB)
+    (16400, 64, 2112, 2, 1, "f16", "gelu"),      # and streamed (69 MB)
+])
+def test_forward_stores_of_high_tiles(T, d, f, E, k, dtype, act):
+    from paper_2504_03871_amd import synth as S
+    from tests.test_gpu_parity import run_case
+    run_case(S.WORKLOADS["cfg1"].scaled(T=T, d=d, f=f, E=E, k=k, dtype=getattr(S, "DT_" + dtype.upper()), act=getattr(S, "ACT_" + act.upper())))
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 def test_last_round_split_along_k_in_the_input_gradient_of_low_tiles(dtype):
     """dx = dA W1^T of 160-row tiles, which are too many to share a launch where 256-row ones would not be, with the last
