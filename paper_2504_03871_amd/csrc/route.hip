@@ -424,9 +424,17 @@ __global__ __launch_bounds__(NW * 64) void route_small_kernel(
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), r = lane & 15, c = lane >> 4;
   const int tok0 = blockIdx.x * TOK, nkb = (d + KB - 1) / KB;
   const T* xrow = x + (size_t)min(tok0 + r, Tn - 1) * d + c * (KB / 4);   // rows past the batch repeat the last token
-  rt_f32x4 acc[NET];
+  // Chains of sums, piece s in chain s % CH.  fp32: four, since one chain of 64 products rounds more often than the four-way
+  // vector sums of route_kernel do: error of the logits against 64 bits (2-norm, route_kernel | one chain | four), 8 experts,
+  // d 64 1.06e-7 | 1.44e-7 | 0.83e-7, d 128 1.09e-7 | 1.49e-7 | 0.89e-7, d 1024 2.91e-7 | 1.63e-7 | 1.14e-7; same time.
+  // Two expert tiles in sixteen waves have no registers left for it and no need: 32 experts, d 1024 5.74e-7 | 1.63e-7; two chains
+  // 9.0 -> 11.1 us.  16-bit: one, the error is that of the weight's second term (2.45e-6 in both kernels).
+  constexpr int CH = std::is_same<T, float>::value && NET * NW <= 16 ? 4 : 1;
+  rt_f32x4 acc[NET][CH];
 #pragma unroll
-  for (int nt = 0; nt < NET; ++nt) acc[nt] = rt_f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int nt = 0; nt < NET; ++nt)
+#pragma unroll
+    for (int h = 0; h < CH; ++h) acc[nt][h] = rt_f32x4{0.f, 0.f, 0.f, 0.f};
   for (int kb = wave; kb < nkb; kb += NW) {
     const int k0 = kb * KB + c * (KB / 4);
     const float* wk = Wr + (size_t)kb * KB * E;
@@ -456,7 +464,7 @@ __global__ __launch_bounds__(NW * 64) void route_small_kernel(
 #pragma unroll
         for (int i = 0; i < P; ++i)
 #pragma unroll
-          for (int nt = 0; nt < NET; ++nt) acc[nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(xv[i], w[nt][s][i], acc[nt], 0, 0, 0);
+          for (int nt = 0; nt < NET; ++nt) acc[nt][s % CH] = __builtin_amdgcn_mfma_f32_16x16x4f32(xv[i], w[nt][s][i], acc[nt][s % CH], 0, 0, 0);
       } else {
         constexpr int XT = XTerms<T>::N;
         rt_bf16x8 t[XT];
@@ -471,8 +479,8 @@ __global__ __launch_bounds__(NW * 64) void route_small_kernel(
           }
 #pragma unroll
           for (int xt = 0; xt < XT; ++xt) {
-            acc[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(t[xt], hi, acc[nt], 0, 0, 0);
-            acc[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(t[xt], lo, acc[nt], 0, 0, 0);
+            acc[nt][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(t[xt], hi, acc[nt][0], 0, 0, 0);
+            acc[nt][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(t[xt], lo, acc[nt][0], 0, 0, 0);
           }
         }
       }
@@ -483,7 +491,11 @@ __global__ __launch_bounds__(NW * 64) void route_small_kernel(
 #pragma unroll
   for (int nt = 0; nt < NET; ++nt)
 #pragma unroll
-    for (int v = 0; v < 4; ++v) mine[(c * 4 + v) * LD + nt * 16 + r] = acc[nt][v];
+    for (int v = 0; v < 4; ++v) {
+      float sum = acc[nt][0][v];
+      if constexpr (CH == 4) sum = (sum + acc[nt][1][v]) + (acc[nt][2][v] + acc[nt][3][v]);
+      mine[(c * 4 + v) * LD + nt * 16 + r] = sum;
+    }
   __syncthreads();
   const int ntok = min(TOK, Tn - tok0);
   for (int i = tid; i < TOK * LD; i += NW * 64) {

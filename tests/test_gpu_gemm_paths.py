@@ -288,6 +288,26 @@ def test_gate_of_few_tokens(T, d, E, k, dtype):
     run_case(base.scaled(T=T, d=d, f=64, E=E, k=k, dtype=getattr(S, dtype)))
 
 
+@pytest.mark.parametrize("T, d, E", [(2048, 64, 8), (2048, 128, 8), (1000, 260, 13), (1000, 512, 32), (2000, 516, 8)])
+def test_fp32_gate_sums_in_short_chains(T, d, E):
+    """Logits against 64 bits.  A chain of n like-sized sums is off by about u sqrt(n / 6) (u = 2^-24, rounding errors uniform,
+    partial sums that grow like a random walk): 1.6 u for chains of 16 products, 3.3 u for chains of 64; bound 2 u."""
+    import numpy as np
+    import torch
+    rng = np.random.default_rng(d)
+    x, Wr = rng.standard_normal((T, d)).astype(np.float32), (rng.standard_normal((d, E)) * d ** -0.5).astype(np.float32)
+    cfg = B.make_cfg(T, d, 64, E, 2, dtype=B.DTYPE_F32)
+    e = lambda n, t: torch.empty(T, n, dtype=t, device="cuda")
+    logits, idx, w = e(E, torch.float32), e(2, torch.int32), e(2, torch.float32)
+    ws = torch.empty(B.moe_workspace_bytes(cfg), dtype=torch.uint8, device="cuda")
+    B.moe_route(cfg, torch.from_numpy(x).cuda(), torch.from_numpy(Wr).cuda(), None, None, logits, idx, w, ws)
+    torch.cuda.synchronize()
+    want = x.astype(np.float64) @ Wr.astype(np.float64)
+    err = np.linalg.norm(logits.cpu().numpy() - want) / np.linalg.norm(want)
+    print(f"T {T} d {d} E {E}: {err:.3e}")
+    assert err <= 2 * 2.0 ** -24
+
+
 @pytest.mark.parametrize("A, E", [(65 * 1024, 5), (97 * 1024 + 3, 256), (200000, 100)])
 def test_dispatch_with_scanned_prefixes(A, E):
     """More than 64 blocks: whole and ragged batches of the scan, more experts than one of its blocks has threads.  Exact."""
