@@ -1,8 +1,8 @@
-"""Seeded synthetic inputs for the MoE expert layer (shared by tests, bench and the CPU checker).
+"""Seeded synthetic inputs for the MoE expert layer (shared by tests, bench and the CPU oracle).
 
 This module holds no arithmetic of the method itself: it only draws numbers, rounds them to the
 storage type and describes the workloads.  Every tensor is a pure function of (seed, element index),
-so any slice of any tensor can be regenerated independently and the GPU path and the CPU checker
+so any slice of any tensor can be regenerated independently and the GPU path and the CPU oracle
 consume byte-identical inputs.
 
 Generator: a SplitMix64 counter stream (the 64-bit finaliser published by Steele, Lea and Flood,
