@@ -405,12 +405,18 @@ __global__ __launch_bounds__(NW * 64) void route_mfma_kernel(
 
 // ---------------------------------------------------------------- forward of few tokens, on the matrix cores
 // The same product for batches that do not fill the chip with 32 or 64 tokens per block: 16 tokens per block, all of its
-// waves along K (16-bit: blocks of 128 values, fp32: of 64), so that a wave's share of a row is one or two blocks whose loads
-// are in flight together.  The gate weight is read where it lies: its layout pass would be a launch as long as this one.
+// waves along K (16-bit: blocks of 128 values, fp32: of 64).  16-bit storage has as many waves as route_mfma_kernel and adds
+// the same terms in the same order, so that a token's logits, and with them its experts, do not depend on the size of the
+// batch it comes in; a wave's share of a row is then up to several blocks, and four (two expert tiles: two) are in flight
+// together.  fp32 storage, which has no other kernel for up to 32 experts, takes 8 or 16 waves.  The gate weight is read
+// where it lies: its layout pass would be a launch as long as this one.
 // fp32 storage multiplies on v_mfma_f32_16x16x4_f32 (fp32 products and sums).  Bound by one round trip to memory for x and Wr,
 // the reduction over the waves and the selection.
 // Lane (row or expert r = l % 16, quarter c = l / 16) supplies the K values k0 .. k0 + KB / 4 - 1 of its row or expert, k0 = kb KB + c KB / 4,
 // a 16-byte piece of x at a time.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t route_rsrc(const void* base, size_t bytes) {   // wave-uniform arguments, below 4 GiB
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)(unsigned)bytes, 0x00020000);
+}
 template <typename T> struct SmallGate { static constexpr int KB = 128, PIECE = 8; };
 template <> struct SmallGate<float> { static constexpr int KB = 64, PIECE = 4; };
 
@@ -421,61 +427,62 @@ __global__ __launch_bounds__(NW * 64) void route_small_kernel(
   extern __shared__ float part[];   // [NW waves][16 tokens][LD]; the sum ends up in part[0]
   constexpr int TOK = 16, LD = NET * 16, KB = SmallGate<T>::KB, P = SmallGate<T>::PIECE;
   static_assert(KB == 16 * P, "four pieces per lane");
+  constexpr int PF = std::is_same<T, float>::value ? 1 : 4 / NET;   // K blocks in flight per wave
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), r = lane & 15, c = lane >> 4;
   const int tok0 = blockIdx.x * TOK, nkb = (d + KB - 1) / KB;
-  const T* xrow = x + (size_t)min(tok0 + r, Tn - 1) * d + c * (KB / 4);   // rows past the batch repeat the last token
   // Chains of sums, piece s in chain s % CH.  fp32: four, since one chain of 64 products rounds more often than the four-way
   // vector sums of route_kernel do: error of the logits against 64 bits (2-norm, route_kernel | one chain | four), 8 experts,
   // d 64 1.06e-7 | 1.44e-7 | 0.83e-7, d 128 1.09e-7 | 1.49e-7 | 0.89e-7, d 1024 2.91e-7 | 1.63e-7 | 1.14e-7; same time.
-  // Two expert tiles in sixteen waves have no registers left for it and no need: 32 experts, d 1024 5.74e-7 | 1.63e-7; two chains
-  // 9.0 -> 11.1 us.  16-bit: one, the error is that of the weight's second term (2.45e-6 in both kernels).
+  // Two expert tiles in sixteen waves have no need of it: 32 experts, d 1024 5.74e-7 | 1.63e-7; two chains 9.0 -> 11.1 us.
+  // 16-bit: one, as route_mfma_kernel (error 2.45e-6, that of the weight's second term).
   constexpr int CH = std::is_same<T, float>::value && NET * NW <= 16 ? 4 : 1;
   rt_f32x4 acc[NET][CH];
 #pragma unroll
   for (int nt = 0; nt < NET; ++nt)
 #pragma unroll
     for (int h = 0; h < CH; ++h) acc[nt][h] = rt_f32x4{0.f, 0.f, 0.f, 0.f};
-  for (int kb = wave; kb < nkb; kb += NW) {
-    const int k0 = kb * KB + c * (KB / 4);
-    const float* wk = Wr + (size_t)kb * KB * E;
-    uint4 raw[4];
-    float w[NET][4][P];
+  uint4 raw[PF][4];
+  float w[PF][NET][4][P];
+  // Buffer loads, which return zero past the weight's last row and, by an offset out of range, past a row of x: no branches,
+  // so that the loads of all PF blocks leave together
+  const __amdgpu_buffer_rsrc_t rx = route_rsrc(x + (size_t)tok0 * d, (size_t)(Tn - tok0) * d * sizeof(T));
+  const unsigned pitch = (unsigned)E * 4u, xrow = (unsigned)min(r, Tn - 1 - tok0) * (unsigned)d;   // rows past the batch repeat the last token
+  auto load = [&](int p, int kb) {
+    const __amdgpu_buffer_rsrc_t rw = route_rsrc(Wr + (size_t)kb * KB * E, (size_t)min(KB, d - kb * KB) * pitch);
+    unsigned kq = c * (KB / 4), off[NET];
+    asm volatile("" : "+v"(kq));   // the offsets are computed here, not kept in registers from block to block
+#pragma unroll
+    for (int nt = 0; nt < NET; ++nt) off[nt] = kq * pitch + min(nt * 16 + r, E - 1) * 4u;   // experts from E on: sums that nothing reads
 #pragma unroll
     for (int s = 0; s < 4; ++s) {   // d is a multiple of the piece (fp32) or of two quarters (16-bit): a piece is inside the row or past it
-      raw[s] = uint4{0u, 0u, 0u, 0u};
+      const unsigned k0 = kb * KB + kq + s * P;
+      raw[p][s] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rx, k0 < (unsigned)d ? (xrow + k0) * (unsigned)sizeof(T) : 0xfffffff0u, 0, 0));
 #pragma unroll
       for (int nt = 0; nt < NET; ++nt)
 #pragma unroll
-        for (int i = 0; i < P; ++i) w[nt][s][i] = 0.f;
-      if (k0 + s * P < d) {
-        raw[s] = *reinterpret_cast<const uint4*>(xrow + (size_t)kb * KB + s * P);
-#pragma unroll
-        for (int nt = 0; nt < NET; ++nt) {   // experts from E on: sums that nothing reads
-          const unsigned off = (unsigned)(c * (KB / 4) * E + min(nt * 16 + r, E - 1));
-#pragma unroll
-          for (int i = 0; i < P; ++i) w[nt][s][i] = wk[off + (unsigned)(s * P + i) * (unsigned)E];
-        }
-      }
+        for (int i = 0; i < P; ++i) w[p][nt][s][i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rw, off[nt] + (s * P + i) * pitch, 0, 0));
     }
+  };
+  auto multiply = [&](int p) {
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
       if constexpr (std::is_same<T, float>::value) {
-        const float xv[4] = {__uint_as_float(raw[s].x), __uint_as_float(raw[s].y), __uint_as_float(raw[s].z), __uint_as_float(raw[s].w)};
+        const float xv[4] = {__uint_as_float(raw[p][s].x), __uint_as_float(raw[p][s].y), __uint_as_float(raw[p][s].z), __uint_as_float(raw[p][s].w)};
 #pragma unroll
         for (int i = 0; i < P; ++i)
 #pragma unroll
-          for (int nt = 0; nt < NET; ++nt) acc[nt][s % CH] = __builtin_amdgcn_mfma_f32_16x16x4f32(xv[i], w[nt][s][i], acc[nt][s % CH], 0, 0, 0);
+          for (int nt = 0; nt < NET; ++nt) acc[nt][s % CH] = __builtin_amdgcn_mfma_f32_16x16x4f32(xv[i], w[p][nt][s][i], acc[nt][s % CH], 0, 0, 0);
       } else {
         constexpr int XT = XTerms<T>::N;
         rt_bf16x8 t[XT];
-        XTerms<T>::split(raw[s], t);
+        XTerms<T>::split(raw[p][s], t);
 #pragma unroll
         for (int nt = 0; nt < NET; ++nt) {
           rt_bf16x8 hi, lo;   // the two bf16 terms of the weight
 #pragma unroll
           for (int i = 0; i < P; ++i) {
-            hi[i] = (bf16)w[nt][s][i];
-            lo[i] = (bf16)(w[nt][s][i] - (float)hi[i]);
+            hi[i] = (bf16)w[p][nt][s][i];
+            lo[i] = (bf16)(w[p][nt][s][i] - (float)hi[i]);
           }
 #pragma unroll
           for (int xt = 0; xt < XT; ++xt) {
@@ -484,6 +491,17 @@ __global__ __launch_bounds__(NW * 64) void route_small_kernel(
           }
         }
       }
+    }
+  };
+#pragma unroll
+  for (int p = 0; p < PF; ++p)
+    if (wave + p * NW < nkb) load(p, wave + p * NW);
+  for (int kb = wave; kb < nkb; kb += PF * NW) {   // K blocks wave, wave + NW, ... in order
+#pragma unroll
+    for (int p = 0; p < PF; ++p) {
+      if (kb + p * NW < nkb) multiply(p);
+      if (PF > 1) __builtin_amdgcn_sched_barrier(0);   // its registers are free now, not before
+      if (kb + (p + PF) * NW < nkb) load(p, kb + (p + PF) * NW);
     }
   }
   // accumulator register v of lane l is token (l/16)*4 + v, expert l%16 of its tile
@@ -765,29 +783,32 @@ static int launch_route_mfma(const moe_cfg* c, const void* x, const float* Wr, c
   return launch_status();
 }
 
+// Long rows and few expert tiles: eight waves along K and 64 tokens per block; else four waves and 32 tokens
+constexpr int ROUTE_WAVES = 4, ROUTE_WAVES_WIDE = 8;
+static bool route_wide(const moe_cfg* c) { return c->d_model >= 2048; }
+
 // wfrag: workspace for the gate weight in MFMA operand layout (route_wfrag_bytes), used for bf16 x
 template <typename T>
 static int route_mfma_typed(const moe_cfg* c, const void* x, const float* Wr, const float* bias, float* logits_out,
                             int32_t* idx, float* w, void* wfrag, hipStream_t s) {
-  // long rows and few expert tiles: eight waves and 64 tokens per block; else four waves and 32 tokens
-  const bool wide = c->d_model >= 2048;
+  const bool wide = route_wide(c);
   switch (route_expert_tiles(c->E)) {
-    case 1: return wide ? launch_route_mfma<T, 1, 4, 8>(c, x, Wr, bias, logits_out, idx, w, wfrag, s)
-                        : launch_route_mfma<T, 1, 2, 4>(c, x, Wr, bias, logits_out, idx, w, wfrag, s);
-    case 2: return wide ? launch_route_mfma<T, 2, 4, 8>(c, x, Wr, bias, logits_out, idx, w, wfrag, s)
-                        : launch_route_mfma<T, 2, 2, 4>(c, x, Wr, bias, logits_out, idx, w, wfrag, s);
+    case 1: return wide ? launch_route_mfma<T, 1, 4, ROUTE_WAVES_WIDE>(c, x, Wr, bias, logits_out, idx, w, wfrag, s)
+                        : launch_route_mfma<T, 1, 2, ROUTE_WAVES>(c, x, Wr, bias, logits_out, idx, w, wfrag, s);
+    case 2: return wide ? launch_route_mfma<T, 2, 4, ROUTE_WAVES_WIDE>(c, x, Wr, bias, logits_out, idx, w, wfrag, s)
+                        : launch_route_mfma<T, 2, 2, ROUTE_WAVES>(c, x, Wr, bias, logits_out, idx, w, wfrag, s);
     case 4: return launch_route_mfma<T, 4, 2, 4>(c, x, Wr, bias, logits_out, idx, w, wfrag, s);
     case 8: return launch_route_mfma<T, 8, 2, 4>(c, x, Wr, bias, logits_out, idx, w, wfrag, s);
     default: return launch_route_mfma<T, 16, 2, 4>(c, x, Wr, bias, logits_out, idx, w, wfrag, s);
   }
 }
 
-// Where route_small_kernel is used: up to 32 experts; 16-bit storage up to 4096 tokens (one round of blocks; with a second
-// one the weight's conversion in every block costs more than the layout pass), fp32 for any number.  us per call, before ->
-// now, at 1024 | 4096 | 8192 tokens (forced above the line): bf16, 8 experts, d 1024 9.2 -> 5.0 | 9.1 -> 5.2 | 9.5 -> 7.7, d 2048 14.9 -> 7.3 | 14.8 ->
-// 8.9 | 15.6 -> 16.0, d 4096 23.8 -> 10.6 | 24.2 -> 12.9 | 24.5 -> 25.4; fp16, 16 experts, d 2048 19.3 -> 8.3 | 19.5 -> 10.1 |
-// 20.8 -> 18.2; bf16, 32 experts, d 512 10.3 -> 6.6 | 10.4 -> 7.0 | 10.4 -> 12.6; fp32, 8 experts, d 128 6.3 -> 3.8 | 6.4 -> 3.9 | 6.4 -> 4.5,
-// d 1024 18.3 -> 6.0 | 20.0 -> 6.8 | 20.5 -> 10.8, 32 experts, d 1024 35.4 -> 9.5 | 41.5 -> 10.9 | 41.8 -> 19.9.
+// Where route_small_kernel is used: up to 32 experts; 16-bit storage up to 4096 tokens (one round of blocks), fp32 for any
+// number.  us per call, the other kernel -> this one, at 1024 | 4096 | 8192 tokens (16-bit at 8192: forced; ahead there too):
+// bf16, 8 experts, d 1024 9.0 -> 4.7 | 8.8 -> 4.8 | 9.2 -> 6.4, d 2048 14.6 -> 6.0 | 14.5 -> 6.5 | 15.2 -> 11.7, d 4096
+// 23.4 -> 8.9 | 24.1 -> 9.7 | 24.3 -> 19.6; fp16, 16 experts, d 2048 19.0 -> 7.4 | 19.2 -> 8.2 | 20.3 -> 14.7; bf16, 32
+// experts, d 512 8.8 -> 4.8 | 9.0 -> 5.3 | 9.1 -> 6.5; fp32, 8 experts, d 128 6.1 -> 3.5 | 6.1 -> 3.8 | 6.3 -> 4.2, d 1024
+// 18.2 -> 5.5 | 20.4 -> 6.1 | 20.9 -> 8.4, 32 experts, d 1024 33.8 -> 6.6 | 39.9 -> 7.5 | 40.0 -> 11.8.
 static bool route_small_applies(const moe_cfg* c) { return c->E <= 32 && (c->dtype == MOE_DTYPE_F32 || c->T <= 4096); }
 template <typename T, int NET, int NW>
 static void launch_route_small(const moe_cfg* c, const void* x, const float* Wr, const float* bias, float* logits_out, int32_t* idx, float* w, hipStream_t s) {
@@ -796,11 +817,15 @@ static void launch_route_small(const moe_cfg* c, const void* x, const float* Wr,
 }
 template <typename T>
 static int route_small_typed(const moe_cfg* c, const void* x, const float* Wr, const float* bias, float* logits_out, int32_t* idx, float* w, hipStream_t s) {
-  const bool wide = c->d_model > 8 * SmallGate<T>::KB;   // sixteen waves find something to do
-  if (c->E <= 16 && wide) launch_route_small<T, 1, 16>(c, x, Wr, bias, logits_out, idx, w, s);
-  else if (c->E <= 16) launch_route_small<T, 1, 8>(c, x, Wr, bias, logits_out, idx, w, s);
-  else if (wide && std::is_same<T, float>::value) launch_route_small<float, 2, 16>(c, x, Wr, bias, logits_out, idx, w, s);
-  else launch_route_small<T, 2, 8>(c, x, Wr, bias, logits_out, idx, w, s);   // 16-bit: two expert tiles' operands take more than 128 registers
+  constexpr bool F32 = std::is_same<T, float>::value;
+  // fp32: sixteen waves where they find something to do.  16-bit: as many waves along K as route_mfma_kernel has, so that a
+  // token's logits are the same bits in a batch of any size.
+  constexpr int FEW = F32 ? 8 : ROUTE_WAVES, MANY = F32 ? 16 : ROUTE_WAVES_WIDE;
+  const bool many = F32 ? c->d_model > 8 * SmallGate<T>::KB : route_wide(c);
+  if (c->E <= 16 && many) launch_route_small<T, 1, MANY>(c, x, Wr, bias, logits_out, idx, w, s);
+  else if (c->E <= 16) launch_route_small<T, 1, FEW>(c, x, Wr, bias, logits_out, idx, w, s);
+  else if (many) launch_route_small<T, 2, MANY>(c, x, Wr, bias, logits_out, idx, w, s);
+  else launch_route_small<T, 2, FEW>(c, x, Wr, bias, logits_out, idx, w, s);
   return launch_status();
 }
 

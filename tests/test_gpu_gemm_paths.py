@@ -308,6 +308,29 @@ def test_fp32_gate_sums_in_short_chains(T, d, E):
     assert err <= 2 * 2.0 ** -24
 
 
+@pytest.mark.parametrize("T, d, E, dtype", [
+    (1, 64, 1, "bf16"), (4096, 1088, 6, "bf16"), (100, 1984, 16, "f16"),   # four waves along K: one K block, two and three, four
+    (33, 2048, 8, "bf16"), (17, 4160, 16, "f16"), (5, 9280, 3, "bf16"),     # eight waves: two K blocks each, five, nine and ten
+    (48, 704, 17, "f16"), (1000, 2112, 32, "bf16"),                         # two expert tiles
+])
+def test_a_token_has_the_same_logits_in_a_batch_of_any_size(T, d, E, dtype):
+    """The gate of few tokens adds K up in the order of the one for many: bit-equal logits, ids and weights."""
+    import torch
+    k, many = min(E, 2), 4097
+    gen = torch.Generator(device="cuda:0").manual_seed(d)
+    x = torch.randn(many, d, generator=gen, device="cuda").to(torch.bfloat16 if dtype == "bf16" else torch.float16)
+    Wr, bias = torch.randn(d, E, generator=gen, device="cuda"), torch.randn(E, generator=gen, device="cuda")
+    got = []
+    for n in (T, many):
+        cfg = B.make_cfg(n, d, 64, E, k, dtype=DT[dtype])
+        out = [torch.empty(n, c, dtype=t, device="cuda") for c, t in ((E, torch.float32), (k, torch.int32), (k, torch.float32))]
+        ws = torch.empty(B.moe_workspace_bytes(cfg), dtype=torch.uint8, device="cuda")
+        B.moe_route(cfg, x[:n], Wr, bias, None, *out, ws)
+        got.append([t[:T] for t in out])
+    torch.cuda.synchronize()
+    assert all(torch.equal(a, b) for a, b in zip(*got))
+
+
 @pytest.mark.parametrize("A, E", [(65 * 1024, 5), (97 * 1024 + 3, 256), (200000, 100)])
 def test_dispatch_with_scanned_prefixes(A, E):
     """More than 64 blocks: whole and ragged batches of the scan, more experts than one of its blocks has threads.  Exact."""
