@@ -8,12 +8,12 @@ namespace moe {
 // Block tile 256 x 256 (SwiGLU forward: 256 x 128 for each of its two weight matrices), 2 x 4 waves: two
 // waves per SIMD, so one wave's LDS and global traffic hides under the other's MFMAs.  Global loads write LDS
 // directly, two 64-wide K stages for all three operand layouts.
-constexpr int T_BM = 256, T_BN = 256, T_BN_DUAL = 128, T_WGM = 2, T_WGN = 4;
+constexpr int T_BM = 256, T_BN = 256, T_BN_DUAL = 128, T_BN_SEGS = 128, T_WGM = 2, T_WGN = 4;
 int gemm_bf16_tile_rows() { return T_BM; }
 
 // blocks of a weight-gradient launch (dw_block), of two gradients where the second is asked for
-static long long dw_blocks(const GemmArgs& g) {
-  const long long p = (long long)((g.N + T_BN - 1) / T_BN) * ((g.M + T_BM - 1) / T_BM);
+static long long dw_blocks(const GemmArgs& g, int bn = T_BN) {
+  const long long p = (long long)((g.N + bn - 1) / bn) * ((g.M + T_BM - 1) / T_BM);
   return (p + NUM_XCD - 1) / NUM_XCD * NUM_XCD * g.E * (g.C2 != nullptr ? 2 : 1);
 }
 // blocks of a split launch beyond one per tile
@@ -103,11 +103,11 @@ static int launch_pair(const GemmArgs& g1, int max_tiles, const GemmArgs& g2, hi
 
 template <typename ST>
 static int dw_segs_for(const GemmArgs& g1, const DwSegs& s1, const GemmArgs& g2, const DwSegs& s2, hipStream_t s) {
-  constexpr int lds = gemm_bf16_lds_bytes<T_BM, T_BN, false>();
-  auto kern = gemm_bf16_dw_segs_kernel<ST, T_BM, T_BN, T_WGM, T_WGN>;
+  constexpr int BN = T_BN_SEGS, lds = gemm_bf16_lds_bytes<T_BM, BN, false>();
+  auto kern = gemm_bf16_dw_segs_kernel<ST, T_BM, BN, 4, 2>;
   hipError_t err = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
   if (err != hipSuccess) return set_hip_error(err);
-  const long long n1 = dw_blocks(g1), n2 = dw_blocks(g2);
+  const long long n1 = dw_blocks(g1, BN), n2 = dw_blocks(g2, BN);
   if (n1 + n2 > 0x7fffffffll) return MOE_ERR_BAD_SHAPE;
   kern<<<dim3(gemm_bf16_grid(n1 + n2)), T_WGM * T_WGN * 64, lds, s>>>(DwSegsPair{{g1, g2}, {s1, s2}, (int)n1});
   return launch_status();

@@ -77,9 +77,11 @@ template <> struct Half16<f16> {
 };
 
 constexpr int BKT = 64;   // K values per LDS stage: two MFMA K steps; an operand row with contiguous K is one 128-byte line
-// LDS stages: two of a 256-row tile (128 KB), three of a 160-row one (156 KB)
-template <int BM>
-constexpr int gemm_bf16_stages() { return BM == 256 ? 2 : 3; }
+// bytes of an LDS stage, and how many there are: two of 256 x 256 (128 KB), three where the LDS holds them (160 x 256: 156 KB)
+template <int BM, int BN, bool DUAL>
+constexpr int gemm_bf16_stage_bytes() { return BM * BKT * 2 + BN * BKT * 2 * (DUAL ? 2 : 1); }
+template <int BM, int BN, bool DUAL>
+constexpr int gemm_bf16_stages() { return gemm_bf16_stage_bytes<BM, BN, DUAL>() * 3 <= 160 * 1024 ? 3 : 2; }
 
 // ---- LDS layouts -------------------------------------------------------------------------------
 // K-contiguous tile: [rows][BKT] bf16.  The 16-byte chunks of a row are XOR-swizzled with the index
@@ -298,18 +300,17 @@ __device__ __forceinline__ void epilogue_fwd(const OutPlanes& o, const unsigned 
   }
 }
 
-template <int BM, int BN, bool DUAL>
-constexpr int gemm_bf16_stage_bytes() { return BM * BKT * 2 + BN * BKT * 2 * (DUAL ? 2 : 1); }
 // TAB: a GELU table (the GELU epilogues) sits behind two stages; three leave no room, it then takes the stage that is free
 // before the loop's last two iterations
 template <int BM, int BN, bool DUAL, bool TAB = false>
 constexpr int gemm_bf16_lds_bytes() {
-  return gemm_bf16_stages<BM>() * gemm_bf16_stage_bytes<BM, BN, DUAL>() + (TAB && gemm_bf16_stages<BM>() == 2 ? GELU_TAB_FLOATS * 4 : 0);
+  return gemm_bf16_stages<BM, BN, DUAL>() * gemm_bf16_stage_bytes<BM, BN, DUAL>() + (TAB && gemm_bf16_stages<BM, BN, DUAL>() == 2 ? GELU_TAB_FLOATS * 4 : 0);
 }
 
 // One output tile; vb = the tile's number in dispatch order.  Block-uniform control flow; returns at
 // once for numbers past the last tile (the grid is sized for the worst case).
-// SEGS (weight gradients): the K range is that of several calls, one after the other through one pipeline.
+// SEGS (weight gradients): the K range is that of several calls, one after the other through one pipeline, each call's
+// products in a sum of their own that is added to the total: the sums, and their rounding, of call after call.
 template <typename ST, int MODE, int EPI, bool DUAL, bool CHAIN, int BM, int BN, int WGM, int WGN, bool SEGS = false>
 __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs& g, const int vb, char* smem, const DwSegs* segs = nullptr) {
   constexpr int NT = WGM * WGN * 64;
@@ -320,7 +321,7 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs& g, const int vb, 
   constexpr bool B_KC = (MODE == MODE_NT);
   constexpr int A_BYTES = BM * BKT * 2, B_BYTES = BN * BKT * 2;
   constexpr int STAGE = gemm_bf16_stage_bytes<BM, BN, DUAL>();
-  constexpr int NBUF = gemm_bf16_stages<BM>();
+  constexpr int NBUF = gemm_bf16_stages<BM, BN, DUAL>();
   constexpr bool TAB = (EPI == EPI_GELU_BWD || EPI == EPI_GELU_FWD) && Half16<ST>::GELU_TABLE;
   static_assert(KS == 2 && (NBUF == 2 || NBUF == 3), "the pipeline below: two or three stages of two K steps");
 
@@ -427,6 +428,7 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs& g, const int vb, 
       acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
       if constexpr (DUAL) acc2[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
+  f32x4 total[SEGS ? TM : 1][SEGS ? TNN : 1] = {};
 
   const int KT = (klen + BKT - 1) / BKT;
   int tab_stage = 0;   // (three stages) the buffer that ends up with the GELU table
@@ -502,6 +504,23 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs& g, const int vb, 
       rb = make_rsrc(reinterpret_cast<const bf16*>(b) + r0 * g.N + n0, ((size_t)rows * g.N - n0) * 2);
       seg_k = 0;
       seg_n = (rows + BKT - 1) / BKT;
+    };
+    int mul_seg = -1, mul_end = 0;   // SEGS: the segment that is being multiplied and the stage behind its last
+    auto next_product = [&]() {
+      int rows;
+      do rows = __builtin_amdgcn_readlane(seg_rows, ++mul_seg); while (rows == 0 && mul_seg + 1 < DW_MAX_SEGS);
+      mul_end += (rows + BKT - 1) / BKT;
+    };
+    auto end_of_stage = [&](int stage) {   // the last one of a segment: its sum joins the total
+      if (stage + 1 != mul_end) return;
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TNN; ++j) {
+          total[SEGS ? i : 0][SEGS ? j : 0] += acc[i][j];
+          acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+      if (mul_end < seg_stages) next_product();
     };
     const int KT1 = KT;                      // stages of one operand pair
     const int KTT = SEGS ? seg_stages : !CHAIN ? KT1 : part_stages > 0 ? part_stages : 2 * KT1;   // stages in all
@@ -638,6 +657,7 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs& g, const int vb, 
     else { const int t__ = b0; b0 = b1; b1 = b2; b2 = t__; }                                                \
   } while (0)
       if (KTT > 0) {
+        if constexpr (SEGS) next_product();
         int b0 = 0, b1 = STAGE, b2 = 2 * STAGE;
 #pragma unroll
         for (int q = 0; q < NBUF; ++q)
@@ -656,10 +676,14 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs& g, const int vb, 
     MOE_FRAGS(0, b0, 0);                                                                        \
     __builtin_amdgcn_s_waitcnt(WAIT_LGKM0);   /* nothing pending at the loop head: the waits inside the loop then count only its own reads */ \
     int S = 0;                                                                                  \
-    _Pragma("unroll 1") for (; S + NBUF < KTT; ++S) MOE_ITER(S, true, true, true, NI_);          \
+    _Pragma("unroll 1") for (; S + NBUF < KTT; ++S) {                                            \
+      MOE_ITER(S, true, true, true, NI_);                                                       \
+      if constexpr (SEGS) end_of_stage(S);                                                      \
+    }                                                                                           \
     _Pragma("unroll 1") for (; S < KTT; ++S) {                                                   \
       const int free__ = b0;                                                                    \
       MOE_ITER(S, S + 1 < KTT, NBUF == 2 && S + 2 < KTT, S + 2 < KTT, NI_);                      \
+      if constexpr (SEGS) end_of_stage(S);                                                      \
       if constexpr (TAB && NBUF == 3) { if (S + 3 == KTT) load_table(free__); }                  \
     }                                                                                           \
   } while (0)
@@ -687,6 +711,12 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs& g, const int vb, 
   // slows a main loop by as much as the writing takes, so that staggered blocks gain nothing.
   constexpr int C = WTN * 32;
   if (wn * C >= nvalid) return;
+  if constexpr (SEGS) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TNN; ++j) acc[i][j] = total[i][j];
+  }
   const int grp = lane >> 4, r8 = lane & 7, right = (lane >> 3) & 1;   // after swap8: row of eight, left or right half of a line
   auto band_row = [&](int i) { return ((i >> 1) * WGM + wm) * 32 + (i & 1) * 16; };   // first row of row tile i
   auto empty = [&](int i) { return band_row(i) >= mvalid; };
@@ -886,9 +916,10 @@ __global__ __launch_bounds__(WGM* WGN * 64, 1) void gemm_bf16_pair_kernel(GemmAr
 
 // Both weight gradients over the rows of several calls: blocks below `first_blocks` take a tile of the first.
 // Per call, a micro-batch of 512 rows per expert has eight K stages of arithmetic per tile and moves 512 KB of old and new
-// sums for it; over all calls the sums are written once.  Four micro-batches of 2048 tokens, d 1024, f 4096, eight experts:
-// backward GEMMs 1040 us with the gradients accumulated call by call in launches shared with dH and dx, 4 x 122 + 278 now,
-// an iteration 1939 -> 1670.
+// sums for it; over all calls the sums are written once.  Tiles of 256 x 128, whose registers hold the call's sum and the
+// total: one chain over all calls would round more often (four calls of 512 rows, simulated: 0.85e-7 -> 1.4e-7 of the
+// gradient).  Four micro-batches of 2048 tokens, d 1024, f 4096, eight experts: backward GEMMs 1040 us with the gradients
+// accumulated call by call in launches shared with dH and dx; 4 x 88 + 335 now, 284 of them in 256 x 256 tiles and one chain.
 struct DwSegsPair { GemmArgs g[2]; DwSegs s[2]; int first_blocks; };
 template <typename ST, int BM, int BN, int WGM, int WGN>
 __global__ __launch_bounds__(WGM* WGN * 64, 1) void gemm_bf16_dw_segs_kernel(DwSegsPair p) {

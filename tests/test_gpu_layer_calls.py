@@ -133,6 +133,40 @@ def test_weight_gradients_over_several_calls(T, d, f, E, k, dtype, act, n, acc):
         assert (g.double() - w).norm() <= 1e-5 * w.norm()      # fp32 sums
 
 
+@pytest.mark.parametrize("T, d, f, E, k, dtype, act, n", [
+    (40, 64, 192, 6, 1, "bf16", B.ACT_GELU, 9),        # a second pass of one call
+    (300, 320, 576, 3, 2, "f16", B.ACT_SWIGLU, 3),
+    (1100, 192, 320, 2, 1, "bf16", B.ACT_SWIGLU, 2),
+    (50, 36, 68, 3, 1, "f32", B.ACT_SWIGLU, 3),
+])
+def test_weight_gradients_over_several_calls_are_those_of_call_after_call(T, d, f, E, k, dtype, act, n):
+    """One pass over all calls has the very sums of a backward after the other that accumulates: no longer chains."""
+    import torch
+    from paper_2504_03871_amd.layer import MoELayer
+    first = filled_layer(T, d, f, E, k, dtype, act, seed=1)
+    calls = [first] + [MoELayer(T, d, f, E, k, dtype=first.cfg.dtype, act=act, params=first) for _ in range(n - 1)]
+    gen = torch.Generator(device="cuda:0").manual_seed(2)
+    for m in calls:
+        for t in (m.x, m.d_out):
+            t.copy_(torch.randn(t.shape, generator=gen, device="cuda"))
+        m.forward()
+    if n > 2:
+        calls[1].set_slices([0] * E, [0] * E)                                # a call without any rows
+        calls[-1].set_slices([0] * E, [T * k if e == 1 else 0 for e in range(E)])
+    grads = [g for g in (first.dW1, first.dW1b, first.dW2) if g is not None]
+    for j, m in enumerate(calls):
+        m.backward(1 if j > 0 else 0)
+    want = [g.clone() for g in grads]
+    for g in grads:
+        g.fill_(U.SENTINEL)
+    for m in calls:
+        m.backward_inputs()
+    MoELayer.expert_dw(calls)
+    torch.cuda.synchronize()
+    for g, w in zip(grads, want):
+        assert torch.equal(g, w)
+
+
 @pytest.mark.parametrize("T, d, f, E, k, dtype, act", [
     (700, 192, 2112, 4, 2, "bf16", B.ACT_GELU),        # 33 stages in eight parts
     (700, 192, 1088, 4, 2, "f16", B.ACT_SWIGLU),       # 17 and 17 stages of two products, a part across the seam
