@@ -303,7 +303,8 @@ static int launch_bm(const GemmArgs& g, int max_tiles, hipStream_t s) {
   gemm_f32_kernel<MODE, EPI, DUAL, CHAIN, BM><<<dim3((unsigned)blocks), 256, 0, s>>>(g);
   return launch_status();
 }
-static int dw_tile_rows(const GemmArgs& g) { return f32_tile_rows((long long)g.M * g.E * (g.C2 != nullptr ? 2 : 1), 0, g.N); }
+// by one gradient's tiles, also where two share the launch: the height decides how many chains a sum is made of
+static int dw_tile_rows(const GemmArgs& g) { return f32_tile_rows((long long)g.M * g.E, 0, g.N); }
 // tile_rows: rows per entry of the tile map (row-tile GEMMs)
 template <int MODE, int EPI, bool DUAL, bool CHAIN>
 static int launch_one(const GemmArgs& g, int tile_rows, int max_tiles, hipStream_t s) {

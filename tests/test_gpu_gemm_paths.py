@@ -63,6 +63,41 @@ def test_fp32_gemms_at_tile_and_stage_edges(T, d, f, E, k, act):
     run_case(S.WORKLOADS["cfg0"].scaled(T=T, d=d, f=f, E=E, k=k, act=act))
 
 
+@pytest.mark.parametrize("T, d, f, dtype, act, per_rounding, chains", [
+    (1920, 256, 1024, "f32", B.ACT_SWIGLU, 1, 2),    # 512 tiles of 64 rows per gradient: 32-row tiles, two chains per sum
+    (512, 256, 1024, "f32", B.ACT_SWIGLU, 1, 2),
+    (1920, 256, 1024, "f32", B.ACT_GELU, 1, 2),
+    (2000, 516, 1540, "f32", B.ACT_SWIGLU, 1, 1),    # 64-row tiles
+    (1920, 256, 1024, "bf16", B.ACT_SWIGLU, 8, 1),
+    (8192, 256, 1024, "f16", B.ACT_GELU, 8, 1),
+])
+def test_weight_gradient_sums_round_as_seldom_as_their_chains_say(T, d, f, dtype, act, per_rounding, chains):
+    """Weight gradients against fp64 products of the stored tensors.  A rounding is off by 0.425 u of the partial sum
+    (u = 2^-24; uniform within half a unit, evenly spread logarithms), and like-sized products in random order make partial
+    sums whose squares grow evenly: a chain of L roundings is off by 0.425 u sqrt(L / 2) = 0.30 u sqrt(L).  fp32 instructions
+    round after every product, 16-bit ones after eight.  Bound: a tenth more."""
+    import torch
+    E, k = 8, 2
+    L = filled_layer(T, d, f, E, k, dtype, act)
+    L.forward()
+    L.combine_bwd()
+    L.ffn_bwd()
+    torch.cuda.synchronize()
+    planes, n = 2 if act == B.ACT_SWIGLU else 1, T * k * f * L.x.element_size()
+    dact = L.ws[L.ws.numel() - planes * n:].view(L.tdtype).view(planes, T * k, f).double()    # the workspace's last region
+    pairs = [(L.x_perm.double(), dact[i], g) for i, g in enumerate([L.dW1, L.dW1b][:planes])] + [(L.saved_plane(planes).double(), L.dy_perm.double(), L.dW2)]
+    for a, b, g in pairs:
+        err = size = roundings = 0.0
+        for e in range(E):
+            r = slice(int(L.offsets[e]), int(L.offsets[e + 1]))
+            want = a[r].t() @ b[r]
+            err += float((g[e].double() - want).norm() ** 2)
+            size += float(want.norm() ** 2)
+            roundings += float(want.norm() ** 2) * (r.stop - r.start) / per_rounding / chains
+        print(f"{dtype} {T} {d} {f}: {(err / size) ** 0.5 * 2 ** 24:.2f} u, {0.3 * (roundings / size) ** 0.5:.2f} u expected")
+        assert (err / size) ** 0.5 <= 1.1 * 0.3 * (roundings / size) ** 0.5 * 2.0 ** -24
+
+
 @pytest.mark.parametrize("dtype, d, f", [("f32", 36, 68), ("bf16", 64, 64)])
 def test_a_row_with_nan_stays_in_its_row(dtype, d, f):
     """What lies behind the last K value of a row (the next row) takes no part in its sums."""
