@@ -321,10 +321,14 @@ MOE_API int moe_layer_bwd(const moe_cfg* cfg, const moe_layer_bufs* b, int32_t a
  * (same cfg, each with buffers and a workspace of its own, untouched since) into the buffers of calls[0], overwriting or,
  * accumulate != 0, adding to them: 16-bit storage multiplies the rows of up to eight calls through one pass over the
  * gradients instead of reading and writing them once per call.
- * A workspace of moe_layer_bwd_inputs_ws_bytes (at least moe_workspace_bytes) lets dx's last round of tiles be split.
+ * dx's last round of tiles can be split where there is room for its partial sums, which is free again when the call is
+ * done: behind the workspace, if that has moe_layer_bwd_inputs_ws_bytes (at least moe_workspace_bytes), or, for any number
+ * of calls on one stream, in a `room` of moe_layer_bwd_inputs_room_bytes (0: dx is never split; room may be NULL: not split).
  */
 MOE_API int moe_layer_bwd_inputs_ws_bytes(const moe_cfg* cfg, size_t* bytes);
 MOE_API int moe_layer_bwd_inputs(const moe_cfg* cfg, const moe_layer_bufs* b, int32_t accumulate, void* stream);
+MOE_API int moe_layer_bwd_inputs_room_bytes(const moe_cfg* cfg, size_t* bytes);
+MOE_API int moe_layer_bwd_inputs_in(const moe_cfg* cfg, const moe_layer_bufs* b, void* room, size_t room_bytes, int32_t accumulate, void* stream);
 MOE_API int moe_layer_expert_dw(const moe_cfg* cfg, const moe_layer_bufs* const* calls, int32_t n, int32_t accumulate, void* stream);
 
 /*

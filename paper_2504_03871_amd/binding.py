@@ -20,6 +20,7 @@ MAX_E, MAX_K = 256, 8
 SYMBOLS = ("moe_error_string", "moe_last_hip_error", "moe_workspace_bytes", "moe_saved_bytes", "moe_route",
            "moe_dispatch", "moe_dispatch_static", "moe_expert_ffn_fwd", "moe_expert_ffn_fwd_light", "moe_expert_ffn_recompute", "moe_combine", "moe_combine_bwd", "moe_expert_ffn_bwd",
            "moe_route_bwd", "moe_layer_fwd", "moe_layer_bwd", "moe_layer_bwd_inputs_ws_bytes", "moe_layer_bwd_inputs",
+           "moe_layer_bwd_inputs_room_bytes", "moe_layer_bwd_inputs_in",
            "moe_layer_expert_dw", "moe_asymea_plan", "moe_asymea_shares", "moe_bench_stream", "moe_bench_clock_probe", "moe_bench_mfma_loop", "moe_gemm_block_tile")
 
 PROF = {"gemm1_fwd": 0, "gemm2_fwd": 1, "dh_bwd": 2, "dw2_bwd": 3, "dw1_bwd": 4, "dx_bwd": 5, "gather": 6,
@@ -84,6 +85,8 @@ def lib():
             "moe_layer_bwd": [cfgp, p, i32, p],
             "moe_layer_bwd_inputs_ws_bytes": [cfgp, ctypes.POINTER(ctypes.c_size_t)],
             "moe_layer_bwd_inputs": [cfgp, p, i32, p],
+            "moe_layer_bwd_inputs_room_bytes": [cfgp, ctypes.POINTER(ctypes.c_size_t)],
+            "moe_layer_bwd_inputs_in": [cfgp, p, p, sz, i32, p],
             "moe_layer_expert_dw": [cfgp, p, i32, i32, p],
             "moe_asymea_plan": [i32] * 4 + [ctypes.c_double] * 3 + [i32, i32, ctypes.POINTER(i32)],
             "moe_asymea_shares": [i32] * 6 + [ctypes.POINTER(i32), ctypes.POINTER(i32)],
@@ -261,10 +264,22 @@ def moe_layer_bwd_inputs_ws_bytes(cfg) -> int:
     return n.value
 
 
+def moe_layer_bwd_inputs_room_bytes(cfg) -> int:
+    n = ctypes.c_size_t(0)
+    _check("moe_layer_bwd_inputs_room_bytes", lib().moe_layer_bwd_inputs_room_bytes(ctypes.byref(cfg), ctypes.byref(n)))
+    return n.value
+
+
 def moe_layer_bwd_inputs(cfg, bufs, accumulate=0, stream=None):
     """moe_layer_bwd without the expert weight gradients."""
     _check("moe_layer_bwd_inputs", lib().moe_layer_bwd_inputs(ctypes.byref(cfg), _layer_bufs(bufs), int(accumulate),
                                                               _stream() if stream is None else stream))
+
+
+def moe_layer_bwd_inputs_in(cfg, bufs, room, accumulate=0, stream=None):
+    """The same with dx's partial sums in `room` (a tensor, or None)."""
+    _check("moe_layer_bwd_inputs_in", lib().moe_layer_bwd_inputs_in(ctypes.byref(cfg), _layer_bufs(bufs), _ptr(room), _nbytes(room), int(accumulate),
+                                                                    _stream() if stream is None else stream))
 
 
 def moe_layer_expert_dw(cfg, calls, accumulate=0, stream=None):

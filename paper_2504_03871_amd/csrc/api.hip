@@ -612,8 +612,8 @@ int moe_route_bwd(const moe_cfg* cfg, const void* x, const float* Wr, const int3
 }
 
 namespace {
-// Room for dx's partial sums behind the workspace of a backward that leaves the weight gradients to a later call: the
-// chip has nothing else to do beside dx's last round then
+// Room for dx's partial sums in a backward that leaves the weight gradients to a later call: the chip has nothing else to
+// do beside dx's last round then
 size_t inputs_split_bytes(const moe_cfg* c) {
   if (!is_half(c) || (c->act == MOE_ACT_SWIGLU ? 2 : 1) * c->d_ff < SPLIT_MIN_K) return 0;
   const bool small = c->act == MOE_ACT_GELU && splits_small_tiles(c);
@@ -671,7 +671,8 @@ int moe_layer_fwd(const moe_cfg* cfg, const moe_layer_bufs* b, int32_t mode, voi
 }
 
 namespace {
-int layer_bwd(const moe_cfg* cfg, const moe_layer_bufs* b, int32_t accumulate, bool inputs_only, void* stream) {
+// room: inputs_split_bytes for dx's partial sums, or NULL
+int layer_bwd(const moe_cfg* cfg, const moe_layer_bufs* b, int32_t accumulate, bool inputs_only, float* room, void* stream) {
   CHECK(check_layer(cfg, b, false, true, !inputs_only));
   if (cfg->T == 0)
     return moe_route_bwd(cfg, b->x, b->Wr, b->topk_idx, b->topk_w, b->d_topk_w, b->d_logits, b->dWr, b->dx, accumulate, b->ws, b->ws_bytes, stream);
@@ -685,19 +686,37 @@ int layer_bwd(const moe_cfg* cfg, const moe_layer_bufs* b, int32_t accumulate, b
     CHECK(launch_combine_bwd(cfg, b->d_out, b->y_perm, b->topk_w, b->topk_idx, b->row_of, b->offsets, b->kept, b->slice_lo, b->slice_hi, b->dy_perm,
                              b->d_topk_w, &side, s));
   }
-  const size_t room = inputs_only ? inputs_split_bytes(cfg) : 0, behind = align_up(w.total, 256);
-  float* dx_sums = room > 0 && b->ws_bytes >= behind + room ? reinterpret_cast<float*>(ws + behind) : nullptr;
   CHECK(ffn_bwd_impl(cfg, b->dy_perm, b->x_perm, b->saved, b->W1, b->W1b, b->W2, b->offsets, b->kept, b->slice_lo, b->slice_hi, b->dx_perm, b->dW1,
-                     b->dW1b, b->dW2, accumulate, b->ws, true, s, inputs_only, dx_sums));
+                     b->dW1b, b->dW2, accumulate, b->ws, true, s, inputs_only, room));
   const bool dwr = input_grad_has_dwr(cfg);
   CHECK(launch_input_grad(cfg, b, wrt, partials, dwr, s));
   return launch_gate_dwr(cfg, b->x, b->d_logits, b->dWr, accumulate != 0, partials, dwr, s);
 }
 }  // namespace
 
-int moe_layer_bwd(const moe_cfg* cfg, const moe_layer_bufs* b, int32_t accumulate, void* stream) { return layer_bwd(cfg, b, accumulate, false, stream); }
+int moe_layer_bwd(const moe_cfg* cfg, const moe_layer_bufs* b, int32_t accumulate, void* stream) { return layer_bwd(cfg, b, accumulate, false, nullptr, stream); }
 
-int moe_layer_bwd_inputs(const moe_cfg* cfg, const moe_layer_bufs* b, int32_t accumulate, void* stream) { return layer_bwd(cfg, b, accumulate, true, stream); }
+int moe_layer_bwd_inputs(const moe_cfg* cfg, const moe_layer_bufs* b, int32_t accumulate, void* stream) {
+  CHECK(check_layer(cfg, b, false, true, false));
+  const size_t room = inputs_split_bytes(cfg), behind = align_up(ws_layout(cfg).total, 256);
+  const bool there = room > 0 && b->ws_bytes >= behind + room;
+  return layer_bwd(cfg, b, accumulate, true, there ? reinterpret_cast<float*>(static_cast<char*>(b->ws) + behind) : nullptr, stream);
+}
+
+int moe_layer_bwd_inputs_in(const moe_cfg* cfg, const moe_layer_bufs* b, void* room, size_t room_bytes, int32_t accumulate, void* stream) {
+  CHECK(check_cfg(cfg));
+  ALIGNED(room);
+  const size_t need = inputs_split_bytes(cfg);
+  if (room != nullptr && room_bytes < need) return MOE_ERR_WORKSPACE;
+  return layer_bwd(cfg, b, accumulate, true, need > 0 ? static_cast<float*>(room) : nullptr, stream);
+}
+
+int moe_layer_bwd_inputs_room_bytes(const moe_cfg* cfg, size_t* bytes) {
+  CHECK(check_cfg(cfg));
+  REQUIRE(bytes);
+  *bytes = inputs_split_bytes(cfg);
+  return MOE_OK;
+}
 
 int moe_layer_bwd_inputs_ws_bytes(const moe_cfg* cfg, size_t* bytes) {
   CHECK(check_cfg(cfg));

@@ -16,7 +16,7 @@ class MoELayer:
                  params=None, defer_dw=False):
         """`params`: another MoELayer whose weights and weight-gradient buffers this one aliases (one
         layer seen by several micro-batches, each with activation buffers of its own).  `defer_dw`: backward_inputs
-        will be used, with a workspace for it."""
+        will be used, with room for it behind the workspace."""
         self.cfg = B.make_cfg(T, d_model, d_ff, E, k, dtype, act, capacity)
         self.T, self.d, self.f, self.E, self.k, self.act = T, d_model, d_ff, E, k, act
         self.tdtype = {B.DTYPE_BF16: torch.bfloat16, B.DTYPE_F16: torch.float16}.get(dtype, torch.float32)
@@ -146,9 +146,12 @@ class MoELayer:
             return self.backward_overlapped(accumulate)
         B.moe_layer_bwd(self.cfg, self.bufs(), accumulate)
 
-    def backward_inputs(self, accumulate=0):
-        """The backward without the expert weight gradients (`accumulate`: the gate's); expert_dw adds them up."""
-        B.moe_layer_bwd_inputs(self.cfg, self.bufs(), accumulate)
+    def backward_inputs(self, accumulate=0, room=None):
+        """The backward without the expert weight gradients (`accumulate`: the gate's); expert_dw adds them up.  `room`:
+        scratch of moe_layer_bwd_inputs_room_bytes that layers whose calls follow each other on a stream can share."""
+        if room is None:
+            return B.moe_layer_bwd_inputs(self.cfg, self.bufs(), accumulate)
+        B.moe_layer_bwd_inputs_in(self.cfg, self.bufs(), room, accumulate)
 
     @staticmethod
     def expert_dw(calls, accumulate=0):

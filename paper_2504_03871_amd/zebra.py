@@ -50,10 +50,12 @@ class ZebraExpertEngine:
         self.L, self.R, self.T_mb = L, R, T_mb
         self.device = torch.device(device)
         # one parameter set per layer; one set of activation buffers per (layer, micro-batch)
-        self.params = [MoELayer(T_mb, d_model, d_ff, E, k, dtype, act, device=device, defer_dw=True) for _ in range(L)]
+        self.params = [MoELayer(T_mb, d_model, d_ff, E, k, dtype, act, device=device) for _ in range(L)]
         self.mb = [[self.params[i] if j == 0 else
-                    MoELayer(T_mb, d_model, d_ff, E, k, dtype, act, device=device, params=self.params[i], defer_dw=True)
+                    MoELayer(T_mb, d_model, d_ff, E, k, dtype, act, device=device, params=self.params[i])
                     for j in range(R)] for i in range(L)]
+        # scratch of a backward, one for all of them: they follow each other on the compute stream
+        self.room = torch.empty(B.moe_layer_bwd_inputs_room_bytes(self.params[0].cfg), dtype=torch.uint8, device=self.device)
         td = self.params[0].tdtype
         buf = lambda: [torch.empty(T_mb, d_model, dtype=td, device=self.device) for _ in range(R)]
         # the attention side: what it sends into layer i (act[i]), what comes out of the last layer
@@ -100,7 +102,7 @@ class ZebraExpertEngine:
                     self.recv_b[i][j].record(self.combine)
                 with torch.cuda.stream(self.compute):            # E^B_{i,j}
                     self.compute.wait_event(self.recv_b[i][j])
-                    m.backward_inputs(accumulate=1 if j > 0 else 0)
+                    m.backward_inputs(accumulate=1 if j > 0 else 0, room=self.room)
                     self.done_b[i][j].record(self.compute)
                     if j == R - 1:
                         MoELayer.expert_dw(self.mb[i])

@@ -259,3 +259,17 @@ def test_weight_gradients_over_calls_validate_before_any_launch():
     assert code(n=1, dW1=0) == -1 and code(n=1, dW2=Q) == -5 and code(n=1, dW1b=P) == -3
     assert lib.moe_layer_expert_dw(ctypes.byref(cfg), None, 1, 0, None) == -1
     assert B.moe_layer_bwd_inputs_ws_bytes(cfg) >= B.moe_workspace_bytes(cfg)
+
+
+def test_room_of_the_split_input_gradient_is_checked_before_any_launch():
+    import ctypes
+    cfg = B.make_cfg(2048, 256, 4096, 4, 2, act=B.ACT_GELU)
+    lib, P = B.lib(), 0x10000
+    need = B.moe_layer_bwd_inputs_room_bytes(cfg)
+    assert need > 0 and B.moe_layer_bwd_inputs_ws_bytes(cfg) == -(-B.moe_workspace_bytes(cfg) // 256) * 256 + need
+    assert B.moe_layer_bwd_inputs_room_bytes(B.make_cfg(2048, 256, 1024, 4, 2)) == 0     # K too short to split
+    bufs = (ctypes.c_size_t * (len(B.LAYER_BUFS) + 1))()
+    call = lambda room, n: lib.moe_layer_bwd_inputs_in(ctypes.byref(cfg), bufs, ctypes.c_void_p(room), ctypes.c_size_t(n), 0, None)
+    assert call(P, need - 1) == -7 and call(P + 8, need) == -5
+    assert call(P, need) == call(0, 0) == -1                                             # the room is fine, the buffers are not
+    assert lib.moe_layer_bwd_inputs_in(ctypes.byref(cfg), None, None, ctypes.c_size_t(0), 0, None) == -1

@@ -86,3 +86,30 @@ def test_micro_batched_streams_equal_the_whole_batch(name):
     U.assert_close("engine input gradient vs oracle", U.host(g0), ref["dx"], U.TOL[w.dtype])
     for n, key in (("dW1", "dW1"), ("dW2", "dW2"), ("dWr", "dWr")) + ((("dW1b", "dW1b"),) if w.act == S.ACT_SWIGLU else ()):
         U.assert_close(f"engine layer 0 {n} vs oracle", U.host(getattr(eng.params[0], n)), ref[key], U.TOL[w.dtype])
+
+
+def test_one_room_for_the_split_input_gradients_of_all_micro_batches():
+    """The engine keeps one scratch for dx's partial sums, not one per (layer, micro-batch), and splits dx as a layer with
+    a room of its own does."""
+    import torch
+    from paper_2504_03871_amd import binding as B
+    from paper_2504_03871_amd.layer import MoELayer
+    from paper_2504_03871_amd.zebra import ZebraExpertEngine
+    T, d, f, E, k, R = 700, 192, 2112, 4, 2, 3
+    eng = ZebraExpertEngine(1, R, T, d, f, E, k)
+    cfg = eng.params[0].cfg
+    assert eng.room.numel() == B.moe_layer_bwd_inputs_room_bytes(cfg) > 0
+    assert all(m.ws.numel() == B.moe_workspace_bytes(cfg) for m in eng.mb[0])
+    gen = torch.Generator(device="cuda:0").manual_seed(4)
+    p = eng.params[0]
+    for t, std in [(p.Wr, d ** -0.5), (p.W1, d ** -0.5), (p.W2, f ** -0.5)] + [(t, 1.0) for t in eng.act[0] + eng.grad[1]]:
+        t.copy_(torch.randn(t.shape, generator=gen, device="cuda") * std)
+    eng.run_iteration()
+    own = MoELayer(T, d, f, E, k, params=p, defer_dw=True)
+    for j in range(R):
+        own.x.copy_(eng.act[0][j])
+        own.d_out.copy_(eng.grad[1][j])
+        own.forward()
+        own.backward_inputs()
+        torch.cuda.synchronize()
+        assert torch.equal(bits(eng.act[1][j]), bits(own.out)) and torch.equal(bits(eng.grad[0][j]), bits(own.dx))
