@@ -243,6 +243,16 @@ MOE_API int moe_expert_ffn_bwd(const moe_cfg* cfg, const void* dy_perm, const vo
                        void* ws, size_t ws_bytes, void* stream);
 
 /*
+ * The same without the weight gradients, which moe_layer_expert_dw adds up later from what this call leaves in `ws`.
+ * `room`: as in moe_layer_bwd_inputs_in below.
+ */
+MOE_API int moe_expert_ffn_bwd_inputs(const moe_cfg* cfg, const void* dy_perm, const void* saved,
+                       const void* W1, const void* W1b, const void* W2,
+                       const int32_t* offsets, const int32_t* kept,
+                       const int32_t* slice_lo, const int32_t* slice_hi,
+                       void* dx_perm, void* room, size_t room_bytes, void* ws, size_t ws_bytes, void* stream);
+
+/*
  * Gate backward (Section 5: the branch through the confidence scores to the gate weights and to
  * the block input, accumulated with the gradient that comes back through the experts).
  * g = sum_j w_j dw_j;  d_logits[t][e_j] = w_j (dw_j - g), 0 for unselected experts;

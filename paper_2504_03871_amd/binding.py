@@ -18,7 +18,7 @@ ACT_GELU, ACT_SWIGLU = 0, 1
 MAX_E, MAX_K = 256, 8
 
 SYMBOLS = ("moe_error_string", "moe_last_hip_error", "moe_workspace_bytes", "moe_saved_bytes", "moe_route",
-           "moe_dispatch", "moe_dispatch_static", "moe_expert_ffn_fwd", "moe_expert_ffn_fwd_light", "moe_expert_ffn_recompute", "moe_combine", "moe_combine_bwd", "moe_expert_ffn_bwd",
+           "moe_dispatch", "moe_dispatch_static", "moe_expert_ffn_fwd", "moe_expert_ffn_fwd_light", "moe_expert_ffn_recompute", "moe_combine", "moe_combine_bwd", "moe_expert_ffn_bwd", "moe_expert_ffn_bwd_inputs",
            "moe_route_bwd", "moe_layer_fwd", "moe_layer_bwd", "moe_layer_bwd_inputs_ws_bytes", "moe_layer_bwd_inputs",
            "moe_layer_bwd_inputs_room_bytes", "moe_layer_bwd_inputs_in",
            "moe_layer_expert_dw", "moe_asymea_plan", "moe_asymea_shares", "moe_bench_stream", "moe_bench_clock_probe", "moe_bench_mfma_loop", "moe_gemm_block_tile")
@@ -80,6 +80,7 @@ def lib():
             "moe_combine": [cfgp] + [p] * 9 + [i32, p],
             "moe_combine_bwd": [cfgp] + [p] * 12,
             "moe_expert_ffn_bwd": [cfgp] + [p] * 14 + [i32, p, sz, p],
+            "moe_expert_ffn_bwd_inputs": [cfgp] + [p] * 11 + [sz, p, sz, p],
             "moe_route_bwd": [cfgp] + [p] * 8 + [i32, p, sz, p],
             "moe_layer_fwd": [cfgp, p, i32, p],
             "moe_layer_bwd": [cfgp, p, i32, p],
@@ -221,6 +222,12 @@ def moe_expert_ffn_bwd(cfg, dy_perm, x_perm, saved, W1, W1b, W2, offsets, kept, 
                                                           _ptr(dW1b), _ptr(dW2), int(accumulate), _ptr(ws),
                                                           _nbytes(ws) if ws_bytes is None else ws_bytes,
                                                           _stream() if stream is None else stream))
+
+
+def moe_expert_ffn_bwd_inputs(cfg, dy_perm, saved, W1, W1b, W2, offsets, kept, lo, hi, dx_perm, room, ws, stream=None):
+    _check("moe_expert_ffn_bwd_inputs", lib().moe_expert_ffn_bwd_inputs(
+        ctypes.byref(cfg), _ptr(dy_perm), _ptr(saved), _ptr(W1), _ptr(W1b), _ptr(W2), _ptr(offsets), _ptr(kept), _ptr(lo), _ptr(hi),
+        _ptr(dx_perm), _ptr(room), _nbytes(room), _ptr(ws), _nbytes(ws), _stream() if stream is None else stream))
 
 
 def moe_route_bwd(cfg, x, Wr, topk_idx, topk_w, d_topk_w, d_logits, dWr, dx, ws, accumulate=0, stream=None,

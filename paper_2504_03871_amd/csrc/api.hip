@@ -589,6 +589,42 @@ int moe_expert_ffn_bwd(const moe_cfg* cfg, const void* dy_perm, const void* x_pe
                       ws, false, (hipStream_t)stream);
 }
 
+namespace {
+// Room for dx's partial sums in a backward that leaves the weight gradients to a later call: the chip has nothing else to
+// do beside dx's last round then
+size_t inputs_split_bytes(const moe_cfg* c) {
+  if (!is_half(c) || (c->act == MOE_ACT_SWIGLU ? 2 : 1) * c->d_ff < SPLIT_MIN_K) return 0;
+  const bool small = c->act == MOE_ACT_GELU && splits_small_tiles(c);
+  return align_up(std::max(small ? split_ws_bytes(c->E, c->d_model) : 0, tail_ws_bytes(max_row_tiles(c->T * c->k, c->E, tile_rows_for(c)), c->d_model)), 256);
+}
+// A caller's room for them: refused if it is too small, not used where nothing is split
+int check_room(const moe_cfg* c, const void* room, size_t room_bytes, float** sums) {
+  ALIGNED(room);
+  const size_t need = inputs_split_bytes(c);
+  if (room != nullptr && room_bytes < need) return MOE_ERR_WORKSPACE;
+  *sums = need > 0 ? static_cast<float*>(const_cast<void*>(room)) : nullptr;
+  return MOE_OK;
+}
+}  // namespace
+
+int moe_expert_ffn_bwd_inputs(const moe_cfg* cfg, const void* dy_perm, const void* saved, const void* W1, const void* W1b, const void* W2,
+                              const int32_t* offsets, const int32_t* kept, const int32_t* slice_lo, const int32_t* slice_hi,
+                              void* dx_perm, void* room, size_t room_bytes, void* ws, size_t ws_bytes, void* stream) {
+  CHECK(check_cfg(cfg));
+  CHECK(check_slices(slice_lo, slice_hi));
+  REQUIRE(dy_perm); REQUIRE(saved); REQUIRE(W1); REQUIRE(W2); REQUIRE(offsets); REQUIRE(kept); REQUIRE(dx_perm); REQUIRE(ws);
+  if (cfg->act == MOE_ACT_SWIGLU) REQUIRE(W1b);
+  else if (W1b != nullptr) return MOE_ERR_BAD_DTYPE;
+  ALIGNED(dy_perm); ALIGNED(saved); ALIGNED(W1); ALIGNED(W1b); ALIGNED(W2); ALIGNED(offsets); ALIGNED(kept); ALIGNED(slice_lo);
+  ALIGNED(slice_hi); ALIGNED(dx_perm); ALIGNED(ws);
+  CHECK(check_ws(cfg, ws, ws_bytes));
+  float* sums = nullptr;
+  CHECK(check_room(cfg, room, room_bytes, &sums));
+  if (cfg->T == 0) return MOE_OK;
+  return ffn_bwd_impl(cfg, dy_perm, nullptr, saved, W1, W1b, W2, offsets, kept, slice_lo, slice_hi, dx_perm, nullptr, nullptr, nullptr, 0, ws, false,
+                      (hipStream_t)stream, true, sums);
+}
+
 int moe_route_bwd(const moe_cfg* cfg, const void* x, const float* Wr, const int32_t* topk_idx, const float* topk_w,
                   const float* d_topk_w, float* d_logits, float* dWr, void* dx, int32_t accumulate, void* ws,
                   size_t ws_bytes, void* stream) {
@@ -612,13 +648,6 @@ int moe_route_bwd(const moe_cfg* cfg, const void* x, const float* Wr, const int3
 }
 
 namespace {
-// Room for dx's partial sums in a backward that leaves the weight gradients to a later call: the chip has nothing else to
-// do beside dx's last round then
-size_t inputs_split_bytes(const moe_cfg* c) {
-  if (!is_half(c) || (c->act == MOE_ACT_SWIGLU ? 2 : 1) * c->d_ff < SPLIT_MIN_K) return 0;
-  const bool small = c->act == MOE_ACT_GELU && splits_small_tiles(c);
-  return align_up(std::max(small ? split_ws_bytes(c->E, c->d_model) : 0, tail_ws_bytes(max_row_tiles(c->T * c->k, c->E, tile_rows_for(c)), c->d_model)), 256);
-}
 // Arguments of the calls that a whole-layer call stands for, checked before anything is launched
 int check_layer(const moe_cfg* cfg, const moe_layer_bufs* b, bool combine, bool backward, bool dw = true) {
   CHECK(check_cfg(cfg));
@@ -705,10 +734,9 @@ int moe_layer_bwd_inputs(const moe_cfg* cfg, const moe_layer_bufs* b, int32_t ac
 
 int moe_layer_bwd_inputs_in(const moe_cfg* cfg, const moe_layer_bufs* b, void* room, size_t room_bytes, int32_t accumulate, void* stream) {
   CHECK(check_cfg(cfg));
-  ALIGNED(room);
-  const size_t need = inputs_split_bytes(cfg);
-  if (room != nullptr && room_bytes < need) return MOE_ERR_WORKSPACE;
-  return layer_bwd(cfg, b, accumulate, true, need > 0 ? static_cast<float*>(room) : nullptr, stream);
+  float* sums = nullptr;
+  CHECK(check_room(cfg, room, room_bytes, &sums));
+  return layer_bwd(cfg, b, accumulate, true, sums, stream);
 }
 
 int moe_layer_bwd_inputs_room_bytes(const moe_cfg* cfg, size_t* bytes) {

@@ -122,6 +122,10 @@ class MoELayer:
                              self.offsets, self.kept, self.slice_lo, self.slice_hi, self.dx_perm, self.dW1,
                              self.dW1b, self.dW2, accumulate, self.ws)
 
+    def ffn_bwd_inputs(self, room=None):
+        B.moe_expert_ffn_bwd_inputs(self.cfg, self.dy_perm, self.saved, self.W1, self.W1b, self.W2, self.offsets, self.kept,
+                                    self.slice_lo, self.slice_hi, self.dx_perm, room, self.ws)
+
     def dispatch_bwd(self):
         # the input-gradient un-permute is a combine with unit weights
         B.moe_combine(self.cfg, self.dx_perm, None, self.topk_idx, self.row_of, self.offsets, self.kept,
@@ -149,6 +153,8 @@ class MoELayer:
     def backward_inputs(self, accumulate=0, room=None):
         """The backward without the expert weight gradients (`accumulate`: the gate's); expert_dw adds them up.  `room`:
         scratch of moe_layer_bwd_inputs_room_bytes that layers whose calls follow each other on a stream can share."""
+        if self.side is not None:
+            return self.backward_overlapped(accumulate, lambda: self.ffn_bwd_inputs(room))
         if room is None:
             return B.moe_layer_bwd_inputs(self.cfg, self.bufs(), accumulate)
         B.moe_layer_bwd_inputs_in(self.cfg, self.bufs(), room, accumulate)
@@ -166,7 +172,7 @@ class MoELayer:
         self.side_d_logits = torch.empty_like(self.d_logits)
         self.ev_fork, self.ev_join = torch.cuda.Event(), torch.cuda.Event()
 
-    def backward_overlapped(self, accumulate=0):
+    def backward_overlapped(self, accumulate=0, ffn=None):
         main = torch.cuda.current_stream(self.device)
         self.combine_bwd()
         self.ev_fork.record(main)
@@ -175,7 +181,7 @@ class MoELayer:
             B.moe_route_bwd(self.cfg, self.x, self.Wr, self.topk_idx, self.topk_w, self.d_topk_w, self.d_logits,
                             self.dWr, None, self.side_ws, accumulate)
             self.ev_join.record(self.side)
-        self.ffn_bwd(accumulate)
+        self.ffn_bwd(accumulate) if ffn is None else ffn()
         self.dispatch_bwd()
         # dx += d_logits Wr^T once the gradient through the experts is in dx
         B.moe_route_bwd(self.cfg, self.x, self.Wr, self.topk_idx, self.topk_w, self.d_topk_w, self.side_d_logits,

@@ -272,4 +272,6 @@ def test_room_of_the_split_input_gradient_is_checked_before_any_launch():
     call = lambda room, n: lib.moe_layer_bwd_inputs_in(ctypes.byref(cfg), bufs, ctypes.c_void_p(room), ctypes.c_size_t(n), 0, None)
     assert call(P, need - 1) == -7 and call(P + 8, need) == -5
     assert call(P, need) == call(0, 0) == -1                                             # the room is fine, the buffers are not
+    ffn = lambda room, n, first=P: lib.moe_expert_ffn_bwd_inputs(ctypes.byref(cfg), first, P, P, None, P, P, P, None, None, P, room, n, P, 1 << 40, None)
+    assert ffn(P, need - 1) == -7 and ffn(P + 8, need) == -5 and ffn(P, need, 0) == -1 and ffn(P, need, P + 8) == -5
     assert lib.moe_layer_bwd_inputs_in(ctypes.byref(cfg), None, None, ctypes.c_size_t(0), 0, None) == -1

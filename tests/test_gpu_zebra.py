@@ -113,3 +113,33 @@ def test_one_room_for_the_split_input_gradients_of_all_micro_batches():
         own.backward_inputs()
         torch.cuda.synchronize()
         assert torch.equal(bits(eng.act[1][j]), bits(own.out)) and torch.equal(bits(eng.grad[0][j]), bits(own.dx))
+
+
+@pytest.mark.parametrize("dtype, act, f", [("f16", "swiglu", 192), ("bf16", "gelu", 2112), ("f32", "gelu", 96)])
+def test_gate_overlap_of_engine_layers(dtype, act, f):
+    """enable_gate_overlap on some of the engine's layers: their gate weight gradients run on the side stream (which alone
+    writes side_d_logits), and every result keeps its bits."""
+    import torch
+    from paper_2504_03871_amd.zebra import ZebraExpertEngine
+    T, d, E, k, R = 600, 128, 6, 2, 3
+    eng = ZebraExpertEngine(1, R, T, d, f, E, k, dtype=getattr(S, "DT_" + dtype.upper()), act=getattr(S, "ACT_" + act.upper()))
+    gen = torch.Generator(device="cuda:0").manual_seed(4)
+    p = eng.params[0]
+    for t, std in [(p.Wr, d ** -0.5), (p.W1, d ** -0.5), (p.W1b, d ** -0.5), (p.W2, f ** -0.5)] + [(t, 1.0) for t in eng.act[0] + eng.grad[1]]:
+        if t is not None:
+            t.copy_(torch.randn(t.shape, generator=gen, device="cuda") * std)
+
+    def results():
+        eng.run_iteration()
+        torch.cuda.synchronize()
+        return [t.clone() for t in eng.act[1] + eng.grad[0] + [p.dW1, p.dW2, p.dWr] + ([p.dW1b] if p.dW1b is not None else [])]
+
+    want = results()
+    for m in eng.mb[0][:2]:
+        m.enable_gate_overlap()
+        m.side_d_logits.fill_(U.SENTINEL)
+    for _ in range(2):
+        got = results()
+        assert all(torch.equal(bits(g), bits(w)) for g, w in zip(got, want))
+    for m in eng.mb[0][:2]:
+        assert torch.equal(m.side_d_logits, m.d_logits)
