@@ -411,7 +411,8 @@ MOE_API int moe_bench_mfma_loop(int32_t kind, int32_t iters, const void* operand
  * kind 5, few-row forward GEMMs of ntm experts on n_rt row tiles, expert by expert: n_full_rt = 1 if an expert has
  * several, n_split = 1 if the tiles are split along K; out as kind 4.  out[0] = 0: a surplus block that exits at once.
  * kind 6: out[0] = 1 if the last round may be split, with the launch that adds the parts, for `block` = T k rows of n_rt
- * experts, ntm = K / 64, n_split = 1 if capacity or slices leave some of the rows out; 0 if it cannot be.
+ * experts, ntm = K / 64, n_split = 1 if capacity or slices leave some of the rows out, n_full_rt = 1 for row tiles of 160
+ * rows instead of 256; 0 if it cannot be.
  */
 MOE_API int moe_gemm_block_tile(int32_t kind, int64_t block, int32_t n_rt, int32_t n_full_rt, int32_t n_split,
                         int32_t ntm, int32_t ntn, int32_t* out);

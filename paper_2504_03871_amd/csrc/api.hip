@@ -253,7 +253,7 @@ int moe_gemm_block_tile(int32_t kind, int64_t block, int32_t n_rt, int32_t n_ful
     return MOE_ERR_BAD_SHAPE;
   // the kernels count tiles, K parts and K values in 32 bits
   const long long parts = kind == 5 ? (long long)(n_split ? SPLIT_K : 1) * n_rt : n_rt + (long long)(SPLIT_K - 1) * n_split;
-  const long long tiles = kind == 1 ? (long long)ntm * ntn : kind == 6 ? (block / 256 + n_rt) * ntn : parts * ntn;
+  const long long tiles = kind == 1 ? (long long)ntm * ntn : kind == 6 ? (block / MID_ROWS + n_rt) * ntn : parts * ntn;
   if (tiles > 0x7fffffffll - NUM_XCD || ((kind == 4 || kind == 6) && ntm > 0x7fffffff / 64)) return MOE_ERR_BAD_SHAPE;
   for (int i = 0; i < 6; ++i) out[i] = -1;
   if (kind == 0 || kind == 3) {
@@ -272,7 +272,7 @@ int moe_gemm_block_tile(int32_t kind, int64_t block, int32_t n_rt, int32_t n_ful
   }
   if (kind == 6) {
     if (ntm < 1) return MOE_ERR_BAD_SHAPE;
-    out[0] = tail_may_split((int)block, n_rt, n_split == 0, ntn, ntm * 64) ? 1 : 0;
+    out[0] = tail_may_split((int)block, n_rt, n_split == 0, ntn, ntm * 64, n_full_rt == 1 ? MID_ROWS : gemm_bf16_tile_rows()) ? 1 : 0;
     return MOE_OK;
   }
   if (kind == 5) {

@@ -135,6 +135,16 @@ def test_the_reduction_is_launched_where_a_tile_count_can_split_and_only_there(r
     assert B.moe_gemm_block_tile(6, rows, E, 0, 1, stages, ntn)[0] == (stages >= 32)     # some rows left out: any count
 
 
+@pytest.mark.parametrize("rows, E, ntn, stages", [
+    (4096, 8, 4, 64), (700, 2, 5, 45), (1280, 8, 32, 64), (159, 1, 9, 33), (320, 2, 256, 32), (16000, 32, 8, 128), (4096, 8, 4, 31), (1, 4, 1, 32)])
+def test_the_same_of_160_row_tiles(rows, E, ntn, stages):
+    counts = range((rows + 159) // 160, min(rows, rows // 160 + E) + 1)
+    splits = [B.moe_gemm_block_tile(4, 0, n, 0, 0, stages, ntn)[2] > 1 for n in counts]
+    assert B.moe_gemm_block_tile(6, rows, E, 1, 0, stages, ntn)[0] == any(splits)
+    if E > 1:
+        assert B.moe_gemm_block_tile(6, rows, E, 1, 1, stages, ntn)[0] == (stages >= 32)
+
+
 @pytest.mark.parametrize("kind, n_rt, n_split, ntm, ntn", [
     (4, 4, 0, 1 << 26, 1), (6, 4, 0, 1 << 26, 1), (6, 1 << 16, 0, 32, 1 << 16),                # K = 64 ntm beyond 32 bits
     (0, 1 << 16, 0, 1, 1 << 16), (3, 1 << 16, 0, 1, 1 << 16), (4, 1 << 16, 0, 32, 1 << 16),  # tiles beyond 32 bits
