@@ -129,17 +129,22 @@ def test_few_rows_per_expert(T, d, f, E, k, dtype, act, zipf):
     run_case(S.WORKLOADS["cfg1"].scaled(T=T, d=d, f=f, E=E, k=k, dtype=getattr(S, dtype), act=getattr(S, act), zipf_s=zipf))
 
 
+@pytest.mark.parametrize("T, f", [(3, 9 << 20), (3, 15 << 20), (33, 15 << 20)])
 @pytest.mark.parametrize("act", [B.ACT_GELU, B.ACT_SWIGLU])
-def test_rows_past_a_tile_whose_offsets_wrap_32_bits_are_not_stored(act):
-    """Three rows of 2^22 elements and more: row 255 of a tile lies beyond 4 GiB from the tile's start."""
+def test_rows_past_a_tile_whose_offsets_wrap_32_bits_are_not_stored(act, T, f):
+    """A few rows of millions of elements.  With f = 15 << 20 row 159 of a 160-row tile, which the backward runs and, above 32
+    rows, the forward, lies beyond 4 GiB from the tile's start, and the rows in between fall back into the valid ones.  The
+    64-row tiles of the forward of three rows cannot wrap (64 rows of d f < 2^30 elements, d = 64, are at most 2 GiB), nor can
+    256-row ones, which more than 512 rows or 128 per expert of at most 4 GiB in all get."""
     import torch
-    T, d, f = 3, 64, 9 << 20
+    d = 64
     L = filled_layer(T, d, f, 1, 1, "bf16", act)
     L.forward()
     L.combine_bwd()
     L.ffn_bwd()
     torch.cuda.synchronize()
-    assert 255 * f * 2 > 1 << 32
+    assert 255 * f * 2 > 1 << 32 and tile_rows(L) == 160
+    assert any(m * f * 2 % (1 << 32) < T * f * 2 for m in range(T, 160)) == (f == 15 << 20)   # rows past the tile's that wrap into it
     # the last region of the workspace: dA, or dG and dU
     planes = 2 if act == B.ACT_SWIGLU else 1
     dact = L.ws[L.ws.numel() - planes * T * f * 2:].view(L.tdtype).view(planes, T, f).float()
@@ -159,6 +164,11 @@ def test_rows_past_a_tile_whose_offsets_wrap_32_bits_are_not_stored(act):
         for got, ref in zip([t[:, s] for t in saved] + [t[:, s] for t in dact], want):
             # two roundings to bf16 (2^-9 each) at most, the pre-activation's and the result's
             assert (got - ref).norm() <= 2.0 ** -7 * ref.norm()
+
+
+def tile_rows(L):
+    """Rows of a 16-bit layer's row tiles (more than 32 rows per expert)."""
+    return 160 if L.T * L.k <= (512 if L.E <= 32 else 128) * L.E else 256
 
 
 def last_round_parts(kept, f, N, rows=256):
