@@ -178,8 +178,9 @@ def last_round_parts(kept, f, N, rows=256):
 
 
 @pytest.mark.parametrize("T, d, f, E, k, dtype, act", [
-    (700, 192, 2112, 4, 2, "bf16", B.ACT_GELU),        # 33 stages of 64 in 8 parts, full and partly filled tiles
+    (700, 192, 2112, 4, 2, "bf16", B.ACT_GELU),        # 160-row tiles: 33 stages of 64 in 7 parts or so, full and partly filled tiles
     (450, 320, 2048, 3, 1, "f16", B.ACT_SWIGLU),       # a last column tile of 64
+    (1090, 320, 2112, 2, 1, "bf16", B.ACT_SWIGLU),     # and of 256 rows
     (4096, 128, 2048, 40, 2, "bf16", B.ACT_SWIGLU),    # expert-major tile list
     (8200, 1088, 4096, 4, 2, "f16", B.ACT_GELU),       # a whole round before the split tiles
 ])
@@ -189,7 +190,7 @@ def test_last_round_split_along_k(T, d, f, E, k, dtype, act):
     L = filled_layer(T, d, f, E, k, dtype, act)
     L.forward()
     torch.cuda.synchronize()
-    tiles, parts = last_round_parts(L.kept, f, d)
+    tiles, parts = last_round_parts(L.kept, f, d, tile_rows(L))
     assert parts > 1 and (tiles > 256) == (T == 8200)
     hid = L.saved_plane(2 if act == B.ACT_SWIGLU else 1)
     tol = {"bf16": 2.0 ** -9, "f16": 2.0 ** -12}[dtype]   # one rounding of the result: 2^-9 (2^-12) relative at most
@@ -198,6 +199,25 @@ def test_last_round_split_along_k(T, d, f, E, k, dtype, act):
         ref = hid[o:o + n].double() @ L.W2[e].double()
         err = (L.y_perm[o:o + n].double() - ref).norm() / ref.norm()
         assert err < tol, (e, float(err))
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+def test_small_remainders_split_along_k_in_the_gelu_input_gradient(dtype):
+    """dx = dA W1^T of 256-row tiles in a launch shared with dW1: remainders of at most 64 rows are split along K on their own."""
+    import torch
+    T, d, f, E, k = 1100, 128, 2560, 4, 2
+    L = filled_layer(T, d, f, E, k, dtype)
+    L.forward()
+    L.combine_bwd()
+    L.ffn_bwd()
+    torch.cuda.synchronize()
+    assert tile_rows(L) == 256 and any(0 < int(n) % 256 <= 64 for n in L.kept) and any(int(n) % 256 > 64 or int(n) > 256 for n in L.kept)
+    dact = L.ws[L.ws.numel() - T * k * f * 2:].view(L.tdtype).view(T * k, f)   # the workspace's last region
+    tol = {"bf16": 2.0 ** -9, "f16": 2.0 ** -12}[dtype]                        # one rounding of the result
+    for e in range(E):
+        r = slice(int(L.offsets[e]), int(L.offsets[e + 1]))
+        ref = dact[r].double() @ L.W1[e].double().t()
+        assert (L.dx_perm[r].double() - ref).norm() < tol * ref.norm(), e
 
 
 @pytest.mark.parametrize("dtype, cap", [("bf16", 2000), ("f16", 1100)])

@@ -4,7 +4,7 @@ import pytest
 
 from paper_2504_03871_amd import binding as B
 from tests import gpu_util as U
-from tests.test_gpu_gemm_paths import filled_layer
+from tests.test_gpu_gemm_paths import filled_layer, last_round_parts, tile_rows
 
 pytestmark = pytest.mark.gpu
 
@@ -168,13 +168,18 @@ def test_weight_gradients_over_several_calls_are_those_of_call_after_call(T, d, 
 
 
 @pytest.mark.parametrize("T, d, f, E, k, dtype, act", [
-    (700, 192, 2112, 4, 2, "bf16", B.ACT_GELU),        # 33 stages in eight parts
+    (700, 192, 2112, 4, 2, "bf16", B.ACT_GELU),        # 160-row tiles, 33 stages in seven parts or so
     (700, 192, 1088, 4, 2, "f16", B.ACT_SWIGLU),       # 17 and 17 stages of two products, a part across the seam
     (450, 320, 2048, 3, 1, "bf16", B.ACT_SWIGLU),
-    (450, 320, 4096, 3, 1, "f16", B.ACT_GELU),         # and 64-row tiles that would be split on their own
+    (450, 320, 4096, 3, 1, "f16", B.ACT_GELU),
+    (1100, 192, 1088, 2, 1, "bf16", B.ACT_SWIGLU),     # the same of 256-row tiles
+    (1100, 192, 2112, 2, 1, "f16", B.ACT_GELU),
+    (1100, 320, 4096, 2, 1, "bf16", B.ACT_GELU),       # with remainders of up to 64 rows, which a whole last round would split on their own
+    (9356, 1024, 4096, 4, 1, "f16", B.ACT_GELU),       # and as it does: too many tiles behind the last whole round for two parts each
 ])
 def test_input_gradient_split_along_k(T, d, f, E, k, dtype, act):
-    """dx_perm of the backward that leaves the weight gradients out, its tiles split along K, against the unsplit one."""
+    """dx_perm of the backward that leaves the weight gradients out, its tiles split along K, against the unsplit one; the
+    partial sums behind the workspace and in a room of the caller's."""
     import torch
     from paper_2504_03871_amd.layer import MoELayer
     src = filled_layer(T, d, f, E, k, dtype, act)
@@ -184,13 +189,19 @@ def test_input_gradient_split_along_k(T, d, f, E, k, dtype, act):
     L.forward()
     L.backward()
     whole = L.dx_perm.double()
-    n_rt, ntn = sum(-(-int(c) // 256) for c in L.kept), -(-d // 256)
-    parts = B.moe_gemm_block_tile(4, 0, n_rt, 0, 0, (2 if act == B.ACT_SWIGLU else 1) * f // 64, ntn)[2]
-    assert parts > 1 and B.moe_layer_bwd_inputs_ws_bytes(L.cfg) > B.moe_workspace_bytes(L.cfg)
-    L.dx_perm.fill_(U.SENTINEL)
-    L.backward_inputs()
-    torch.cuda.synchronize()
+    tiles, parts = last_round_parts(L.kept, (2 if act == B.ACT_SWIGLU else 1) * f, d, tile_rows(L))
+    small = any(0 < int(c) % 256 <= 64 for c in L.kept)
+    assert tile_rows(L) == (256 if T > 1000 else 160) and (parts > 1) == (T < 9000) and (small or f != 4096 or T < 1000), (tiles, parts)
+    room = torch.empty(B.moe_layer_bwd_inputs_room_bytes(L.cfg), dtype=torch.uint8, device="cuda")
+    assert room.numel() > 0 and L.ws.numel() >= B.moe_workspace_bytes(L.cfg) + room.numel()
     n = int(L.offsets[E])
-    err = (L.dx_perm.double()[:n] - whole[:n]).norm() / whole[:n].norm()
-    # two results rounded to the storage type once each
-    assert err < {"bf16": 2.0 ** -8, "f16": 2.0 ** -11}[dtype], float(err)
+    split = []
+    for r in (None, room):
+        L.dx_perm.fill_(U.SENTINEL)
+        L.backward_inputs(room=r)
+        torch.cuda.synchronize()
+        err = (L.dx_perm.double()[:n] - whole[:n]).norm() / whole[:n].norm()
+        # two results rounded to the storage type once each
+        assert err < {"bf16": 2.0 ** -8, "f16": 2.0 ** -11}[dtype], float(err)
+        split.append(bits(L.dx_perm).clone())
+    assert torch.equal(*split)

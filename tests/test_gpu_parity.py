@@ -44,6 +44,7 @@ CASES = {
     # d_ff long enough for split-K of the smallest row tiles: only such tiles / a full tile plus a small rest
     "split_k_tiny": W["cfg1"].scaled(T=40, d=128, f=2048, E=4, k=2),
     "split_k_mixed": W["cfg1"].scaled(T=620, d=128, f=2560, E=4, k=2),
+    "split_k_mixed_high_tiles": W["cfg1"].scaled(T=1100, d=128, f=2560, E=4, k=2),
     # fp16 storage (the paper trains in FP16 mixed precision, Section 6.1): the bf16 cases again
     "f16_cfg1_small": W["cfg1"].scaled(T=1000, d=256, f=512, dtype=S.DT_F16),
     "f16_cfg2_small": W["cfg2"].scaled(T=2048, d=256, f=384, dtype=S.DT_F16),
@@ -54,6 +55,7 @@ CASES = {
     "f16_many_experts": W["cfg1"].scaled(T=700, d=128, f=128, E=200, k=8, dtype=S.DT_F16),
     "f16_one_token": W["cfg1"].scaled(T=1, d=64, f=128, E=4, k=2, dtype=S.DT_F16),
     "f16_split_k_mixed": W["cfg1"].scaled(T=620, d=128, f=2560, E=4, k=2, dtype=S.DT_F16),
+    "f16_split_k_mixed_high_tiles": W["cfg1"].scaled(T=1100, d=128, f=2560, E=4, k=2, dtype=S.DT_F16),
     # one token, two slots, both d_topk_w values a fifth of their uncancelled size
     "f16_one_token_cancelling": W["cfg1"].scaled(T=1, d=128, f=2560, E=64, k=2, dtype=S.DT_F16, zipf_s=0.8),
 }

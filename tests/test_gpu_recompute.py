@@ -13,6 +13,7 @@ CASES = {
     "f32": W["cfg0"],
     "bf16_gelu": W["cfg1"].scaled(T=1000, d=256, f=512),
     "bf16_gelu_split_k": W["cfg1"].scaled(T=620, d=128, f=2560, E=4, k=2),
+    "bf16_gelu_split_k_high_tiles": W["cfg1"].scaled(T=1100, d=128, f=2560, E=4, k=2),
     "bf16_swiglu_partial_cap": W["cfg3"].scaled(T=1200, d=256, f=320, E=6, k=3, capacity_factor=0.8, partial=True,
                                                 zipf_s=0.7),
     "f16_gelu": W["cfg1"].scaled(T=1000, d=256, f=512, dtype=S.DT_F16),
