@@ -37,11 +37,22 @@ def find_csv(d, suffix):
     return sorted(hits)[-1]
 
 
-def gemm_role(name, nth=0):
+PAIR = re.compile(r"gemm_(?:bf16_pair_kernelIDF16[b_]Li\d|f32_pair_kernelI)E?Li(\d)ELb([01])E")
+GRADIENTS = {"dw2_bwd": "dW2 = H^T dy", "dw1_bwd": "dW1 = x_perm^T dA (SwiGLU: with dW1b)"}
+
+
+def gradient_launches(names):
+    """The weight gradients that have a launch of their own in a step with these kernels (mangled names), in order: not
+    those that share dH's launch or dx's."""
+    epilogues = [m.group(1) for m in map(PAIR.search, names) if m]
+    shared = {"dw2_bwd": any(e in "34" for e in epilogues), "dw1_bwd": any(e == "0" for e in epilogues)}
+    return [g for g in GRADIENTS if not shared[g]]
+
+
+def gemm_role(name, gradient="dw1_bwd"):
     """(bench bracket, description) of a grouped-GEMM kernel from its MANGLED name (rocprofv3 -M: its demangler
-    does not know the bf16 type); nth = index of the launch within a step for the weight-gradient kernel, which
-    serves dW2 and dW1 (SwiGLU: with dW1b) in that order."""
-    m = re.search(r"gemm_(?:bf16_pair_kernelIDF16[b_]Li\d|f32_pair_kernelI)E?Li(\d)ELb([01])E", name)
+    does not know the bf16 type); `gradient`: which one this launch of the weight-gradient kernel computes."""
+    m = PAIR.search(name)
     if m:
         epi, chain = int(m.group(1)), m.group(2) == "1"
         if epi in (3, 4):
@@ -65,7 +76,7 @@ def gemm_role(name, nth=0):
     if mode == 1 and epi == 0:
         return "dx_bwd", "dx_perm = dA W1^T" + (" (dG W1^T + dU W1b^T chained)" if chain else "")
     if mode == 2:
-        return ("dw2_bwd", "dw1_bwd")[min(nth, 1)], "weight gradient x^T dy (dW2, then dW1, with dW1b for SwiGLU)"
+        return gradient, GRADIENTS[gradient]
     return None, ""
 
 
@@ -188,7 +199,8 @@ def main():
                 continue
             role, desc = gemm_role(r["Name"])
             if role and role.startswith("dw"):
-                role = "dw2_bwd / dw1_bwd"
+                own = gradient_launches([x["Name"] for x in rows])
+                role, desc = " / ".join(own), "; ".join(GRADIENTS[g] for g in own)
             out.append(f"| `{short(r['Name'])}` | {r['Calls']} | {float(r['AverageNs'])/1e3:.1f} | {float(r['MinNs'])/1e3:.1f} | "
                        f"{float(r['MaxNs'])/1e3:.1f} | {float(r['Percentage']):.2f} | {((role or '') + '  ' + desc).strip()} |")
         if bench:
@@ -223,12 +235,9 @@ def main():
             if role0 is None or k not in pw:
                 continue
             groups = collections.OrderedDict()
-            tn = role0.startswith("dw")
-            n_per = 1
-            if tn and bench:     # launches per step of the weight-gradient kernel
-                n_per = 2
+            own = gradient_launches(pf)   # launches per step of the weight-gradient kernel
             for i, ((_, vf), (_, vw)) in enumerate(zip(pf[k], pw[k])):
-                role, desc = gemm_role(k, i % n_per if tn else 0)
+                role, desc = gemm_role(k, own[i % len(own)]) if own else gemm_role(k)
                 groups.setdefault((role, desc), []).append((vf["FETCH_SIZE"] * sf, vw["WRITE_SIZE"] * sw))
             for (role, desc), vals in groups.items():
                 rd = sum(x for x, _ in vals) / len(vals)
@@ -265,7 +274,7 @@ def main():
                 acc.update(v)
             n = len(lst)
             b = acc["SQ_BUSY_CU_CYCLES"] / n
-            name = "dW (all weight gradients)" if role0.startswith("dw") else role0
+            name = " / ".join(gradient_launches(pk)) if role0.startswith("dw") else role0
             lines.append(f"| {name} `{short(k)}` | {acc['SQ_VALU_MFMA_BUSY_CYCLES']/n/b/4:.2f} | {acc['SQ_WAIT_ANY']/max(acc['SQ_WAVE_CYCLES'],1):.2f} | "
                          f"{acc['SQ_LDS_BANK_CONFLICT']/n/b:.3f} | {acc['SQ_VMEM_TA_ADDR_FIFO_FULL']/n/b:.3f} | {acc['SQ_INSTS_VALU_MFMA_MOPS_BF16']/n:.0f} |")
         open(os.path.join(a.out, f"{tag}_gemm_mfma_busy.md"), "w").write("\n".join(lines) + "\n")
