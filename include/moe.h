@@ -271,7 +271,8 @@ MOE_API int moe_route_bwd(const moe_cfg* cfg, const void* x, const float* Wr, co
 /*
  * A whole layer in one call: the calls above in the order of the block, with the same kernels and the same bits, but
  * with the small jobs (tile maps, tables, the transposed gate weight) riding in other kernels' launches and the two
- * halves of the input gradient in one pass: a step of 17 to 20 launches and eight calls becomes one of 11 to 15 and two.
+ * halves of the input gradient in one pass.  A step is 11 launches at least (fp32, short lists, shared weight gradients) and
+ * 19 at most (16-bit gate layout pass, histogram and scan, four separate backward GEMMs, split sums of y and dx).
  * The struct is a HOST struct of DEVICE pointers, read during the call only; each field is the argument of that name
  * above.  `saved` holds every plane in both modes of the forward that use one.
  */

@@ -162,7 +162,8 @@ MOE_HD inline bool row_tile_block(int vb, int n_rt, int n_full_rt, int n_sp, int
 // them in its L2, while the chip as a whole reads whole weight rows (runs that walk down a strip of eight columns leave
 // the other half of 4 KB rows, and half of the memory channels, untouched: 256 experts of 48 rows, d 2048, f 1024, second
 // GEMM 244 us against 199; runs of 32 tiles are within 5 % either way, bands of 16 row tiles up to 10 % slower).
-// Split along K (up to 32 experts): eight parts, four where an expert has several tiles, which are at most 1.75 E then.
+// Split along K (up to 32 experts): eight parts, four where an expert has several tiles, which are at most 1.5 E then
+// (SKINNY_AVERAGE rows per expert, SKINNY_ROWS per tile).
 constexpr int SKINNY_RUN = 64, SKINNY_BAND = 8;
 struct SkinnyOrder { int n_rt, E, shift; bool mates; };   // 1 << shift K parts per tile
 MOE_HD inline SkinnyOrder skinny_order(int n_rt, bool mates, int E, bool split) {
@@ -298,6 +299,12 @@ struct GemmArgs {
   int tile_rows; // row-tile GEMMs: rows per entry of the tile map
 };
 
+// blocks of a weight-gradient launch of bm x bn tiles (dw_block), of two gradients where the second is asked for
+inline long long dw_blocks(const GemmArgs& g, int bm, int bn) {
+  const long long p = (long long)((g.N + bn - 1) / bn) * ((g.M + bm - 1) / bm);
+  return (p + NUM_XCD - 1) / NUM_XCD * NUM_XCD * g.E * (g.C2 != nullptr ? 2 : 1);
+}
+
 struct TileMapArgs;   // tile_map.h
 int launch_tile_map(const TileMapArgs& tm, hipStream_t s);
 
@@ -319,11 +326,14 @@ int launch_gemm_half_pair(int dtype, int epi1, bool chain1, const GemmArgs& g1, 
 int gemm_bf16_tile_rows();
 // Height of the 16-bit row tiles.  256 rows (two stages of operands in LDS) move the fewest bytes per product; 160 rows
 // leave room for a third stage, so loads may take one iteration longer, and fill the chip more evenly where an expert has
-// few tiles.  The line is on the average rows per expert: skew only favours the low tiles.  256 -> 160 rows:
-//   up to 128 rows, 8 to 128 experts, even and skewed load: forward x0.75 to 0.98, backward x0.92 to 0.99
-//   129 to 512 rows, up to 32 experts: forward x0.76 to 1.06 (worst: 16 experts of 144 to 224 rows each, exactly even;
-//     skewed x0.75 to 0.90), backward x0.88 to 1.00.  eight experts of 512 rows, d 1024, f 4096, us:
-//     GEMM1 57 -> 48, GEMM2 49 -> 41, dH 57 -> 48, dx 50 -> 41
+// few tiles.  The host sees the average rows per expert, not the load, and the line is drawn on that.  256 -> 160 rows,
+// layers of d 1024 to 4096 and d_ff 1024 to 14336:
+//   33 to 140 rows, up to 32 experts: forward x0.79 to 1.09 (even load, most of them below 1), x0.73 to 1.03 (router bias -0.7
+//     log(e + 1)), backward x0.80 to 1.02; up to 128 rows, 40 to 128 experts: forward x0.78 to 0.98, backward x0.90 to 1.00
+//   150 to 220 rows, up to 32 experts: an evenly loaded expert is one tile of 256 or two of 160.  Forward x1.00 to 1.21, at the
+//     bias x0.73 to 0.95 (one expert of several tiles, others of one); backward x0.75 to 1.02
+//   240 to 512 rows, up to 32 experts: forward x0.64 to 1.10, at the bias x0.80 to 1.09 (most of both below 1), backward x0.75 to
+//     1.05.  Eight experts of 512 rows, d 1024, f 4096, us: GEMM1 57 -> 48, GEMM2 49 -> 41, dH 57 -> 48, dx 50 -> 41
 //   129 to 512 rows, 64 and 128 experts: forward x0.92 to 1.15, backward x0.97 to 1.00; the tiles are many either way
 //   above 512 rows: 2048 rows, d 1024, f 4096, GEMM1 189 -> 196, dH with dW2 324 -> 329; 3001 rows, d 1088, f 2880,
 //     SwiGLU GEMM1 113 -> 135

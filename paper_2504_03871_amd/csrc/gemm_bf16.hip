@@ -11,11 +11,6 @@ namespace moe {
 constexpr int T_BM = 256, T_BN = 256, T_BN_DUAL = 128, T_BN_SEGS = 128, T_WGM = 2, T_WGN = 4;
 int gemm_bf16_tile_rows() { return T_BM; }
 
-// blocks of a weight-gradient launch (dw_block), of two gradients where the second is asked for
-static long long dw_blocks(const GemmArgs& g, int bn = T_BN) {
-  const long long p = (long long)((g.N + bn - 1) / bn) * ((g.M + T_BM - 1) / T_BM);
-  return (p + NUM_XCD - 1) / NUM_XCD * NUM_XCD * g.E * (g.C2 != nullptr ? 2 : 1);
-}
 // blocks of a split launch beyond one per tile
 static long long split_blocks(const GemmArgs& g, long long ntn) {
   const long long small = g.split_small ? (long long)g.E * ntn * (SPLIT_K - 1) : 0;
@@ -50,7 +45,7 @@ static int launch_rows(const GemmArgs& g, int max_tiles, hipStream_t s) {
   }
   const int ntn = (g.N + BN - 1) / BN;
   long long tiles;
-  if (MODE == MODE_TN) tiles = dw_blocks(g);
+  if (MODE == MODE_TN) tiles = dw_blocks(g, T_BM, T_BN);
   else tiles = (long long)ntn * max_tiles;
   const bool split = MODE != MODE_TN && EPI == EPI_STORE && g.split_ws != nullptr;
   kern<<<dim3(gemm_bf16_grid(tiles + (split ? split_blocks(g, ntn) : 0))), T_WGM * T_WGN * 64, lds, s>>>(g);
@@ -88,7 +83,7 @@ static int launch_pair_rows(const GemmArgs& g1, int max_tiles, const GemmArgs& g
   const bool split = EPI1 == EPI_STORE && !CHAIN1 && g1.split_ws != nullptr;
   const long long tiles1 = (long long)ntn1 * max_tiles, t1 = tiles1 + (split ? split_blocks(g1, ntn1) : 0);
   const long long n1 = (t1 + NUM_XCD - 1) / NUM_XCD * NUM_XCD;
-  const long long n2 = dw_blocks(g2);
+  const long long n2 = dw_blocks(g2, T_BM, T_BN);
   if (n1 + n2 > 0x7fffffffll) return MOE_ERR_BAD_SHAPE;
   kern<<<dim3(gemm_bf16_grid(n1 + n2)), T_WGM * T_WGN * 64, lds, s>>>(g1, g2, (int)n1);
   const int rc = launch_status();
@@ -107,7 +102,7 @@ static int dw_segs_for(const GemmArgs& g1, const DwSegs& s1, const GemmArgs& g2,
   auto kern = gemm_bf16_dw_segs_kernel<ST, T_BM, BN, 4, 2>;
   hipError_t err = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
   if (err != hipSuccess) return set_hip_error(err);
-  const long long n1 = dw_blocks(g1, BN), n2 = dw_blocks(g2, BN);
+  const long long n1 = dw_blocks(g1, T_BM, BN), n2 = dw_blocks(g2, T_BM, BN);
   if (n1 + n2 > 0x7fffffffll) return MOE_ERR_BAD_SHAPE;
   kern<<<dim3(gemm_bf16_grid(n1 + n2)), T_WGM * T_WGN * 64, lds, s>>>(DwSegsPair{{g1, g2}, {s1, s2}, (int)n1});
   return launch_status();

@@ -243,8 +243,11 @@ __device__ __forceinline__ void swap8(V& a, V& b) {
 
 // ---- epilogue accesses through buffer descriptors: 32-bit offsets; what lies past the byte count is not touched ----
 // Outputs are streamed, which keeps them from displacing operand panels in the L2 (dH -1.3 %, whole GELU steps -0.4 to
-// -1.5 % against plain stores): a writer of 3.7 TB/s on half of the compute units slows the two-stage main loop on the
-// others from 84 to 187 us with plain stores, to 87 with streaming and to 80 with streaming, written through.
+// -1.5 % against plain stores).  What a writer costs the blocks beside it: the two-stage main loop of 128 tiles (K 4096, 34 MB
+// of operands) on half of the compute units takes 76 us alone; with 134 | 268 | 537 MB written by others meanwhile (at 4.0 |
+// 5.4 | 5.7 TB/s) 84 | 116 | 188 us beside plain stores, 85 | 95 | 122 beside streaming ones, 81 | 93 | 116 if those are written
+// through (which takes the writer longer: 56 us instead of 34, 67 instead of 50, 100 instead of 94).  A streaming writer thus
+// costs the loops beside it a quarter to half of the time it takes, a plain one all of it and more.
 constexpr int AUX_NT = 2;    // streaming access
 constexpr int AUX_WT = 18;   // streaming and written through: for half lines
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t out_rsrc(const void* base, size_t bytes) {
@@ -707,8 +710,8 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs& g, const int vb, 
   // (widths are multiples of 64).  A round trip through LDS took 2.4-2.7 us per tile instead.  Launches of four rounds,
   // with it -> without, us: plain store x W K 1024 132 -> 123, GELU forward 157 -> 150, GELU backward 163 -> 155, weight
   // gradient of 1024 rows 153 -> 143; at K 4096 1-2 %; the SwiGLU epilogues (two planes in, two out) stay within 1 %.
-  // What is left is the memory's time: 128 KB per plane and tile, 4 us, and a streaming writer on other compute units
-  // slows a main loop by as much as the writing takes, so that staggered blocks gain nothing.
+  // What is left is the memory's time: 128 KB per plane and tile, 4 us, of which blocks that are out of step hide about half
+  // (what a writer costs: AUX_NT above).
   constexpr int C = WTN * 32;
   if (wn * C >= nvalid) return;
   if constexpr (SEGS) {

@@ -291,14 +291,9 @@ __global__ __launch_bounds__(256, BM1 == SB || BM2 == SB ? 3 : 4) void gemm_f32_
   else gemm_f32_tile<MODE_TN, EPI_DW, false, false, BM2>(g2, blockIdx.x - first_blocks, smem);
 }
 
-// blocks of a weight-gradient launch (dw_block), of two gradients where the second is asked for
-static long long dw_blocks(const GemmArgs& g, int bm) {
-  const long long p = (long long)((g.N + SB - 1) / SB) * ((g.M + bm - 1) / bm);
-  return (p + NUM_XCD - 1) / NUM_XCD * NUM_XCD * g.E * (g.C2 != nullptr ? 2 : 1);
-}
 template <int MODE, int EPI, bool DUAL, bool CHAIN, int BM>
 static int launch_bm(const GemmArgs& g, int max_tiles, hipStream_t s) {
-  const long long ntn = (g.N + SB - 1) / SB, blocks = MODE == MODE_TN ? dw_blocks(g, BM) : ntn * max_tiles;
+  const long long ntn = (g.N + SB - 1) / SB, blocks = MODE == MODE_TN ? dw_blocks(g, BM, SB) : ntn * max_tiles;
   if (blocks > 0x7fffffffll) return MOE_ERR_BAD_SHAPE;
   gemm_f32_kernel<MODE, EPI, DUAL, CHAIN, BM><<<dim3((unsigned)blocks), 256, 0, s>>>(g);
   return launch_status();
@@ -328,7 +323,7 @@ int launch_gemm_f32(int mode, int epi, bool dual, bool chain, const GemmArgs& g,
 template <int EPI1, bool CHAIN1, int BM1, int BM2>
 static int launch_pair_bm(const GemmArgs& g1, int max_tiles, const GemmArgs& g2, hipStream_t s) {
   // a multiple of the XCD count: a tile number still tells the XCD for the second GEMM
-  const long long n1 = ((g1.N + SB - 1) / SB * (long long)max_tiles + NUM_XCD - 1) / NUM_XCD * NUM_XCD, n2 = dw_blocks(g2, BM2);
+  const long long n1 = ((g1.N + SB - 1) / SB * (long long)max_tiles + NUM_XCD - 1) / NUM_XCD * NUM_XCD, n2 = dw_blocks(g2, BM2, SB);
   if (n1 + n2 > 0x7fffffffll) return MOE_ERR_BAD_SHAPE;
   gemm_f32_pair_kernel<EPI1, CHAIN1, BM1, BM2><<<dim3((unsigned)(n1 + n2)), 256, 0, s>>>(g1, g2, (int)n1);
   return launch_status();
