@@ -129,8 +129,13 @@ def main():
         title = bench["config"]["workload"]
     bench_cmd = f"python3 bench.py --workload {w} --also none --no-cpu-baseline" + (" --f16" if a.f16 else "")
     case_run = w not in synth.WORKLOADS
+    few_steps = " --steps 3 --warmup 1"
     if case_run:
-        bench_cmd = "python3 case.py"
+        bench_cmd, few_steps = "python3 case.py", " 3"
+    case_program = ["    import sys, torch", "    from paper_2504_03871_amd import binding as B", "    from perf import cases as P",
+                    f"    s = P.prepare({{c['name']: c for c in P.listed()}}['{w}'], 1)",
+                    "    for _ in range(int((sys.argv[1:] or [30])[0])): P.run(s)",
+                    "    a, b = torch.empty(2, 1 << 29, dtype=torch.uint8, device='cuda')", "    B.moe_bench_stream(a, b, a.numel())", "    torch.cuda.synchronize()", ""]
     tag = w + ("_f16" if a.f16 else "")   # file name stem
     if a.f16:
         title += " (fp16 storage)"
@@ -186,10 +191,7 @@ def main():
                "Command (run from /tmp with TMPDIR=/tmp on an MI355X):", "",
                f"    rocprofv3 -M --kernel-trace --stats --output-format csv -d <out> -o {w} -- {bench_cmd}", ""]
         if case_run:
-            out += ["case.py, with the repository on PYTHONPATH, is thirty passes of the case; durations in microseconds over all of them:", "",
-                    "    import torch", "    from perf import cases as P",
-                    f"    s = P.prepare({{c['name']: c for c in P.listed()}}['{w}'], 1)",
-                    "    for _ in range(30): P.run(s)", "    torch.cuda.synchronize()", ""]
+            out += ["case.py, with the repository on PYTHONPATH, is thirty passes of the case; durations in microseconds over all of them:", "", *case_program]
         else:
             out += ["bench.py runs its warm-up steps, a detail pass (every kernel bracketed by events), the timed steps and a",
                "cold pass of the HBM-bound calls; durations in microseconds over all of them.", ""]
@@ -223,9 +225,10 @@ def main():
         sf, sw = 524288.0 / cf, 524288.0 / cw
         lines = [f"# {title}: HBM traffic of the grouped-GEMM kernels from rocprofv3 counters", "",
                  "Commands (each counter in a run of its own; run from /tmp with TMPDIR=/tmp):", "",
-                 f"    rocprofv3 -M --pmc FETCH_SIZE --output-format csv -d <out> -o {w} -- {bench_cmd} --steps 3 --warmup 1",
-                 f"    rocprofv3 -M --pmc WRITE_SIZE --output-format csv -d <out> -o {w} -- {bench_cmd} --steps 3 --warmup 1", "",
-                 "Calibration: the library's 512 MiB streaming copy that bench.py times for its `device` entry (524288 KiB read,",
+                 f"    rocprofv3 -M --pmc FETCH_SIZE --output-format csv -d <out> -o {w} -- {bench_cmd}{few_steps}",
+                 f"    rocprofv3 -M --pmc WRITE_SIZE --output-format csv -d <out> -o {w} -- {bench_cmd}{few_steps}", "",
+                 *(case_program if case_run else []),
+                 "Calibration: the library's 512 MiB streaming copy that " + ("ends the program" if case_run else "bench.py times for its `device` entry") + " (524288 KiB read,",
                  f"524288 KiB written) reads FETCH_SIZE = {cf:.1f} and WRITE_SIZE = {cw:.1f} per dispatch, so FETCH_SIZE is scaled",
                  f"by {sf:.3f} and WRITE_SIZE by {sw:.3f} to get KiB.  Averages over the dispatches of each kind.", "",
                  "| launch | read MiB | written MiB | total bytes | role |", "|---|---|---|---|---|"]
@@ -250,7 +253,8 @@ def main():
         open(os.path.join(a.out, f"{tag}_gemm_hbm_traffic.md"), "w").write("\n".join(lines) + "\n")
         tpath = os.path.join(a.out, "hbm_traffic.json")
         cur = json.load(open(tpath)) if os.path.exists(tpath) else {}
-        cur[w] = tj
+        if not case_run:   # bench.py's workloads
+            cur[w] = tj
         cur["_note"] = ("bytes per launch of each GEMM bracket (FETCH_SIZE and WRITE_SIZE scaled to KiB by the copy "
                         "calibration), written by paper_2504_03871_amd/profsummary.py; see <workload>_gemm_hbm_traffic.md")
         json.dump(cur, open(tpath, "w"), indent=1)
@@ -260,7 +264,7 @@ def main():
         lines = [f"# {title}: matrix-core occupancy of the grouped-GEMM launches from rocprofv3 counters", "",
                  "Command (run from /tmp with TMPDIR=/tmp on an MI355X):", "",
                  "    rocprofv3 -M --pmc SQ_BUSY_CU_CYCLES SQ_VALU_MFMA_BUSY_CYCLES SQ_WAVE_CYCLES SQ_WAIT_ANY SQ_INSTS_VALU_MFMA_MOPS_BF16 "
-                 f"SQ_VMEM_TA_ADDR_FIFO_FULL SQ_LDS_BANK_CONFLICT SQ_ACTIVE_INST_LDS --output-format csv -d <out> -o {w} -- {bench_cmd} --steps 3 --warmup 1", "",
+                 f"SQ_VMEM_TA_ADDR_FIFO_FULL SQ_LDS_BANK_CONFLICT SQ_ACTIVE_INST_LDS --output-format csv -d <out> -o {w} -- {bench_cmd}{few_steps}", "",
                  "Averages per dispatch.  SQ_VALU_MFMA_BUSY_CYCLES counts the four SIMDs of a compute unit separately, so",
                  "busy / (4 x SQ_BUSY_CU_CYCLES) is the share of a busy compute unit's cycles in which a matrix core works.", "",
                  "| launch | MFMA busy / (4 x busy CU cycles) | wait-any / wave cycles | LDS bank-conflict cycles / busy CU cycles | address FIFO full / busy CU cycles | MFMA MOPS (bf16) |",
