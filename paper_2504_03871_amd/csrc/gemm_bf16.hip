@@ -28,8 +28,7 @@ static int launch_split_reduce(const GemmArgs& g, long long tiles, hipStream_t s
 template <typename ST, int MODE, int EPI, bool DUAL, bool CHAIN, int BM>
 static int launch_rows(const GemmArgs& g, int max_tiles, hipStream_t s) {
   constexpr int BN = DUAL ? T_BN_DUAL : T_BN;
-  constexpr bool TAB = (EPI == EPI_GELU_BWD || EPI == EPI_GELU_FWD) && Half16<ST>::GELU_TABLE;
-  constexpr int lds = gemm_bf16_lds_bytes<BM, BN, DUAL, TAB>();
+  constexpr int lds = gemm_bf16_lds_bytes<BM, BN, DUAL>();
   // Two matrices of 128 columns: 4 x 2 waves of 64 rows and 64 columns of either, which write whole lines, streamed
   // (2 x 4: 32 columns, half lines).  GEMM1 of SwiGLU, 16 rounds of tiles, us per round, 2 x 4 and plain stores -> 4 x 2:
   // K 512 28.8 -> 25.0, 1024 38.6 -> 35.5, 2048 62.4 -> 60.2, 4096 112 -> 108.5; forward passes: eight experts of 2048 rows,
@@ -66,7 +65,7 @@ static int launch_one(const GemmArgs& g, int max_tiles, hipStream_t s) {
 // blocks come first.
 template <typename ST, int EPI1, bool CHAIN1, int BM1>
 static int launch_pair_rows(const GemmArgs& g1, int max_tiles, const GemmArgs& g2, hipStream_t s) {
-  constexpr int lds1 = gemm_bf16_lds_bytes<BM1, T_BN, false, EPI1 == EPI_GELU_BWD && Half16<ST>::GELU_TABLE>();
+  constexpr int lds1 = gemm_bf16_lds_bytes<BM1, T_BN, false>();
   constexpr int lds2 = gemm_bf16_lds_bytes<T_BM, T_BN, false>();
   constexpr int lds = lds1 > lds2 ? lds1 : lds2;
   auto kern = gemm_bf16_pair_kernel<ST, MODE_NT, EPI1, CHAIN1, BM1, MODE_TN, EPI_DW, T_BM, T_BN, T_WGM, T_WGN>;

@@ -15,15 +15,25 @@
 // per stage, 32 per MFMA ("K step").  Interleaving the bands spreads a partly filled row tile over every
 // wave row.
 //
-// Pipeline: two LDS stages of 64 K values, filled by buffer loads that write LDS directly (no staging
-// registers, no LDS store instructions).  An iteration multiplies one stage in two K steps; the first reads
-// the fragments of the second, then every wave waits for its own loads of the next stage and joins the
+// Pipeline: LDS stages of 64 K values, two of one operand and three of the other, filled by buffer loads that write LDS
+// directly (no staging registers, no LDS store instructions).  An iteration multiplies one stage in two K steps; the first
+// reads the fragments of the second, then every wave waits for its own loads of the next stage and joins the
 // iteration's one block barrier; the second K step reads the first fragments of the next stage and issues
-// the loads of the stage after that into the buffer just released.  64-wide because a 32-wide stage fetches
+// the loads of a later one, the second or the third after this, into the LDS just released.  64-wide because a 32-wide stage fetches
 // an operand with contiguous K as 64-byte pieces of 128-byte lines, which fills the address FIFO of the
 // memory pipe (counters: full thirteen times as often); the operands with strided K gain a little from the
 // halved number of barriers (weight gradients +2 % against a ring of four 32-wide stages).
-// A tile of 160 rows and 256 columns (or twice 128) leaves LDS for a third stage (156 of 160 KB): loads then have two
+// 160 KB of LDS hold two stages of 256 x 256 and a third of one operand.  Its loads may take an iteration longer, and those of
+// the other go first and have the whole of theirs; waits for loads were what the loop lost (two stages of both: 0.27 to 0.40 of
+// the wave cycles).  us, two stages of both -> three of A -> three of B, on one box:
+//   16384 rows in 16 skewed experts, d 2048, f 8192, fp16: y 494 -> 467 -> 462, GEMM1 610 -> 592 -> 579, dH 626 -> 601 -> 605,
+//     dW2 622 -> 606 -> 638, dx + dW1 1181 -> 1140 -> 1119
+//   65536 rows in 8, d 4096, f 14336, SwiGLU: GEMM1 12.10 -> 12.22 -> 11.93 ms, y 5.53 -> 5.33 -> 5.38, dH 6.37 -> 6.25 -> 6.28,
+//     dW 8.56 -> 8.50 -> 8.39, dx 11.87 -> 11.14 -> 11.01
+//   65536 rows in 128, d 2048, f 1024, SwiGLU: GEMM1 602 -> 577 -> 576, y 334 -> 316 -> 323, dx 575 -> 531 -> 530, dW1 842 -> 849 -> 843
+//   16384 rows in 8, d 1024, f 4096, GELU: GEMM1 178 -> 179 -> 181, y 131 -> 123 -> 125, dx + dW1 259 -> 249 -> 253
+// so three of B where two weight matrices take part (GEMM1 and dx of SwiGLU), three of A elsewhere.
+// A tile of 160 rows and 256 columns (or twice 128) leaves LDS for three stages of both (156 of 160 KB): loads then have two
 // stages' worth of MFMAs to land instead of one, which is what a GEMM of few rows per expert waits for, and the chip is
 // left with smaller remainders (512 micro-batch rows per expert, d 1024, f 4096: GEMM1 57 -> 48 us; 125 rows, d 2048,
 // f 8192, forward pass 282 -> 271).  It moves 13 % more bytes per product from L2, so 256 rows stay ahead where tiles are
@@ -77,12 +87,18 @@ template <> struct Half16<f16> {
 };
 
 constexpr int BKT = 64;   // K values per LDS stage: two MFMA K steps; an operand row with contiguous K is one 128-byte line
-// bytes of an LDS stage, and how many there are: two of 256 x 256 (128 KB), three where the LDS holds them (160 x 256: 156 KB)
+// bytes of an LDS stage of either operand and how many stages of it there are: three where the LDS holds them (160 x 256: 156 KB),
+// else (256 x 256: 160 KB) three of one operand and two of the other
+constexpr int LDS_BYTES = 160 * 1024;
+template <int BM> constexpr int gemm_bf16_a_bytes() { return BM * BKT * 2; }
+template <int BN, bool DUAL> constexpr int gemm_bf16_b_bytes() { return BN * BKT * 2 * (DUAL ? 2 : 1); }
 template <int BM, int BN, bool DUAL>
-constexpr int gemm_bf16_stage_bytes() { return BM * BKT * 2 + BN * BKT * 2 * (DUAL ? 2 : 1); }
+constexpr bool gemm_bf16_three() { return (gemm_bf16_a_bytes<BM>() + gemm_bf16_b_bytes<BN, DUAL>()) * 3 <= LDS_BYTES; }
 template <int BM, int BN, bool DUAL>
-constexpr int gemm_bf16_stages() { return gemm_bf16_stage_bytes<BM, BN, DUAL>() * 3 <= 160 * 1024 ? 3 : 2; }
-
+constexpr int gemm_bf16_lds_bytes() {
+  constexpr int A = gemm_bf16_a_bytes<BM>(), B = gemm_bf16_b_bytes<BN, DUAL>();
+  return gemm_bf16_three<BM, BN, DUAL>() ? 3 * (A + B) : 2 * (A + B) + (A > B ? A : B);
+}
 // ---- LDS layouts -------------------------------------------------------------------------------
 // K-contiguous tile: [rows][BKT] bf16.  The 16-byte chunks of a row are XOR-swizzled with the index
 // of the 256-byte LDS line the row lies in, so 16 lanes reading the same chunk of 16 consecutive
@@ -303,13 +319,6 @@ __device__ __forceinline__ void epilogue_fwd(const OutPlanes& o, const unsigned 
   }
 }
 
-// TAB: a GELU table (the GELU epilogues) sits behind two stages; three leave no room, it then takes the stage that is free
-// before the loop's last two iterations
-template <int BM, int BN, bool DUAL, bool TAB = false>
-constexpr int gemm_bf16_lds_bytes() {
-  return gemm_bf16_stages<BM, BN, DUAL>() * gemm_bf16_stage_bytes<BM, BN, DUAL>() + (TAB && gemm_bf16_stages<BM, BN, DUAL>() == 2 ? GELU_TAB_FLOATS * 4 : 0);
-}
-
 // One output tile; vb = the tile's number in dispatch order.  Block-uniform control flow; returns at
 // once for numbers past the last tile (the grid is sized for the worst case).
 // SEGS (weight gradients): the K range is that of several calls, one after the other through one pipeline, each call's
@@ -322,11 +331,15 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs& g, const int vb, 
   constexpr int TM = 2 * WTM, TNN = 2 * WTN; // 16 x 16 MFMA tiles of a wave
   constexpr bool A_KC = (MODE != MODE_TN);   // A stored with K contiguous
   constexpr bool B_KC = (MODE == MODE_NT);
-  constexpr int A_BYTES = BM * BKT * 2, B_BYTES = BN * BKT * 2;
-  constexpr int STAGE = gemm_bf16_stage_bytes<BM, BN, DUAL>();
-  constexpr int NBUF = gemm_bf16_stages<BM, BN, DUAL>();
+  constexpr int A_BYTES = gemm_bf16_a_bytes<BM>(), B_BYTES = BN * BKT * 2, B_STAGE = gemm_bf16_b_bytes<BN, DUAL>();   // B_STAGE: of both matrices
+  constexpr bool THREE = gemm_bf16_three<BM, BN, DUAL>(), THREE_B = THREE || DUAL || CHAIN;
+  constexpr int NA = THREE || !THREE_B ? 3 : 2, NB = THREE_B ? 3 : 2, B_AT = NA * A_BYTES;   // LDS: the stages of A, then those of B
   constexpr bool TAB = (EPI == EPI_GELU_BWD || EPI == EPI_GELU_FWD) && Half16<ST>::GELU_TABLE;
-  static_assert(KS == 2 && (NBUF == 2 || NBUF == 3), "the pipeline below: two or three stages of two K steps");
+  static_assert(KS == 2, "the pipeline below: stages of two K steps");
+  static_assert(NA * A_BYTES + NB * B_STAGE <= gemm_bf16_lds_bytes<BM, BN, DUAL>(), "the caller's LDS");
+  // the GELU table takes a stage that is free before the loop's last two iterations
+  constexpr int TAB_AT = NB == 3 ? B_AT : 0, TAB_STAGE = NB == 3 ? B_STAGE : A_BYTES;
+  static_assert(!TAB || TAB_STAGE >= GELU_TAB_FLOATS * 4, "room for the table");
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform: keeps wave-dependent values scalar
@@ -434,7 +447,7 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs& g, const int vb, 
   f32x4 total[SEGS ? TM : 1][SEGS ? TNN : 1] = {};
 
   const int KT = (klen + BKT - 1) / BKT;
-  int tab_stage = 0;   // (three stages) the buffer that ends up with the GELU table
+  int tab_stage = 0;   // the stage that ends up with the GELU table
   // MFMA row bands of this wave that contain valid rows
   // (row band b of the tile belongs to wave row b % WGM, as its band b / WGM: a partly filled tile then
   // spreads its valid bands over all wave rows instead of loading the first ones only)
@@ -458,12 +471,12 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs& g, const int vb, 
   if constexpr (B_KC) {
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks)
-      b_fr[ks] = A_BYTES + kc_off(wn * WTN * 32 + (lane & 15), ks * 4 + (lane >> 4));
+      b_fr[ks] = B_AT + kc_off(wn * WTN * 32 + (lane & 15), ks * 4 + (lane >> 4));
   } else {
 #pragma unroll
     for (int j = 0; j < TNN; ++j)
-      b_fr[j] = A_BYTES + ks_off<BN>((lane >> 4) * 8 + ((lane & 15) >> 2),
-                                     (wn * WTN * 32 + j * 16 + (lane & 3) * 4) * 2);
+      b_fr[j] = B_AT + ks_off<BN>((lane >> 4) * 8 + ((lane & 15) >> 2),
+                                  (wn * WTN * 32 + j * 16 + (lane & 3) * 4) * 2);
   }
 
   {
@@ -527,19 +540,18 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs& g, const int vb, 
     };
     const int KT1 = KT;                      // stages of one operand pair
     const int KTT = SEGS ? seg_stages : !CHAIN ? KT1 : part_stages > 0 ? part_stages : 2 * KT1;   // stages in all
-    tab_stage = KTT % NBUF;
-    // Iteration kt issues the loads of stage kt+D, multiplies stage kt (reading the fragments of stage
-    // kt+1 meanwhile), then waits until its own loads of stage kt+2 have landed (all but the newest D-2
-    // stages) and joins the block barrier, after which stage kt+2 is visible to every wave and stage
-    // kt's buffer may be overwritten.
-    constexpr int L = StA::CH + StB::CH * (DUAL ? 2 : 1);   // loads per thread per stage
-    constexpr int LMIN = L - (StA::LAST < NT ? 1 : 0);       // of the waves that sit out the last load of A
+    tab_stage = KTT % 3;
+    constexpr int LB = StB::CH * (DUAL ? 2 : 1), L = StA::CH + LB;   // loads per thread per stage: of B, in all
+    constexpr int LA_MIN = StA::CH - (StA::LAST < NT ? 1 : 0);       // of A by the waves that sit out the last one
+    constexpr int B_Q = NB == 2 ? 0 : StA::CH, A_Q = NB == 2 ? LB : 0;   // where the loads of B and of A start among a stage's
     static_assert(StB::LAST == NT, "whole loads of B");
-    constexpr int PEND = (NBUF - 1) * LMIN;                  // loads that may stay in flight at the prologue's barrier: all but stage 0's
-    static_assert(PEND < 64 && LMIN < 16, "the wait counter has six bits");
+    static_assert(!SEGS || NA == NB, "a segment's operands are requested together");
+    constexpr int PEND = (NA - 1) * LA_MIN + (NB - 1) * LB;   // loads that may stay in flight at the prologue's barrier: all but stage 0's
+    constexpr int AHEAD_MIN = (NA == 3 ? LA_MIN : 0) + (NB == 3 ? LB : 0);    // of the newest stage that may stay in flight in the loop: A's alone where B has two
+    static_assert(PEND < 64 && AHEAD_MIN < 16, "the wait counter has six bits");
     constexpr int WAIT_P = (PEND & 15) | ((PEND >> 4) << 14) | 0x70 | (15 << 8);   // s_waitcnt vmcnt(PEND) only
     constexpr int WAIT_0 = 0x70 | (15 << 8);                                       // s_waitcnt vmcnt(0) only
-    constexpr int WAIT_AHEAD = LMIN | 0x70;                                        // s_waitcnt vmcnt(LMIN) lgkmcnt(0)
+    constexpr int WAIT_AHEAD = AHEAD_MIN | 0x70;                                   // s_waitcnt vmcnt(AHEAD_MIN) lgkmcnt(0)
     constexpr int WAIT_LGKM0 = 0xC07F;                                             // s_waitcnt lgkmcnt(0) only
     unsigned a_vo[StA::CH], b_vo[StB::CH];
 #pragma unroll
@@ -558,28 +570,22 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs& g, const int vb, 
     // cannot issue a load cannot issue the MFMAs behind it either.
     constexpr int NR = TM;                           // regions per K step
     bf16x8 af[TM], bfr[2][TNN], bfr2[2][DUAL ? TNN : 1];
-#define MOE_LOAD(kt_, buf_)                                                                                 \
+// load q_ of a stage: the chunks of A and those of B (DUAL: both weight matrices in turn).  Where B has two stages, its loads go
+// first: they have to land an iteration earlier
+#define MOE_LOAD1(akt_, abuf_, bkt_, bbuf_, q_)                                                             \
   do {                                                                                                      \
-    if constexpr (SEGS) next_stage();                                                                       \
-    _Pragma("unroll") for (int q__ = 0; q__ < L; ++q__) MOE_LOAD1(kt_, buf_, q__);                          \
-    if constexpr (SEGS) ++seg_k;                                                                            \
-  } while (0)
-// load q_ (0 .. L-1) of a stage: the A chunks, then the B chunks (DUAL: both weight matrices in turn)
-#define MOE_LOAD1(kt_, buf_, q_)                                                                            \
-  do {                                                                                                      \
-    const int kq__ = SEGS ? seg_k : CHAIN ? (kt_) + skip : (kt_);                                           \
+    const int kq__ = SEGS ? seg_k : ((q_) >= B_Q && (q_) < B_Q + LB ? (bkt_) : (akt_)) + (CHAIN ? skip : 0);                     \
     const bool sec__ = CHAIN && kq__ >= KT1;                                                                \
     const unsigned kl__ = (unsigned)(sec__ ? kq__ - KT1 : kq__);                                            \
-    const unsigned st__ = smem_base + (buf_) + wbase;                                                       \
-    if ((q_) < StA::CH) {                                                                                   \
-      if ((q_) < StA::CH - 1 || StA::LAST == NT || wave < StA::LAST / 64)                                   \
-      load_to_lds16(sec__ ? ra1 : ra, st__ + NT * 16 * (q_), a_vo[(q_) < StA::CH ? (q_) : 0] + kl__ * astep); \
+    if ((q_) >= B_Q && (q_) < B_Q + LB) {                                                                   \
+      const int c__ = ((q_) - B_Q) / (DUAL ? 2 : 1);                                                        \
+      const unsigned st__ = smem_base + B_AT + (bbuf_) + wbase + NT * 16 * c__;                             \
+      if (!DUAL || ((q_) - B_Q) % 2 == 0) load_to_lds16(sec__ ? rb1 : rb, st__, b_vo[c__] + kl__ * bstep);          \
+      else load_to_lds16(rb1, st__ + B_BYTES, b_vo[c__] + kl__ * bstep);                                    \
     } else {                                                                                                \
-      const int c__ = ((q_) - StA::CH) / (DUAL ? 2 : 1) % StB::CH;                                          \
-      if (!DUAL || ((q_) - StA::CH) % 2 == 0)                                                               \
-        load_to_lds16(sec__ ? rb1 : rb, st__ + A_BYTES + NT * 16 * c__, b_vo[c__] + kl__ * bstep);          \
-      else                                                                                                  \
-        load_to_lds16(rb1, st__ + A_BYTES + B_BYTES + NT * 16 * c__, b_vo[c__] + kl__ * bstep);             \
+      const int c__ = (q_) - A_Q;                                                                           \
+      if (c__ < StA::CH - 1 || StA::LAST == NT || wave < StA::LAST / 64)                                    \
+        load_to_lds16(sec__ ? ra1 : ra, smem_base + (abuf_) + wbase + NT * 16 * c__, a_vo[c__] + kl__ * astep); \
     }                                                                                                       \
   } while (0)
 // A fragment of row tile i_ / B fragment(s) of column tile j_ for K step ks_ of the stage at buf_
@@ -597,14 +603,14 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs& g, const int vb, 
     else bfr[set_][j_] = lds_read_ks2<BN>(st__ + b_fr[j_] + (ks_) * 32 * BN * 2);                           \
     if constexpr (DUAL) bfr2[set_][j_] = lds_read_ks2<BN>(st__ + B_BYTES + b_fr[j_] + (ks_) * 32 * BN * 2); \
   } while (0)
-#define MOE_FRAGS(set_, buf_, ks_)                                                                          \
+#define MOE_FRAGS(set_, abuf_, bbuf_, ks_)                                                                  \
   do {                                                                                                      \
-    _Pragma("unroll") for (int i__ = 0; i__ < TM; ++i__) MOE_FRAG_A(i__, buf_, ks_);                        \
-    _Pragma("unroll") for (int j__ = 0; j__ < TNN; ++j__) MOE_FRAG_B(set_, j__, buf_, ks_);                 \
+    _Pragma("unroll") for (int i__ = 0; i__ < TM; ++i__) MOE_FRAG_A(i__, abuf_, ks_);                       \
+    _Pragma("unroll") for (int j__ = 0; j__ < TNN; ++j__) MOE_FRAG_B(set_, j__, bbuf_, ks_);                \
   } while (0)
-// One K step on B register set set_; DO_NEXT_: read the fragments of K step rks_ of the stage at rbuf_;
-// DO_LOAD_: issue the loads LQ0_ .. LQ0_+LQN_-1 of stage lkt_ into the buffer at lbuf_.
-#define MOE_STEP(set_, DO_NEXT_, rbuf_, rks_, DO_LOAD_, lkt_, lbuf_, LQ0_, LQN_, NI_)                       \
+// One K step on B register set set_; DO_NEXT_: read the fragments of K step rks_ of the stages at rabuf_, rbbuf_;
+// issue the loads LQ0_ .. LQ0_+LQN_-1 of A's stage S_+NA into a0 and B's stage S_+NB into bb0.
+#define MOE_STEP(set_, DO_NEXT_, rabuf_, rbbuf_, rks_, S_, LQN_, NI_)                                       \
   do {                                                                                                      \
     _Pragma("unroll") for (int r__ = 0; r__ < NR; ++r__) {                                                  \
       if ((r__ >> 1) < (NI_)) {                                                                             \
@@ -614,13 +620,11 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs& g, const int vb, 
         }                                                                                                   \
       }                                                                                                     \
       if (DO_NEXT_) {                                                                                       \
-        MOE_FRAG_A(r__, rbuf_, rks_);                                                                       \
-        if (r__ < TNN) MOE_FRAG_B((set_) ^ 1, r__ < TNN ? r__ : 0, rbuf_, rks_);                            \
+        MOE_FRAG_A(r__, rabuf_, rks_);                                                                      \
+        if (r__ < TNN) MOE_FRAG_B((set_) ^ 1, r__ < TNN ? r__ : 0, rbbuf_, rks_);                           \
       }                                                                                                     \
-      if (DO_LOAD_) {                                                                                       \
-        _Pragma("unroll") for (int q__ = 0; q__ < (LQN_); ++q__)                                            \
-          if (q__ * NR / ((LQN_) > 0 ? (LQN_) : 1) == r__) MOE_LOAD1(lkt_, lbuf_, (LQ0_) + q__);            \
-      }                                                                                                     \
+      _Pragma("unroll") for (int q__ = 0; q__ < L; ++q__)                                                   \
+        if (q__ < (LQN_) && q__ * NR / L == r__) MOE_LOAD1((S_) + NA, a0, (S_) + NB, bb0, q__);             \
       __builtin_amdgcn_sched_barrier(0);                                                                    \
     }                                                                                                       \
   } while (0)
@@ -634,70 +638,77 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs& g, const int vb, 
     auto load_table = [&](unsigned at) {
       static_assert(GELU_TAB_FLOATS * 4 % (NT * 16) == 0, "whole block-wide loads");
       const rsrc_t rt = make_rsrc(g.gelu_tab, (size_t)GELU_TAB_FLOATS * 4);
+      const unsigned to = __builtin_amdgcn_readfirstlane(smem_base + at + wbase);
 #pragma unroll
       for (int i = 0; i < GELU_TAB_FLOATS * 4 / (NT * 16); ++i)
-        load_to_lds16(rt, smem_base + at + i * NT * 16 + wbase, (unsigned)(i * NT + tid) * 16u);
+        load_to_lds16(rt, to + i * NT * 16, (unsigned)(i * NT + tid) * 16u);
     };
-    if constexpr (TAB && NBUF == 2) load_table(NBUF * STAGE);   // with the first stage loads, older than they are: the first wait covers it
     {
-      // Iteration S multiplies stage S (two K steps) out of buffer S % NBUF.  K step 0 reads the fragments of
-      // K step 1; then every wave waits for its own loads of stage S+1 (three stages: those of S+2 stay in flight) and for
-      // its fragment reads and joins the one block barrier of the iteration, after which stage S+1 is visible to all and
-      // nobody reads buffer S % NBUF again; K step 1 reads the fragments of step 0 of stage S+1 and issues the loads of
-      // stage S+NBUF into buffer S % NBUF (they have NBUF - 1 stages' worth of MFMAs to land).  MORE_: stage S+2 exists.
-#define MOE_ITER(S_, DO_NEXT_, DO_LOAD_, MORE_, NI_)                                                         \
+      // Iteration S multiplies stage S (two K steps).  K step 0 reads the fragments of K step 1; then every wave waits for its
+      // own loads of stage S+1 (what was requested of stage S+2 stays in flight: all of it, or A's where B has two stages) and
+      // for its fragment reads and joins the one block barrier of the iteration, after which stage S+1 is visible to all and
+      // nobody reads stage S's LDS again; K step 1 reads the fragments of step 0 of stage S+1 and requests B's stage S+NB and
+      // A's stage S+NA into it.  MORE_: stage S+2 exists; LQN_: how many loads of a stage are requested.
+#define MOE_ITER(S_, DO_NEXT_, LQN_, MORE_, NI_)                                                            \
   do {                                                                                                      \
-    MOE_STEP(0, true, b0, 1, false, 0, 0, 0, 0, NI_);                                                       \
+    MOE_STEP(0, true, a0, bb0, 1, 0, 0, NI_);                                                               \
     if (DO_NEXT_) {                                                                                         \
-      if (NBUF == 3 && (MORE_)) __builtin_amdgcn_s_waitcnt(WAIT_AHEAD);                                     \
+      if (MORE_) __builtin_amdgcn_s_waitcnt(WAIT_AHEAD);                                                    \
       else __builtin_amdgcn_s_waitcnt(0);   /* vmcnt(0) lgkmcnt(0) */                                       \
       MOE_BLOCK_BARRIER();                                                                                  \
     }                                                                                                       \
-    if constexpr (SEGS) { if (DO_LOAD_) next_stage(); }                                                     \
-    MOE_STEP(1, DO_NEXT_, b1, 0, DO_LOAD_, (S_) + NBUF, b0, 0, L, NI_);                                     \
-    if constexpr (SEGS) { if (DO_LOAD_) ++seg_k; }                                                          \
-    if constexpr (NBUF == 2) { const int t__ = b0; b0 = b1; b1 = t__; }                                     \
-    else { const int t__ = b0; b0 = b1; b1 = b2; b2 = t__; }                                                \
+    if constexpr (SEGS) { if ((LQN_) > 0) next_stage(); }                                                   \
+    MOE_STEP(1, DO_NEXT_, a1, bb1, 0, S_, LQN_, NI_);                                                       \
+    if constexpr (SEGS) { if ((LQN_) > 0) ++seg_k; }                                                        \
+    if constexpr (NA == 2) { const int t__ = a0; a0 = a1; a1 = t__; }                                       \
+    else { const int t__ = a0; a0 = a1; a1 = a2; a2 = t__; }                                                   \
+    if constexpr (NB == 2) { const int t__ = bb0; bb0 = bb1; bb1 = t__; }                                   \
+    else { const int t__ = bb0; bb0 = bb1; bb1 = bb2; bb2 = t__; }                                          \
   } while (0)
       if (KTT > 0) {
         if constexpr (SEGS) next_product();
-        int b0 = 0, b1 = STAGE, b2 = 2 * STAGE;
+        int a0 = 0, a1 = A_BYTES, a2 = NA == 3 ? 2 * A_BYTES : 0, bb0 = 0, bb1 = B_STAGE, bb2 = NB == 3 ? 2 * B_STAGE : 0;
 #pragma unroll
-        for (int q = 0; q < NBUF; ++q)
-          if (q < KTT) MOE_LOAD(q, q * STAGE);
-        if (KTT >= NBUF) {
-          __builtin_amdgcn_s_waitcnt(WAIT_P);   // stage 0 (and a table) have landed, the others may be in flight
+        for (int q = 0; q < 3; ++q)
+          if (q < KTT) {
+            if constexpr (SEGS) next_stage();
+#pragma unroll
+            for (int l = 0; l < L; ++l)
+              if (q < (l >= B_Q && l < B_Q + LB ? NB : NA)) MOE_LOAD1(q, q * A_BYTES, q, q * B_STAGE, l);
+            if constexpr (SEGS) ++seg_k;
+          }
+        if (KTT >= 3) {
+          __builtin_amdgcn_s_waitcnt(WAIT_P);   // stage 0 has landed, the others may be in flight
         } else {
-          if constexpr (TAB && NBUF == 3) load_table(KTT * STAGE);
+          if constexpr (TAB) load_table(TAB_AT + KTT * TAB_STAGE);
           __builtin_amdgcn_s_waitcnt(WAIT_0);
         }
         MOE_BLOCK_BARRIER();
-        // (three stages) the table takes the buffer of stage KTT - 3 once that is free; the wait and the barrier of the
-        // iteration after that make it visible to all
+        // the table takes the place of stage KTT - 3 once that is free; the wait and the barrier of the iteration after that
+        // make it visible to all
 #define MOE_MAINLOOP(NI_)                                                                        \
   do {                                                                                          \
-    MOE_FRAGS(0, b0, 0);                                                                        \
+    MOE_FRAGS(0, a0, bb0, 0);                                                                   \
     __builtin_amdgcn_s_waitcnt(WAIT_LGKM0);   /* nothing pending at the loop head: the waits inside the loop then count only its own reads */ \
     int S = 0;                                                                                  \
-    _Pragma("unroll 1") for (; S + NBUF < KTT; ++S) {                                            \
-      MOE_ITER(S, true, true, true, NI_);                                                       \
+    _Pragma("unroll 1") for (; S + 3 < KTT; ++S) {                                              \
+      MOE_ITER(S, true, L, true, NI_);                                                          \
       if constexpr (SEGS) end_of_stage(S);                                                      \
     }                                                                                           \
     _Pragma("unroll 1") for (; S < KTT; ++S) {                                                   \
-      const int free__ = b0;                                                                    \
-      MOE_ITER(S, S + 1 < KTT, NBUF == 2 && S + 2 < KTT, S + 2 < KTT, NI_);                      \
+      const int free__ = TAB_AT + (NB == 3 ? bb0 : a0);                                         \
+      MOE_ITER(S, S + 1 < KTT, !THREE && S + 2 < KTT ? (NA == 2 ? StA::CH : LB) : 0, S + 2 < KTT, NI_);              \
       if constexpr (SEGS) end_of_stage(S);                                                      \
-      if constexpr (TAB && NBUF == 3) { if (S + 3 == KTT) load_table(free__); }                  \
+      if constexpr (TAB) { if (S + 3 == KTT) load_table(free__); }                              \
     }                                                                                           \
   } while (0)
         if (ni == WTM) MOE_MAINLOOP(WTM);
-        else if (NBUF == 3 && ni == WTM - 1) MOE_MAINLOOP(WTM - 1);
+        else if (NB == 3 && ni == WTM - 1) MOE_MAINLOOP(WTM - 1);
         else MOE_MAINLOOP(ni);
 #undef MOE_MAINLOOP
       }
 #undef MOE_ITER
     }
-#undef MOE_LOAD
 #undef MOE_LOAD1
 #undef MOE_FRAG_A
 #undef MOE_FRAG_B
@@ -784,7 +795,7 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs& g, const int vb, 
     const size_t first = (size_t)row0 * g.N + n0, bytes = ((size_t)mvalid * g.N - n0) * 2;
     const OutPlanes o = out_planes<ST, EPI>(g, first, bytes);
     const unsigned pitch = (unsigned)g.N * 2u;
-    const float* tab_lds = reinterpret_cast<const float*>(smem + (NBUF == 2 ? NBUF * STAGE : tab_stage * STAGE));
+    const float* tab_lds = reinterpret_cast<const float*>(smem + TAB_AT + tab_stage * TAB_STAGE);
     if constexpr (TNN == 2) {   // 32 columns per wave and matrix, half lines (the neighbouring wave has the other half)
       const unsigned col = (unsigned)(wn * C + lane_col8(grp)) * 2u;
 #pragma unroll

@@ -277,6 +277,21 @@ def test_forward_stores_of_high_tiles(T, d, f, E, k, dtype, act):
     run_case(S.WORKLOADS["cfg1"].scaled(T=T, d=d, f=f, E=E, k=k, dtype=getattr(S, "DT_" + dtype.upper()), act=getattr(S, "ACT_" + act.upper())))
 
 
+@pytest.mark.parametrize("T, d, f, dtype, act", [
+    (600, 64, 64, "bf16", "gelu"),        # one K stage in every row-tile GEMM (SwiGLU's dx: two)
+    (600, 64, 64, "bf16", "swiglu"),
+    (600, 128, 192, "f16", "gelu"),       # two and three, as many as the operand with more LDS has
+    (600, 192, 128, "f16", "swiglu"),
+    (600, 256, 192, "bf16", "gelu"),      # four: the first that meets the loop's steady state
+    (600, 192, 256, "bf16", "swiglu"),
+])
+def test_short_k_in_high_tiles(T, d, f, dtype, act):
+    """256-row tiles whose operands have two and three LDS stages, with fewer K stages than these, as many, and one more."""
+    from paper_2504_03871_amd import synth as S
+    from tests.test_gpu_parity import run_case
+    run_case(S.WORKLOADS["cfg1"].scaled(T=T, d=d, f=f, E=1, k=1, dtype=getattr(S, "DT_" + dtype.upper()), act=getattr(S, "ACT_" + act.upper())))
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 def test_last_round_split_along_k_in_the_input_gradient_of_low_tiles(dtype):
     """dx = dA W1^T of 160-row tiles, which are too many to share a launch where 256-row ones would not be, with the last
