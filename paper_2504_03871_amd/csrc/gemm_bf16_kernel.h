@@ -18,14 +18,15 @@
 // Pipeline: LDS stages of 64 K values, two of one operand and three of the other, filled by buffer loads that write LDS
 // directly (no staging registers, no LDS store instructions).  An iteration multiplies one stage in two K steps; the first
 // reads the fragments of the second, then every wave waits for its own loads of the next stage and joins the
-// iteration's one block barrier; the second K step reads the first fragments of the next stage and issues
-// the loads of a later one, the second or the third after this, into the LDS just released.  64-wide because a 32-wide stage fetches
-// an operand with contiguous K as 64-byte pieces of 128-byte lines, which fills the address FIFO of the
+// iteration's one block barrier; the second K step reads the first fragments of the next stage.  The loads of the
+// stage after that go where stages have been read: the barrier releases the LDS of this one to the operand with two, that of
+// the one before has been free since the last barrier, and the operand with three is loaded in the first K step already.
+// 64-wide because a 32-wide stage fetches an operand with contiguous K as 64-byte pieces of 128-byte lines, which fills the address FIFO of the
 // memory pipe (counters: full thirteen times as often); the operands with strided K gain a little from the
 // halved number of barriers (weight gradients +2 % against a ring of four 32-wide stages).
-// 160 KB of LDS hold two stages of 256 x 256 and a third of one operand.  Its loads may take an iteration longer, and those of
-// the other go first and have the whole of theirs; waits for loads were what the loop lost (two stages of both: 0.27 to 0.40 of
-// the wave cycles).  us, two stages of both -> three of A -> three of B, on one box:
+// 160 KB of LDS hold two stages of 256 x 256 and a third of one operand.  Its loads have half an iteration more to land, and
+// those of the other can go first in their half; waits for loads were what the loop lost (two stages of both: 0.27 to 0.40 of the
+// wave cycles).  us, two stages of both -> three of A -> three of B, all loads still in the second K step (LSH below has the rest):
 //   16384 rows in 16 skewed experts, d 2048, f 8192, fp16: y 494 -> 467 -> 462, GEMM1 610 -> 592 -> 579, dH 626 -> 601 -> 605,
 //     dW2 622 -> 606 -> 638, dx + dW1 1181 -> 1140 -> 1119
 //   65536 rows in 8, d 4096, f 14336, SwiGLU: GEMM1 12.10 -> 12.22 -> 11.93 ms, y 5.53 -> 5.33 -> 5.38, dH 6.37 -> 6.25 -> 6.28,
@@ -543,10 +544,18 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs& g, const int vb, 
     tab_stage = KTT % 3;
     constexpr int LB = StB::CH * (DUAL ? 2 : 1), L = StA::CH + LB;   // loads per thread per stage: of B, in all
     constexpr int LA_MIN = StA::CH - (StA::LAST < NT ? 1 : 0);       // of A by the waves that sit out the last one
+    // Which K step makes a stage's loads (numbered q, below): where one operand has two LDS stages, its LSH loads are K step 1's,
+    // in the first half of its regions, and those of the other are K step 0's, over all of its regions; else all are K step 1's.
+    // (All in K step 1 -> as it is, us: SwiGLU, 65536 rows in 8 experts, d 4096, f 14336, GEMM1 12150 -> 12100, dx 11190 -> 10940, dH
+    // 6360 -> 6290, dW 8670 -> 8570, y 5440 -> 5440; in 128, d 2048, f 1024, GEMM1 588 -> 569, y 324 -> 309, dx 539 -> 514; fp16 GELU, 16384
+    // in 16, d 2048, f 8192, dx + dW1 1167 -> 1120, dH 628 -> 611.  K step 1's over all its regions: dx of the first 11630; in the
+    // first quarter: 10980.)
+    constexpr int LSH = THREE ? L : NB == 2 ? LB : StA::CH;
     constexpr int B_Q = NB == 2 ? 0 : StA::CH, A_Q = NB == 2 ? LB : 0;   // where the loads of B and of A start among a stage's
     static_assert(StB::LAST == NT, "whole loads of B");
     static_assert(!SEGS || NA == NB, "a segment's operands are requested together");
-    constexpr int PEND = (NA - 1) * LA_MIN + (NB - 1) * LB;   // loads that may stay in flight at the prologue's barrier: all but stage 0's
+    constexpr int DEPTH = THREE ? 3 : 2;                      // stages requested before the loop
+    constexpr int PEND = (DEPTH - 1) * (LA_MIN + LB);         // loads that may stay in flight at the prologue's barrier: all but stage 0's
     constexpr int AHEAD_MIN = (NA == 3 ? LA_MIN : 0) + (NB == 3 ? LB : 0);    // of the newest stage that may stay in flight in the loop: A's alone where B has two
     static_assert(PEND < 64 && AHEAD_MIN < 16, "the wait counter has six bits");
     constexpr int WAIT_P = (PEND & 15) | ((PEND >> 4) << 14) | 0x70 | (15 << 8);   // s_waitcnt vmcnt(PEND) only
@@ -569,6 +578,8 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs& g, const int vb, 
     // steady trickle: loads issued in one burst fill the address FIFO of the memory pipe, and a wave that
     // cannot issue a load cannot issue the MFMAs behind it either.
     constexpr int NR = TM;                           // regions per K step
+    auto load_region = [](int q) { return THREE ? q * NR / L : q < LSH ? q * NR / (2 * LSH) : (q - LSH + 1) * NR / (L - LSH) - 1; };
+    static_assert(THREE || NR % (L - LSH) == 0, "every load has a region");
     bf16x8 af[TM], bfr[2][TNN], bfr2[2][DUAL ? TNN : 1];
 // load q_ of a stage: the chunks of A and those of B (DUAL: both weight matrices in turn).  Where B has two stages, its loads go
 // first: they have to land an iteration earlier
@@ -609,8 +620,8 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs& g, const int vb, 
     _Pragma("unroll") for (int j__ = 0; j__ < TNN; ++j__) MOE_FRAG_B(set_, j__, bbuf_, ks_);                \
   } while (0)
 // One K step on B register set set_; DO_NEXT_: read the fragments of K step rks_ of the stages at rabuf_, rbbuf_;
-// issue the loads LQ0_ .. LQ0_+LQN_-1 of A's stage S_+NA into a0 and B's stage S_+NB into bb0.
-#define MOE_STEP(set_, DO_NEXT_, rabuf_, rbbuf_, rks_, S_, LQN_, NI_)                                       \
+// request the loads Q0_ .. Q1_-1 of stage S_+DEPTH.
+#define MOE_STEP(set_, DO_NEXT_, rabuf_, rbbuf_, rks_, S_, Q0_, Q1_, NI_)                                  \
   do {                                                                                                      \
     _Pragma("unroll") for (int r__ = 0; r__ < NR; ++r__) {                                                  \
       if ((r__ >> 1) < (NI_)) {                                                                             \
@@ -624,7 +635,8 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs& g, const int vb, 
         if (r__ < TNN) MOE_FRAG_B((set_) ^ 1, r__ < TNN ? r__ : 0, rbbuf_, rks_);                           \
       }                                                                                                     \
       _Pragma("unroll") for (int q__ = 0; q__ < L; ++q__)                                                   \
-        if (q__ < (LQN_) && q__ * NR / L == r__) MOE_LOAD1((S_) + NA, a0, (S_) + NB, bb0, q__);             \
+        if (q__ >= (Q0_) && q__ < (Q1_) && load_region(q__) == r__)                                         \
+          MOE_LOAD1((S_) + DEPTH, THREE || NA == 2 ? a0 : a2, (S_) + DEPTH, THREE || NB == 2 ? bb0 : bb2, q__); \
       __builtin_amdgcn_sched_barrier(0);                                                                    \
     }                                                                                                       \
   } while (0)
@@ -645,21 +657,21 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs& g, const int vb, 
     };
     {
       // Iteration S multiplies stage S (two K steps).  K step 0 reads the fragments of K step 1; then every wave waits for its
-      // own loads of stage S+1 (what was requested of stage S+2 stays in flight: all of it, or A's where B has two stages) and
-      // for its fragment reads and joins the one block barrier of the iteration, after which stage S+1 is visible to all and
-      // nobody reads stage S's LDS again; K step 1 reads the fragments of step 0 of stage S+1 and requests B's stage S+NB and
-      // A's stage S+NA into it.  MORE_: stage S+2 exists; LQN_: how many loads of a stage are requested.
-#define MOE_ITER(S_, DO_NEXT_, LQN_, MORE_, NI_)                                                            \
+      // own loads of stage S+1 (of stage S+2 those stay in flight that are made by now: all, with three stages of both, else
+      // this K step's) and for its fragment reads and joins the one block barrier of the iteration, after which stage S+1 is
+      // visible to all and nobody reads stage S's LDS again; K step 1 reads the fragments of step 0 of stage S+1.
+      // DO_LOAD_: stage S+DEPTH is requested; MORE_: stage S+2 exists and is on its way.
+#define MOE_ITER(S_, DO_NEXT_, DO_LOAD_, MORE_, NI_)                                                        \
   do {                                                                                                      \
-    MOE_STEP(0, true, a0, bb0, 1, 0, 0, NI_);                                                               \
+    MOE_STEP(0, true, a0, bb0, 1, S_, LSH, !THREE && (DO_LOAD_) ? L : 0, NI_);                              \
     if (DO_NEXT_) {                                                                                         \
       if (MORE_) __builtin_amdgcn_s_waitcnt(WAIT_AHEAD);                                                    \
       else __builtin_amdgcn_s_waitcnt(0);   /* vmcnt(0) lgkmcnt(0) */                                       \
       MOE_BLOCK_BARRIER();                                                                                  \
     }                                                                                                       \
-    if constexpr (SEGS) { if ((LQN_) > 0) next_stage(); }                                                   \
-    MOE_STEP(1, DO_NEXT_, a1, bb1, 0, S_, LQN_, NI_);                                                       \
-    if constexpr (SEGS) { if ((LQN_) > 0) ++seg_k; }                                                        \
+    if constexpr (SEGS) { if (DO_LOAD_) next_stage(); }                                                     \
+    MOE_STEP(1, DO_NEXT_, a1, bb1, 0, S_, 0, (DO_LOAD_) ? LSH : 0, NI_);                                    \
+    if constexpr (SEGS) { if (DO_LOAD_) ++seg_k; }                                                          \
     if constexpr (NA == 2) { const int t__ = a0; a0 = a1; a1 = t__; }                                       \
     else { const int t__ = a0; a0 = a1; a1 = a2; a2 = t__; }                                                   \
     if constexpr (NB == 2) { const int t__ = bb0; bb0 = bb1; bb1 = t__; }                                   \
@@ -669,37 +681,36 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs& g, const int vb, 
         if constexpr (SEGS) next_product();
         int a0 = 0, a1 = A_BYTES, a2 = NA == 3 ? 2 * A_BYTES : 0, bb0 = 0, bb1 = B_STAGE, bb2 = NB == 3 ? 2 * B_STAGE : 0;
 #pragma unroll
-        for (int q = 0; q < 3; ++q)
+        for (int q = 0; q < DEPTH; ++q)
           if (q < KTT) {
             if constexpr (SEGS) next_stage();
 #pragma unroll
             for (int l = 0; l < L; ++l)
-              if (q < (l >= B_Q && l < B_Q + LB ? NB : NA)) MOE_LOAD1(q, q * A_BYTES, q, q * B_STAGE, l);
+              MOE_LOAD1(q, q * A_BYTES, q, q * B_STAGE, l);
             if constexpr (SEGS) ++seg_k;
           }
-        if (KTT >= 3) {
+        if (KTT >= 3 || (!TAB && KTT >= DEPTH)) {
           __builtin_amdgcn_s_waitcnt(WAIT_P);   // stage 0 has landed, the others may be in flight
         } else {
           if constexpr (TAB) load_table(TAB_AT + KTT * TAB_STAGE);
           __builtin_amdgcn_s_waitcnt(WAIT_0);
         }
         MOE_BLOCK_BARRIER();
-        // the table takes the place of stage KTT - 3 once that is free; the wait and the barrier of the iteration after that
-        // make it visible to all
+        // the table takes the place of stage KTT - 3, free from that iteration's barrier on; the wait and the barrier of the next
+        // iteration make it visible to all
 #define MOE_MAINLOOP(NI_)                                                                        \
   do {                                                                                          \
     MOE_FRAGS(0, a0, bb0, 0);                                                                   \
     __builtin_amdgcn_s_waitcnt(WAIT_LGKM0);   /* nothing pending at the loop head: the waits inside the loop then count only its own reads */ \
     int S = 0;                                                                                  \
-    _Pragma("unroll 1") for (; S + 3 < KTT; ++S) {                                              \
-      MOE_ITER(S, true, L, true, NI_);                                                          \
+    _Pragma("unroll 1") for (; S + DEPTH < KTT; ++S) {                                              \
+      MOE_ITER(S, true, true, true, NI_);                                                          \
       if constexpr (SEGS) end_of_stage(S);                                                      \
     }                                                                                           \
     _Pragma("unroll 1") for (; S < KTT; ++S) {                                                   \
-      const int free__ = TAB_AT + (NB == 3 ? bb0 : a0);                                         \
-      MOE_ITER(S, S + 1 < KTT, !THREE && S + 2 < KTT ? (NA == 2 ? StA::CH : LB) : 0, S + 2 < KTT, NI_);              \
+      if constexpr (TAB) { if (S + 2 == KTT && S > 0) load_table(TAB_AT + (NB == 3 ? bb2 : a2)); } \
+      MOE_ITER(S, S + 1 < KTT, false, THREE && S + 2 < KTT, NI_);                               \
       if constexpr (SEGS) end_of_stage(S);                                                      \
-      if constexpr (TAB) { if (S + 3 == KTT) load_table(free__); }                              \
     }                                                                                           \
   } while (0)
         if (ni == WTM) MOE_MAINLOOP(WTM);
