@@ -33,7 +33,8 @@
 //     dW 8.56 -> 8.50 -> 8.39, dx 11.87 -> 11.14 -> 11.01
 //   65536 rows in 128, d 2048, f 1024, SwiGLU: GEMM1 602 -> 577 -> 576, y 334 -> 316 -> 323, dx 575 -> 531 -> 530, dW1 842 -> 849 -> 843
 //   16384 rows in 8, d 1024, f 4096, GELU: GEMM1 178 -> 179 -> 181, y 131 -> 123 -> 125, dx + dW1 259 -> 249 -> 253
-// so three of B where two weight matrices take part (GEMM1 and dx of SwiGLU), three of A elsewhere.
+// so three of B where two products are chained (dx of SwiGLU), three of A elsewhere, with the loads as they are now also in
+// SwiGLU's GEMM1 (three of B -> of A: 65536 rows in 8 experts 12.37 -> 12.27 ms, in 128 experts 561 -> 555 us).
 // A tile of 160 rows and 256 columns (or twice 128) leaves LDS for three stages of both (156 of 160 KB): loads then have two
 // stages' worth of MFMAs to land instead of one, which is what a GEMM of few rows per expert waits for, and the chip is
 // left with smaller remainders (512 micro-batch rows per expert, d 1024, f 4096: GEMM1 57 -> 48 us; 125 rows, d 2048,
@@ -333,7 +334,7 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs& g, const int vb, 
   constexpr bool A_KC = (MODE != MODE_TN);   // A stored with K contiguous
   constexpr bool B_KC = (MODE == MODE_NT);
   constexpr int A_BYTES = gemm_bf16_a_bytes<BM>(), B_BYTES = BN * BKT * 2, B_STAGE = gemm_bf16_b_bytes<BN, DUAL>();   // B_STAGE: of both matrices
-  constexpr bool THREE = gemm_bf16_three<BM, BN, DUAL>(), THREE_B = THREE || DUAL || CHAIN;
+  constexpr bool THREE = gemm_bf16_three<BM, BN, DUAL>(), THREE_B = THREE || CHAIN;
   constexpr int NA = THREE || !THREE_B ? 3 : 2, NB = THREE_B ? 3 : 2, B_AT = NA * A_BYTES;   // LDS: the stages of A, then those of B
   constexpr bool TAB = (EPI == EPI_GELU_BWD || EPI == EPI_GELU_FWD) && Half16<ST>::GELU_TABLE;
   static_assert(KS == 2, "the pipeline below: stages of two K steps");
