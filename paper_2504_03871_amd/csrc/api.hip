@@ -388,6 +388,7 @@ int ffn_fwd_impl(const moe_cfg* cfg, const void* x_perm, const void* W1, const v
   char* sv = static_cast<char*>(saved);
   GemmArgs g = {};
   g.tiles = map.tiles; g.ntiles = map.header; g.order = map.order; g.gelu_tab = map.gelu_tab; g.tile_rows = tr;
+  g.stream = is_half(cfg) && streams_weights(A, tr, cfg->E, d, f, swiglu ? 3 : 2, (int)elt_size(cfg));
   g.offsets = offsets; g.kept = kept; g.lo = slice_lo; g.hi = slice_hi; g.E = cfg->E;
   // hidden = act(x_perm W1)
   g.A = x_perm; g.B = W1; g.B2 = W1b; g.N = f; g.K = d;
@@ -521,6 +522,7 @@ int ffn_bwd_impl(const moe_cfg* cfg, const void* dy_perm, const void* x_perm, co
   const void* hidden = swiglu ? sv + 2 * plane : sv + plane;
   GemmArgs g = {};
   g.tiles = map.tiles; g.ntiles = map.header; g.order = map.order; g.gelu_tab = map.gelu_tab; g.tile_rows = tr;
+  g.stream = is_half(cfg) && streams_weights(A, tr, cfg->E, d, f, swiglu ? 3 : 2, (int)elt_size(cfg));
   g.offsets = offsets; g.kept = kept; g.lo = slice_lo; g.hi = slice_hi; g.E = cfg->E;
   g.accumulate = accumulate;
   // Four GEMMs: dH = dy W2^T fused with the activation derivative -> dA (GELU) or dG, dU (SwiGLU);

@@ -14,7 +14,7 @@ struct RowTile {
   int32_t e;      // expert
   int32_t row0;   // first row (absolute index into the permuted buffers)
   int32_t nrows;  // valid rows in this tile (1..tile height)
-  int32_t mates;  // expert-major lists: whether the expert has other tiles too (0 in the other lists)
+  int32_t mates;  // whether the expert has other tiles too
 };
 
 // Tables over the bf16 numbers for the bf16 GELU epilogues.  The pre-activation is stored as a bf16
@@ -296,6 +296,7 @@ struct GemmArgs {
   int E;
   int accumulate;
   int chunked;   // row-tile GEMMs: order of the full tiles (block_to_tile)
+  int stream;    // row-tile GEMMs: whether weights that one row tile takes are requested as streaming data (streams_weights)
   int tile_rows; // row-tile GEMMs: rows per entry of the tile map
 };
 
@@ -340,6 +341,22 @@ int gemm_bf16_tile_rows();
 constexpr int MID_ROWS = 160;
 constexpr int MID_FEW_EXPERTS = 32, MID_AVERAGE_FEW = 512, MID_AVERAGE_MANY = 128;
 inline bool mid_applies(long long rows, int E) { return rows <= (long long)(E <= MID_FEW_EXPERTS ? MID_AVERAGE_FEW : MID_AVERAGE_MANY) * E; }
+// Whether the weights of an expert with a single row tile are requested as streaming data: they are read once per launch, and
+// as plain loads they push each other through the caches.  Asked for where experts have a tile each on average and the layer's
+// weights do not fit the memory-side cache with room to spare; smaller ones are found there by the launch that reads them next
+// (dx after GEMM1, dH after y, the next step).  90 rows per expert, us, plain -> streaming, forward pass | step, by the
+// megabytes of a layer's weights:
+//    64  d 1024, f 2048, 8 experts, GELU       57 ->  62 | 139 -> 152      192  d 1024, f 4096, 8, SwiGLU      73 ->  80 | 262 -> 293
+//   256  d 1024, f 4096, 16, GELU              87 ->  88 | 301 -> 302      256  d 1024, f 1024, 64, GELU       94 ->  92 | 307 -> 300
+//   288  d 2048, f 3072, 8, SwiGLU            102 ->  96 | 332 -> 341      384  d 1536, f 4096, 16, GELU      123 -> 116 | 402 -> 397
+//   384  d 1024, f 4096, 16, SwiGLU           130 -> 116 | 430 -> 424      384  d 1024, f 1024, 64, SwiGLU    132 -> 119 | 424 -> 398
+//   512  d 1024, f 4096, 32, GELU             158 -> 146 | 541 -> 508      576  d 1536, f 4096, 16, SwiGLU    165 -> 154 | 570 -> 550
+// 160-row tiles: 125 rows, d 2048, f 8192, 16 experts, fp16 GELU, forward pass 273 -> 260; 75 rows, d 4096, f 14336, 8, SwiGLU 559
+// -> 514.  256-row tiles: 160 rows, d 2048, f 2048, 128, GELU 552 -> 532; 150 rows, d 2048, f 2048, 64, step 1167 -> 1138; 200 rows,
+// d 2048, f 1024, 256, SwiGLU 936 -> 909; where experts have two or three tiles (512 rows, 128 experts, step) 3370 -> 3480.
+inline bool streams_weights(long long rows, int tile_rows, long long E, long long d, long long f, int matrices, int elt) {
+  return rows <= tile_rows * E && E * d * f * matrices * elt > MEMORY_SIDE_CACHE / 4 * 5;
+}
 // Whether GELU's hidden plane, which GEMM2 reads next, is stored plainly instead of streamed.  Up to about twice the L2
 // caches' 32 MB much of it is still near when GEMM2 starts; beyond, it only displaces operands.  Forward pass, us, streamed
 // -> plain: eight experts of 1000 rows, d 832, f 3264 (52 MB) 168 -> 158; six of 1200, d 1088, f 2880 (41 MB) 138 -> 126;
@@ -419,6 +436,11 @@ __device__ __forceinline__ rsrc_t make_rsrc(const void* base, size_t bytes) {
 // explicit vmcnt waits and block barriers; the memory clobber keeps LDS reads from moving across.
 __device__ __forceinline__ void load_to_lds16(rsrc_t rs, unsigned lds, unsigned voffset) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+               :: "s"(lds), "v"(voffset), "s"(rs) : "memory", "m0");
+}
+// load_to_lds16 for data that one block reads once: the weights do not displace anything in the caches
+__device__ __forceinline__ void load_to_lds16_nt(rsrc_t rs, unsigned lds, unsigned voffset) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen nt lds"
                :: "s"(lds), "v"(voffset), "s"(rs) : "memory", "m0");
 }
 // a byte offset past any operand: they are multiples of 16 bytes below 4 GiB (offsets_fit_32_bits)

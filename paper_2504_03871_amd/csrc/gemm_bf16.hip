@@ -25,7 +25,7 @@ static int launch_split_reduce(const GemmArgs& g, long long tiles, hipStream_t s
   return launch_status();
 }
 
-template <typename ST, int MODE, int EPI, bool DUAL, bool CHAIN, int BM>
+template <typename ST, int MODE, int EPI, bool DUAL, bool CHAIN, int BM, bool STREAM>
 static int launch_rows(const GemmArgs& g, int max_tiles, hipStream_t s) {
   constexpr int BN = DUAL ? T_BN_DUAL : T_BN;
   constexpr int lds = gemm_bf16_lds_bytes<BM, BN, DUAL>();
@@ -35,7 +35,7 @@ static int launch_rows(const GemmArgs& g, int max_tiles, hipStream_t s) {
   // d 1024, f 4096 510 -> 457, 16 of 600, d 2048, f 8192 1149 -> 1112, six of 1200, d 1088, f 2880 194 -> 195.  160 rows
   // have five bands, which four wave rows would share unevenly.
   constexpr int WGM = DUAL && BM == T_BM ? 4 : T_WGM;
-  auto kern = gemm_bf16_kernel<ST, MODE, EPI, DUAL, CHAIN, BM, BN, WGM, 8 / WGM>;
+  auto kern = gemm_bf16_kernel<ST, MODE, EPI, DUAL, CHAIN, BM, BN, WGM, 8 / WGM, STREAM>;
   // more than 64 KB of dynamic LDS needs the attribute on the current device; set on every launch (a cheap
   // host-side call) rather than remembered, so the library keeps no per-process or per-device state
   {
@@ -56,19 +56,21 @@ static int launch_rows(const GemmArgs& g, int max_tiles, hipStream_t s) {
 template <typename ST, int MODE, int EPI, bool DUAL, bool CHAIN>
 static int launch_one(const GemmArgs& g, int max_tiles, hipStream_t s) {
   if constexpr (MODE != MODE_TN) {
-    if (g.tile_rows == MID_ROWS) return launch_rows<ST, MODE, EPI, DUAL, CHAIN, MID_ROWS>(g, max_tiles, s);
+    if (g.tile_rows == MID_ROWS && g.stream) return launch_rows<ST, MODE, EPI, DUAL, CHAIN, MID_ROWS, true>(g, max_tiles, s);
+    if (g.tile_rows == MID_ROWS) return launch_rows<ST, MODE, EPI, DUAL, CHAIN, MID_ROWS, false>(g, max_tiles, s);
+    if (g.stream) return launch_rows<ST, MODE, EPI, DUAL, CHAIN, T_BM, true>(g, max_tiles, s);
   }
-  return launch_rows<ST, MODE, EPI, DUAL, CHAIN, T_BM>(g, max_tiles, s);
+  return launch_rows<ST, MODE, EPI, DUAL, CHAIN, T_BM, false>(g, max_tiles, s);
 }
 
 // A row-tile GEMM (NT) and a weight-gradient GEMM (TN, one gradient or two of the same A) in one launch; the first one's
 // blocks come first.
-template <typename ST, int EPI1, bool CHAIN1, int BM1>
+template <typename ST, int EPI1, bool CHAIN1, int BM1, bool STREAM>
 static int launch_pair_rows(const GemmArgs& g1, int max_tiles, const GemmArgs& g2, hipStream_t s) {
   constexpr int lds1 = gemm_bf16_lds_bytes<BM1, T_BN, false>();
   constexpr int lds2 = gemm_bf16_lds_bytes<T_BM, T_BN, false>();
   constexpr int lds = lds1 > lds2 ? lds1 : lds2;
-  auto kern = gemm_bf16_pair_kernel<ST, MODE_NT, EPI1, CHAIN1, BM1, MODE_TN, EPI_DW, T_BM, T_BN, T_WGM, T_WGN>;
+  auto kern = gemm_bf16_pair_kernel<ST, MODE_NT, EPI1, CHAIN1, BM1, MODE_TN, EPI_DW, T_BM, T_BN, T_WGM, T_WGN, STREAM>;
   // more than 64 KB of dynamic LDS needs the attribute on the current device; set on every launch (a cheap
   // host-side call) rather than remembered, so the library keeps no per-process or per-device state
   {
@@ -92,7 +94,8 @@ static int launch_pair_rows(const GemmArgs& g1, int max_tiles, const GemmArgs& g
 
 template <typename ST, int EPI1, bool CHAIN1>
 static int launch_pair(const GemmArgs& g1, int max_tiles, const GemmArgs& g2, hipStream_t s) {
-  return g1.tile_rows == MID_ROWS ? launch_pair_rows<ST, EPI1, CHAIN1, MID_ROWS>(g1, max_tiles, g2, s) : launch_pair_rows<ST, EPI1, CHAIN1, T_BM>(g1, max_tiles, g2, s);
+  if (g1.tile_rows != MID_ROWS) return launch_pair_rows<ST, EPI1, CHAIN1, T_BM, false>(g1, max_tiles, g2, s);
+  return g1.stream ? launch_pair_rows<ST, EPI1, CHAIN1, MID_ROWS, true>(g1, max_tiles, g2, s) : launch_pair_rows<ST, EPI1, CHAIN1, MID_ROWS, false>(g1, max_tiles, g2, s);
 }
 
 template <typename ST>

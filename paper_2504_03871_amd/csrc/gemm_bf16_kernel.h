@@ -325,7 +325,9 @@ __device__ __forceinline__ void epilogue_fwd(const OutPlanes& o, const unsigned 
 // once for numbers past the last tile (the grid is sized for the worst case).
 // SEGS (weight gradients): the K range is that of several calls, one after the other through one pipeline, each call's
 // products in a sum of their own that is added to the total: the sums, and their rounding, of call after call.
-template <typename ST, int MODE, int EPI, bool DUAL, bool CHAIN, int BM, int BN, int WGM, int WGN, bool SEGS = false>
+// STREAM (row tiles): the weights of an expert with a single row tile are requested as streaming data (streams_weights).  A
+// template parameter because the choice, once per load, costs a main loop that never takes it 1 to 3 %.
+template <typename ST, int MODE, int EPI, bool DUAL, bool CHAIN, int BM, int BN, int WGM, int WGN, bool SEGS = false, bool STREAM = false>
 __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs& g, const int vb, char* smem, const DwSegs* segs = nullptr) {
   constexpr int NT = WGM * WGN * 64;
   constexpr int WTM = (BM / 32 + WGM - 1) / WGM, WTN = BN / WGN / 32;   // (an odd number of bands: the last wave row has one less)
@@ -352,6 +354,7 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs& g, const int vb, 
   int seg_rows = 0, seg_row0 = 0, seg_stages = 0;          // SEGS: lane s holds segment s's rows and first row; stages in all
   unsigned seg_a[2] = {}, seg_b[2] = {};                   // and its operands' addresses
   bool second = false;          // TN with two gradients: this block's tile is one of the second's (B2, C2)
+  bool once = false;            // STREAM: no other row tile takes the same weights
   float* part_sums = nullptr;   // this block computes one K part of a split tile: where its fp32 sums go, and their pitch
   int part_pitch = 0;
   {
@@ -433,6 +436,7 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs& g, const int vb, 
       e = t.e;
       row0 = t.row0;
       mvalid = t.nrows;
+      if constexpr (STREAM) once = __builtin_amdgcn_readfirstlane(t.mates) == 0;
     }
     n0 = nt * BN;
   }
@@ -592,8 +596,10 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs& g, const int vb, 
     if ((q_) >= B_Q && (q_) < B_Q + LB) {                                                                   \
       const int c__ = ((q_) - B_Q) / (DUAL ? 2 : 1);                                                        \
       const unsigned st__ = smem_base + B_AT + (bbuf_) + wbase + NT * 16 * c__;                             \
-      if (!DUAL || ((q_) - B_Q) % 2 == 0) load_to_lds16(sec__ ? rb1 : rb, st__, b_vo[c__] + kl__ * bstep);          \
-      else load_to_lds16(rb1, st__ + B_BYTES, b_vo[c__] + kl__ * bstep);                                    \
+      const bool first__ = !DUAL || ((q_) - B_Q) % 2 == 0;                                                  \
+      if (STREAM && once)                                                                                   \
+        load_to_lds16_nt(!first__ || sec__ ? rb1 : rb, st__ + (first__ ? 0 : B_BYTES), b_vo[c__] + kl__ * bstep); \
+      else load_to_lds16(!first__ || sec__ ? rb1 : rb, st__ + (first__ ? 0 : B_BYTES), b_vo[c__] + kl__ * bstep); \
     } else {                                                                                                \
       const int c__ = (q_) - A_Q;                                                                           \
       if (c__ < StA::CH - 1 || StA::LAST == NT || wave < StA::LAST / 64)                                    \
@@ -921,21 +927,21 @@ __global__ __launch_bounds__(256) void split_reduce_kernel(GemmArgs g) {
   put(t.row0 + m, n, sum);
 }
 
-template <typename ST, int MODE, int EPI, bool DUAL, bool CHAIN, int BM, int BN, int WGM, int WGN>
+template <typename ST, int MODE, int EPI, bool DUAL, bool CHAIN, int BM, int BN, int WGM, int WGN, bool STREAM>
 __global__ __launch_bounds__(WGM* WGN * 64, 1) void gemm_bf16_kernel(GemmArgs g) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  gemm_bf16_tile<ST, MODE, EPI, DUAL, CHAIN, BM, BN, WGM, WGN>(g, blockIdx.x, smem);
+  gemm_bf16_tile<ST, MODE, EPI, DUAL, CHAIN, BM, BN, WGM, WGN, false, STREAM>(g, blockIdx.x, smem);
 }
 
 // Two independent GEMMs in one launch: blocks below `first_blocks` take a tile of the first, the others a
 // tile of the second.  Blocks are dispatched in order, so the second GEMM's tiles start on the compute
 // units that the first one's last, partly filled round leaves idle (no stream or event in between,
 // and the two never compete for the cache from the start as two concurrent kernels would).
-template <typename ST, int MODE1, int EPI1, bool CHAIN1, int BM1, int MODE2, int EPI2, int BM, int BN, int WGM, int WGN>
+template <typename ST, int MODE1, int EPI1, bool CHAIN1, int BM1, int MODE2, int EPI2, int BM, int BN, int WGM, int WGN, bool STREAM>
 __global__ __launch_bounds__(WGM* WGN * 64, 1) void gemm_bf16_pair_kernel(GemmArgs g1, GemmArgs g2, int first_blocks) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   if ((int)blockIdx.x < first_blocks)
-    gemm_bf16_tile<ST, MODE1, EPI1, false, CHAIN1, BM1, BN, WGM, WGN>(g1, blockIdx.x, smem);
+    gemm_bf16_tile<ST, MODE1, EPI1, false, CHAIN1, BM1, BN, WGM, WGN, false, STREAM>(g1, blockIdx.x, smem);
   else
     gemm_bf16_tile<ST, MODE2, EPI2, false, false, BM, BN, WGM, WGN>(g2, blockIdx.x - first_blocks, smem);
 }

@@ -20,12 +20,6 @@ constexpr int skinny_stage_bytes() { return SKINNY_ROWS * BKT * 2 + SKINNY_BN * 
 template <bool DUAL>
 constexpr int skinny_stages() { return 80 * 1024 / skinny_stage_bytes<DUAL>(); }   // two blocks per compute unit
 
-// load_to_lds16 for data that one block reads once: the weights do not displace anything in the caches
-__device__ __forceinline__ void load_to_lds16_nt(rsrc_t rs, unsigned lds, unsigned voffset) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen nt lds"
-               :: "s"(lds), "v"(voffset), "s"(rs) : "memory", "m0");
-}
-
 template <typename ST, int EPI, bool DUAL>
 __global__ __launch_bounds__(256, 2) void gemm_skinny_kernel(GemmArgs g) {
   constexpr int BM = SKINNY_ROWS, BN = SKINNY_BN, A_BYTES = BM * BKT * 2, B_BYTES = BN * BKT * 2;

@@ -135,7 +135,7 @@ __device__ inline void build_tile_map(const TileMapArgs& a) {
       t.e = e;
       t.row0 = base + i * per;
       t.nrows = min(per, len - i * per);
-      t.mates = s_major && ntile > 1;
+      t.mates = nfull + (rem > 0) > 1;
       a.map.tiles[s_start[e] + i] = t;
     }
     if (!s_major && part == 0 && rem > 0) {   // position among the partial tiles: more rows first, ties by expert id
@@ -143,7 +143,7 @@ __device__ inline void build_tile_map(const TileMapArgs& a) {
       t.e = e;
       t.row0 = base + nfull * tile_rows;
       t.nrows = rem;
-      t.mates = 0;
+      t.mates = nfull > 0;
       a.map.tiles[s_nfull + s_rank[e]] = t;
     }
   }

@@ -292,6 +292,47 @@ def test_short_k_in_high_tiles(T, d, f, dtype, act):
     run_case(S.WORKLOADS["cfg1"].scaled(T=T, d=d, f=f, E=1, k=1, dtype=getattr(S, "DT_" + dtype.upper()), act=getattr(S, "ACT_" + act.upper())))
 
 
+@pytest.mark.parametrize("T, d, f, E, k, dtype, act", [
+    (1440, 1024, 2624, 32, 2, "bf16", B.ACT_GELU),     # 160-row tiles; dH and dx share launches with the weight gradients
+    (700, 1088, 1792, 32, 2, "f16", B.ACT_SWIGLU),     # a last column tile of 64 columns
+    (1200, 1088, 832, 64, 8, "bf16", B.ACT_SWIGLU),    # 256-row tiles
+    (1600, 576, 2432, 64, 6, "f16", B.ACT_GELU),
+])
+def test_weights_requested_as_streaming_data(T, d, f, E, k, dtype, act):
+    """Layers of more than 320 MB of weights and at most a row tile per expert on average, some experts with several tiles:
+    every row-tile GEMM against the same rows multiplied in fp64."""
+    import torch
+    swiglu = act == B.ACT_SWIGLU
+    rows = 160 if T * k <= 128 * E or (E <= 32 and T * k <= 512 * E) else 256
+    assert T * k <= rows * E and E * d * f * (3 if swiglu else 2) * 2 > 320 << 20
+    L = filled_layer(T, d, f, E, k, dtype, act)
+    L.bias = torch.tensor([2.5] + [0.0] * (E - 1), device=L.device)
+    L.forward()
+    L.combine_bwd()
+    L.ffn_bwd()
+    torch.cuda.synchronize()
+    assert int(L.kept.max()) > rows >= int(L.kept.median()) and T * k > 32 * E
+    one = {"bf16": 2.0 ** -9, "f16": 2.0 ** -12}[dtype]   # one rounding of the result
+    planes = 2 if swiglu else 1
+    dact = L.ws[L.ws.numel() - planes * T * k * f * 2:].view(L.tdtype).view(planes, T * k, f)   # the workspace's last region
+    for e in range(E):
+        o, n = int(L.offsets[e]), int(L.kept[e])
+        at = lambda t: t[o:o + n].double()
+        pre = [at(L.x_perm) @ w[e].double() for w in (L.W1, L.W1b) if w is not None]
+        dh = at(L.dy_perm) @ L.W2[e].double().t()
+        v = [at(L.saved_plane(i)) for i in range(planes)]
+        if swiglu:
+            sg = torch.sigmoid(v[0])
+            da = [dh * v[1] * sg * (1 + v[0] * (1 - sg)), dh * v[0] * sg]
+        else:
+            da = [dh * (0.5 * torch.erfc(-v[0] / 2 ** 0.5) + v[0] * torch.exp(-v[0] * v[0] / 2) / (2 * torch.pi) ** 0.5)]
+        dx = sum(at(dact[i]) @ w[e].double().t() for i, w in enumerate((L.W1, L.W1b)[:planes]))
+        # (dA: its rounding, and fp16's polynomial derivative or the fast sigmoid, well below another one)
+        for got, ref, tol in [*((a, b, one) for a, b in zip(v, pre)), (at(L.y_perm), at(L.saved_plane(planes)) @ L.W2[e].double(), one),
+                              *((at(dact[i]), da[i], 2 * one) for i in range(planes)), (at(L.dx_perm), dx, one)]:
+            assert (got - ref).norm() <= tol * ref.norm(), e
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 def test_last_round_split_along_k_in_the_input_gradient_of_low_tiles(dtype):
     """dx = dA W1^T of 160-row tiles, which are too many to share a launch where 256-row ones would not be, with the last
