@@ -61,7 +61,7 @@ WsLayout ws_layout(const moe_cfg* c) {
   size_t fwd = 0, bwd = 0;
   if (is_half(c) && c->d_ff >= SPLIT_MIN_K) {
     const int max_tiles = max_row_tiles((int)A, c->E, tile_rows_for(c));
-    const bool skinny = skinny_applies(A, c->E), small = splits_small_tiles(c);
+    const bool skinny = skinny_applies(A, c->E, c->d_model, c->d_ff, c->act == MOE_ACT_SWIGLU, (int)elt_size(c)), small = splits_small_tiles(c);
     const size_t rows = split_ws_bytes(c->E, c->d_model), tail = tail_ws_bytes(max_tiles, c->d_model);
     fwd = skinny ? (skinny_split(c->E, c->d_ff) ? rows : 0) : std::max(small ? rows : 0, tail);
     if (c->act == MOE_ACT_GELU) bwd = std::max(small ? rows : 0, shares_launch(c, c->d_model, max_tiles) ? 0 : tail);
@@ -360,7 +360,7 @@ int moe_dispatch_static(const moe_cfg* cfg, const void* x, const int32_t* topk_i
 }
 
 namespace {
-bool fwd_skinny(const moe_cfg* cfg) { return is_half(cfg) && skinny_applies(cfg->T * cfg->k, cfg->E); }   // few rows per expert
+bool fwd_skinny(const moe_cfg* cfg) { return is_half(cfg) && skinny_applies(cfg->T * cfg->k, cfg->E, cfg->d_model, cfg->d_ff, cfg->act == MOE_ACT_SWIGLU, (int)elt_size(cfg)); }   // few rows per expert
 // the row-tile map of a forward or backward FFN call and its table
 TileMapArgs tile_map_args(const moe_cfg* cfg, const int32_t* offsets, const int32_t* kept, const int32_t* lo, const int32_t* hi, bool forward, void* ws) {
   TileMapArgs t = {offsets, kept, lo, hi, cfg->E};

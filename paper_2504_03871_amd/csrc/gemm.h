@@ -396,8 +396,43 @@ int launch_gemm_half_skinny(int dtype, int epi, bool dual, const GemmArgs& g, in
 //   d 1024, f 512, 128 experts, SwiGLU     16    90 ->  74    84 ->  74    44 ->  50
 //                                          32    98 ->  84   116 ->  99    66 ->  67
 //                                          48   103 -> 101   115 -> 108    70 ->  84
+// These are with plain loads on the left.  Where 160-row tiles stream the weights too (streams_weights), both stream, and the
+// ring of 64 KB per block in whole rounds of 256 blocks is ahead: forward pass, us, this kernel -> 160-row tiles,
+//   rows per expert                                 even          -0.7          -1.2
+//   d 4096, f 14336, 8 experts, SwiGLU      4   479 -> 458                 441 -> 427
+//                                          16   517 -> 481   517 -> 481   517 -> 484
+//   d 4096, f 14336, 8 experts, GELU        4   322 -> 307                 227 -> 240
+//                                           8   330 -> 313   334 -> 313   334 -> 316
+//                                          24   371 -> 334   369 -> 340   346 -> 349
+//   d 2048, f 8192, 16 experts, GELU        4   194 -> 197                 132 -> 142
+//                                           8   201 -> 201   195 -> 191   175 -> 173
+//                                          24   227 -> 209   220 -> 215   223 -> 218
+//                                          32   237 -> 212   233 -> 220   240 -> 257
+//   d 2048, f 1024, 128 experts, SwiGLU     4   299 -> 294                 156 -> 161
+//                                           8   314 -> 305   273 -> 280   174 -> 176
+//                                          32   343 -> 324   367 -> 345   273 -> 245
+//   d 2048, f 1024, 256 experts, GELU       8   424 -> 406   324 -> 310   201 -> 203
+//                                          32   485 -> 439   496 -> 451   329 -> 288
+//   d 4096, f 1024, 40 experts, SwiGLU     16   230 -> 235   223 -> 243   175 -> 165   (GEMM1: 320 tiles, 1.25 rounds)
+//   d 3200, f 5120, 12 experts, SwiGLU      8   219 -> 223   211 -> 217   203 -> 215   (y: 156 tiles, neither a round nor split)
+//   d 4096, f 8192, 16 experts, SwiGLU      1   404 -> 379   231 -> 229   205 -> 214
+//                                           2   535 -> 529   290 -> 289   262 -> 265
+//                                          16   584 -> 553   598 -> 550   589 -> 523
+// so from 8 rows on (16 with more than 32 experts) where the rounds of both GEMMs are at least four fifths full or the last one
+// is split, up to 24 with few experts (at a skewed load their y has too many tiles for the split); and from 2 rows on where
+// a SwiGLU expert's matrices have 64 MB each.
 constexpr int SKINNY_AVERAGE = 32;
-inline bool skinny_applies(long long rows, int E) { return rows <= (long long)SKINNY_AVERAGE * E; }
+inline bool few_rows_streamed(long long rows, int E, int d, int f, bool swiglu, int elt) {
+  if (!streams_weights(rows, MID_ROWS, E, d, f, swiglu ? 3 : 2, elt) || rows > (long long)(E <= MID_FEW_EXPERTS ? 24 : SKINNY_AVERAGE) * E) return false;
+  const int cols = swiglu ? 128 : 256, tiles1 = E * ((f + cols - 1) / cols), tiles2 = E * ((d + 255) / 256);
+  auto full = [](int tiles) { return (long long)tiles * 5 >= (tiles + 255) / 256 * 256ll * 4; };
+  if (!full(tiles1) || !(full(tiles2) || tail_split(tiles2, f).parts > 1)) return false;
+  const bool large = swiglu && E <= MID_FEW_EXPERTS && (long long)d * f * elt >= 64ll << 20;
+  return rows >= (long long)(large ? 2 : E <= MID_FEW_EXPERTS ? 8 : 16) * E;
+}
+inline bool skinny_applies(long long rows, int E, int d, int f, bool swiglu, int elt) {
+  return rows <= (long long)SKINNY_AVERAGE * E && !few_rows_streamed(rows, E, d, f, swiglu, elt);
+}
 
 // A weight gradient over the rows of several calls (micro-batches) at once: operand s of call s, each with its own share
 // bounds.  GemmArgs holds what they have in common.
