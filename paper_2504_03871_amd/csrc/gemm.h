@@ -354,6 +354,9 @@ inline bool mid_applies(long long rows, int E) { return rows <= (long long)(E <=
 // 160-row tiles: 125 rows, d 2048, f 8192, 16 experts, fp16 GELU, forward pass 273 -> 260; 75 rows, d 4096, f 14336, 8, SwiGLU 559
 // -> 514.  256-row tiles: 160 rows, d 2048, f 2048, 128, GELU 552 -> 532; 150 rows, d 2048, f 2048, 64, step 1167 -> 1138; 200 rows,
 // d 2048, f 1024, 256, SwiGLU 936 -> 909; where experts have two or three tiles (512 rows, 128 experts, step) 3370 -> 3480.
+// In launches shared with a weight gradient too: 256-row tiles, whole step, us, 140 rows, d 1024, f 1536, 64, SwiGLU 675 -> 631; 160,
+// d 2048, f 1024, 128, fp16 GELU 1307 -> 1250; 200, d 2048, f 4096, 48, SwiGLU 2645 -> 2563; 250, d 1024, f 768, 128 1039 -> 1037; 150,
+// d 1024, f 1024, 96, GELU, router bias -1.2 log(e + 1), 553 -> 521.
 inline bool streams_weights(long long rows, int tile_rows, long long E, long long d, long long f, int matrices, int elt) {
   return rows <= tile_rows * E && E * d * f * matrices * elt > MEMORY_SIDE_CACHE / 4 * 5;
 }

@@ -94,8 +94,10 @@ static int launch_pair_rows(const GemmArgs& g1, int max_tiles, const GemmArgs& g
 
 template <typename ST, int EPI1, bool CHAIN1>
 static int launch_pair(const GemmArgs& g1, int max_tiles, const GemmArgs& g2, hipStream_t s) {
-  if (g1.tile_rows != MID_ROWS) return launch_pair_rows<ST, EPI1, CHAIN1, T_BM, false>(g1, max_tiles, g2, s);
-  return g1.stream ? launch_pair_rows<ST, EPI1, CHAIN1, MID_ROWS, true>(g1, max_tiles, g2, s) : launch_pair_rows<ST, EPI1, CHAIN1, MID_ROWS, false>(g1, max_tiles, g2, s);
+  if (g1.tile_rows == MID_ROWS && g1.stream) return launch_pair_rows<ST, EPI1, CHAIN1, MID_ROWS, true>(g1, max_tiles, g2, s);
+  if (g1.tile_rows == MID_ROWS) return launch_pair_rows<ST, EPI1, CHAIN1, MID_ROWS, false>(g1, max_tiles, g2, s);
+  if (g1.stream) return launch_pair_rows<ST, EPI1, CHAIN1, T_BM, true>(g1, max_tiles, g2, s);
+  return launch_pair_rows<ST, EPI1, CHAIN1, T_BM, false>(g1, max_tiles, g2, s);
 }
 
 template <typename ST>

@@ -1,4 +1,4 @@
-"""The compiled 16-bit GEMMs (the device code in the built library) keep their values in registers."""
+"""The compiled 16-bit GEMMs: the device code in the built library."""
 import os
 import re
 import struct
@@ -23,19 +23,35 @@ def device_code(lib):
             pos += 24 + n
 
 
-def test_no_gemm_kernel_spills_registers(tmp_path):
-    """A value that comes back from scratch memory waits for every load in flight; in a main loop that is the next stages'."""
+def instructions(tmp_path):
+    """16-bit GEMM kernel -> its instructions."""
     if not os.path.exists(build.LIB):
         pytest.skip("library not built")
-    kernels, spilled, name = set(), set(), ""
+    kernels, name = {}, ""
     for code in device_code(build.LIB):
         (tmp_path / "code").write_bytes(code)
         listing = subprocess.run([OBJDUMP, "-d", "--no-show-raw-insn", str(tmp_path / "code")], capture_output=True, text=True, check=True).stdout
         for line in listing.splitlines():
             if m := re.match(r"[0-9a-f]+ <(\S+)>:", line):
                 name = m[1]
-                if "gemm_bf16" in name:
-                    kernels.add(name)
-            elif line.lstrip().startswith("scratch_") and name in kernels:
-                spilled.add(name)
-    assert len(kernels) > 20 and not spilled, sorted(spilled)
+            elif "gemm_bf16" in name:
+                kernels.setdefault(name, []).append(line.strip())
+    assert len(kernels) > 20
+    return kernels
+
+
+def test_no_gemm_kernel_spills_registers(tmp_path):
+    """A value that comes back from scratch memory waits for every load in flight; in a main loop that is the next stages'."""
+    spilled = [name for name, ops in instructions(tmp_path).items() if any(op.startswith("scratch_") for op in ops)]
+    assert not spilled, spilled
+
+
+def test_every_row_tile_kernel_has_an_instance_that_streams_weights(tmp_path):
+    """A layer whose weights are to be requested as streaming data (the last template argument) gets them so from all of its
+    row-tile GEMMs, at both tile heights and in shared launches too."""
+    kernels = instructions(tmp_path)
+    row_tiles = [name for name in kernels if name.startswith(("_ZN3moe16gemm_bf16_kernel", "_ZN3moe21gemm_bf16_pair_kernel")) and "kernelIDF16_Li2E" not in name and "kernelIDF16bLi2E" not in name]
+    for name in row_tiles:
+        assert name.replace("ELb0EEEv", "ELb1EEEv") in kernels, name
+        streams = any(op.startswith("buffer_load_dwordx4") and re.search(r"\bnt lds\b", op) for op in kernels[name])
+        assert streams == ("ELb1EEEv" in name), name
