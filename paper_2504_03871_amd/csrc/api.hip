@@ -33,6 +33,13 @@ static int tile_rows_for(const moe_cfg* c) {   // both row-tile GEMMs of a pass 
 }
 // The smallest row tiles of a 16-bit GEMM with K = d_ff are split along K (gemm.h): 256-row tiles only
 static bool splits_small_tiles(const moe_cfg* c) { return is_half(c) && tile_rows_for(c) != MID_ROWS && split_k_applies(c->E, c->d_ff); }
+// Forward GEMMs of few rows per expert
+static bool fwd_skinny(const moe_cfg* c) {
+  return is_half(c) && skinny_applies((long long)c->T * c->k, c->E, c->d_model, c->d_ff, c->act == MOE_ACT_SWIGLU, (int)elt_size(c));
+}
+static bool weights_streamed(const moe_cfg* c, int tile_rows) {
+  return is_half(c) && streams_weights((long long)c->T * c->k, tile_rows, c->E, c->d_model, c->d_ff, c->act == MOE_ACT_SWIGLU ? 3 : 2, (int)elt_size(c));
+}
 // backward: a row-tile GEMM of N columns with at most about eight rounds of tiles shares its launch (moe_expert_ffn_bwd)
 static bool shares_launch(const moe_cfg* c, int N, int max_tiles) {
   const int cols = is_half(c) ? gemm_bf16_tile_rows() : F32_TILE_COLS;
@@ -61,7 +68,7 @@ WsLayout ws_layout(const moe_cfg* c) {
   size_t fwd = 0, bwd = 0;
   if (is_half(c) && c->d_ff >= SPLIT_MIN_K) {
     const int max_tiles = max_row_tiles((int)A, c->E, tile_rows_for(c));
-    const bool skinny = skinny_applies(A, c->E, c->d_model, c->d_ff, c->act == MOE_ACT_SWIGLU, (int)elt_size(c)), small = splits_small_tiles(c);
+    const bool skinny = fwd_skinny(c), small = splits_small_tiles(c);
     const size_t rows = split_ws_bytes(c->E, c->d_model), tail = tail_ws_bytes(max_tiles, c->d_model);
     fwd = skinny ? (skinny_split(c->E, c->d_ff) ? rows : 0) : std::max(small ? rows : 0, tail);
     if (c->act == MOE_ACT_GELU) bwd = std::max(small ? rows : 0, shares_launch(c, c->d_model, max_tiles) ? 0 : tail);
@@ -253,7 +260,7 @@ int moe_gemm_block_tile(int32_t kind, int64_t block, int32_t n_rt, int32_t n_ful
     return MOE_ERR_BAD_SHAPE;
   // the kernels count tiles, K parts and K values in 32 bits
   const long long parts = kind == 5 ? (long long)(n_split ? SPLIT_K : 1) * n_rt : n_rt + (long long)(SPLIT_K - 1) * n_split;
-  const long long tiles = kind == 1 ? (long long)ntm * ntn : kind == 6 ? (block / MID_ROWS + n_rt) * ntn : parts * ntn;
+  const long long tiles = kind == 1 ? (long long)ntm * ntn : kind == 6 ? (block / MID_ROWS + n_rt) * ntn : kind == 7 ? 0 : parts * ntn;
   if (tiles > 0x7fffffffll - NUM_XCD || ((kind == 4 || kind == 6) && ntm > 0x7fffffff / 64)) return MOE_ERR_BAD_SHAPE;
   for (int i = 0; i < 6; ++i) out[i] = -1;
   if (kind == 0 || kind == 3) {
@@ -273,6 +280,16 @@ int moe_gemm_block_tile(int32_t kind, int64_t block, int32_t n_rt, int32_t n_ful
   if (kind == 6) {
     if (ntm < 1) return MOE_ERR_BAD_SHAPE;
     out[0] = tail_may_split((int)block, n_rt, n_split == 0, ntn, ntm * 64, n_full_rt == 1 ? MID_ROWS : gemm_bf16_tile_rows()) ? 1 : 0;
+    return MOE_OK;
+  }
+  if (kind == 7) {
+    if (n_full_rt > 1) return MOE_ERR_BAD_SHAPE;
+    const moe_cfg c = {(int)block, ntm, ntn, n_rt, 1, MOE_DTYPE_BF16, n_full_rt == 1 ? MOE_ACT_SWIGLU : MOE_ACT_GELU, 0, nullptr};
+    CHECK(check_cfg(&c));
+    out[0] = fwd_skinny(&c) ? SKINNY_ROWS : tile_rows_for(&c);
+    out[1] = !fwd_skinny(&c) && weights_streamed(&c, out[0]) ? 1 : 0;
+    out[2] = tile_rows_for(&c);
+    out[3] = weights_streamed(&c, out[2]) ? 1 : 0;
     return MOE_OK;
   }
   if (kind == 5) {
@@ -360,7 +377,6 @@ int moe_dispatch_static(const moe_cfg* cfg, const void* x, const int32_t* topk_i
 }
 
 namespace {
-bool fwd_skinny(const moe_cfg* cfg) { return is_half(cfg) && skinny_applies(cfg->T * cfg->k, cfg->E, cfg->d_model, cfg->d_ff, cfg->act == MOE_ACT_SWIGLU, (int)elt_size(cfg)); }   // few rows per expert
 // the row-tile map of a forward or backward FFN call and its table
 TileMapArgs tile_map_args(const moe_cfg* cfg, const int32_t* offsets, const int32_t* kept, const int32_t* lo, const int32_t* hi, bool forward, void* ws) {
   TileMapArgs t = {offsets, kept, lo, hi, cfg->E};
@@ -388,7 +404,7 @@ int ffn_fwd_impl(const moe_cfg* cfg, const void* x_perm, const void* W1, const v
   char* sv = static_cast<char*>(saved);
   GemmArgs g = {};
   g.tiles = map.tiles; g.ntiles = map.header; g.order = map.order; g.gelu_tab = map.gelu_tab; g.tile_rows = tr;
-  g.stream = is_half(cfg) && streams_weights(A, tr, cfg->E, d, f, swiglu ? 3 : 2, (int)elt_size(cfg));
+  g.stream = weights_streamed(cfg, tr);
   g.offsets = offsets; g.kept = kept; g.lo = slice_lo; g.hi = slice_hi; g.E = cfg->E;
   // hidden = act(x_perm W1)
   g.A = x_perm; g.B = W1; g.B2 = W1b; g.N = f; g.K = d;
@@ -522,7 +538,7 @@ int ffn_bwd_impl(const moe_cfg* cfg, const void* dy_perm, const void* x_perm, co
   const void* hidden = swiglu ? sv + 2 * plane : sv + plane;
   GemmArgs g = {};
   g.tiles = map.tiles; g.ntiles = map.header; g.order = map.order; g.gelu_tab = map.gelu_tab; g.tile_rows = tr;
-  g.stream = is_half(cfg) && streams_weights(A, tr, cfg->E, d, f, swiglu ? 3 : 2, (int)elt_size(cfg));
+  g.stream = weights_streamed(cfg, tr);
   g.offsets = offsets; g.kept = kept; g.lo = slice_lo; g.hi = slice_hi; g.E = cfg->E;
   g.accumulate = accumulate;
   // Four GEMMs: dH = dy W2^T fused with the activation derivative -> dA (GELU) or dG, dU (SwiGLU);

@@ -166,9 +166,14 @@ def test_rows_past_a_tile_whose_offsets_wrap_32_bits_are_not_stored(act, T, f):
             assert (got - ref).norm() <= 2.0 ** -7 * ref.norm()
 
 
+def routes(L):
+    """Rows of a 16-bit layer's forward tiles, whether their weights are streamed, the same of the backward's."""
+    return B.moe_gemm_block_tile(7, L.T * L.k, L.E, L.act == B.ACT_SWIGLU, 0, L.d, L.f)[:4]
+
+
 def tile_rows(L):
     """Rows of a 16-bit layer's row tiles (more than 32 rows per expert)."""
-    return 160 if L.T * L.k <= (512 if L.E <= 32 else 128) * L.E else 256
+    return routes(L)[2]
 
 
 def last_round_parts(kept, f, N, rows=256):
@@ -284,6 +289,8 @@ def test_forward_stores_of_high_tiles(T, d, f, E, k, dtype, act):
     (600, 192, 128, "f16", "swiglu"),
     (600, 256, 192, "bf16", "gelu"),      # four: the first that meets the loop's steady state
     (600, 192, 256, "bf16", "swiglu"),
+    (600, 192, 192, "bf16", "gelu"),      # three with a GELU table, which takes the place of the first; and in a longer loop, six
+    (600, 384, 384, "bf16", "gelu"),
 ])
 def test_short_k_in_high_tiles(T, d, f, dtype, act):
     """256-row tiles whose operands have two and three LDS stages, with fewer K stages than these, as many, and one more."""
@@ -297,26 +304,36 @@ def test_short_k_in_high_tiles(T, d, f, dtype, act):
     (700, 1088, 1792, 32, 2, "f16", B.ACT_SWIGLU),     # a last column tile of 64 columns
     (1200, 1088, 832, 64, 8, "bf16", B.ACT_SWIGLU),    # 256-row tiles
     (1600, 576, 2432, 64, 6, "f16", B.ACT_GELU),
+    (2000, 2048, 2048, 160, 8, "f16", B.ACT_GELU),     # 160-row tiles, too many of them to share a launch
+    (2625, 2304, 2304, 160, 8, "bf16", B.ACT_SWIGLU),  # and 256-row ones
     (250, 2048, 2048, 32, 2, "bf16", B.ACT_GELU),      # 16 rows per expert, still in 160-row tiles
     (9, 4096, 8192, 4, 1, "f16", B.ACT_SWIGLU),        # 2 rows; y split along K
 ])
 def test_weights_requested_as_streaming_data(T, d, f, E, k, dtype, act):
     """Layers of more than 320 MB of weights and at most a row tile per expert on average, one expert with several tiles:
-    every row-tile GEMM against the same rows multiplied in fp64."""
+    every row-tile GEMM against the same rows multiplied in fp64, those of the backward with the weight gradients (in one
+    launch up to 2048 tiles) and without them (always in launches of their own)."""
     import torch
     swiglu = act == B.ACT_SWIGLU
     rows = 160 if T * k <= 128 * E or (E <= 32 and T * k <= 512 * E) else 256
     assert T * k <= rows * E and E * d * f * (3 if swiglu else 2) * 2 > 320 << 20
     L = filled_layer(T, d, f, E, k, dtype, act)
+    assert routes(L) == [rows, 1, rows, 1]
+    assert all((-(-n // 256) * (T * k // rows + E) > 2048) == (E == 160) for n in (d, f))
     L.bias = torch.tensor([2.5] + [0.0] * (E - 1), device=L.device)
     L.forward()
     L.combine_bwd()
-    L.ffn_bwd()
-    torch.cuda.synchronize()
-    assert T < 10 or int(L.kept.max()) > rows >= int(L.kept.median())
     one = {"bf16": 2.0 ** -9, "f16": 2.0 ** -12}[dtype]   # one rounding of the result
     planes = 2 if swiglu else 1
     dact = L.ws[L.ws.numel() - planes * T * k * f * 2:].view(L.tdtype).view(planes, T * k, f)   # the workspace's last region
+    grads = []
+    for backward in (L.ffn_bwd, L.ffn_bwd_inputs):
+        dact.fill_(float("nan"))
+        L.dx_perm.fill_(float("nan"))
+        backward()
+        grads.append(torch.cat([t.view(T * k, -1) for t in (*dact, L.dx_perm)], 1))
+    torch.cuda.synchronize()
+    assert T < 10 or int(L.kept.max()) > rows >= int(L.kept.median())
     for e in range(E):
         o, n = int(L.offsets[e]), int(L.kept[e])
         at = lambda t: t[o:o + n].double()
@@ -328,10 +345,13 @@ def test_weights_requested_as_streaming_data(T, d, f, E, k, dtype, act):
             da = [dh * v[1] * sg * (1 + v[0] * (1 - sg)), dh * v[0] * sg]
         else:
             da = [dh * (0.5 * torch.erfc(-v[0] / 2 ** 0.5) + v[0] * torch.exp(-v[0] * v[0] / 2) / (2 * torch.pi) ** 0.5)]
-        dx = sum(at(dact[i]) @ w[e].double().t() for i, w in enumerate((L.W1, L.W1b)[:planes]))
-        # (dA: its rounding, and fp16's polynomial derivative or the fast sigmoid, well below another one)
-        for got, ref, tol in [*((a, b, one) for a, b in zip(v, pre)), (at(L.y_perm), at(L.saved_plane(planes)) @ L.W2[e].double(), one),
-                              *((at(dact[i]), da[i], 2 * one) for i in range(planes)), (at(L.dx_perm), dx, one)]:
+        checks = [*((a, b, one) for a, b in zip(v, pre)), (at(L.y_perm), at(L.saved_plane(planes)) @ L.W2[e].double(), one)]
+        for got in (at(g) for g in grads):
+            parts = [got[:, i * f:(i + 1) * f] for i in range(planes)]
+            dx = sum(p @ w[e].double().t() for p, w in zip(parts, (L.W1, L.W1b)))
+            # (dA: its rounding, and fp16's polynomial derivative or the fast sigmoid, well below another one)
+            checks += [*((p, r, 2 * one) for p, r in zip(parts, da)), (got[:, planes * f:], dx, one)]
+        for got, ref, tol in checks:
             assert (got - ref).norm() <= tol * ref.norm(), e
 
 
