@@ -424,9 +424,21 @@ int launch_gemm_half_skinny(int dtype, int epi, bool dual, const GemmArgs& g, in
 // so from 8 rows on (16 with more than 32 experts) where the rounds of both GEMMs are at least four fifths full or the last one
 // is split, up to 24 with few experts (at a skewed load their y has too many tiles for the split); and from 2 rows on where
 // a SwiGLU expert's matrices have 64 MB each.
+// GEMM1's loop is d long, and a block that has its compute unit to itself waits for the fill in front of it and the stores behind it
+// (here the other block runs on; y, f long, loses less): the wider the layer, the more the 160-row tiles gain.  Forward pass,
+// this kernel -> 160-row tiles where the lines above take them, geometric mean over the three loads and layers of random
+// width (multiples of 64, d 512 to 4096, d_ff 512 to 14336, 4 to 256 experts, more than 320 MB of weights):
+//   d                            512 - 767   768 - 1279   1280 - 1791   1792 - 2303   2304 - 3071   from 3072
+//   up to 32 experts, GELU            1.12         1.04          1.04          1.01          1.00        0.97   (d 2048: 1.00)
+//   up to 32 experts, SwiGLU          1.16         1.07          1.06          1.00          0.99        0.97   (d 2048: 0.98)
+//   more, GELU                        1.01         0.97          0.97          0.96          0.96        0.95
+//   more, SwiGLU                      1.05         0.99          0.97          0.95          0.95        0.94   (d 1024: 0.98)
+// so from d 2048 on with few experts, and with many from 1024 on for SwiGLU, which has twice as much in front of and behind its
+// loop.  The 64 MB: d from 2048, 2 to 8 rows, 40 to 64 MB 1.01, 64 to 100 MB 0.98.
 constexpr int SKINNY_AVERAGE = 32;
 inline bool few_rows_streamed(long long rows, int E, int d, int f, bool swiglu, int elt) {
   if (!streams_weights(rows, MID_ROWS, E, d, f, swiglu ? 3 : 2, elt) || rows > (long long)(E <= MID_FEW_EXPERTS ? 24 : SKINNY_AVERAGE) * E) return false;
+  if (d < (E <= MID_FEW_EXPERTS ? 2048 : swiglu ? 1024 : 0)) return false;
   const int cols = swiglu ? 128 : 256, tiles1 = E * ((f + cols - 1) / cols), tiles2 = E * ((d + 255) / 256);
   auto full = [](int tiles) { return (long long)tiles * 5 >= (tiles + 255) / 256 * 256ll * 4; };
   if (!full(tiles1) || !(full(tiles2) || tail_split(tiles2, f).parts > 1)) return false;

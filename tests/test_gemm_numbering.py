@@ -155,3 +155,40 @@ def test_sizes_beyond_32_bits_are_refused(kind, n_rt, n_split, ntm, ntn):
     import ctypes
     out = (ctypes.c_int32 * 6)()
     assert B.lib().moe_gemm_block_tile(kind, 0, n_rt, 0, n_split, ntm, ntn, out) == -2
+
+
+def forward_rows(rows, E, d, f, swiglu):
+    return B.moe_gemm_block_tile(7, rows, E, int(swiglu), 0, d, f)[0]
+
+
+@pytest.mark.parametrize("E, d, f, swiglu, rows", [
+    (32, 2048, 8192, True, 8), (32, 2048, 8192, False, 8),   # from eight rows per expert and d 2048 on
+    (64, 1024, 2048, True, 16), (64, 960, 2048, False, 16),  # more than 32 experts: from 16 rows on, SwiGLU from d 1024 on
+    (8, 4096, 8192, True, 2), (4, 4096, 8192, True, 2),      # SwiGLU's matrices of 64 MB: from two rows on
+])
+def test_few_rows_in_160_row_tiles_from_a_width_and_a_row_count_on(E, d, f, swiglu, rows):
+    assert forward_rows(rows * E, E, d, f, swiglu) == 160 and forward_rows(rows * E - 1, E, d, f, swiglu) == 64
+    most = 24 if E <= 32 else 32
+    assert forward_rows(most * E, E, d, f, swiglu) == 160
+    assert forward_rows(24 * E + 1, E, d, f, swiglu) == (64 if E <= 32 else 160) and forward_rows(32 * E + 1, E, d, f, swiglu) == 160
+
+
+@pytest.mark.parametrize("E, d, f, swiglu, rows", [
+    (32, 1984, 8192, True, 16), (32, 1984, 8192, False, 16), (64, 960, 2048, True, 24), (7, 1344, 7552, True, 16),   # narrower
+    (8, 4096, 7936, True, 2), (8, 4096, 14336, False, 2),    # matrices of 62 MB; GELU
+    (8, 4096, 2560, False, 16),                              # 320 MB of weights in all
+    (12, 3200, 5120, True, 8),                               # y: 156 tiles, neither most of a round nor split
+])
+def test_few_rows_in_their_own_kernel(E, d, f, swiglu, rows):
+    assert forward_rows(rows * E, E, d, f, swiglu) == 64
+
+
+@pytest.mark.parametrize("T, E, d, f", [(8, 8, 4096, 8192), (7, 8, 4096, 8192), (64, 16, 2048, 14336), (64, 16, 1984, 14336), (192, 16, 4096, 2048)])
+def test_workspace_of_few_rows_is_the_routes(T, E, d, f):
+    """Room for y's partial sums: eight parts of 64 rows per expert in the few-row kernel, up to 256 tiles of 256 x 256 else;
+    what does not fit the region of dA adds to the workspace."""
+    need = lambda f: B.moe_workspace_bytes(B.make_cfg(T, d, f, E, 2, B.DTYPE_BF16, B.ACT_SWIGLU))
+    dact = lambda f: 2 * (2 * T) * f * 2
+    tiles = (2 * T // 160 + E) * -(-d // 256)
+    sums = E * 8 * 64 * d * 4 if forward_rows(2 * T, E, d, f, True) == 64 else min(8 * tiles, 256) * 256 * 256 * 4
+    assert need(f) - need(1984) == max(dact(f), sums) - dact(1984)     # 1984 columns: no split
