@@ -415,8 +415,9 @@ MOE_API int moe_bench_mfma_loop(int32_t kind, int32_t iters, const void* operand
  * experts, ntm = K / 64, n_split = 1 if capacity or slices leave some of the rows out, n_full_rt = 1 for row tiles of 160
  * rows instead of 256; 0 if it cannot be.
  * kind 7, which tiles the row-tile GEMMs of a layer get, for `block` = T k rows of n_rt experts, d_model = ntm, d_ff = ntn,
- * n_full_rt = 1 for SwiGLU: out = {rows per tile of the forward GEMMs (64: their few-row kernel), 1 if those request weights
- * that one tile takes as streaming data, both for the backward GEMMs, -1, -1}; sizes that moe_cfg may not have are refused.
+ * n_full_rt = 1 for SwiGLU: out = {rows per tile of the forward GEMMs (64: their few-row kernel), the number of row tiles from
+ * which on those request weights that one tile takes as streaming data (0: never), both for the backward GEMMs, -1, -1}; sizes
+ * that moe_cfg may not have are refused.
  */
 MOE_API int moe_gemm_block_tile(int32_t kind, int64_t block, int32_t n_rt, int32_t n_full_rt, int32_t n_split,
                         int32_t ntm, int32_t ntn, int32_t* out);

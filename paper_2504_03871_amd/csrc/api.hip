@@ -37,8 +37,8 @@ static bool splits_small_tiles(const moe_cfg* c) { return is_half(c) && tile_row
 static bool fwd_skinny(const moe_cfg* c) {
   return is_half(c) && skinny_applies((long long)c->T * c->k, c->E, c->d_model, c->d_ff, c->act == MOE_ACT_SWIGLU, (int)elt_size(c));
 }
-static bool weights_streamed(const moe_cfg* c, int tile_rows) {
-  return is_half(c) && streams_weights((long long)c->T * c->k, tile_rows, c->E, c->d_model, c->d_ff, c->act == MOE_ACT_SWIGLU ? 3 : 2, (int)elt_size(c));
+static int weights_streamed_from(const moe_cfg* c, int tile_rows) {
+  return is_half(c) ? streamed_from((long long)c->T * c->k, tile_rows, c->E, c->d_model, c->d_ff, c->act == MOE_ACT_SWIGLU ? 3 : 2, (int)elt_size(c)) : 0;
 }
 // backward: a row-tile GEMM of N columns with at most about eight rounds of tiles shares its launch (moe_expert_ffn_bwd)
 static bool shares_launch(const moe_cfg* c, int N, int max_tiles) {
@@ -287,9 +287,9 @@ int moe_gemm_block_tile(int32_t kind, int64_t block, int32_t n_rt, int32_t n_ful
     const moe_cfg c = {(int)block, ntm, ntn, n_rt, 1, MOE_DTYPE_BF16, n_full_rt == 1 ? MOE_ACT_SWIGLU : MOE_ACT_GELU, 0, nullptr};
     CHECK(check_cfg(&c));
     out[0] = fwd_skinny(&c) ? SKINNY_ROWS : tile_rows_for(&c);
-    out[1] = !fwd_skinny(&c) && weights_streamed(&c, out[0]) ? 1 : 0;
+    out[1] = fwd_skinny(&c) ? 0 : weights_streamed_from(&c, out[0]);
     out[2] = tile_rows_for(&c);
-    out[3] = weights_streamed(&c, out[2]) ? 1 : 0;
+    out[3] = weights_streamed_from(&c, out[2]);
     return MOE_OK;
   }
   if (kind == 5) {
@@ -404,7 +404,7 @@ int ffn_fwd_impl(const moe_cfg* cfg, const void* x_perm, const void* W1, const v
   char* sv = static_cast<char*>(saved);
   GemmArgs g = {};
   g.tiles = map.tiles; g.ntiles = map.header; g.order = map.order; g.gelu_tab = map.gelu_tab; g.tile_rows = tr;
-  g.stream = weights_streamed(cfg, tr);
+  g.stream = weights_streamed_from(cfg, tr);
   g.offsets = offsets; g.kept = kept; g.lo = slice_lo; g.hi = slice_hi; g.E = cfg->E;
   // hidden = act(x_perm W1)
   g.A = x_perm; g.B = W1; g.B2 = W1b; g.N = f; g.K = d;
@@ -538,7 +538,7 @@ int ffn_bwd_impl(const moe_cfg* cfg, const void* dy_perm, const void* x_perm, co
   const void* hidden = swiglu ? sv + 2 * plane : sv + plane;
   GemmArgs g = {};
   g.tiles = map.tiles; g.ntiles = map.header; g.order = map.order; g.gelu_tab = map.gelu_tab; g.tile_rows = tr;
-  g.stream = weights_streamed(cfg, tr);
+  g.stream = weights_streamed_from(cfg, tr);
   g.offsets = offsets; g.kept = kept; g.lo = slice_lo; g.hi = slice_hi; g.E = cfg->E;
   g.accumulate = accumulate;
   // Four GEMMs: dH = dy W2^T fused with the activation derivative -> dA (GELU) or dG, dU (SwiGLU);

@@ -296,7 +296,7 @@ struct GemmArgs {
   int E;
   int accumulate;
   int chunked;   // row-tile GEMMs: order of the full tiles (block_to_tile)
-  int stream;    // row-tile GEMMs: whether weights that one row tile takes are requested as streaming data (streams_weights)
+  int stream;    // row-tile GEMMs: row tiles from which on weights that one of them takes are requested as streaming data, 0: never (streamed_from)
   int tile_rows; // row-tile GEMMs: rows per entry of the tile map
 };
 
@@ -357,8 +357,13 @@ inline bool mid_applies(long long rows, int E) { return rows <= (long long)(E <=
 // In launches shared with a weight gradient too: 256-row tiles, whole step, us, 140 rows, d 1024, f 1536, 64, SwiGLU 675 -> 631; 160,
 // d 2048, f 1024, 128, fp16 GELU 1307 -> 1250; 200, d 2048, f 4096, 48, SwiGLU 2645 -> 2563; 250, d 1024, f 768, 128 1039 -> 1037; 150,
 // d 1024, f 1024, 96, GELU, router bias -1.2 log(e + 1), 553 -> 521.
-inline bool streams_weights(long long rows, int tile_rows, long long E, long long d, long long f, int matrices, int elt) {
-  return rows <= tile_rows * E && E * d * f * matrices * elt > MEMORY_SIDE_CACHE / 4 * 5;
+// The weights that count are those of experts with rows.  The host does not know these; the kernel knows the row tiles, at least
+// one per such expert, so the answer is how many of those it takes (0: no number passes the line).  Backward, us, the line drawn
+// at all experts -> at those with rows: 26 experts, d 512, f 4352, SwiGLU (332 MB), 32 tokens of four at a router bias of
+// -1.2 log(e + 1) 265 -> 207; 14, d 1024, f 7168, GELU (392 MB), 70 tokens of one, the same bias 267 -> 214.
+inline int streamed_from(long long rows, int tile_rows, long long E, long long d, long long f, int matrices, int elt) {
+  const long long expert = d * f * matrices * elt, least = MEMORY_SIDE_CACHE / 4 * 5 / expert + 1;
+  return rows <= tile_rows * E && least <= E ? (int)least : 0;
 }
 // Whether GELU's hidden plane, which GEMM2 reads next, is stored plainly instead of streamed.  Up to about twice the L2
 // caches' 32 MB much of it is still near when GEMM2 starts; beyond, it only displaces operands.  Forward pass, us, streamed
@@ -399,7 +404,7 @@ int launch_gemm_half_skinny(int dtype, int epi, bool dual, const GemmArgs& g, in
 //   d 1024, f 512, 128 experts, SwiGLU     16    90 ->  74    84 ->  74    44 ->  50
 //                                          32    98 ->  84   116 ->  99    66 ->  67
 //                                          48   103 -> 101   115 -> 108    70 ->  84
-// These are with plain loads on the left.  Where 160-row tiles stream the weights too (streams_weights), both stream, and the
+// These are with plain loads on the left.  Where 160-row tiles stream the weights too (streamed_from), both stream, and the
 // ring of 64 KB per block in whole rounds of 256 blocks is ahead: forward pass, us, this kernel -> 160-row tiles,
 //   rows per expert                                 even          -0.7          -1.2
 //   d 4096, f 14336, 8 experts, SwiGLU      4   479 -> 458                 441 -> 427
@@ -437,7 +442,7 @@ int launch_gemm_half_skinny(int dtype, int epi, bool dual, const GemmArgs& g, in
 // loop.  The 64 MB: d from 2048, 2 to 8 rows, 40 to 64 MB 1.01, 64 to 100 MB 0.98.
 constexpr int SKINNY_AVERAGE = 32;
 inline bool few_rows_streamed(long long rows, int E, int d, int f, bool swiglu, int elt) {
-  if (!streams_weights(rows, MID_ROWS, E, d, f, swiglu ? 3 : 2, elt) || rows > (long long)(E <= MID_FEW_EXPERTS ? 24 : SKINNY_AVERAGE) * E) return false;
+  if (!streamed_from(rows, MID_ROWS, E, d, f, swiglu ? 3 : 2, elt) || rows > (long long)(E <= MID_FEW_EXPERTS ? 24 : SKINNY_AVERAGE) * E) return false;
   if (d < (E <= MID_FEW_EXPERTS ? 2048 : swiglu ? 1024 : 0)) return false;
   const int cols = swiglu ? 128 : 256, tiles1 = E * ((f + cols - 1) / cols), tiles2 = E * ((d + 255) / 256);
   auto full = [](int tiles) { return (long long)tiles * 5 >= (tiles + 255) / 256 * 256ll * 4; };

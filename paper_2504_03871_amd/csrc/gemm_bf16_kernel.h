@@ -325,7 +325,7 @@ __device__ __forceinline__ void epilogue_fwd(const OutPlanes& o, const unsigned 
 // once for numbers past the last tile (the grid is sized for the worst case).
 // SEGS (weight gradients): the K range is that of several calls, one after the other through one pipeline, each call's
 // products in a sum of their own that is added to the total: the sums, and their rounding, of call after call.
-// STREAM (row tiles): the weights of an expert with a single row tile are requested as streaming data (streams_weights).  A
+// STREAM (row tiles): the weights of an expert with a single row tile are requested as streaming data (streamed_from).  A
 // template parameter because the choice, once per load, costs a main loop that never takes it 1 to 3 %.
 template <typename ST, int MODE, int EPI, bool DUAL, bool CHAIN, int BM, int BN, int WGM, int WGN, bool SEGS = false, bool STREAM = false>
 __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs& g, const int vb, char* smem, const DwSegs* segs = nullptr) {
@@ -354,7 +354,7 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs& g, const int vb, 
   int seg_rows = 0, seg_row0 = 0, seg_stages = 0;          // SEGS: lane s holds segment s's rows and first row; stages in all
   unsigned seg_a[2] = {}, seg_b[2] = {};                   // and its operands' addresses
   bool second = false;          // TN with two gradients: this block's tile is one of the second's (B2, C2)
-  bool once = false;            // STREAM: no other row tile takes the same weights
+  bool once = false;            // STREAM: no other row tile takes the same weights, and those of all do not fit the caches
   float* part_sums = nullptr;   // this block computes one K part of a split tile: where its fp32 sums go, and their pitch
   int part_pitch = 0;
   {
@@ -436,7 +436,7 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgs& g, const int vb, 
       e = t.e;
       row0 = t.row0;
       mvalid = t.nrows;
-      if constexpr (STREAM) once = __builtin_amdgcn_readfirstlane(t.mates) == 0;
+      if constexpr (STREAM) once = __builtin_amdgcn_readfirstlane(t.mates) == 0 && n_rt >= g.stream;
     }
     n0 = nt * BN;
   }

@@ -183,6 +183,18 @@ def test_few_rows_in_their_own_kernel(E, d, f, swiglu, rows):
     assert forward_rows(rows * E, E, d, f, swiglu) == 64
 
 
+@pytest.mark.parametrize("E, d, f, swiglu, least", [
+    (26, 512, 4352, True, 26), (8, 4096, 14336, True, 1), (8, 4096, 2560, False, 0), (8, 4096, 2624, False, 8), (256, 2048, 1024, False, 41),
+])
+def test_weights_are_streamed_from_320_mb_of_experts_with_rows_on(E, d, f, swiglu, least):
+    """A launch has at least one row tile per expert with rows."""
+    bytes_of = lambda tiles: tiles * d * f * (3 if swiglu else 2) * 2
+    for rows in (E, 100 * E):
+        assert B.moe_gemm_block_tile(7, rows, E, int(swiglu), 0, d, f)[3] == least
+    assert (bytes_of(least) > 320 << 20 >= bytes_of(least - 1)) if least else bytes_of(E) <= 320 << 20
+    assert B.moe_gemm_block_tile(7, 513 * E, E, int(swiglu), 0, d, f)[3] == 0     # several tiles per expert
+
+
 @pytest.mark.parametrize("T, E, d, f", [(8, 8, 4096, 8192), (7, 8, 4096, 8192), (64, 16, 2048, 14336), (64, 16, 1984, 14336), (192, 16, 4096, 2048)])
 def test_workspace_of_few_rows_is_the_routes(T, E, d, f):
     """Room for y's partial sums: eight parts of 64 rows per expert in the few-row kernel, up to 256 tiles of 256 x 256 else;

@@ -167,7 +167,7 @@ def test_rows_past_a_tile_whose_offsets_wrap_32_bits_are_not_stored(act, T, f):
 
 
 def routes(L):
-    """Rows of a 16-bit layer's forward tiles, whether their weights are streamed, the same of the backward's."""
+    """Rows of a 16-bit layer's forward tiles, how many of them there are when weights are streamed, the same of the backward's."""
     return B.moe_gemm_block_tile(7, L.T * L.k, L.E, L.act == B.ACT_SWIGLU, 0, L.d, L.f)[:4]
 
 
@@ -318,7 +318,8 @@ def test_weights_requested_as_streaming_data(T, d, f, E, k, dtype, act):
     rows = 160 if T * k <= 128 * E or (E <= 32 and T * k <= 512 * E) else 256
     assert T * k <= rows * E and E * d * f * (3 if swiglu else 2) * 2 > 320 << 20
     L = filled_layer(T, d, f, E, k, dtype, act)
-    assert routes(L) == [rows, 1, rows, 1]
+    least = (320 << 20) // (d * f * (3 if swiglu else 2) * 2) + 1
+    assert routes(L) == [rows, least, rows, least]
     assert all((-(-n // 256) * (T * k // rows + E) > 2048) == (E == 160) for n in (d, f))
     L.bias = torch.tensor([2.5] + [0.0] * (E - 1), device=L.device)
     L.forward()
@@ -334,6 +335,7 @@ def test_weights_requested_as_streaming_data(T, d, f, E, k, dtype, act):
         grads.append(torch.cat([t.view(T * k, -1) for t in (*dact, L.dx_perm)], 1))
     torch.cuda.synchronize()
     assert T < 10 or int(L.kept.max()) > rows >= int(L.kept.median())
+    assert int((L.kept > 0).sum()) >= least
     for e in range(E):
         o, n = int(L.offsets[e]), int(L.kept[e])
         at = lambda t: t[o:o + n].double()
