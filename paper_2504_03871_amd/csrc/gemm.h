@@ -325,19 +325,21 @@ int launch_gemm_half(int dtype, int mode, int epi, bool dual, bool chain, const 
 // one launch for an NT GEMM (epilogue epi1, chained or not) followed by a TN weight-gradient GEMM
 int launch_gemm_half_pair(int dtype, int epi1, bool chain1, const GemmArgs& g1, int max_tiles, const GemmArgs& g2, hipStream_t s);
 int gemm_bf16_tile_rows();
-// Height of the 16-bit row tiles.  256 rows (two stages of operands in LDS) move the fewest bytes per product; 160 rows
-// leave room for a third stage, so loads may take one iteration longer, and fill the chip more evenly where an expert has
-// few tiles.  The host sees the average rows per expert, not the load, and the line is drawn on that.  256 -> 160 rows,
-// layers of d 1024 to 4096 and d_ff 1024 to 14336:
-//   33 to 140 rows, up to 32 experts: forward x0.79 to 1.09 (even load, most of them below 1), x0.73 to 1.03 (router bias -0.7
-//     log(e + 1)), backward x0.80 to 1.02; up to 128 rows, 40 to 128 experts: forward x0.78 to 0.98, backward x0.90 to 1.00
-//   150 to 220 rows, up to 32 experts: an evenly loaded expert is one tile of 256 or two of 160.  Forward x1.00 to 1.21, at the
-//     bias x0.73 to 0.95 (one expert of several tiles, others of one); backward x0.75 to 1.02
-//   240 to 512 rows, up to 32 experts: forward x0.64 to 1.10, at the bias x0.80 to 1.09 (most of both below 1), backward x0.75 to
-//     1.05.  Eight experts of 512 rows, d 1024, f 4096, us: GEMM1 57 -> 48, GEMM2 49 -> 41, dH 57 -> 48, dx 50 -> 41
-//   129 to 512 rows, 64 and 128 experts: forward x0.92 to 1.15, backward x0.97 to 1.00; the tiles are many either way
-//   above 512 rows: 2048 rows, d 1024, f 4096, GEMM1 189 -> 196, dH with dW2 324 -> 329; 3001 rows, d 1088, f 2880,
-//     SwiGLU GEMM1 113 -> 135
+// Height of the 16-bit row tiles.  256 rows move the fewest bytes per product; LDS holds three stages of one operand and two of the
+// other.  160 rows leave room for three of both, so all loads have the longer time to land, and fill the chip more evenly where
+// an expert has few tiles.  The host sees the average rows per expert, not the load, and the line is drawn on that.
+// 256 -> 160 rows, geometric mean over 1800 layers of random sizes (d 512 to 4096, d_ff 512 to 14336, both activations and
+// types), forward pass | forward and backward, at an even load and router biases of -0.7 and -1.2 log(e + 1):
+//   rows per expert          even           -0.7           -1.2                                even           -0.7           -1.2
+//   up to 32 experts                                                   more
+//   100 - 128          0.94 | 0.95    0.94 | 0.94    0.93 | 0.92                         0.95 | 0.99    0.96 | 0.98    0.97 | 0.98
+//   129 - 160          0.98 | 0.98    0.93 | 0.93    0.99 | 0.95                         1.01 | 1.01    0.97 | 0.99    0.96 | 0.98
+//   161 - 256          1.02 | 0.98    0.96 | 0.96    0.97 | 0.95                         1.13 | 1.08    1.00 | 1.01    1.00 | 1.01
+//   257 - 320          0.88 | 0.91    1.00 | 0.97    0.97 | 0.97                         0.97 | 0.99    0.99 | 1.01    1.00 | 1.00
+//   321 - 512          0.99 | 0.96    1.02 | 1.00    0.97 | 0.97                         1.06 | 1.04    1.03 | 1.02    1.03 | 1.02
+//   513 - 650          0.98 | 0.97    1.02 | 0.99    1.01 | 1.00                         1.04 | 1.03    1.03 | 1.03    1.04 | 1.03
+//   650 - 1000         1.04 | 1.01    1.03 | 1.01    0.99 | 1.00                         1.05 | 1.04    1.06 | 1.04    1.05 | 1.04
+// (a layer's own ratio lies within about a tenth of these.)
 constexpr int MID_ROWS = 160;
 constexpr int MID_FEW_EXPERTS = 32, MID_AVERAGE_FEW = 512, MID_AVERAGE_MANY = 128;
 inline bool mid_applies(long long rows, int E) { return rows <= (long long)(E <= MID_FEW_EXPERTS ? MID_AVERAGE_FEW : MID_AVERAGE_MANY) * E; }
@@ -351,9 +353,11 @@ inline bool mid_applies(long long rows, int E) { return rows <= (long long)(E <=
 //   288  d 2048, f 3072, 8, SwiGLU            102 ->  96 | 332 -> 341      384  d 1536, f 4096, 16, GELU      123 -> 116 | 402 -> 397
 //   384  d 1024, f 4096, 16, SwiGLU           130 -> 116 | 430 -> 424      384  d 1024, f 1024, 64, SwiGLU    132 -> 119 | 424 -> 398
 //   512  d 1024, f 4096, 32, GELU             158 -> 146 | 541 -> 508      576  d 1536, f 4096, 16, SwiGLU    165 -> 154 | 570 -> 550
-// 160-row tiles: 125 rows, d 2048, f 8192, 16 experts, fp16 GELU, forward pass 273 -> 260; 75 rows, d 4096, f 14336, 8, SwiGLU 559
-// -> 514.  256-row tiles: 160 rows, d 2048, f 2048, 128, GELU 552 -> 532; 150 rows, d 2048, f 2048, 64, step 1167 -> 1138; 200 rows,
-// d 2048, f 1024, 256, SwiGLU 936 -> 909; where experts have two or three tiles (512 rows, 128 experts, step) 3370 -> 3480.
+// 160-row tiles: 125 rows, d 2048, f 8192, 16 experts, fp16 GELU 280 -> 265 | 1109 -> 1036; 75 rows, d 4096, f 14336, 8, SwiGLU 577
+// -> 534 | 2397 -> 2253.  256-row tiles: 160 rows, d 2048, f 2048, 128, GELU 558 -> 536 | 2339 -> 2264; 200 rows, d 2048, f 1024, 256,
+// GELU 710 -> 684 | 2804 -> 2729, SwiGLU 941 -> 906 | 3734 -> 3663; where experts have two or three tiles (512 rows, 128 experts,
+// SwiGLU) 1003 -> 1001 | 3299 -> 3323.  1200 layers of random sizes beyond 320 MB: step x0.96 to 0.98 in each class of weights, rows and
+// load; 220 of 200 to 320 MB: x1.02 to 1.03 up to 32 experts, 0.99 to 1.00 beyond.
 // In launches shared with a weight gradient too: 256-row tiles, whole step, us, 140 rows, d 1024, f 1536, 64, SwiGLU 675 -> 631; 160,
 // d 2048, f 1024, 128, fp16 GELU 1307 -> 1250; 200, d 2048, f 4096, 48, SwiGLU 2645 -> 2563; 250, d 1024, f 768, 128 1039 -> 1037; 150,
 // d 1024, f 1024, 96, GELU, router bias -1.2 log(e + 1), 553 -> 521.

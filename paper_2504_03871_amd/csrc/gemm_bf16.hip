@@ -7,7 +7,7 @@ namespace moe {
 
 // Block tile 256 x 256 (SwiGLU forward: 256 x 128 for each of its two weight matrices), 2 x 4 waves: two
 // waves per SIMD, so one wave's LDS and global traffic hides under the other's MFMAs.  Global loads write LDS
-// directly, two 64-wide K stages for all three operand layouts.
+// directly, in 64-wide K stages for all three operand layouts: two of one operand and three of the other.
 constexpr int T_BM = 256, T_BN = 256, T_BN_DUAL = 128, T_BN_SEGS = 128, T_WGM = 2, T_WGN = 4;
 int gemm_bf16_tile_rows() { return T_BM; }
 

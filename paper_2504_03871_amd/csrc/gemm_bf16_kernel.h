@@ -26,19 +26,19 @@
 // halved number of barriers (weight gradients +2 % against a ring of four 32-wide stages).
 // 160 KB of LDS hold two stages of 256 x 256 and a third of one operand.  Its loads have half an iteration more to land, and
 // those of the other can go first in their half; waits for loads were what the loop lost (two stages of both: 0.27 to 0.40 of the
-// wave cycles).  us, two stages of both -> three of A -> three of B, all loads still in the second K step (LSH below has the rest):
-//   16384 rows in 16 skewed experts, d 2048, f 8192, fp16: y 494 -> 467 -> 462, GEMM1 610 -> 592 -> 579, dH 626 -> 601 -> 605,
-//     dW2 622 -> 606 -> 638, dx + dW1 1181 -> 1140 -> 1119
-//   65536 rows in 8, d 4096, f 14336, SwiGLU: GEMM1 12.10 -> 12.22 -> 11.93 ms, y 5.53 -> 5.33 -> 5.38, dH 6.37 -> 6.25 -> 6.28,
-//     dW 8.56 -> 8.50 -> 8.39, dx 11.87 -> 11.14 -> 11.01
-//   65536 rows in 128, d 2048, f 1024, SwiGLU: GEMM1 602 -> 577 -> 576, y 334 -> 316 -> 323, dx 575 -> 531 -> 530, dW1 842 -> 849 -> 843
-//   16384 rows in 8, d 1024, f 4096, GELU: GEMM1 178 -> 179 -> 181, y 131 -> 123 -> 125, dx + dW1 259 -> 249 -> 253
-// so three of B where two products are chained (dx of SwiGLU), three of A elsewhere, with the loads as they are now also in
-// SwiGLU's GEMM1 (three of B -> of A: 65536 rows in 8 experts 12.37 -> 12.27 ms, in 128 experts 561 -> 555 us).
+// wave cycles).  us, two stages of both, requested in the second K step -> three of A -> three of B, as the loads are now (LSH below):
+//   16384 rows in 16 skewed experts, d 2048, f 8192, fp16 GELU: GEMM1 632 -> 607 -> 609, y 506 -> 474 -> 473, dH 629 -> 598 -> 603,
+//     dW2 636 -> 626 -> 639, dx + dW1 1197 -> 1103 -> 1109; bf16: GEMM1 594 -> 562 -> 563, dx + dW1 1167 -> 1090 -> 1086, step 3604 -> 3402 -> 3421
+//   65536 rows in 8, d 4096, f 14336, SwiGLU: GEMM1 12.52 -> 12.15 -> 12.23 ms, y 5.74 -> 5.51 -> 5.50, dH 6.53 -> 6.35 -> 6.39,
+//     dW1 + dW1b 11.67 -> 11.63 -> 11.57, dx 12.03 -> 11.10 -> 11.13
+//   65536 rows in 128, d 2048, f 1024, SwiGLU: GEMM1 604 -> 540 -> 551, y 335 -> 303 -> 312, dx 575 -> 501 -> 499, dW1 + dW1b 856 -> 876 -> 880
+//   16384 rows in 8, d 1024, f 4096, GELU: GEMM1 174 -> 172 -> 178, y 142 -> 129 -> 132, dx + dW1 257 -> 241 -> 249
+//   16384 rows in 8, d 2048, f 8192, SwiGLU, dx alone: bf16 1129 -> 945 -> 928, fp16 1146 -> 1001 -> 976
+// so three of B where two products are chained (dx of SwiGLU), three of A elsewhere.
 // A tile of 160 rows and 256 columns (or twice 128) leaves LDS for three stages of both (156 of 160 KB): loads then have two
 // stages' worth of MFMAs to land instead of one, which is what a GEMM of few rows per expert waits for, and the chip is
-// left with smaller remainders (512 micro-batch rows per expert, d 1024, f 4096: GEMM1 57 -> 48 us; 125 rows, d 2048,
-// f 8192, forward pass 282 -> 271).  It moves 13 % more bytes per product from L2, so 256 rows stay ahead where tiles are
+// left with smaller remainders (512 micro-batch rows per expert, d 1024, f 4096: GEMM1 59 -> 53 us, y 63 -> 53, dx + dW1 116 -> 92).
+// It moves 13 % more bytes per product from L2, so 256 rows stay ahead where tiles are
 // many and full (the line: mid_applies).  Its five bands of 32 rows go three and two to the two wave rows, one wave of
 // either on each SIMD.
 // The direct loads are raw instructions: if the compiler knew that they write LDS it would wait for

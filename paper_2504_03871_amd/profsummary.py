@@ -82,7 +82,8 @@ def gemm_role(name, gradient="dw1_bwd"):
 
 def short(n):
     """Readable form of a mangled kernel name: the function name and, for the GEMMs, the integer template arguments
-    <MODE, EPI, DUAL, CHAIN, BM, BN, BK, waves M, waves N, stages> (pair: <MODE1, EPI1, CHAIN1, BK1, NB1, MODE2, ...>)."""
+    <MODE, EPI, DUAL, CHAIN, BM, BN, waves M, waves N, STREAM> (pair: <MODE1, EPI1, CHAIN1, BM1, MODE2, EPI2, BM, BN, waves M,
+    waves N, STREAM>)."""
     m = re.search(r"_ZN3moe\d+([a-z_0-9]+?)I(.*?)EEv", n)
     if m and m.group(1).startswith("gemm_"):
         args = re.findall(r"L[ib](\d+)E", m.group(2))
