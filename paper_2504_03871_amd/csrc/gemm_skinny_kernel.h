@@ -2,8 +2,8 @@
 //
 // Such a GEMM reads every weight once and does next to no arithmetic with it: HBM bounds it, and what counts is how
 // many bytes each compute unit keeps in flight.  The 256-row kernel keeps one block per compute unit with one 32 KB
-// stage of weights in flight and drains it at every stage; the 160-row one, with two, is ahead of this kernel where it streams the
-// weights and fills its rounds (few_rows_streamed).  Here a block owns 64 rows x 128 columns, four waves of 32
+// stage of weights in flight and drains it at every stage; the 160-row one, with two, is ahead of this kernel in wide layers where it
+// streams the weights and fills its rounds (few_rows_streamed).  Here a block owns 64 rows x 128 columns, four waves of 32
 // columns each; its K stages of 64 go through a ring of LDS stages that buffer loads fill directly, all but one of
 // them in flight, and two blocks share a compute unit: 64 KB of weights on their way per compute unit at any time.
 // The weights of an expert with a single row tile are requested as streaming data; row tiles that share weights run
