@@ -23,33 +23,33 @@ def device_code(lib):
             pos += 24 + n
 
 
-def instructions(tmp_path):
+@pytest.fixture(scope="module")
+def kernels(tmp_path_factory):
     """16-bit GEMM kernel -> its instructions."""
     if not os.path.exists(build.LIB):
         pytest.skip("library not built")
-    kernels, name = {}, ""
+    found, name, path = {}, "", tmp_path_factory.mktemp("code") / "code"
     for code in device_code(build.LIB):
-        (tmp_path / "code").write_bytes(code)
-        listing = subprocess.run([OBJDUMP, "-d", "--no-show-raw-insn", str(tmp_path / "code")], capture_output=True, text=True, check=True).stdout
+        path.write_bytes(code)
+        listing = subprocess.run([OBJDUMP, "-d", "--no-show-raw-insn", str(path)], capture_output=True, text=True, check=True).stdout
         for line in listing.splitlines():
             if m := re.match(r"[0-9a-f]+ <(\S+)>:", line):
                 name = m[1]
             elif "gemm_bf16" in name:
-                kernels.setdefault(name, []).append(line.strip())
-    assert len(kernels) > 20
-    return kernels
+                found.setdefault(name, []).append(line.strip())
+    assert len(found) > 20
+    return found
 
 
-def test_no_gemm_kernel_spills_registers(tmp_path):
+def test_no_gemm_kernel_spills_registers(kernels):
     """A value that comes back from scratch memory waits for every load in flight; in a main loop that is the next stages'."""
-    spilled = [name for name, ops in instructions(tmp_path).items() if any(op.startswith("scratch_") for op in ops)]
+    spilled = [name for name, ops in kernels.items() if any(op.startswith("scratch_") for op in ops)]
     assert not spilled, spilled
 
 
-def test_every_row_tile_kernel_has_an_instance_that_streams_weights(tmp_path):
+def test_every_row_tile_kernel_has_an_instance_that_streams_weights(kernels):
     """A layer whose weights are to be requested as streaming data (the last template argument) gets them so from all of its
     row-tile GEMMs, at both tile heights and in shared launches too."""
-    kernels = instructions(tmp_path)
     row_tiles = [name for name in kernels if name.startswith(("_ZN3moe16gemm_bf16_kernel", "_ZN3moe21gemm_bf16_pair_kernel")) and "kernelIDF16_Li2E" not in name and "kernelIDF16bLi2E" not in name]
     for name in row_tiles:
         assert name.replace("ELb0EEEv", "ELb1EEEv") in kernels, name
