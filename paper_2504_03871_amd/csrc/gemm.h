@@ -356,8 +356,9 @@ inline bool mid_applies(long long rows, int E) { return rows <= (long long)(E <=
 // 160-row tiles: 125 rows, d 2048, f 8192, 16 experts, fp16 GELU 280 -> 265 | 1109 -> 1036; 75 rows, d 4096, f 14336, 8, SwiGLU 577
 // -> 534 | 2397 -> 2253.  256-row tiles: 160 rows, d 2048, f 2048, 128, GELU 558 -> 536 | 2339 -> 2264; 200 rows, d 2048, f 1024, 256,
 // GELU 710 -> 684 | 2804 -> 2729, SwiGLU 941 -> 906 | 3734 -> 3663; where experts have two or three tiles (512 rows, 128 experts,
-// SwiGLU) 1003 -> 1001 | 3299 -> 3323.  1200 layers of random sizes beyond 320 MB: step x0.96 to 0.98 in each class of weights, rows and
-// load; 220 of 200 to 320 MB: x1.02 to 1.03 up to 32 experts, 0.99 to 1.00 beyond.
+// SwiGLU) 1003 -> 1001 | 3299 -> 3323.  1250 layers of random sizes beyond 320 MB, the line drawn at all experts: step x0.94 to 0.98 in
+// each class of weights, rows and load but one (up to 32 experts, 320 to 400 MB, bias -1.2: 1.00, see the last lines); 225 of 200
+// to 320 MB: x1.02 to 1.03 up to 32 experts, 1.00 beyond.
 // In launches shared with a weight gradient too: 256-row tiles, whole step, us, 140 rows, d 1024, f 1536, 64, SwiGLU 675 -> 631; 160,
 // d 2048, f 1024, 128, fp16 GELU 1307 -> 1250; 200, d 2048, f 4096, 48, SwiGLU 2645 -> 2563; 250, d 1024, f 768, 128 1039 -> 1037; 150,
 // d 1024, f 1024, 96, GELU, router bias -1.2 log(e + 1), 553 -> 521.
